@@ -1,4 +1,4 @@
-// dK / dV kernel for head dims 64 and 128 with producer / consumer wave specialisation (same mathematics
+// dK / dV kernel for head dims 64, 96 and 128 with producer / consumer wave specialisation (same mathematics
 // and the same ownership rule as the other dK/dV kernels: one workgroup owns a 128-key tile of one KV
 // head; a shared-prompt tile sums the contributions of ALL sequences and heads of the group in fp32
 // registers and is cast once -- Alg. 1 with the race of the shared prompt gradients removed by ownership).
@@ -19,6 +19,14 @@
 //     first row, row count), which is all a producer needs to know about the schedule.
 //   * the main loop is unrolled over the six LDS stages, so every LDS address is an immediate offset;
 //     every LDS operand is read one interval before its use, across the single barrier per row block.
+//
+// Head dim 96 has three 32-wide head-dim blocks for the four consumer waves.  Three of them own a block each and do
+// nothing but accumulate (like the producers they learn from the header whether a block exists); the fourth owns no
+// accumulator and is the loader: it walks the schedule, writes the headers and makes all twelve requests of a row block.
+// Of the 28 MFMAs that the busiest SIMD then has per interval 24 are the average; in return the requests and the scalar
+// work, a third of a consumer's time at head dim 128, leave the accumulating waves altogether.  Measured on N = 8,
+// P = 4111, R ~ U(131, 2048), 16 / 4 heads: 0.88 + 0.35 ms (Call 2 + Call 1), against 1.95 + 0.82 ms for the kernel with
+// register staging, transposed copies and a barrier per phase that served this head dim before.
 //
 // The compiler does not know about the global -> LDS loads: the consumers count them themselves
 // (s_waitcnt vmcnt) before the barrier that publishes a row block, and no compiler-visible vector memory
@@ -48,7 +56,9 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
   constexpr int XCH_OFF = NBUF * STAGE_BYTES;
   constexpr int XCH_BYTES = 16384;                 // [key subtile][P k-step 0,1 | dS k-step 0,1][lane] x 16 B
   constexpr int NIT = HT_BYTES / 1024;             // 1 KB load instructions per row block and tensor
-  constexpr int IPB = 2 * NIT / 4;                 // per consumer wave (Q and dO)
+  constexpr bool LOADER = kSplitRow<D>;            // one consumer wave makes all requests
+  constexpr int IPB = LOADER ? 2 * NIT : 2 * NIT / 4;   // per requesting wave (Q and dO)
+  constexpr int LOAD_WAVE = 7, HDR_WAVE = LOADER ? LOAD_WAVE : 4, STAT_WAVE = 5;
   constexpr int RPI = 1024 / RB;                   // rows per load instruction
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -260,14 +270,29 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     // per-lane global offsets of this wave's load instructions for a block of 32 valid rows (a partial last
     // block clamps its rows instead: rare, computed on the spot)
     uint32_t voff_full[IPB];
+    int sp_row[3], sp_coff[3];   // (loader) row and byte offset of instructions t, t + 3, ... (16 rows apart)
+    if constexpr (LOADER) {
 #pragma unroll
-    for (int t = 0; t < IPB; ++t)
+      for (int t = 0; t < 3; ++t) {
+        sp_row[t] = split_row<D>(t, lane);
+        sp_coff[t] = (split_pos<D>(t, lane) ^ swz<D>(sp_row[t])) * 16;
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < IPB; ++t) {
+      if constexpr (LOADER) {
+        const int tt = t % NIT, row = sp_row[tt % 3] + tt / 3 * kSplitRows<D>;
+        voff_full[t] = (uint32_t)(row * (t < NIT ? q_ts : do_ts) * 2 + sp_coff[tt % 3]);
+        continue;
+      }
       voff_full[t] = LOCAL ? 0u : (uint32_t)((ld_row0 + (t % (IPB / 2)) * 4 * RPI) * (t < IPB / 2 ? q_ts : do_ts) * 2 + ld_coff);
+    }
     // row statistics: lanes 0-31 fetch LSE*log2e, lanes 32-63 fetch D; both arrays live in one workspace, D
     // first and LSE*log2e less than 4 GB behind it (checked by the launcher), so one scalar base plus an
     // unsigned 32-bit lane offset addresses both
     const float* stat_ptr = p.dvec;
     const uint32_t stat_lane_off = hi ? 0u : (uint32_t)((const char*)p.lse2 - (const char*)p.dvec);
+    const float* stat_lane = hi ? p.dvec : p.lse2;   // (the loader uses 64-bit lane addresses)
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
     // blocks of 32 that see at least one key of the tile, query heads of the group innermost.  All state is
@@ -276,7 +301,8 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
     int64_t st_row = 0, st_cur = 0;
     bool more = false;
-    uint32_t gflags = 0;   // wave 4, lanes 0-3: flags of key subtile `lane` for the current row group
+    uint32_t gflags = 0;   // wave 4, lanes 0-3: flags of key subtile `lane` for the current row group (loader: byte i of
+                           // a scalar: those of subtile i)
     auto enter_group = [&]() __attribute__((always_inline)) {
       row0 = rb * HB;
       nvalid = min(HB, R - row0);
@@ -284,7 +310,27 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       do_cur = do_row;
       st_cur = st_row;
       g = 0;
-      if (wave == 4) {
+      if constexpr (LOADER) {
+        gflags = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int k_lo = key0 + i * 32, k_hi = k_lo + 31;
+          bool a, m;
+          if (is_ctx) {
+            a = !LOCAL || (k_hi > P + row0 - W);
+            m = LOCAL && (k_lo <= P + row0 + 31 - W);
+          } else {
+            a = k_lo <= row0 + 31;
+            m = k_hi > row0;
+            if (LOCAL) {
+              a = a && (k_hi > row0 - W);
+              m = m || (k_lo <= row0 + 31 - W);
+            }
+          }
+          m = m || nvalid < HB;
+          gflags |= (uint32_t)(HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0)) << (8 * i);
+        }
+      } else if (wave == HDR_WAVE) {
         const int k_lo = key0 + (lane & 3) * 32, k_hi = k_lo + 31;
         bool a, m;
         if (is_ctx) {
@@ -342,16 +388,17 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       }
     };
     uint32_t vbits = 0;   // bit i: block (request position - 1 - i) exists
-    // requests the next block of the schedule (or marks the end) in stage IS and advances the schedule
-    auto issue_block = [&](auto ISc) __attribute__((always_inline)) {
+    // requests the next block of the schedule (or marks the end) in stage IS (the loader: at stage_off) and advances the
+    // schedule
+    auto issue_block = [&](auto ISc, uint32_t stage_off = 0) __attribute__((always_inline)) {
       constexpr int IS = decltype(ISc)::value;
-      if (wave == 4 && lane < 4) {
+      if (wave == HDR_WAVE && lane < 4) {
         u32x4 h;
-        h.x = more ? gflags : 0u;
+        h.x = more ? (LOADER ? (gflags >> (8 * lane)) & 0xffu : gflags) : 0u;
         h.y = (uint32_t)row0;
         h.z = (uint32_t)nvalid;
         h.w = 0u;
-        *reinterpret_cast<u32x4*>(smem + IS * STAGE_BYTES + HDR_OFF + lane * 16) = h;
+        *reinterpret_cast<u32x4*>(smem + stage_off + IS * STAGE_BYTES + HDR_OFF + lane * 16) = h;
       }
       vbits = (vbits << 1) | (more ? 1u : 0u);
       if (__builtin_expect(more, 1)) {
@@ -359,7 +406,22 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
         const u16* q_base = uniform_ptr(q_cur);
         const u16* do_base = uniform_ptr(do_cur);
         // (one branch for the whole block, not one per load)
-        if (__builtin_expect(!LOCAL && nvalid == HB, 1)) {
+        if constexpr (LOADER) {
+          if (__builtin_expect(nvalid == HB, 1)) {
+            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
+              constexpr int t = decltype(Tc)::value;
+              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff_full[t], smem_addr + stage_off);
+            });
+          } else {
+            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
+              constexpr int t = decltype(Tc)::value, tt = t % NIT;
+              const int row = sp_row[tt % 3] + tt / 3 * kSplitRows<D>;
+              const uint32_t voff =
+                  __umul24((unsigned)min(row, last), (unsigned)((t < NIT ? q_ts : do_ts) * 2)) + (uint32_t)sp_coff[tt % 3];
+              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff, smem_addr + stage_off);
+            });
+          }
+        } else if (__builtin_expect(!LOCAL && nvalid == HB, 1)) {
           static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
             constexpr int t = decltype(Tc)::value;
             dma16_at<IS * STAGE_BYTES + (t < IPB / 2 ? 0 : HT_BYTES) + (t % (IPB / 2)) * 4096>(
@@ -374,7 +436,9 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
             dma16_at<IS * STAGE_BYTES + (is_q ? 0 : HT_BYTES) + (t % (IPB / 2)) * 4096>(is_q ? q_base : do_base, voff, ld_lds);
           });
         }
-        if (wave == 5) {
+        if (LOADER) {
+          dma4_from<IS * STAGE_BYTES + STAT_OFF>(stat_lane + st_cur + min(l32, last), smem_addr + stage_off);
+        } else if (wave == STAT_WAVE) {
           dma4_at<IS * STAGE_BYTES + STAT_OFF>(uniform_ptr(reinterpret_cast<const u16*>(stat_ptr + st_cur)),
                                                stat_lane_off + (uint32_t)min(l32, last) * 4u, smem_addr);
         }
@@ -392,29 +456,50 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     // wave; wave 5 issues one more, for it the bound is a little stricter) may stay in flight.  If the
     // newest request was the end mark, fewer loads are outstanding: wait for all of them.
     auto wait_loads = [&]() __attribute__((always_inline)) {
-      wait_vm<(AHEAD - 2) * IPB>();
+      wait_vm<(AHEAD - 2) * (IPB + (LOADER ? 1 : 0))>();
       if (__builtin_expect(!(vbits & 1u), 0)) wait_vm<0>();
     };
 
-    for (; seq < seq_hi; ++seq) {
-      init_seq();
-      if (rb < rb_end) {
-        more = true;
-        enter_group();
-        break;
+    if (!LOADER || wave == LOAD_WAVE) {
+      for (; seq < seq_hi; ++seq) {
+        init_seq();
+        if (rb < rb_end) {
+          more = true;
+          enter_group();
+          break;
+        }
+      }
+      if constexpr (!LOADER) {
+        issue_block(IC<0>{});
+        issue_block(IC<1>{});
+        issue_block(IC<2>{});
+        issue_block(IC<3>{});
+        issue_block(IC<4>{});
+        wait_loads();
       }
     }
-    issue_block(IC<0>{});
-    issue_block(IC<1>{});
-    issue_block(IC<2>{});
-    issue_block(IC<3>{});
-    issue_block(IC<4>{});
-    wait_loads();
+    if (LOADER && wave == LOAD_WAVE) {
+      // (not unrolled over the stages: this wave has time for a stage offset in a register, and the code stays short)
+#pragma nounroll
+      for (int i = 0; i < AHEAD; ++i) issue_block(IC<0>{}, i * STAGE_BYTES);
+      wait_loads();
+      __syncthreads();   // row blocks 0 and 1 and their headers are in LDS
+      uint32_t stage_off = AHEAD * STAGE_BYTES;
+      bool cur = true;
+      while (cur) {
+        issue_block(IC<0>{}, stage_off);
+        stage_off = stage_off == AHEAD * STAGE_BYTES ? 0 : stage_off + STAGE_BYTES;
+        cur = vbits & (1u << AHEAD);
+        wait_loads();
+        __syncthreads();
+      }
+      return;
+    }
 
     // Each consumer wave owns one 32-wide head-dim block (dblk) of the gradients of NK key subtiles: the
     // transposed Q / dO operands of its head-dim block are shared by all its key subtiles, which keeps the
     // (slow) LDS transpose reads at 8 per row block.
-    constexpr int NK = DSUB;                       // key subtiles per wave: 4 (d = 128) or 2 (d = 64)
+    constexpr int NK = D == 64 ? 2 : 4;            // key subtiles per wave
     const int dblk = jb % DSUB, k0 = (jb / DSUB) * NK;
     f32x16 dk[NK], dv[NK];
 #pragma unroll
@@ -428,14 +513,17 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     const unsigned char* tr1 = smem + tr_off<D>(lane, hi * 4 + 8, dblk * 32);
     const unsigned char* xr_lane = smem + XCH_OFF + k0 * 4096 + lane * 16;
     bf16x8 tq[2], tdo[2];   // Q^T, dO^T operands of the row block accumulated next interval
+    bool prev = false;      // (with a loader wave) block h - 1 exists
 
     // one interval: accumulates block h-1, reads the transposed operands of block h (stage U), requests
     // block h + AHEAD; returns false after the end of the schedule
     auto interval = [&](auto Uc) __attribute__((always_inline)) -> bool {
       constexpr int U = decltype(Uc)::value, IS = (U + AHEAD) % NBUF, XB = (U + 1) & 1;
       // requests first: the producers' MFMAs run meanwhile, the consumers' follow them
-      issue_block(IC<IS>{});
-      if (vbits & (1u << (AHEAD + 1))) {
+      uint32_t hdr = 0;
+      if constexpr (LOADER) hdr = *reinterpret_cast<const uint32_t*>(smem + HDR_OFF + U * STAGE_BYTES);
+      else issue_block(IC<IS>{});
+      if (LOADER ? prev : (vbits & (1u << (AHEAD + 1))) != 0) {
         const unsigned char* xr = xr_lane + XB * XCH_BYTES;
         // all P / -dS operands are requested before the first MFMA (left alone, the compiler reads one operand,
         // waits for it and issues one MFMA, sixteen LDS latencies in a row)
@@ -457,7 +545,7 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
           }
         __builtin_amdgcn_sched_barrier(0);
       }
-      const bool cur = vbits & (1u << AHEAD);
+      const bool cur = LOADER ? (__builtin_amdgcn_readfirstlane((int)hdr) & HDR_VALID) != 0 : (vbits & (1u << AHEAD)) != 0;
       if (__builtin_expect(cur, 1)) {
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
@@ -465,7 +553,8 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
           tq[t2] = tr_pair(tr0 + U * STAGE_BYTES + t2 * 16 * RB, tr1 + U * STAGE_BYTES + t2 * 16 * RB);
         }
       }
-      wait_loads();
+      if constexpr (LOADER) prev = cur;
+      else wait_loads();
       __syncthreads();
       return cur;
     };
@@ -517,9 +606,9 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
-  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset
-  if (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
-      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32))
+  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
+  if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
+      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
   const size_t smem = 6 * (2 * 32 * 2 * D + 256 + 64) + 2 * 16384;
   auto kern = dkdv4_kernel<D, LOCAL>;
@@ -536,6 +625,7 @@ hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) {
   const bool local = p.window > 0;
   switch (head_dim) {
     case 64:  return local ? launch_dkdv4_t<64, true>(p, st) : launch_dkdv4_t<64, false>(p, st);
+    case 96:  return local ? launch_dkdv4_t<96, true>(p, st) : launch_dkdv4_t<96, false>(p, st);
     case 128: return local ? launch_dkdv4_t<128, true>(p, st) : launch_dkdv4_t<128, false>(p, st);
   }
   return hipErrorInvalidValue;

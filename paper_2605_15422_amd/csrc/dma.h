@@ -51,6 +51,14 @@ __device__ __forceinline__ void dma4_at(const void* sbase, uint32_t voff, uint32
                : "s"(lds_base), "v"(voff), "s"(sbase), "n"(OFF)
                : "memory", "m0", "scc");
 }
+// 64 lanes x 4 bytes from 64-bit per-lane addresses (no common base within 4 GB needed).
+template <int OFF>
+__device__ __forceinline__ void dma4_from(const void* vaddr, uint32_t lds_base) {
+  asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+               :
+               : "s"(lds_base), "v"(vaddr), "n"(OFF)
+               : "memory", "m0", "scc");
+}
 // f(std::integral_constant<int, 0>{}), ..., f(std::integral_constant<int, N - 1>{}): a loop whose index is a constant expression
 template <typename F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {

@@ -1,4 +1,4 @@
-// dQ kernel for head dims 64 and 128, tuned variant (same mathematics as the generic dq_kernel):
+// dQ kernel for head dims 64, 96 and 128, tuned variant (same mathematics as the generic dq_kernel):
 //   dQ = scale * dS K,  dS = P * (dP - D),  P = exp(scale * Q K^T - LSE),  dP = dO V^T     (Alg. 1)
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
@@ -9,6 +9,9 @@
 // dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T through LDS transpose
 // reads of the same row-major K tile.  A 64-key tile is consumed as two 32-key halves so only one
 // 32x32 S and dP tile is live at a time.
+// Head dim 96 (tiles of un-padded 192-byte rows, tiles.h; half the waves request K, half V) on N = 8, P = 4111,
+// R ~ U(131, 2048), 16 / 4 heads: 0.45 + 0.12 ms (Call 2 + Call 1), against 0.71 + 0.19 ms for the register-staged kernel
+// that served it before.
 #include "common.h"
 #include "dma.h"
 #include "launch.h"
@@ -25,6 +28,8 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   constexpr int NSTAGE = 3, STAGE_BYTES = 2 * TILE_BYTES;
   constexpr int IPT = TILE_BYTES / 1024 / 8;   // 1 KB load instructions per wave, tile and tensor
   constexpr int RPI = 1024 / RB;               // rows per load instruction
+  constexpr int LPT = 2 * TILE_BYTES / 1024 / 8;   // per wave and tile
+  static_assert(kSplitRow<D> || LPT == 2 * IPT, "tile must split evenly over the waves");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSTAGE][K tile | V tile]
 
   QBlock b;
@@ -91,9 +96,32 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   // (token strides in bytes, read from the kernel arguments once: a scalar load inside the loop would make the
   // wave wait for every LDS read in flight as well)
   const int ktsb_c = (int)p.kc.ts * 2, ktsb_d = (int)p.kd.ts * 2, vtsb_c = (int)p.vc.ts * 2, vtsb_d = (int)p.vd.ts * 2;
+  // (head dim 96: twelve instructions per tensor, three consecutive ones per wave, waves 0-3 for K, 4-7 for V)
+  const u16 *myc_base = wave < 4 ? kc_base : vc_base, *myd_base = wave < 4 ? kd_base : vd_base;
+  const int mytsb_c = wave < 4 ? ktsb_c : vtsb_c, mytsb_d = wave < 4 ? ktsb_d : vtsb_d;
+  int ld_row[LPT], ld_off[LPT];
+  if constexpr (kSplitRow<D>) {
+    static_assert(LPT == 3 && BN == 4 * kSplitRows<D>, "three instructions per wave");
+#pragma unroll
+    for (int t = 0; t < LPT; ++t) {
+      ld_row[t] = (wave & 3) * kSplitRows<D> + split_row<D>(t, lane);
+      ld_off[t] = (split_pos<D>(t, lane) ^ swz<D>(ld_row[t])) * 16;
+    }
+  }
   auto issue_loads = [&](int it, int stage) __attribute__((always_inline)) {
     const bool is_ctx = it < n_ctx_run;
     const int key0 = is_ctx ? (b.c0 + it) * BN : (b.d0 + it - n_ctx_run) * BN;
+    if constexpr (kSplitRow<D>) {
+      const int tsb = is_ctx ? mytsb_c : mytsb_d;
+      const u16* tb = uniform_ptr(reinterpret_cast<const u16*>(
+          reinterpret_cast<const unsigned char*>(is_ctx ? myc_base : myd_base) + (int64_t)key0 * tsb));
+      const int last = (is_ctx ? P : R) - key0 - 1;
+      const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * 3072;   // the V tile follows the K tile
+#pragma unroll
+      for (int t = 0; t < LPT; ++t)
+        dma16(tb, __umul24((unsigned)min(ld_row[t], last), (unsigned)tsb) + ld_off[t], dst + t * 1024);
+      return;
+    }
     const int ktsb = is_ctx ? ktsb_c : ktsb_d, vtsb = is_ctx ? vtsb_c : vtsb_d;
     const u16* kb = uniform_ptr(reinterpret_cast<const u16*>(
         reinterpret_cast<const unsigned char*>(is_ctx ? kc_base : kd_base) + (int64_t)key0 * ktsb));
@@ -108,9 +136,9 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
       dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * 8192);
     }
   };
-  // the tile consumed next must have landed; the 2 IPT loads of the tile after it may stay in flight
+  // the tile consumed next must have landed; the LPT loads of the tile after it may stay in flight
   auto wait_loads = [&](bool newer_in_flight) __attribute__((always_inline)) {
-    wait_vm<2 * IPT>();
+    wait_vm<LPT>();
     if (__builtin_expect(!newer_in_flight, 0)) wait_vm<0>();
   };
 
@@ -166,12 +194,13 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
       // ... so that the exponentials of S issue in the shadow of the dP MFMAs
       const bool need = !plain && tile_needs_mask<LOCAL, 32>(is_ctx, key0, row0, P, R, W);
       float ev[16], dsv[16];
-      constexpr int EPM = 16 / KS;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         dpt = mfma32(vo[ks], dof[ks], ks == 0 ? negd : dpt);
 #pragma unroll
-        for (int e = ks * EPM; e < (ks + 1) * EPM; ++e) {
+        for (int j = 0; j < (16 + KS - 1) / KS; ++j) {
+          const int e = 16 * ks / KS + j;   // the sixteen exponentials spread evenly over the KS MFMAs
+          if (e >= 16 * (ks + 1) / KS) continue;
           ev[e] = __builtin_amdgcn_exp2f(s[e] * c - lse2);
           asm volatile("" : "+v"(ev[e]));
         }
@@ -206,6 +235,7 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   // instead (all stages are free after the last barrier; 16-byte chunks XOR-swizzled by the row) and is read back as
   // whole rows.  Wave-private: no barrier.
   unsigned char* ot = smem + wave * 32 * RB;
+  auto oswz = [](int r) { return D == 96 ? swz<96>(r) : r & (CPR - 1); };
 #pragma unroll
   for (int ds = 0; ds < DSUB; ++ds)
 #pragma unroll
@@ -213,14 +243,12 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
       u32x2 w;
       w.x = pack2_bf16(dqacc[ds][r4 * 4 + 0] * p.scale, dqacc[ds][r4 * 4 + 1] * p.scale);
       w.y = pack2_bf16(dqacc[ds][r4 * 4 + 2] * p.scale, dqacc[ds][r4 * 4 + 3] * p.scale);
-      *reinterpret_cast<u32x2*>(ot + l32 * RB + (((ds * 4 + r4) ^ (l32 & (CPR - 1))) << 4) + hi * 8) = w;
+      *reinterpret_cast<u32x2*>(ot + l32 * RB + (((ds * 4 + r4) ^ oswz(l32)) << 4) + hi * 8) = w;
     }
-  constexpr int RPS = 64 / CPR;   // rows per store instruction
-  const int chunk = lane % CPR;
 #pragma unroll
-  for (int i = 0; i < 32 / RPS; ++i) {
-    const int tr = i * RPS + lane / CPR;
-    const u32x4 w = *reinterpret_cast<const u32x4*>(ot + tr * RB + ((chunk ^ (tr & (CPR - 1))) << 4));
+  for (int i = 0; i < CPR / 2; ++i) {   // 64 of the tile's 32 CPR chunks per store instruction
+    const int tr = (i * 64 + lane) / CPR, chunk = (i * 64 + lane) % CPR;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(ot + tr * RB + ((chunk ^ oswz(tr)) << 4));
     if (row0 + tr < R) {
       u16* op = p.dq.ptr + (int64_t)(b.row_begin + row0 + tr) * p.dq.ts + (int64_t)head * p.dq.hs;
       *reinterpret_cast<u32x4*>(op + chunk * 8) = w;
@@ -245,6 +273,7 @@ hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st) {
   const bool local = p.window > 0;
   switch (head_dim) {
     case 64:  return local ? launch_dq2_t<64, true>(p, st) : launch_dq2_t<64, false>(p, st);
+    case 96:  return local ? launch_dq2_t<96, true>(p, st) : launch_dq2_t<96, false>(p, st);
     case 128: return local ? launch_dq2_t<128, true>(p, st) : launch_dq2_t<128, false>(p, st);
   }
   return hipErrorInvalidValue;

@@ -1,4 +1,4 @@
-// Forward kernel for head dims 64 and 128 (Alg. 3 of the paper re-tiled for CDNA4), tuned variant.
+// Forward kernel for head dims 64, 96 and 128 (Alg. 3 of the paper re-tiled for CDNA4), tuned variant.
 //
 // Same work decomposition as the generic Q-stationary kernel (one workgroup = BMR rows x GP packed
 // query heads of one KV head, prompt tiles then own-response tiles):
@@ -15,6 +15,9 @@
 //     waves per SIMD do not hide a wave's own MFMA -> softmax -> MFMA dependency chain on this chip
 //     (their phases drift together at every barrier); interleaving independent work inside one
 //     instruction stream does.
+// Head dim 96 takes twelve slots per step instead of sixteen and tiles of un-padded 192-byte rows (tiles.h).  On N = 8,
+// P = 4111, R ~ U(131, 2048), 16 / 4 heads it runs 0.41 + 0.13 ms (Call 2 + Call 1), against 0.68 + 0.20 ms for the
+// unpipelined kernel with register staging that served this head dim before.
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
@@ -34,8 +37,10 @@ struct F2Cfg {
   static constexpr int CPR = D / 8;                // 16-byte chunks per row
   static constexpr int RPL = CPR < 16 ? 16 / CPR : 1;   // rows per 256-byte bank line
   static constexpr int TILE_BYTES = BN * RB;
-  __device__ static __forceinline__ int fK(int row) { return (row / RPL) % CPR; }
-  __device__ static __forceinline__ int fV(int row) { return 4 * ((row / RPL) % (CPR / 4)); }
+  // (head dim 96: four consecutive 192-byte rows lie on different quarters of the bank line by themselves, which is all
+  // that the transpose reads of V need)
+  __device__ static __forceinline__ int fK(int row) { return D == 96 ? swz<96>(row) : (row / RPL) % CPR; }
+  __device__ static __forceinline__ int fV(int row) { return D == 96 ? 0 : 4 * ((row / RPL) % (CPR / 4)); }
 };
 
 template <int D, bool LOCAL>
@@ -104,13 +109,23 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   constexpr int LW = C::NW / 2;                       // waves per tensor
   constexpr int IPT = C::TILE_BYTES / 1024 / LW;      // 1 KB load instructions per wave and tile
   constexpr int RPI = 1024 / C::RB;                   // rows per load instruction
-  static_assert(IPT >= 1, "tile must split evenly over the waves");
+  static_assert(IPT >= 1 && C::TILE_BYTES % (1024 * LW) == 0, "tile must split evenly over the waves");
   const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
   const int lwave = wave % LW;
   const bool v_loader = wave >= LW;
   const int ld_row0 = lwave * RPI + lane / C::CPR;
   const int ld_kcoff = ((lane % C::CPR) ^ C::fK(ld_row0)) * 16;
   const int ld_vcoff = ((lane % C::CPR) ^ C::fV(ld_row0)) * 16;
+  // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows, each with an offset of its own)
+  int ld_row[IPT], ld_coff[IPT];
+  if constexpr (kSplitRow<D>) {
+    static_assert(IPT == 3 && C::BN == LW * kSplitRows<D>, "three instructions per wave");
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) {
+      ld_row[t] = lwave * kSplitRows<D> + split_row<D>(t, lane);
+      ld_coff[t] = (split_pos<D>(t, lane) ^ (v_loader ? C::fV(ld_row[t]) : C::fK(ld_row[t]))) * 16;
+    }
+  }
   // which = 0: K tile `it` into the K ring, 1: V tile `it` into the V ring (slot it % 4)
   const int tsb_c[2] = {(int)p.kc.ts * 2, (int)p.vc.ts * 2}, tsb_d[2] = {(int)p.kd.ts * 2, (int)p.vd.ts * 2};
   auto issue_tile = [&](int it, int which) __attribute__((always_inline)) {
@@ -120,7 +135,15 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
     const u16* base = is_ctx ? (which ? vc_base : kc_base) : (which ? vd_base : kd_base);
     const unsigned char* tb = reinterpret_cast<const unsigned char*>(base) + (int64_t)(kt * BN) * tsb;
     const int last = (is_ctx ? P : R) - kt * BN - 1;
-    const uint32_t dst = smem_addr + which * V_RING + (it & (NSTAGE - 1)) * C::TILE_BYTES + lwave * 1024;
+    const uint32_t slot_addr = smem_addr + which * V_RING + (it & (NSTAGE - 1)) * C::TILE_BYTES;
+    if constexpr (kSplitRow<D>) {
+#pragma unroll
+      for (int t = 0; t < IPT; ++t)
+        dma16(uniform_ptr(reinterpret_cast<const u16*>(tb)),
+              (uint32_t)(__umul24((unsigned)min(ld_row[t], last), (unsigned)tsb) + ld_coff[t]), slot_addr + (lwave * IPT + t) * 1024);
+      return;
+    }
+    const uint32_t dst = slot_addr + lwave * 1024;
     const int coff = which ? ld_vcoff : ld_kcoff;
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
@@ -165,8 +188,11 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   // over three slots so that no instruction of a slot depends on another one of the same slot.  Fences keep
   // the compiler from regrouping.  The operands of the first group are requested by the previous step
   // (`pre`), those of the next step's first group here.
-  constexpr int NS = C::KS, NPV = 2 * C::DSUB, NSLOT = NS + NPV, EPS = 16 / NSLOT, LEAD = 4, NG = NSLOT / LEAD;
-  static_assert(NS == NPV && 16 % NSLOT == 0 && NSLOT % LEAD == 0, "slot layout");
+  constexpr int NS = C::KS, NPV = 2 * C::DSUB, NSLOT = NS + NPV, LEAD = 4, NG = NSLOT / LEAD;
+  constexpr int EPS = (16 + NSLOT - 1) / NSLOT;   // most scores per slot
+  static_assert(NS == NPV && NSLOT <= 16 && NSLOT % LEAD == 0, "slot layout");
+  // the sixteen scores of a lane are spread evenly over the slots: slot i finishes scores [sc0(i), sc0(i + 1))
+  auto sc0 = [](int i) constexpr { return i < NSLOT ? 16 * i / NSLOT : 16; };
   auto k_operand = [&](const unsigned char* Kh, int ks) __attribute__((always_inline)) {
     return *reinterpret_cast<const bf16x8*>(Kh + koff[ks]);
   };
@@ -238,12 +264,12 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
 #pragma unroll
     for (int i = 0; i < LEAD; ++i) ob[i] = pre[i];
     uint32_t pw[8];
-    float tv[16 + 2 * EPS], ev[16 + EPS];
+    float tv[16], ev[16];
     float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
-    for (int e = 0; e < 2 * EPS; ++e) tv[e] = sc[e] * c - m_ref;
+    for (int e = 0; e < sc0(2); ++e) tv[e] = sc[e] * c - m_ref;
 #pragma unroll
-    for (int e = 0; e < EPS; ++e) ev[e] = __builtin_amdgcn_exp2f(tv[e]);
+    for (int e = 0; e < sc0(1); ++e) ev[e] = __builtin_amdgcn_exp2f(tv[e]);
     bool first_s = true;
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -272,16 +298,18 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
           }
         }
 #pragma unroll
-        for (int e = (g * LEAD + q) * EPS; e < (g * LEAD + q + 1) * EPS; ++e) {
-          if (e + 2 * EPS < 16) {
-            tv[e + 2 * EPS] = sc[e + 2 * EPS] * c - m_ref;
-            asm volatile("" : "+v"(tv[e + 2 * EPS]));   // (keeps this slot's softmax work inside the slot)
+        for (int j = 0; j < EPS; ++j) {
+          const int n = g * LEAD + q, e2 = sc0(n + 2) + j, e1 = sc0(n + 1) + j, e = sc0(n) + j;
+          if (e2 < sc0(n + 3)) {
+            tv[e2] = sc[e2] * c - m_ref;
+            asm volatile("" : "+v"(tv[e2]));   // (keeps this slot's softmax work inside the slot)
           }
-          if (e + EPS < 16) {
-            ev[e + EPS] = __builtin_amdgcn_exp2f(tv[e + EPS]);
-            asm volatile("" : "+v"(ev[e + EPS]));
+          if (e1 < sc0(n + 2)) {
+            ev[e1] = __builtin_amdgcn_exp2f(tv[e1]);
+            asm volatile("" : "+v"(ev[e1]));
           }
-          if (e & 1) {
+          if (e >= sc0(n + 1)) {
+          } else if (e & 1) {
             ls1 += ev[e];
             pw[e >> 1] = pack2_bf16(ev[e - 1], ev[e]);
             asm volatile("" : "+v"(pw[e >> 1]), "+v"(ls1));
@@ -370,6 +398,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   const float l = xor32_sum(l_sum);
   const float inv = 1.0f / l;
   unsigned char* ot = smem + wave * 32 * C::RB;
+  auto oswz = [](int r) { return D == 96 ? swz<96>(r) : r & (C::CPR - 1); };
 #pragma unroll
   for (int ds = 0; ds < C::DSUB; ++ds)
 #pragma unroll
@@ -377,15 +406,13 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
       u32x2 w;
       w.x = pack2_bf16(oacc[ds][r4 * 4 + 0] * inv, oacc[ds][r4 * 4 + 1] * inv);
       w.y = pack2_bf16(oacc[ds][r4 * 4 + 2] * inv, oacc[ds][r4 * 4 + 3] * inv);
-      *reinterpret_cast<u32x2*>(ot + l32 * C::RB + (((ds * 4 + r4) ^ (l32 & (C::CPR - 1))) << 4) + hi * 8) = w;
+      *reinterpret_cast<u32x2*>(ot + l32 * C::RB + (((ds * 4 + r4) ^ oswz(l32)) << 4) + hi * 8) = w;
     }
   if (hi == 0 && row < R) p.lse[(int64_t)head * p.total + b.row_begin + row] = (m_ref + log2f(l)) * LN2;
-  constexpr int RPS = 64 / C::CPR;   // rows per store instruction
-  const int chunk = lane % C::CPR;
 #pragma unroll
-  for (int i = 0; i < 32 / RPS; ++i) {
-    const int tr = i * RPS + lane / C::CPR;
-    const u32x4 w = *reinterpret_cast<const u32x4*>(ot + tr * C::RB + ((chunk ^ (tr & (C::CPR - 1))) << 4));
+  for (int i = 0; i < C::CPR / 2; ++i) {   // 64 of the tile's 32 CPR chunks per store instruction
+    const int tr = (i * 64 + lane) / C::CPR, chunk = (i * 64 + lane) % C::CPR;
+    const u32x4 w = *reinterpret_cast<const u32x4*>(ot + tr * C::RB + ((chunk ^ oswz(tr)) << 4));
     if (row0 + tr < R) {
       u16* op = p.out_o.ptr + (int64_t)(b.row_begin + row0 + tr) * p.out_o.ts + (int64_t)head * p.out_o.hs;
       *reinterpret_cast<u32x4*>(op + chunk * 8) = w;
@@ -411,6 +438,7 @@ hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st) {
   const bool local = p.window > 0;
   switch (head_dim) {
     case 64:  return local ? launch_fwd2_t<64, true>(p, st) : launch_fwd2_t<64, false>(p, st);
+    case 96:  return local ? launch_fwd2_t<96, true>(p, st) : launch_fwd2_t<96, false>(p, st);
     case 128: return local ? launch_fwd2_t<128, true>(p, st) : launch_fwd2_t<128, false>(p, st);
   }
   return hipErrorInvalidValue;

@@ -6,11 +6,11 @@
 namespace dkv {
 
 hipError_t launch_fwd(const AttnParams& p, int head_dim, hipStream_t st);
-// tuned forward for head dims 64 / 128
+// tuned forward for head dims 64 / 96 / 128
 hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dq(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv(const AttnParams& p, int head_dim, hipStream_t st);
-// tuned backward kernels for head dims 64 / 128
+// tuned backward kernels for head dims 64 / 96 / 128
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned kernels for head dim 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)

@@ -1,4 +1,4 @@
-// Un-padded, XOR-swizzled LDS tiles for head dims 64 / 128 / 256 / 512 and the LDS transpose read.
+// Un-padded, XOR-swizzled LDS tiles for head dims 64 / 96 / 128 / 192 / 256 / 512 and the LDS transpose read.
 //
 // A tile is ROWS x D bf16, row-major, 2*D bytes per row, made of 16-byte chunks.  Chunk c of row r is
 // stored at chunk position c ^ swz<D>(r).  The swizzle makes all three access patterns used by the
@@ -25,12 +25,28 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 template <int D>
 __device__ __forceinline__ int swz(int row) {
-  static_assert(D == 64 || D == 128 || D == 256 || D == 512, "swizzle defined for 64 / 128 / 256 / 512");
+  static_assert(D == 64 || D == 96 || D == 128 || D == 192 || D == 256 || D == 512, "swizzle defined for these head dims");
   // (the 512- and 1024-byte rows of head dims 256 and 512 span several bank lines: the chunk index bits from 4 on
   // do not select a bank)
-  if (D >= 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+  // The 192- and 384-byte rows of head dims 96 and 192 are not powers of two, but row r starts 4 (-r mod 4) resp.
+  // 8 (r mod 2) chunks into a 256-byte bank line, which separates four (two) consecutive rows by itself; the XOR of the
+  // lowest two (three) chunk bits separates the others and stays inside the row's 12 = 3 x 4 (24 = 3 x 8) chunks.
+  if (D == 96) return (row >> 2) & 3;
+  if (D == 128 || D == 256 || D == 512) return ((row & 3) << 2) | ((row >> 2) & 3);
   return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
 }
+
+// Rows that do not divide the 1 KB of a global -> LDS load instruction (head dims 96 and 192): lane l of the t-th
+// consecutive instruction lands at 16-byte unit 64 t + l, i.e. chunk position (64 t + l) % CPR of row (64 t + l) / CPR.
+// Three instructions cover kSplitRows<D> whole rows (16 or 8), and the pattern of rows and chunk positions repeats.
+template <int D>
+constexpr bool kSplitRow = 1024 % (2 * D) != 0;
+template <int D>
+constexpr int kSplitRows = 3 * 64 / (D / 8);
+template <int D>
+__device__ __forceinline__ int split_row(int t, int lane) { return (64 * (t % 3) + lane) / (D / 8) + (t / 3) * kSplitRows<D>; }
+template <int D>
+__device__ __forceinline__ int split_pos(int t, int lane) { return (64 * (t % 3) + lane) % (D / 8); }
 
 // byte offset of chunk `chunk` of row `row` inside a tile
 template <int D>
