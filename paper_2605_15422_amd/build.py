@@ -9,15 +9,9 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdualkv.so")
-SOURCES = ["api.hip", "qstat.hip", "fwd2.hip", "dq2.hip", "dkdv4.hip", "fwd256.hip", "dq256.hip", "dkdv256.hip", "dkdv512.hip", "dq512.hip", "fwd512.hip", "kvstat.hip", "aux.hip"]
+SOURCES = ["api.hip", "fwd2.hip", "dq2.hip", "dkdv4.hip", "fwd256.hip", "dq256.hip", "dkdv256.hip", "dkdv512.hip", "dq512.hip", "fwd512.hip", "aux.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-inline-asm"]
-
-
-# The generic kernels run four waves of up to 512 registers at some head dims.  There the compiler's default puts MFMA
-# results in the accumulation half of the register file and copies them back and forth for the vector ALU (256 copies
-# per tile in the d = 256 dQ kernel); with the MFMAs in their VGPR form it allocates the two halves itself (8 % faster).
-PER_FILE_FLAGS = {"qstat.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"], "kvstat.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _hipcc() -> str:
@@ -35,7 +29,7 @@ def build(verbose: bool = True, extra_flags=()) -> str:
 
     def compile_one(src):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, *PER_FILE_FLAGS.get(src, []), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))

@@ -147,21 +147,18 @@ int hip_rc(hipError_t e) { return e == hipSuccess ? DUALKV_OK : DUALKV_E_HIP; }
 
 hipError_t run_fwd(const AttnParams& p, int d, hipStream_t st) {
   if (d <= 128) return dkv::launch_fwd2(p, d, st);
-  if (d == 256) return dkv::launch_fwd256(p, st);
-  if (d == 512) return dkv::launch_fwd512(p, st);
-  return dkv::launch_fwd(p, d, st);
+  if (d <= 256) return dkv::launch_fwd256(p, d, st);
+  return dkv::launch_fwd512(p, st);
 }
 hipError_t run_dq(const AttnParams& p, int d, hipStream_t st) {
   if (d <= 128) return dkv::launch_dq2(p, d, st);
-  if (d == 256) return dkv::launch_dq256(p, st);
-  if (d == 512) return dkv::launch_dq512(p, st);
-  return dkv::launch_dq(p, d, st);
+  if (d <= 256) return dkv::launch_dq256(p, d, st);
+  return dkv::launch_dq512(p, st);
 }
 hipError_t run_dkdv(const AttnParams& p, int d, hipStream_t st) {
   if (d <= 128) return dkv::launch_dkdv4(p, d, st);
-  if (d == 256) return dkv::launch_dkdv256(p, st);
-  if (d == 512) return dkv::launch_dkdv512(p, st);
-  return dkv::launch_dkdv(p, d, st);
+  if (d <= 256) return dkv::launch_dkdv256(p, d, st);
+  return dkv::launch_dkdv512(p, st);
 }
 
 void base_params(AttnParams& p, const dualkv_shape* s) {

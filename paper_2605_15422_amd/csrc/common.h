@@ -8,7 +8,7 @@
 // Because the contraction index only has to agree between A and B, an accumulator tile can be fed
 // back as the K-indexed operand of the next MFMA without leaving registers: registers 8t..8t+7 of a
 // C tile are 16 distinct rows {16t + 8a + 4*(l/32) + c}, and the matching operand of the other
-// matrix is stored in LDS with the same permutation of the contraction index ("kperm" below).
+// matrix is read from LDS with the same permutation of the contraction index (the row pairs of tr_pair).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -77,92 +77,6 @@ __device__ __forceinline__ float xor32_sum(float x) {
 
 // Row of a C tile held in register r by this lane.
 __device__ __forceinline__ int crow(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
-
-// Position of contraction index k (0..ROWS-1) inside a "kperm" LDS row: within every group of 16 the
-// two middle groups of four are swapped, so that the eight indices one lane needs are contiguous.
-__device__ __forceinline__ int kperm4(int k4) {  // k4 = k / 4
-  return (k4 & ~3) | ((k4 & 1) << 1) | ((k4 >> 1) & 1);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Cooperative global -> register -> LDS tile staging.
-// A tile is ROWS x D bf16 taken from `ROWS` consecutive token rows of one head.  Thread t owns
-// "units" of 4 rows x 8 columns (four 16-byte loads), so it can write both the row-major image
-// (4 x 16 B) and the transposed, kperm-ordered image (8 x 8 B) without any cross-lane traffic.
-// Consecutive threads take consecutive row quads of one 8-column chunk: their 8-byte writes into the
-// transposed image are then contiguous within an image row (with consecutive chunks per thread they land
-// eight image rows apart, on two banks: the transposed stores then cost 40 % of the head-dim-512 dK/dV kernel).
-// ---------------------------------------------------------------------------------------------
-template <int ROWS, int D, int NT>
-struct TileRegs {
-  static constexpr int CH = D / 8;                       // 16-byte chunks per row
-  static constexpr int RQ = ROWS / 4;                    // row quads; consecutive threads take consecutive quads
-  static constexpr int NUNITS = (ROWS / 4) * CH;
-  static constexpr int UPT = (NUNITS + NT - 1) / NT;     // units per thread
-  u32x4 v[UPT][4];
-
-  // base: pointer to (row 0, column 0) of the tile (the same for every thread); rows >= nvalid are zero-filled.
-  // Addresses are the uniform base plus a 32-bit byte offset per thread (token strides are bounded by the API),
-  // one register per load instead of a 64-bit pointer pair: with pointer pairs the d = 512 dQ kernel spilled them
-  // and waited for each load before it could issue the next.
-  __device__ __forceinline__ void load(const u16* base, int64_t tok_stride, int nvalid, int tid) {
-    const unsigned char* b8 = reinterpret_cast<const unsigned char*>(base);
-    const uint32_t sb = (uint32_t)tok_stride * 2u;
-#pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      const int unit = tid + u * NT;
-      const int rq = unit % RQ, ch = unit / RQ;
-      uint32_t off0 = (uint32_t)(rq * 4) * sb + (uint32_t)(ch * 16);
-      asm volatile("" : "+v"(off0));   // keeps the zero extension next to the load (base + 32-bit offset form)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = rq * 4 + j;
-        u32x4 z = {0u, 0u, 0u, 0u};
-        if ((NUNITS % NT == 0 || unit < NUNITS) && row < nvalid)
-          z = *reinterpret_cast<const u32x4*>(b8 + (off0 + (uint32_t)j * sb));
-        v[u][j] = z;
-      }
-    }
-  }
-
-  // row-major image: lds[row][col], pitch in elements (multiple of 8)
-  __device__ __forceinline__ void store_rowmajor(u16* lds, int pitch, int tid) const {
-#pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      const int unit = tid + u * NT;
-      if (NUNITS % NT != 0 && unit >= NUNITS) continue;
-      const int rq = unit % RQ, ch = unit / RQ;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<u32x4*>(lds + (rq * 4 + j) * pitch + ch * 8) = v[u][j];
-    }
-  }
-
-  // transposed image: lds[col][kperm(row)], pitch in elements (multiple of 4)
-  __device__ __forceinline__ void store_transposed(u16* lds, int pitch, int tid) const {
-#pragma unroll
-    for (int u = 0; u < UPT; ++u) {
-      const int unit = tid + u * NT;
-      if (NUNITS % NT != 0 && unit >= NUNITS) continue;
-      const int rq = unit % RQ, ch = unit / RQ;
-      const int pos = kperm4(rq) * 4;
-      const uint32_t* w0 = reinterpret_cast<const uint32_t*>(&v[u][0]);
-      const uint32_t* w1 = reinterpret_cast<const uint32_t*>(&v[u][1]);
-      const uint32_t* w2 = reinterpret_cast<const uint32_t*>(&v[u][2]);
-      const uint32_t* w3 = reinterpret_cast<const uint32_t*>(&v[u][3]);
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        u32x2 lo, hi;
-        lo.x = (w0[m] & 0xffffu) | (w1[m] << 16);
-        lo.y = (w2[m] & 0xffffu) | (w3[m] << 16);
-        hi.x = (w0[m] >> 16) | (w1[m] & 0xffff0000u);
-        hi.y = (w2[m] >> 16) | (w3[m] & 0xffff0000u);
-        *reinterpret_cast<u32x2*>(lds + (ch * 8 + 2 * m) * pitch + pos) = lo;
-        *reinterpret_cast<u32x2*>(lds + (ch * 8 + 2 * m + 1) * pitch + pos) = hi;
-      }
-    }
-  }
-};
 
 // A bf16 tensor view: element strides.
 struct TView {

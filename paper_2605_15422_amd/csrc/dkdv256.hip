@@ -1,4 +1,4 @@
-// dK / dV kernel for head dim 256 with producer / consumer wave specialisation (the mathematics, the
+// dK / dV kernel for head dims 192 and 256 with producer / consumer wave specialisation (the mathematics, the
 // ownership rule and the row-block schedule of the head-dim 64 / 128 kernel: one workgroup owns a key tile of
 // one KV head; a shared-prompt tile sums the contributions of ALL sequences and heads of the group in fp32
 // registers and is cast once -- Alg. 1 with the race of the shared prompt gradients removed by ownership).
@@ -20,6 +20,11 @@
 //     blocks ahead into four stages of 32 rows and leave a 16-byte header per key subtile and stage;
 //   * the main loop is unrolled over the four stages (immediate LDS offsets), one barrier per row block.
 // LDS: 4 x (16 KB Q + 16 KB dO + statistics + headers) + 2 x 8 KB exchange = 145 KB.
+//
+// Head dim 192 has six head-dim blocks: consumer waves 4-6 own blocks c and c + 3 and only accumulate, the fourth (wave 7)
+// owns none and is the loader: schedule, headers and all 25 requests of a row block, in a loop that keeps the stage as an
+// offset in a register instead of unrolling.  On N = 8, P = 4096, R ~ U(131, 2048), 12 / 4 heads: 0.95 + 0.28 ms (Call 2 +
+// Call 1), against 3.53 + 1.10 ms for the register-staged kernel that served this head dim before.
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
@@ -38,27 +43,39 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-constexpr int D = 256;
 constexpr int BN = 64, HB = 32, NKS = BN / 32;   // keys per workgroup, query rows per block, key subtiles
 static_assert(NKS == 2, "the header store selects between two subtiles");
-constexpr int KS = D / 32;                       // k-steps of the 16x16x32 MFMA
-constexpr int RB = 2 * D, CPR = D / 8;
-constexpr int HT_BYTES = HB * RB;                // one Q or dO row block
-constexpr int STAT_OFF = 2 * HT_BYTES;           // lse2[32] | D[32]
-constexpr int HDR_OFF = STAT_OFF + 256;          // NKS x {flags, row0, nvalid, -}
-constexpr int STAGE_BYTES = HDR_OFF + 64;
 constexpr int NBUF = 4, AHEAD = NBUF - 1;        // row blocks requested ahead of the one being computed
-constexpr int XCH_OFF = NBUF * STAGE_BYTES;
 constexpr int XCH_BYTES = NKS * 4096;            // [key subtile][P k-step 0,1 | dS k-step 0,1][lane] x 16 B
-constexpr int SMEM_BYTES = XCH_OFF + 2 * XCH_BYTES;
-constexpr int NIT = HT_BYTES / 1024;             // 1 KB load instructions per row block and tensor
-constexpr int IPB = 2 * NIT / 4;                 // per consumer wave (Q and dO)
-constexpr int RPI = 1024 / RB;                   // rows per load instruction
-constexpr int HALF = (NBUF / 2) * STAGE_BYTES;   // second base register of every LDS operand (16-bit offset field)
-static_assert(NBUF % 2 == 0 && STAGE_BYTES + HT_BYTES + 16 * RB + 512 < 65536, "immediate offsets");
 
-template <bool LOCAL>
+template <int D>
+struct Cfg {
+  static constexpr bool LOADER = kSplitRow<D>;   // one consumer wave makes all requests and owns no accumulator
+  static constexpr int KS = D / 32;              // k-steps of the 16x16x32 MFMA
+  static constexpr int RB = 2 * D, CPR = D / 8;
+  static constexpr int HT_BYTES = HB * RB;       // one Q or dO row block
+  static constexpr int STAT_OFF = 2 * HT_BYTES;  // lse2[32] | D[32]
+  static constexpr int HDR_OFF = STAT_OFF + 256; // NKS x {flags, row0, nvalid, -}
+  static constexpr int STAGE_BYTES = HDR_OFF + 64;
+  static constexpr int XCH_OFF = NBUF * STAGE_BYTES;
+  static constexpr int SMEM_BYTES = XCH_OFF + 2 * XCH_BYTES;
+  static constexpr int NIT = HT_BYTES / 1024;    // 1 KB load instructions per row block and tensor
+  static constexpr int IPB = LOADER ? 2 * NIT : 2 * NIT / 4;   // per requesting wave (Q and dO)
+  static constexpr int RPI = 1024 / RB;          // rows per load instruction
+  static constexpr int HALF = (NBUF / 2) * STAGE_BYTES;   // second base register of every LDS operand (16-bit offset field)
+  static_assert(NBUF % 2 == 0 && STAGE_BYTES + HT_BYTES + 16 * RB + 512 < 65536, "immediate offsets");
+  static constexpr int NFB = LOADER ? 2 : 4;     // base registers of the fragment reads (see fr_lo)
+  static constexpr int EBLK = D / 64;            // a consumer wave owns head-dim blocks jb and jb + EBLK
+};
+
+template <int D, bool LOCAL>
 __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
+  using C = Cfg<D>;
+  constexpr bool LOADER = C::LOADER;
+  constexpr int KS = C::KS, RB = C::RB, CPR = C::CPR, HT_BYTES = C::HT_BYTES, STAT_OFF = C::STAT_OFF, HDR_OFF = C::HDR_OFF;
+  constexpr int STAGE_BYTES = C::STAGE_BYTES, XCH_OFF = C::XCH_OFF, NIT = C::NIT, IPB = C::IPB, RPI = C::RPI;
+  constexpr int HALF = C::HALF, NFB = C::NFB, EBLK = C::EBLK;
+  constexpr int LOAD_WAVE = 7, HDR_WAVE = LOADER ? LOAD_WAVE : 4, STAT_WAVE = 5;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -144,13 +161,15 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     // Q / dO fragment of k-step ks: row rh*16 + l16, chunk 4 ks + cg.  With the tile swizzle (low two row bits
     // into chunk bits 2-3, row bits 2-3 into chunk bits 0-1) the chunk position is
     // 4 ((ks % 4) ^ (row % 4)) + (cg ^ (row / 4 % 4)) + 16 (ks / 4): four base registers serve all eight k-steps.
+    // At head dim 192 (row bit 1 into chunk bit 2) it is 4 ((ks % 2) ^ (row / 2 % 2)) + (cg ^ (row / 4 % 4)) + 8 (ks / 2).
     const int frow = rh * 16 + l16;
-    const unsigned char* fr_lo[4];
+    const int fsel = LOADER ? (frow >> 1) & 1 : frow & 3;
+    const unsigned char* fr_lo[NFB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fr_lo[j] = smem + frow * RB + 64 * (j ^ (frow & 3)) + 16 * (cg ^ ((frow >> 2) & 3));
-    const unsigned char* fr_hi[4];
+    for (int j = 0; j < NFB; ++j) fr_lo[j] = smem + frow * RB + 64 * (j ^ fsel) + 16 * (cg ^ ((frow >> 2) & 3));
+    const unsigned char* fr_hi[NFB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fr_hi[j] = fr_lo[j] + HALF;
+    for (int j = 0; j < NFB; ++j) fr_hi[j] = fr_lo[j] + HALF;
     const unsigned char* stat_lo = smem + STAT_OFF + (rh * 16 + 4 * g) * 4;   // this lane's rows rh*16 + 4 g + r
     const unsigned char* stat_hi = stat_lo + HALF;
     const unsigned char* hdr_lo = smem + HDR_OFF + kvs * 16;
@@ -170,9 +189,9 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       constexpr int U = decltype(Uc)::value;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const unsigned char* b = U >= NBUF / 2 ? fr_hi[ks & 3] : fr_lo[ks & 3];
+        const unsigned char* b = U >= NBUF / 2 ? fr_hi[ks % NFB] : fr_lo[ks % NFB];
         out[ks] = *reinterpret_cast<const bf16x8*>(b + (U % (NBUF / 2)) * STAGE_BYTES + decltype(which)::value * HT_BYTES +
-                                                   (ks >> 2) * 256);
+                                                   ks / NFB * (NFB * 64));
       }
     };
     auto load_stat = [&](auto Uc, int which) __attribute__((always_inline)) {
@@ -307,8 +326,22 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     // per-lane global offsets of this wave's load instructions for a block of 32 valid rows (a partial last
     // block clamps its rows instead: rare, computed on the spot)
     uint32_t voff_full[IPB];
+    int sp_row[3], sp_coff[3];   // (loader) row and byte offset of instructions t, t + 3, ... (8 rows apart)
+    if constexpr (LOADER) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        sp_row[t] = split_row<D>(t, lane);
+        sp_coff[t] = (split_pos<D>(t, lane) ^ swz<D>(sp_row[t])) * 16;
+      }
+    }
 #pragma unroll
     for (int t = 0; t < IPB; ++t) {
+      if constexpr (LOADER) {
+        const int tt = t % NIT;
+        voff_full[t] = (uint32_t)((sp_row[tt % 3] + tt / 3 * kSplitRows<D>) * (t < NIT ? q_ts : do_ts) * 2 +
+                                  (sp_coff[tt % 3] ^ ((tt / 3 & 1) * 32)));
+        continue;
+      }
       const int tt = t % (IPB / 2);
       voff_full[t] = (uint32_t)((ld_row0 + tt * 4 * RPI) * (t < IPB / 2 ? q_ts : do_ts) * 2 + (ld_coff ^ ((tt & 1) * 32)));
     }
@@ -317,6 +350,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     // unsigned 32-bit lane offset addresses both
     const float* stat_ptr = p.dvec;
     const uint32_t stat_lane_off = hi ? 0u : (uint32_t)((const char*)p.lse2 - (const char*)p.dvec);
+    const float* stat_lane = hi ? p.dvec : p.lse2;   // (the loader uses 64-bit lane addresses)
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
     // blocks of 32 that see at least one key of the tile, query heads of the group innermost.  All state is
@@ -328,7 +362,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
     int64_t st_row = 0, st_cur = 0;
     bool more = false;
-    uint32_t gflags[NKS] = {};   // wave 4: flags of the key subtiles for the current row group
+    uint32_t gflags[NKS] = {};   // header wave: flags of the key subtiles for the current row group
     // Row blocks [plain_lo, plain_hi) (first rows) of a windowed run see every key of the tile, none masked: in the response
     // region those whose first row is at or past the tile's last key and whose last row is still inside the window of its
     // first key; in the prompt region (every response row is past every prompt key) only the window bounds them.
@@ -346,7 +380,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
         st_cur = st_row;
         g = 0;
       }
-      if (wave == 4) {
+      if (wave == HDR_WAVE) {
         // most row blocks see every key of the tile: two comparisons settle them
         if (LOCAL && row0 >= plain_lo && row0 < plain_hi && nvalid == HB) {
 #pragma unroll
@@ -425,23 +459,23 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     int ib_last = 0;
     // requests the next block of the schedule (or marks the end) in stage IS and advances the schedule; without its
     // loads if the caller issues them itself (issue_one)
-    auto issue_block = [&](auto ISc, auto with_loads) __attribute__((always_inline)) {
+    auto issue_block = [&](auto ISc, auto with_loads, uint32_t stage_off = 0) __attribute__((always_inline)) {
       constexpr int IS = decltype(ISc)::value;
       constexpr bool LOADS = decltype(with_loads)::value;
-      if (wave == 4 && lane < NKS) {
+      if (wave == HDR_WAVE && lane < NKS) {
         u32x4 h;
         h.x = more ? (lane == 0 ? gflags[0] : gflags[1]) : 0u;
         h.y = (uint32_t)row0;
         h.z = (uint32_t)nvalid;
         h.w = 0u;
-        *reinterpret_cast<u32x4*>(smem + IS * STAGE_BYTES + HDR_OFF + lane * 16) = h;
+        *reinterpret_cast<u32x4*>(smem + stage_off + IS * STAGE_BYTES + HDR_OFF + lane * 16) = h;
       }
       vbits = (vbits << 1) | (more ? 1u : 0u);
       if (__builtin_expect(more, 1)) {
         const int last = nvalid - 1;   // rows past the end of the sequence re-read its last row
         const u16* q_base = uniform_ptr(q_cur);
         const u16* do_base = uniform_ptr(do_cur);
-        if constexpr (LOCAL) {
+        if constexpr (LOCAL && !LOADER) {
           ib_last = last;
           ib_q = q_base;
           ib_do = do_base;
@@ -449,6 +483,22 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
         }
         // (one branch for the whole block, not one per load)
         if constexpr (!LOADS) {
+        } else if constexpr (LOADER) {
+          if (__builtin_expect(nvalid == HB, 1)) {
+            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
+              constexpr int t = decltype(Tc)::value;
+              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff_full[t], smem_addr + stage_off);
+            });
+          } else {
+            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
+              constexpr int t = decltype(Tc)::value, tt = t % NIT;
+              const int row = sp_row[tt % 3] + tt / 3 * kSplitRows<D>;
+              const uint32_t voff = __umul24((unsigned)min(row, last), (unsigned)((t < NIT ? q_ts : do_ts) * 2)) +
+                                    (uint32_t)(sp_coff[tt % 3] ^ ((tt / 3 & 1) * 32));
+              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff, smem_addr + stage_off);
+            });
+          }
+          dma4_from<IS * STAGE_BYTES + STAT_OFF>(stat_lane + st_cur + min(l32, last), smem_addr + stage_off);
         } else if (__builtin_expect(nvalid == HB, 1)) {
           static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
             constexpr int t = decltype(Tc)::value;
@@ -466,7 +516,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
             dma16_at<IS * STAGE_BYTES + (is_q ? 0 : HT_BYTES) + tt * 4096>(is_q ? q_base : do_base, voff, ld_lds);
           });
         }
-        if (LOADS && wave == 5) {
+        if (!LOADER && LOADS && wave == STAT_WAVE) {
           dma4_at<IS * STAGE_BYTES + STAT_OFF>(uniform_ptr(reinterpret_cast<const u16*>(stat_ptr + st_cur)),
                                                stat_lane_off + (uint32_t)min(l32, last) * 4u, smem_addr);
         }
@@ -511,7 +561,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       const int over = max(ld_row0 + tt * 4 * RPI - ib_last, 0);   // rows past the last valid one step back to it
       const uint32_t voff = (uint32_t)__mul24(over, is_q ? q_neg : do_neg) + voff_full[t];
       dma16_at<IS * STAGE_BYTES + (is_q ? 0 : HT_BYTES) + tt * 4096>(is_q ? ib_q : ib_do, voff, ld_lds);
-      if (t == IPB - 1 && wave == 5)
+      if (t == IPB - 1 && wave == STAT_WAVE)
         dma4_at<IS * STAGE_BYTES + STAT_OFF>(ib_stat, stat_lane_off + (uint32_t)min(l32, ib_last) * 4u, smem_addr);
     };
     // Block b is requested AHEAD blocks early and must have landed by the end of interval b - 2 (the
@@ -519,19 +569,38 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     // issues one more, for it the bound is a little stricter) may stay in flight.  If the newest request was
     // the end mark, fewer loads are outstanding: wait for all of them.
     auto wait_loads = [&]() __attribute__((always_inline)) {
-      wait_vm<(AHEAD - 2) * IPB>();
+      wait_vm<(AHEAD - 2) * (IPB + (LOADER ? 1 : 0))>();
       if (__builtin_expect(!(vbits & 1u), 0)) wait_vm<0>();
     };
 
-    for (; seq < seq_hi; ++seq) {
-      init_seq();
-      if (rb < rb_end) {
-        more = true;
-        enter_group();
-        break;
+    if (!LOADER || wave == LOAD_WAVE) {
+      for (; seq < seq_hi; ++seq) {
+        init_seq();
+        if (rb < rb_end) {
+          more = true;
+          enter_group();
+          break;
+        }
       }
     }
-    if (LOCAL && !more) {
+    if (LOADER && wave == LOAD_WAVE) {
+      // (not unrolled over the stages: this wave has time for a stage offset in a register, and the code stays short)
+#pragma nounroll
+      for (int i = 0; i < AHEAD; ++i) issue_block(IC<0>{}, std::true_type{}, i * STAGE_BYTES);
+      wait_loads();
+      __syncthreads();   // row blocks 0 and 1 and their headers are in LDS
+      uint32_t stage_off = AHEAD * STAGE_BYTES;
+      bool cur = true;
+      while (cur) {
+        issue_block(IC<0>{}, std::true_type{}, stage_off);
+        stage_off = stage_off == AHEAD * STAGE_BYTES ? 0 : stage_off + STAGE_BYTES;
+        cur = vbits & (1u << AHEAD);
+        wait_loads();
+        __syncthreads();
+      }
+      return;
+    }
+    if (LOCAL && !LOADER && !more) {
       // No row block at all: the windowed main loop issues its loads unconditionally and would have no valid address.
       // One empty header ends the producers' schedule after one interval; the gradient of these keys is zero.
       if (wave == 4 && lane < NKS) *reinterpret_cast<u32x4*>(smem + HDR_OFF + lane * 16) = u32x4{0u, 0u, 0u, 0u};
@@ -551,13 +620,15 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       }
       return;
     }
-    issue_block(IC<0>{}, std::true_type{});
-    issue_block(IC<1>{}, std::true_type{});
-    issue_block(IC<2>{}, std::true_type{});
-    wait_loads();
+    if constexpr (!LOADER) {
+      issue_block(IC<0>{}, std::true_type{});
+      issue_block(IC<1>{}, std::true_type{});
+      issue_block(IC<2>{}, std::true_type{});
+      wait_loads();
+    }
 
-    // Each consumer wave owns the head-dim blocks jb and jb + 4 (128 columns apart: the same swizzled chunk
-    // position, 256 bytes further) of both key subtiles; the transposed Q / dO operands of a head-dim block are
+    // Each accumulating consumer wave owns the head-dim blocks jb and jb + EBLK (at head dim 256, 128 columns apart: the
+    // same swizzled chunk position, 256 bytes further) of both key subtiles; the transposed Q / dO operands of a head-dim block are
     // shared by the two subtiles.
     f32x16 dk[NKS][2], dv[NKS][2];
 #pragma unroll
@@ -569,13 +640,19 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
           dk[i][db][r] = 0.f;
           dv[i][db][r] = 0.f;
         }
-    const unsigned char* tr0_lo = smem + tr_off<D>(lane, hi * 4, jb * 32);
-    const unsigned char* tr1_lo = smem + tr_off<D>(lane, hi * 4 + 8, jb * 32);
-    const unsigned char* tr0_hi = tr0_lo + HALF;
-    const unsigned char* tr1_hi = tr1_lo + HALF;
+    const unsigned char *tr0_lo[2], *tr1_lo[2], *tr0_hi[2], *tr1_hi[2];
+#pragma unroll
+    for (int db = 0; db < 2; ++db) {
+      tr0_lo[db] = smem + (LOADER ? tr_off<D>(lane, hi * 4, (jb + db * EBLK) * 32) : tr_off<D>(lane, hi * 4, jb * 32) + db * 256);
+      tr1_lo[db] =
+          smem + (LOADER ? tr_off<D>(lane, hi * 4 + 8, (jb + db * EBLK) * 32) : tr_off<D>(lane, hi * 4 + 8, jb * 32) + db * 256);
+      tr0_hi[db] = tr0_lo[db] + HALF;
+      tr1_hi[db] = tr1_lo[db] + HALF;
+    }
     const unsigned char* xr_lane = smem + XCH_OFF + lane * 16;
+    bool prev = false;              // (with a loader wave) block h - 1 exists
     bf16x8 tq[2][2], tdo[2][2];   // [k-step][head-dim block]: Q^T, dO^T operands of the row block accumulated next interval
-    if constexpr (LOCAL) {
+    if constexpr (LOCAL && !LOADER) {
       // The windowed loop accumulates in every interval, also in the first one, where there is no block yet: zero operands,
       // in the registers and in the exchange buffer that the producers fill in the second interval (every consumer clears
       // exactly the bytes it reads: no barrier needed)
@@ -600,8 +677,10 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       // window, where the schedule costs more scalar work per block, one request behind each MFMA pair measured faster
       // (a wave waits at a load until the memory pipeline takes it, and the MFMAs run meanwhile); the MFMAs are then not
       // conditional (a branch around them and the loads makes the compiler copy the accumulators).
-      issue_block(IC<IS>{}, std::integral_constant<bool, !LOCAL>{});
-      if (LOCAL || (vbits & (1u << (AHEAD + 1)))) {
+      uint32_t hdr = 0;
+      if constexpr (LOADER) hdr = *reinterpret_cast<const uint32_t*>(smem + HDR_OFF + U * STAGE_BYTES);
+      else issue_block(IC<IS>{}, std::integral_constant<bool, !LOCAL>{});
+      if (LOADER ? prev : LOCAL || (vbits & (1u << (AHEAD + 1)))) {
         const unsigned char* xr = xr_lane + XB * XCH_BYTES;
         // all P / -dS operands are requested before the first MFMA
         bf16x8 pa[2][NKS], dsa[2][NKS];
@@ -613,7 +692,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
             dsa[t2][i] = *reinterpret_cast<const bf16x8*>(xr + i * 4096 + (2 + t2) * 1024);
           }
         __builtin_amdgcn_sched_barrier(0);
-        if constexpr (LOCAL) {
+        if constexpr (LOCAL && !LOADER) {
           static_assert(IPB == 4 * NKS, "one load instruction per MFMA pair");
           static_for<IPB>([&](auto Nc) __attribute__((always_inline)) {
             constexpr int n = decltype(Nc)::value, t2 = n / (2 * NKS), db = (n / NKS) % 2, i = n % NKS;
@@ -636,19 +715,20 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
           __builtin_amdgcn_sched_barrier(0);
         }
       }
-      const bool cur = vbits & (1u << AHEAD);
+      const bool cur = LOADER ? (__builtin_amdgcn_readfirstlane((int)hdr) & HDR_VALID) != 0 : (vbits & (1u << AHEAD)) != 0;
       if (__builtin_expect(cur, 1)) {
-        const unsigned char* t0 = (U < NBUF / 2 ? tr0_lo : tr0_hi) + (U % (NBUF / 2)) * STAGE_BYTES;
-        const unsigned char* t1 = (U < NBUF / 2 ? tr1_lo : tr1_hi) + (U % (NBUF / 2)) * STAGE_BYTES;
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
           for (int db = 0; db < 2; ++db) {
-            tdo[t2][db] = tr_pair(t0 + HT_BYTES + t2 * 16 * RB + db * 256, t1 + HT_BYTES + t2 * 16 * RB + db * 256);
-            tq[t2][db] = tr_pair(t0 + t2 * 16 * RB + db * 256, t1 + t2 * 16 * RB + db * 256);
+            const unsigned char* t0 = (U < NBUF / 2 ? tr0_lo[db] : tr0_hi[db]) + (U % (NBUF / 2)) * STAGE_BYTES;
+            const unsigned char* t1 = (U < NBUF / 2 ? tr1_lo[db] : tr1_hi[db]) + (U % (NBUF / 2)) * STAGE_BYTES;
+            tdo[t2][db] = tr_pair(t0 + HT_BYTES + t2 * 16 * RB, t1 + HT_BYTES + t2 * 16 * RB);
+            tq[t2][db] = tr_pair(t0 + t2 * 16 * RB, t1 + t2 * 16 * RB);
           }
       }
-      wait_loads();
+      if constexpr (LOADER) prev = cur;
+      else wait_loads();
       __syncthreads();
       return cur;
     };
@@ -670,7 +750,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     for (int i = 0; i < NKS; ++i)
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
-        const int dcol = (jb + 4 * db) * 32 + l32;
+        const int dcol = (jb + EBLK * db) * 32 + l32;
         const f32x16 gks = dk[i][db], gvs = dv[i][db];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -694,28 +774,34 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
   }
 }
 
-template <bool LOCAL>
+template <int D, bool LOCAL>
 hipError_t launch_t(AttnParams p, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
-  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset
-  if (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
-      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32))
+  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 192 does not)
+  if (!Cfg<D>::LOADER && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
+      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  hipError_t e = ensure_dynamic_lds<dkdv256_kernel<LOCAL>>(SMEM_BYTES);
+  hipError_t e = ensure_dynamic_lds<dkdv256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
                        (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
   if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(dkdv256_kernel<LOCAL>, dim3((unsigned)nblk), dim3(512), SMEM_BYTES, st, p);
+  auto kern = dkdv256_kernel<D, LOCAL>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), Cfg<D>::SMEM_BYTES, st, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_dkdv256(const AttnParams& p, hipStream_t st) {
-  return p.window > 0 ? launch_t<true>(p, st) : launch_t<false>(p, st);
+hipError_t launch_dkdv256(const AttnParams& p, int head_dim, hipStream_t st) {
+  const bool local = p.window > 0;
+  switch (head_dim) {
+    case 192: return local ? launch_t<192, true>(p, st) : launch_t<192, false>(p, st);
+    case 256: return local ? launch_t<256, true>(p, st) : launch_t<256, false>(p, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace dkv

@@ -1,4 +1,4 @@
-// dQ kernel for head dims 64, 96 and 128, tuned variant (same mathematics as the generic dq_kernel):
+// dQ kernel for head dims 64, 96 and 128, tuned variant:
 //   dQ = scale * dS K,  dS = P * (dP - D),  P = exp(scale * Q K^T - LSE),  dP = dO V^T     (Alg. 1)
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.

@@ -1,4 +1,4 @@
-// dQ kernel for head dim 256 with producer / consumer wave specialisation:
+// dQ kernel for head dims 192 and 256 with producer / consumer wave specialisation:
 //   dQ = scale * dS K,  dS = P * (dP - D),  P = exp(scale * Q K^T - LSE),  dP = dO V^T     (Alg. 1)
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), dQ
 // accumulated in registers and written once, as in the head-dim 64 / 128 kernel.
@@ -16,6 +16,9 @@
 //     stages, and read their K^T operands one interval early, so that a stage is free again after one interval.
 // Each SIMD runs one producer and one consumer: 48 MFMAs per 32-key tile and one barrier.
 // LDS: 4 x (16 KB K + 16 KB V) + 2 x 8 KB exchange = 144 KB.
+// Head dim 192: consumer waves 4-6 own head-dim blocks c and c + 3, wave 7 makes all requests, as in the forward kernel.
+// On N = 8, P = 4096, R ~ U(131, 2048), 12 / 4 heads: 0.61 + 0.13 ms (Call 2 + Call 1), against 1.62 + 0.35 ms for the
+// register-staged kernel that served it before.
 #include "common.h"
 #include "dma.h"
 #include "launch.h"
@@ -25,21 +28,32 @@
 namespace dkv {
 namespace {
 
-constexpr int D = 256;
 constexpr int BN = 32, NSUB = 4;                 // keys per tile, 32-row subtiles per workgroup
-constexpr int KS = D / 16, RB = 2 * D, CPR = D / 8;
-constexpr int TILE_BYTES = BN * RB;
-constexpr int NSTAGE = 4, STAGE_BYTES = 2 * TILE_BYTES;   // K tile | V tile
-constexpr int XCH_OFF = NSTAGE * STAGE_BYTES;
+constexpr int NSTAGE = 4;                        // LDS stages of a K tile and a V tile
 constexpr int XCH_BYTES = NSUB * 2048;           // [subtile][k-step 0,1][lane] x 16 B
-constexpr int SMEM_BYTES = XCH_OFF + 2 * XCH_BYTES;
-constexpr int OUT_RS = RB + 16;                  // row stride of the output tile staged in LDS (rows 4 banks apart)
-static_assert(NSUB * 32 * OUT_RS <= XCH_OFF, "the output tile fits the stages");
-constexpr int IPT = TILE_BYTES / 1024 / 4;       // 1 KB load instructions per consumer wave, tile and tensor
-constexpr int RPI = 1024 / RB;                   // rows per load instruction
+template <int D>
+struct Cfg {
+  static constexpr bool LOADER = kSplitRow<D>;   // one consumer wave makes all requests and owns no accumulator
+  static constexpr int KS = D / 16, RB = 2 * D, CPR = D / 8;
+  static constexpr int TILE_BYTES = BN * RB, STAGE_BYTES = 2 * TILE_BYTES;   // K tile | V tile
+  static constexpr int XCH_OFF = NSTAGE * STAGE_BYTES;
+  static constexpr int SMEM_BYTES = XCH_OFF + 2 * XCH_BYTES;
+  static constexpr int OUT_RS = RB + 16;         // row stride of the output tile staged in LDS (rows 4 banks apart)
+  static_assert(NSUB * 32 * OUT_RS <= XCH_OFF, "the output tile fits the stages");
+  static constexpr int IPT = TILE_BYTES / 1024 / (LOADER ? 1 : 4);   // 1 KB load instructions per requesting wave, tile and tensor
+  static constexpr int RPI = 1024 / RB;          // rows per load instruction
+  // The swizzle works on the lowest four (head dim 192: three) bits of the chunk index: NRO per-lane offsets serve all
+  // k-steps, every further NRO k-steps lying NRO * 32 bytes further.
+  static constexpr int NRO = LOADER ? 4 : 8;
+  static constexpr int EBLK = D / 64;            // a consumer wave owns head-dim blocks jb and jb + EBLK
+};
 
-template <bool LOCAL>
+template <int D, bool LOCAL>
 __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
+  using C = Cfg<D>;
+  constexpr int KS = C::KS, RB = C::RB, CPR = C::CPR, TILE_BYTES = C::TILE_BYTES, STAGE_BYTES = C::STAGE_BYTES;
+  constexpr int XCH_OFF = C::XCH_OFF, OUT_RS = C::OUT_RS, IPT = C::IPT, RPI = C::RPI, NRO = C::NRO, EBLK = C::EBLK;
+  constexpr bool LOADER = C::LOADER;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   QBlock b;
@@ -77,11 +91,10 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
       for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qf[ks]), "v"(dof[ks]));
       asm volatile("" : : "v"(lse2), "v"(negd));
     }
-    // 16-byte row operand of k-step ks: row l32, chunk 2 ks + hi.  The swizzle (four bits) leaves bit 4 of the
-    // chunk index alone: eight per-lane offsets serve the sixteen k-steps, the upper eight 256 bytes further.
-    int roff[8];
+    // 16-byte row operand of k-step ks: row l32, chunk 2 ks + hi
+    int roff[NRO];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) roff[j] = tile_off<D>(l32, 2 * j + hi);
+    for (int j = 0; j < NRO; ++j) roff[j] = tile_off<D>(l32, 2 * j + hi);
     unsigned char* xw = smem + XCH_OFF + wave * 2048 + lane * 16;
 
     const bool never_plain = LOCAL || !wave_valid;
@@ -109,7 +122,7 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
           for (int q = 0; q < GRP; ++q) {
             const int ks = (gi * GRP + q) % KS;
             const unsigned char* base = gi * GRP < KS ? kh : vh;
-            out[q] = *reinterpret_cast<const bf16x8*>(base + roff[ks & 7] + (ks >> 3) * 256);
+            out[q] = *reinterpret_cast<const bf16x8*>(base + roff[ks % NRO] + ks / NRO * (NRO * 32));
           }
         };
         request(0, op[0]);
@@ -134,8 +147,13 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
               // ... so that its exponentials issue in the shadow of the dP^T - D = V dO^T - D MFMAs
               const int ks = i - KS;
               dpt = mfma32(op[gi & 1][q], dof[ks], dpt);
-              ev[ks] = __builtin_amdgcn_exp2f(s[ks] * c - lse2);
-              asm volatile("" : "+v"(ev[ks]));
+#pragma unroll
+              for (int j = 0; j < (16 + KS - 1) / KS; ++j) {
+                const int e = 16 * ks / KS + j;   // the sixteen exponentials spread evenly over the KS MFMAs
+                if (e >= 16 * (ks + 1) / KS) continue;
+                ev[e] = __builtin_amdgcn_exp2f(s[e] * c - lse2);
+                asm volatile("" : "+v"(ev[e]));
+              }
             }
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -177,6 +195,15 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
     const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
     const int ld_row0 = jb * RPI + lane / CPR;
     const int ld_coff = ((lane % CPR) ^ swz<D>(ld_row0)) * 16;
+    // (loader: its twelve instructions per tensor are consecutive; t and t + 3 are 8 rows apart)
+    int sp_row[3], sp_coff[3];
+    if constexpr (LOADER) {
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        sp_row[t] = split_row<D>(t, lane);
+        sp_coff[t] = (split_pos<D>(t, lane) ^ swz<D>(sp_row[t])) * 16;
+      }
+    }
     const int ktsb_c = (int)p.kc.ts * 2, ktsb_d = (int)p.kd.ts * 2, vtsb_c = (int)p.vc.ts * 2, vtsb_d = (int)p.vd.ts * 2;
     auto issue_loads = [&](int it) __attribute__((always_inline)) {
       const bool is_ctx = it < n_ctx_run;
@@ -187,7 +214,18 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
       const u16* vb = uniform_ptr(reinterpret_cast<const u16*>(
           reinterpret_cast<const unsigned char*>(is_ctx ? vc_base : vd_base) + (int64_t)key0 * vtsb));
       const int last = (is_ctx ? P : R) - key0 - 1;
-      const uint32_t dst = smem_addr + (it & (NSTAGE - 1)) * STAGE_BYTES + jb * 1024;
+      const uint32_t stage_addr = smem_addr + (it & (NSTAGE - 1)) * STAGE_BYTES;
+      if constexpr (LOADER) {
+        static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
+          constexpr int t = decltype(Tc)::value;
+          const unsigned row = (unsigned)min(sp_row[t % 3] + t / 3 * kSplitRows<D>, last);
+          const uint32_t coff = (uint32_t)(sp_coff[t % 3] ^ ((t / 3 & 1) * 32));
+          dma16_at<t * 1024>(kb, __umul24(row, (unsigned)ktsb) + coff, stage_addr);
+          dma16_at<TILE_BYTES + t * 1024>(vb, __umul24(row, (unsigned)vtsb) + coff, stage_addr);
+        });
+        return;
+      }
+      const uint32_t dst = stage_addr + jb * 1024;
 #pragma unroll
       for (int t = 0; t < IPT; ++t) {
         const unsigned row = (unsigned)min(ld_row0 + t * 4 * RPI, last);
@@ -196,14 +234,26 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
         dma16(vb, __umul24(row, (unsigned)vtsb) + coff, dst + TILE_BYTES + t * 4096);
       }
     };
-    issue_loads(0);
-    if (n_tiles > 1) issue_loads(1);
-    if (n_tiles > 2) issue_loads(2);
-    // tile 0 must have landed; younger tiles may stay in flight
-    if (n_tiles > 2) wait_vm<4 * IPT>();
-    else if (n_tiles > 1) wait_vm<2 * IPT>();
-    else wait_vm<0>();
-
+    // tile it+1 must have landed before the barrier; tiles it+2 and it+3 may stay in flight
+    auto wait_loads = [&](int it) __attribute__((always_inline)) {
+      if (it + 3 < n_tiles) wait_vm<4 * IPT>();
+      else if (it + 2 < n_tiles) wait_vm<2 * IPT>();
+      else wait_vm<0>();
+    };
+    if (!LOADER || jb == 3) {
+#pragma unroll 1
+      for (int it = 0; it < min(n_tiles, 3); ++it) issue_loads(it);
+      wait_loads(-1);   // tile 0
+    }
+    if (LOADER && jb == 3) {
+      // The loader: every request of the workgroup, in intervals of their own (LDS stages as below).
+      __syncthreads();   // tile 0 is in LDS
+      for (int it = 0; it <= n_tiles; ++it) {
+        if (it + 3 < n_tiles) issue_loads(it + 3);
+        wait_loads(it);
+        __syncthreads();
+      }
+    } else {
     f32x16 dq[NSUB][2];
 #pragma unroll
     for (int s = 0; s < NSUB; ++s)
@@ -211,9 +261,14 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
       for (int e = 0; e < 2; ++e)
 #pragma unroll
         for (int r = 0; r < 16; ++r) dq[s][e][r] = 0.f;
-    // transpose reads: rows 4 hi + (lane % 16) / 4 and + 8 of a 16-key group, head-dim block jb (block jb + 4 lies
-    // 256 bytes further: bit 4 of the chunk index)
-    const int toff0 = tr_off<D>(lane, hi * 4, jb * 32), toff1 = tr_off<D>(lane, hi * 4 + 8, jb * 32);
+    // transpose reads: rows 4 hi + (lane % 16) / 4 and + 8 of a 16-key group, head-dim blocks jb and jb + EBLK (at head
+    // dim 256 the second lies 256 bytes further: bit 4 of the chunk index)
+    int toff0[2], toff1[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      toff0[e] = LOADER ? tr_off<D>(lane, hi * 4, (jb + e * EBLK) * 32) : tr_off<D>(lane, hi * 4, jb * 32) + e * 256;
+      toff1[e] = LOADER ? tr_off<D>(lane, hi * 4 + 8, (jb + e * EBLK) * 32) : tr_off<D>(lane, hi * 4 + 8, jb * 32) + e * 256;
+    }
     const unsigned char* xr = smem + XCH_OFF + lane * 16;
     bf16x8 kt[2][2];   // [16-key group][head-dim block]: K^T operands of the tile accumulated next interval
 
@@ -221,7 +276,7 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
     for (int it = 0; it <= n_tiles; ++it) {
       // tile it+3 goes into the stage of tile it-1: the producers read it during the last interval, and its
       // K^T operands are in this wave's registers since then
-      if (it + 3 < n_tiles) issue_loads(it + 3);
+      if (!LOADER && it + 3 < n_tiles) issue_loads(it + 3);
       if (it > 0) {
         const unsigned char* xi = xr + ((it - 1) & 1) * XCH_BYTES;
         bf16x8 ds[2][NSUB];
@@ -245,12 +300,9 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
         for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
           for (int e = 0; e < 2; ++e)
-            kt[t2][e] = tr_pair(kh + t2 * 16 * RB + e * 256 + toff0, kh + t2 * 16 * RB + e * 256 + toff1);
+            kt[t2][e] = tr_pair(kh + t2 * 16 * RB + toff0[e], kh + t2 * 16 * RB + toff1[e]);
       }
-      // tile it+1 must have landed before the barrier; tiles it+2 and it+3 may stay in flight
-      if (it + 3 < n_tiles) wait_vm<4 * IPT>();
-      else if (it + 2 < n_tiles) wait_vm<2 * IPT>();
-      else wait_vm<0>();
+      if (!LOADER) wait_loads(it);
       __syncthreads();
     }
 
@@ -267,17 +319,18 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
           u32x2 w;
           w.x = pack2_bf16(dq[s][e][r4 * 4 + 0] * p.scale, dq[s][e][r4 * 4 + 1] * p.scale);
           w.y = pack2_bf16(dq[s][e][r4 * 4 + 2] * p.scale, dq[s][e][r4 * 4 + 3] * p.scale);
-          *reinterpret_cast<u32x2*>(orow + ((jb + 4 * e) * 32 + r4 * 8 + hi * 4) * 2) = w;
+          *reinterpret_cast<u32x2*>(orow + ((jb + EBLK * e) * 32 + r4 * 8 + hi * 4) * 2) = w;
         }
+    }
     }
   }
   __syncthreads();   // the scaled tile is in LDS
   {
-    // thread t: 16-byte piece t % 32 of tile rows t / 32, + 16, ...
-    const int piece = tid & 31;
+    // 16-byte piece n % CPR of tile row n / CPR, n = thread, + 512, ...
 #pragma unroll
-    for (int i = 0; i < NSUB * 32 / 16; ++i) {
-      const int tr = i * 16 + (tid >> 5), s = tr >> 5;
+    for (int i = 0; i < NSUB * 32 * CPR / 512; ++i) {
+      const unsigned n = (unsigned)(i * 512 + tid);
+      const int tr = n / CPR, piece = n % CPR, s = tr >> 5;
       const int head = b.hk * p.G + b.hc * p.GP + s / p.RSH;
       const int row = b.blk_row0 + (s % p.RSH) * 32 + (tr & 31);
       if (row >= R) continue;
@@ -288,21 +341,27 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
   }
 }
 
-template <bool LOCAL>
+template <int D, bool LOCAL>
 hipError_t launch_t(AttnParams p, hipStream_t st) {
   fill_packing(p, NSUB);
-  hipError_t e = ensure_dynamic_lds<dq256_kernel<LOCAL>>(SMEM_BYTES);
+  auto kern = dq256_kernel<D, LOCAL>;
+  hipError_t e = ensure_dynamic_lds<dq256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
   if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(dq256_kernel<LOCAL>, dim3((unsigned)nblk), dim3(512), SMEM_BYTES, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), Cfg<D>::SMEM_BYTES, st, p);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_dq256(const AttnParams& p, hipStream_t st) {
-  return p.window > 0 ? launch_t<true>(p, st) : launch_t<false>(p, st);
+hipError_t launch_dq256(const AttnParams& p, int head_dim, hipStream_t st) {
+  const bool local = p.window > 0;
+  switch (head_dim) {
+    case 192: return local ? launch_t<192, true>(p, st) : launch_t<192, false>(p, st);
+    case 256: return local ? launch_t<256, true>(p, st) : launch_t<256, false>(p, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace dkv

@@ -1,7 +1,9 @@
 // Forward kernel for head dims 64, 96 and 128 (Alg. 3 of the paper re-tiled for CDNA4), tuned variant.
 //
-// Same work decomposition as the generic Q-stationary kernel (one workgroup = BMR rows x GP packed
-// query heads of one KV head, prompt tiles then own-response tiles):
+// One workgroup owns BMR response rows x GP packed query heads of one KV head ("GQA packing": the staged K / V tiles
+// are shared by all packed heads) and walks the two KV regions in logical order, prompt tiles then own-response tiles.
+// The scores are computed transposed, S^T = K Q^T, so that a lane owns one query row and exp(S^T) is already laid out
+// as the B operand of O^T += V^T P^T:
 //   * 8 waves (two per SIMD), each owning ONE 32-row subtile: Q fragments (B operands) and the O^T
 //     accumulator stay in registers (~200 VGPRs, no spills);
 //   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row so that both the

@@ -5,25 +5,22 @@
 
 namespace dkv {
 
-hipError_t launch_fwd(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned forward for head dims 64 / 96 / 128
 hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st);
-hipError_t launch_dq(const AttnParams& p, int head_dim, hipStream_t st);
-hipError_t launch_dkdv(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned backward kernels for head dims 64 / 96 / 128
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
-// tuned kernels for head dim 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)
-hipError_t launch_fwd256(const AttnParams& p, hipStream_t st);
-hipError_t launch_dq256(const AttnParams& p, hipStream_t st);
-hipError_t launch_dkdv256(const AttnParams& p, hipStream_t st);
+// kernels for head dims 192 / 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)
+hipError_t launch_fwd256(const AttnParams& p, int head_dim, hipStream_t st);
+hipError_t launch_dq256(const AttnParams& p, int head_dim, hipStream_t st);
+hipError_t launch_dkdv256(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned dK/dV kernel for head dim 512 (32-key tile, 16-row blocks)
 hipError_t launch_dkdv512(const AttnParams& p, hipStream_t st);
 // tuned dQ kernel for head dim 512 (64 rows per workgroup, 16-key tiles)
 hipError_t launch_dq512(const AttnParams& p, hipStream_t st);
 hipError_t launch_fwd512(const AttnParams& p, hipStream_t st);
 // key tile (rows of K/V owned by one workgroup) of the dK/dV kernel for a head dim
-int dkdv_key_tile(int head_dim);
+inline int dkdv_key_tile(int head_dim) { return head_dim <= 128 ? 128 : head_dim <= 256 ? 64 : 32; }
 
 hipError_t launch_dot_do_o(const TView& dout, const TView& o, const float* lse, float* dvec, float* lse2, int total,
                            int H, int head_dim, hipStream_t st);

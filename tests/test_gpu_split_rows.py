@@ -1,6 +1,6 @@
-"""GPU parity of the kernels for head dim 96, whose 192-byte rows do not divide the 1 KB of a load
-instruction and whose dK/dV kernel has a wave of its own for the requests.  Sizes around
-the 32-, 64- and 128-key tiles, the 16- and 32-row blocks and the LDS stages; bounds as in parity_util."""
+"""GPU parity of the kernels for head dims 96 and 192, whose 192- and 384-byte rows do not divide the 1 KB of a load
+instruction and whose dK/dV (at 192 also forward and dQ) kernels have a wave of its own for the requests.  Sizes around the
+32-, 64- and 128-key tiles, the 32-row blocks and the LDS stages; bounds as in parity_util."""
 import numpy as np
 import pytest
 
@@ -29,7 +29,7 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("d", [96])
+@pytest.mark.parametrize("d", [96, 192])
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_parity(case, d):
     from paper_2605_15422_amd import binding as B
