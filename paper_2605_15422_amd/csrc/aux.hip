@@ -27,10 +27,7 @@ __global__ __launch_bounds__(256) void dot_do_o_kernel(TView dout, TView o, cons
   if (ok && sub < D / 8) {
     const u32x4 a = *reinterpret_cast<const u32x4*>(dout.ptr + row * dout.ts + (int64_t)h * dout.hs + sub * 8);
     const u32x4 b = *reinterpret_cast<const u32x4*>(o.ptr + row * o.ts + (int64_t)h * o.hs + sub * 8);
-    const uint32_t* aw = reinterpret_cast<const uint32_t*>(&a);
-    const uint32_t* bw = reinterpret_cast<const uint32_t*>(&b);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc += bf16_lo(aw[i]) * bf16_lo(bw[i]) + bf16_hi(aw[i]) * bf16_hi(bw[i]);
+    acc = dot8_bf16(a, b);
   }
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off);

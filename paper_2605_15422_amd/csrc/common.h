@@ -75,6 +75,30 @@ __device__ __forceinline__ float xor32_sum(float x) {
   return a + b;
 }
 
+// D = rowsum(dO * O) is formed by the dQ kernels or by a kernel of its own (aux.hip), bit for bit alike: the eight products
+// of a 16-byte chunk first, then the chunks in a butterfly from the widest distance down.
+__device__ __forceinline__ float dot8_bf16(u32x4 x, u32x4 y) {
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s += bf16_lo(x[i]) * bf16_lo(y[i]) + bf16_hi(x[i]) * bf16_hi(y[i]);
+  return s;
+}
+__device__ __forceinline__ float dot8_bf16(bf16x8 a, bf16x8 b) {
+  return dot8_bf16(__builtin_bit_cast(u32x4, a), __builtin_bit_cast(u32x4, b));
+}
+// the levels of that butterfly whose chunks one lane holds: t[i] + t[i + h], h = the next power of two's half, ..., 1
+template <int N>
+__device__ __forceinline__ float butterfly_sum(float (&t)[N]) {
+  constexpr int top = N <= 4 ? 2 : N <= 8 ? 4 : 8;
+  static_assert(N > 2 && N <= 16, "");
+#pragma unroll
+  for (int h = top; h >= 1; h >>= 1)
+#pragma unroll
+    for (int i = 0; i < h; ++i)
+      if (i + h < N) t[i] += t[i + h];
+  return t[0];
+}
+
 // Row of a C tile held in register r by this lane.
 __device__ __forceinline__ int crow(int r, int hi) { return 8 * (r >> 2) + 4 * hi + (r & 3); }
 
@@ -96,7 +120,8 @@ struct AttnParams {
   TViewOut dq, dkc, dvc, dkd, dvd;       // bwd outputs (bf16)
   float* lse;                            // (H, total) fwd: written, bwd: read
   float* dvec;                           // (H, total) D = rowsum(dO * O), bwd only
-  float* lse2;                           // (H, total) LSE * log2(e), written with D by the preprocess
+  float* lse2;                           // (H, total) LSE * log2(e), written with D
+  int make_stats;                        // dQ kernels: form D from dO and O and write dvec / lse2 (else dvec is read)
   float* dkc_acc;                        // optional fp32 (P, Hk, d) accumulators (atomic adds)
   float* dvc_acc;
   float* dkd_acc;                        // optional fp32 (rows, Hk, d) accumulators for response-region keys

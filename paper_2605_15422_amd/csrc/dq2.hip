@@ -57,7 +57,22 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
       dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
     }
     lse2 = p.lse[(int64_t)head * p.total + grow] * LOG2E;
-    dvec = p.dvec[(int64_t)head * p.total + grow];
+    if (p.make_stats) {
+      const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + hi * 8;
+      bf16x8 of[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) of[ks] = *reinterpret_cast<const bf16x8*>(op + ks * 16);
+      float t[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) t[ks] = dot8_bf16(dof[ks], of[ks]);   // chunk 2 ks + hi
+      dvec = xor32_sum(butterfly_sum(t));
+      if (hi == 0 && row < R) {
+        p.dvec[(int64_t)head * p.total + grow] = dvec;
+        p.lse2[(int64_t)head * p.total + grow] = lse2;
+      }
+    } else {
+      dvec = p.dvec[(int64_t)head * p.total + grow];
+    }
     // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qf[ks]), "v"(dof[ks]));
@@ -144,7 +159,7 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
 
   issue_loads(0, 0);
   if (b.n_tiles > 1) issue_loads(1, 1);
-  wait_loads(b.n_tiles > 1);
+  wait_vm<0>();   // (also the stores of the row statistics: the waits of the main loop count loads only)
   __syncthreads();
 
   f32x16 negd;   // accumulator image of -D: this lane's query row in all sixteen registers

@@ -85,7 +85,22 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
         dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
       }
       lse2 = p.lse[(int64_t)head * p.total + grow] * LOG2E;
-      negd = -p.dvec[(int64_t)head * p.total + grow];
+      if (p.make_stats) {
+        const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + hi * 8;
+        float t[KS];
+        constexpr int GRP = 4;   // (at most GRP operands of O next to the Q and dO fragments)
+#pragma unroll
+        for (int k0 = 0; k0 < KS; k0 += GRP) {
+          bf16x8 of[GRP];
+#pragma unroll
+          for (int q = 0; q < GRP; ++q) of[q] = *reinterpret_cast<const bf16x8*>(op + (k0 + q) * 16);
+#pragma unroll
+          for (int q = 0; q < GRP; ++q) t[k0 + q] = dot8_bf16(dof[k0 + q], of[q]);
+        }
+        negd = -xor32_sum(butterfly_sum(t));
+      } else {
+        negd = -p.dvec[(int64_t)head * p.total + grow];
+      }
       // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qf[ks]), "v"(dof[ks]));
@@ -178,6 +193,11 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
         *reinterpret_cast<u32x4*>(xo + 1024) = z;
       }
       __syncthreads();
+    }
+    if (p.make_stats && hi == 0 && row < R) {
+      const int64_t at = (int64_t)head * p.total + b.row_begin + row;
+      p.dvec[at] = -negd;
+      p.lse2[at] = lse2;
     }
     __syncthreads();   // the consumers' last interval
   } else {
