@@ -53,8 +53,9 @@ STAGES = ["ctx_fwd", "fwd", "zero_acc", "bwd_pre", "bwd_dkdv", "bwd_dq", "ctx_bw
 def time_layer(dg, bufs, steps, warmup):
     """Times `steps` layer passes; returns (ms_per_step, wall ms per step, per-stage average ms).
 
-    The Call-2 / Call-1 backward is issued stage by stage (same kernels, same order as the plain call) so
-    that HIP events on the launch stream bracket every kernel of the path.  With DUALKV_FLAG_ACCUM_CTX_F32 in the
+    The passes are timed as a training step issues them.  For the per-stage figures the Call-2 / Call-1 backward is then
+    issued stage by stage (preprocess, dK/dV, dQ) so that HIP events on the launch stream bracket every kernel; the plain
+    calls run no preprocess (the dQ kernel forms D), so the stages add up to a little more than a pass.  With DUALKV_FLAG_ACCUM_CTX_F32 in the
     group's flags (the default of this benchmark) both backward calls add into the fp32 accumulators, which are
     cleared before and cast once after (Eq. 6); without it each call writes its own bf16 term and the two extra
     stages are empty.
@@ -106,18 +107,41 @@ def time_layer(dg, bufs, steps, warmup):
             B.dualkv_finalize_ctx_grads(s, bufs.dk_c_acc, bufs.dv_c_acc, bufs.dk_c, bufs.dv_c)
         ev[k].record(); k += 1
 
+    def layer_step():
+        if s.ctx_len > 0:
+            B.dualkv_ctx_fwd(s, dg.q_c, dg.k_c, dg.v_c, bufs.o_c, bufs.lse_c)
+        B.dualkv_fwd(s, dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d, dg.cu_dev, None, bufs.o_d, bufs.lse_d)
+        if accum:
+            B.dualkv_zero_ctx_grads(s, bufs.dk_c_acc, bufs.dv_c_acc)
+        bwd2(s)
+        if s.ctx_len > 0:
+            bwd1(s)
+        if accum:
+            B.dualkv_finalize_ctx_grads(s, bufs.dk_c_acc, bufs.dv_c_acc, bufs.dk_c, bufs.dv_c)
+
     nev = len(STAGES) + 1
     dummy = _events(nev)
     for _ in range(warmup):
         one_step(dummy)
     torch.cuda.synchronize()
-    evs = [_events(nev) for _ in range(steps)]
+    # the step itself: the calls as a training step makes them (the backward calls whole, not stage by stage)
+    for _ in range(warmup):
+        layer_step()
+    torch.cuda.synchronize()
+    e0, e1 = _events(2)
     t0 = time.perf_counter()
+    e0.record()
+    for _ in range(steps):
+        layer_step()
+    e1.record()
+    torch.cuda.synchronize()
+    wall_ms = (time.perf_counter() - t0) * 1e3
+    gpu_ms = e0.elapsed_time(e1)
+    # the stages one by one, with an event after each
+    evs = [_events(nev) for _ in range(steps)]
     for i in range(steps):
         one_step(evs[i])
     torch.cuda.synchronize()
-    wall_ms = (time.perf_counter() - t0) * 1e3
-    gpu_ms = evs[0][0].elapsed_time(evs[-1][-1])
     stage = {n: 0.0 for n in STAGES}
     for ev in evs:
         for j, n in enumerate(STAGES):
