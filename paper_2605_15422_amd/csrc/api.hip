@@ -413,8 +413,7 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
     p.n_split = ctx_split(shape, groups);
     // zero-initialise the fp32 scratch (Alg. 1, "Require: zero-initialized")
     if (!(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
-      if ((rc = hip_rc(dkv::launch_fill_f32(p.dkc_acc, n_acc, 0.f, st)))) return rc;
-      if ((rc = hip_rc(dkv::launch_fill_f32(p.dvc_acc, n_acc, 0.f, st)))) return rc;
+      if ((rc = hip_rc(dkv::launch_clear2_f32(p.dkc_acc, p.dvc_acc, n_acc, st)))) return rc;
     }
   } else {
     p.dkc = view(dk_c);
@@ -423,8 +422,7 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
   if ((rc = hip_rc(run_bwd(p, shape->flags, T, d, st)))) return rc;
   if (scratch && !(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
     // Stage 2 (Alg. 2): cast the accumulated prompt gradients once
-    if ((rc = hip_rc(dkv::launch_convert_ctx(p.dkc_acc, view(dk_c), P, p.Hk, d, 1.0f, st)))) return rc;
-    if ((rc = hip_rc(dkv::launch_convert_ctx(p.dvc_acc, view(dv_c), P, p.Hk, d, 1.0f, st)))) return rc;
+    if ((rc = hip_rc(dkv::launch_convert2_ctx(p.dkc_acc, view(dk_c), p.dvc_acc, view(dv_c), P, p.Hk, d, st)))) return rc;
   }
   return DUALKV_OK;
 }
@@ -607,8 +605,7 @@ int dualkv_finalize_ctx_grads(const dualkv_shape* shape, const float* dk_c_acc32
   if ((reinterpret_cast<uintptr_t>(dk_c_acc32) | reinterpret_cast<uintptr_t>(dv_c_acc32)) % 16) return DUALKV_E_ALIGN;
   if ((rc = check_out(dk_c, P, d)) || (rc = check_out(dv_c, P, d))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if ((rc = hip_rc(dkv::launch_convert_ctx(dk_c_acc32, view(dk_c), P, shape->n_kv_heads, d, 1.0f, st)))) return rc;
-  return hip_rc(dkv::launch_convert_ctx(dv_c_acc32, view(dv_c), P, shape->n_kv_heads, d, 1.0f, st));
+  return hip_rc(dkv::launch_convert2_ctx(dk_c_acc32, view(dk_c), dv_c_acc32, view(dv_c), P, shape->n_kv_heads, d, st));
 }
 
 int dualkv_zero_ctx_grads(const dualkv_shape* shape, float* dk_c_acc32, float* dv_c_acc32, void* stream) {
@@ -619,8 +616,7 @@ int dualkv_zero_ctx_grads(const dualkv_shape* shape, float* dk_c_acc32, float* d
   if ((reinterpret_cast<uintptr_t>(dk_c_acc32) | reinterpret_cast<uintptr_t>(dv_c_acc32)) % 16) return DUALKV_E_ALIGN;
   const int64_t n = (int64_t)shape->ctx_len * shape->n_kv_heads * shape->head_dim;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if ((rc = hip_rc(dkv::launch_fill_f32(dk_c_acc32, n, 0.f, st)))) return rc;
-  return hip_rc(dkv::launch_fill_f32(dv_c_acc32, n, 0.f, st));
+  return hip_rc(dkv::launch_clear2_f32(dk_c_acc32, dv_c_acc32, n, st));
 }
 
 static int rows_copy_common(bool to_packed, int32_t n_seqs, int32_t ctx_len, int32_t total_resp,

@@ -56,23 +56,26 @@ hipError_t launch_dot_do_o(const TView& dout, const TView& o, const float* lse, 
 }
 
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void fill_f32_kernel(float* __restrict__ ptr, int64_t n, float value) {
+// Two fp32 arrays of n elements each, cleared by one launch (the dK and the dV accumulator): at small sizes a launch is
+// most of the time.  With the two casts in one launch as well, the layer of 4 x (256 + 128) rows, 4 / 2 heads, d = 64 goes
+// from 91.9 to 88.0 us.
+__global__ __launch_bounds__(256) void clear2_f32_kernel(float* __restrict__ ptr0, float* __restrict__ ptr1, int64_t n) {
+  float* ptr = blockIdx.y ? ptr1 : ptr0;
   const int64_t stride = (int64_t)gridDim.x * 256 * 4;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += stride) {
     if (i + 4 <= n) {
-      f32x4 v = {value, value, value, value};
-      *reinterpret_cast<f32x4*>(ptr + i) = v;
+      *reinterpret_cast<f32x4*>(ptr + i) = f32x4{0.f, 0.f, 0.f, 0.f};
     } else {
-      for (int64_t j = i; j < n; ++j) ptr[j] = value;
+      for (int64_t j = i; j < n; ++j) ptr[j] = 0.f;
     }
   }
 }
 
-hipError_t launch_fill_f32(float* ptr, int64_t n, float value, hipStream_t st) {
+hipError_t launch_clear2_f32(float* ptr0, float* ptr1, int64_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   int64_t blocks = (n + 1023) / 1024;
-  if (blocks > 8192) blocks = 8192;
-  hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ptr, n, value);
+  if (blocks > 4096) blocks = 4096;
+  hipLaunchKernelGGL(clear2_f32_kernel, dim3((unsigned)blocks, 2), dim3(256), 0, st, ptr0, ptr1, n);
   return hipGetLastError();
 }
 
@@ -112,10 +115,13 @@ hipError_t launch_expand_groups(const int32_t* grp, int n_groups, int n_seqs, in
 }
 
 // ---------------------------------------------------------------------------------------------
-// acc (P, Hk, D) fp32 contiguous -> out (P, Hk, D) bf16 strided, multiplied by `mul`
+// acc (P, Hk, D) fp32 contiguous -> out (P, Hk, D) bf16 strided, the dK and the dV accumulator in one launch (blockIdx.y)
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void convert_ctx_kernel(const float* __restrict__ acc, TViewOut out, int64_t n8,
-                                                          int Hk, int D, float mul) {
+__global__ __launch_bounds__(256) void convert2_ctx_kernel(const float* __restrict__ acc0, TViewOut out0,
+                                                           const float* __restrict__ acc1, TViewOut out1, int64_t n8, int Hk,
+                                                           int D) {
+  const float* acc = blockIdx.y ? acc1 : acc0;
+  const TViewOut out = blockIdx.y ? out1 : out0;
   const int64_t stride = (int64_t)gridDim.x * 256;
   const int cpr = D / 8;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n8; i += stride) {
@@ -126,21 +132,29 @@ __global__ __launch_bounds__(256) void convert_ctx_kernel(const float* __restric
     const f32x4 a = *reinterpret_cast<const f32x4*>(acc + i * 8);
     const f32x4 b = *reinterpret_cast<const f32x4*>(acc + i * 8 + 4);
     u32x4 w;
-    w.x = pack2_bf16(a[0] * mul, a[1] * mul);
-    w.y = pack2_bf16(a[2] * mul, a[3] * mul);
-    w.z = pack2_bf16(b[0] * mul, b[1] * mul);
-    w.w = pack2_bf16(b[2] * mul, b[3] * mul);
+    w.x = pack2_bf16(a[0], a[1]);
+    w.y = pack2_bf16(a[2], a[3]);
+    w.z = pack2_bf16(b[0], b[1]);
+    w.w = pack2_bf16(b[2], b[3]);
     *reinterpret_cast<u32x4*>(out.ptr + row * out.ts + (int64_t)h * out.hs + ch * 8) = w;
   }
 }
 
-hipError_t launch_convert_ctx(const float* acc, const TViewOut& out, int P, int Hk, int head_dim, float mul,
-                              hipStream_t st) {
+hipError_t launch_convert2_ctx(const float* acc0, const TViewOut& out0, const float* acc1, const TViewOut& out1, int P, int Hk,
+                               int head_dim, hipStream_t st) {
   const int64_t n8 = (int64_t)P * Hk * head_dim / 8;
   if (n8 == 0) return hipSuccess;
   int64_t blocks = (n8 + 255) / 256;
   if (blocks > 16384) blocks = 16384;
-  hipLaunchKernelGGL(convert_ctx_kernel, dim3((unsigned)blocks), dim3(256), 0, st, acc, out, n8, Hk, head_dim, mul);
+  // (a caller may let the second output overwrite the first accumulator: one after the other then)
+  const uintptr_t a0 = (uintptr_t)acc0, o1 = (uintptr_t)out1.ptr;
+  const uintptr_t o1_end = o1 + (uintptr_t)((int64_t)(P - 1) * out1.ts + (int64_t)(Hk - 1) * out1.hs + head_dim) * 2;
+  if (o1 < a0 + (uintptr_t)n8 * 32 && a0 < o1_end) {
+    hipLaunchKernelGGL(convert2_ctx_kernel, dim3((unsigned)blocks), dim3(256), 0, st, acc0, out0, acc0, out0, n8, Hk, head_dim);
+    hipLaunchKernelGGL(convert2_ctx_kernel, dim3((unsigned)blocks), dim3(256), 0, st, acc1, out1, acc1, out1, n8, Hk, head_dim);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(convert2_ctx_kernel, dim3((unsigned)blocks, 2), dim3(256), 0, st, acc0, out0, acc1, out1, n8, Hk, head_dim);
   return hipGetLastError();
 }
 

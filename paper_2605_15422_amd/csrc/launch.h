@@ -26,9 +26,9 @@ hipError_t launch_dot_do_o(const TView& dout, const TView& o, const float* lse, 
                            int H, int head_dim, hipStream_t st);
 hipError_t launch_group_offsets(const int32_t* grp, int n_groups, int total_ctx, int32_t* cu, hipStream_t st);
 hipError_t launch_expand_groups(const int32_t* grp, int n_groups, int n_seqs, int32_t* seq_ctx, hipStream_t st);
-hipError_t launch_fill_f32(float* ptr, int64_t n, float value, hipStream_t st);
-hipError_t launch_convert_ctx(const float* acc, const TViewOut& out, int P, int Hk, int head_dim, float mul,
-                              hipStream_t st);
+hipError_t launch_clear2_f32(float* ptr0, float* ptr1, int64_t n, hipStream_t st);
+hipError_t launch_convert2_ctx(const float* acc0, const TViewOut& out0, const float* acc1, const TViewOut& out1, int P, int Hk,
+                               int head_dim, hipStream_t st);
 hipError_t launch_rows_copy(bool to_packed, int n_seqs, int ctx_len, int total_resp, const int32_t* cu,
                             int64_t row_bytes, const void* src, void* dst, int32_t* pos_ids, hipStream_t st);
 hipError_t launch_label_map(int n_seqs, int ctx_len, int total_resp, const int32_t* cu, int32_t* next_index,
