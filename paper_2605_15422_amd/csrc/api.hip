@@ -1,5 +1,6 @@
 // C ABI of the library (include/dualkv.h): host-side validation, workspace carving and dispatch.
 // Nothing here touches device memory except through kernel launches on the caller's stream.
+#include <algorithm>
 #include <cstdlib>
 #include <mutex>
 #include "../../include/dualkv.h"
@@ -16,7 +17,7 @@ using dkv::AttnParams;
 using dkv::TView;
 using dkv::TViewOut;
 
-constexpr int kTargetBlocks = 512;   // prompt-tile workgroups wanted before the sequence loop is split
+constexpr int kTargetBlocks = 512;   // prompt-tile workgroups from which on no prompt tile is cut into parts
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -111,6 +112,63 @@ int ctx_split(const dualkv_shape* s, const Groups& g = Groups()) {
   const int64_t seqs_per_group = (s->n_seqs + n_grp - 1) / n_grp;
   if (want > seqs_per_group) want = seqs_per_group;
   return (int)(want < 1 ? 1 : want);
+}
+
+// The number of parts to launch.  ctx_split says whether the caller's workspace holds accumulators for more than one; how
+// many are best follows from rounds of 256 workgroups (one per CU): a part takes as many intervals as it has (row block,
+// head) pairs plus kPartOverhead for its start and its atomic epilogue, and the response tiles fill the gaps that are left.
+// The parts cut the rows evenly.  Before, 512 workgroups were wanted whatever that made of the last round, and the parts were
+// whole sequences: layers of N = 8, P = 4111, R ~ U(131, 2048), 16 / 4 heads, d = 96: 2.04 -> 1.86 ms (528 parts became
+// 396); N = 8, P = 1021, R <= 256, 32 / 8 heads, d = 128: 415 -> 375 us; an overhead of 15 or 25 instead of 40 intervals is
+// 3 % slower at N = 4, P = 5059.
+constexpr int kPartOverhead = 40;
+int ctx_parts(const dualkv_shape* s, const Groups& g, bool accum) {
+  const int most = ctx_split(s, g);
+  if (s->ctx_len == 0 || s->total_resp == 0 || s->window > 0 || (most == 1 && !accum)) return most;
+  const int bn = dkv::dkdv_key_tile(s->head_dim), hb = s->head_dim == 512 ? 16 : 32, n_grp = g.n > 0 ? g.n : 1;
+  const double G = s->n_q_heads / s->n_kv_heads;
+  const int64_t blocks = (int64_t)n_grp * ((s->ctx_len + bn - 1) / bn) * s->n_kv_heads;
+  if (blocks >= kTargetBlocks) return 1;
+  const double chain = (double)s->total_resp / n_grp / hb * G, resp = (double)s->total_resp / s->n_seqs;
+  const double own = (double)s->n_seqs * s->n_kv_heads * ((int)(resp / bn) + 1) * (resp / hb * G / 2 + kPartOverhead);
+  int best = 1;
+  double best_t = 1e30;
+  for (int n = 1; n <= 16 && (n == 1 || chain / n >= 8); ++n) {
+    const double part = chain / n + kPartOverhead, rounds = (double)((blocks * n + 255) / 256);
+    const double t = std::max((blocks * n * part + own) / 256, rounds * part);
+    if (t < 0.98 * best_t) {
+      best = n;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// How the row blocks of Call 1's key tiles are cut into parts for several workgroups (see decode_kvblock), where the
+// gradients are added into fp32 accumulators anyway.  The first tile sees every row block and the last one a single one, so a
+// prompt with too few tiles for the chip waits for its first tiles: a tile is cut into parts of about 3/4 of what a CU gets
+// on average, but not below kPartMin intervals, where the start and the atomic epilogue of a part outweigh it.  Prompts whose
+// longest tile is within a quarter of that average are left alone.  Layers of N = 8, P = 4096, R ~ U(131, 2048): 32 / 8
+// heads, d = 64 3.31 -> 3.23 ms, 16 / 4 heads, d = 96 2.23 -> 2.04; 1/2 or 1 instead of 3/4: 3.30 / 3.25 and 2.10 / 2.07.
+constexpr int kPartMin = 32;
+struct RowSplit {
+  int n = 1, len = 0;   // at most n parts of at most len row blocks
+};
+
+RowSplit ctx_row_split(const dualkv_shape* s, const Groups& g = Groups()) {
+  RowSplit r;
+  const int bn = dkv::dkdv_key_tile(s->head_dim), hb = s->head_dim == 512 ? 16 : 32;
+  const int64_t P = s->ctx_len, G = s->n_q_heads / s->n_kv_heads;
+  if (P == 0 || s->window > 0) return r;   // (a windowed tile sees few row blocks)
+  const int64_t n_seqs = g.n > 0 ? (g.total_ctx + P - 1) / P : 1;   // (prompts of the largest size that fill the rows)
+  const int64_t longest = (P + hb - 1) / hb * G, tiles = (P + bn - 1) / bn;
+  const double per_cu = (double)((longest + 1) / 2) * (double)(tiles * n_seqs * s->n_kv_heads) / 256.0;
+  if ((double)longest <= 1.25 * per_cu || longest < 2 * kPartMin) return r;
+  double len = per_cu * 0.75;
+  if (len < kPartMin) len = kPartMin;
+  r.len = (int)((len + (double)G - 1) / (double)G);
+  r.n = (int)((longest / G + r.len - 1) / r.len);
+  return r;
 }
 
 struct BwdWorkspace {
@@ -338,6 +396,9 @@ int ctx_bwd_impl(const dualkv_shape* shape, dualkv_tin do_c, dualkv_tin o_c, con
   } else {
     p.dkd_acc = dk_c_acc32;
     p.dvd_acc = dv_c_acc32;
+    const RowSplit split = ctx_row_split(shape, groups);
+    p.n_row_split = split.n;
+    p.row_split_len = split.len;
   }
   p.lse = const_cast<float*>(lse_c);
   p.dvec = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.dvec_off);
@@ -406,11 +467,11 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
   if (accum) {
     p.dkc_acc = dk_c_acc32;
     p.dvc_acc = dv_c_acc32;
-    p.n_split = ctx_split(shape, groups);
+    p.n_split = ctx_parts(shape, groups, true);
   } else if (scratch) {
     p.dkc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off);
     p.dvc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off + w.acc_bytes);
-    p.n_split = ctx_split(shape, groups);
+    p.n_split = ctx_parts(shape, groups, false);
     // zero-initialise the fp32 scratch (Alg. 1, "Require: zero-initialized")
     if (!(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
       if ((rc = hip_rc(dkv::launch_clear2_f32(p.dkc_acc, p.dvc_acc, n_acc, st)))) return rc;
@@ -614,7 +675,7 @@ int dualkv_zero_ctx_grads(const dualkv_shape* shape, float* dk_c_acc32, float* d
   if (shape->ctx_len == 0) return DUALKV_OK;
   if (dk_c_acc32 == nullptr || dv_c_acc32 == nullptr) return DUALKV_E_INVALID;
   if ((reinterpret_cast<uintptr_t>(dk_c_acc32) | reinterpret_cast<uintptr_t>(dv_c_acc32)) % 16) return DUALKV_E_ALIGN;
-  const int64_t n = (int64_t)shape->ctx_len * shape->n_kv_heads * shape->head_dim;
+  const int64_t n = (int64_t)shape->ctx_len * shape->n_kv_heads * shape->head_dim;   // per accumulator
   hipStream_t st = static_cast<hipStream_t>(stream);
   return hip_rc(dkv::launch_clear2_f32(dk_c_acc32, dv_c_acc32, n, st));
 }

@@ -69,7 +69,7 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
   const int W = p.window;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, kb)) return;
+  if (!decode_kvblock(p, BN, HB, kb)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;
@@ -348,21 +348,23 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
         gflags = HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0);
       }
     };
-    auto init_seq = [&]() __attribute__((always_inline)) {
+    // (response tiles have one sequence: only the first call has to know them)
+    auto init_seq = [&](auto first) __attribute__((always_inline)) {
       // the offsets are loaded through the vector path: make their uniformity explicit
       row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
       R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
       int rows = R;
-      if (is_ctx) {
+      if (LOCAL ? is_ctx : !decltype(first)::value || is_ctx) {
         const int key_hi = min(P, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W - P);
-        rb = 0;
+        rb = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
         rb_end = rows > 0 ? (rows + HB - 1) / HB : 0;
+        if (!LOCAL && seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
       } else {
         const int key_hi = min(R, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W);
-        rb = key0 / HB;
-        rb_end = (rows + HB - 1) / HB;
+        rb = LOCAL ? key0 / HB : max(key0 / HB, kb.rb_lo);   // (windowed tiles are short: their row blocks are not cut)
+        rb_end = LOCAL ? (rows + HB - 1) / HB : min((rows + HB - 1) / HB, kb.rb_hi);
       }
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
@@ -379,7 +381,7 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       }
       more = false;
       while (++seq < seq_hi) {
-        init_seq();
+        init_seq(std::false_type{});
         if (rb < rb_end) {
           more = true;
           enter_group();
@@ -462,7 +464,7 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
 
     if (!LOADER || wave == LOAD_WAVE) {
       for (; seq < seq_hi; ++seq) {
-        init_seq();
+        init_seq(std::true_type{});
         if (rb < rb_end) {
           more = true;
           enter_group();
@@ -606,6 +608,7 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
+  if (p.n_row_split < 1) p.n_row_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
@@ -615,7 +618,7 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL>>(smem);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
+                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
   if (nblk == 0) return hipSuccess;
   hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), smem, st, p);
   return hipGetLastError();
