@@ -1,0 +1,41 @@
+"""Layout copies (dualkv_repack / dualkv_replicate) at the row sizes where their kernels change (31 and 32 units of 4 and 16
+bytes, 128 and 129 units), bases that allow only 4-byte units, more sequences than a workgroup copies a prompt row for, empty
+sequences and prompts; byte for byte against the oracle's packings."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("P,lens", [(5, [3, 0, 7, 1]), (0, [2, 0, 3]), (3, [0] * 16 + [2]), (130, [1]), (2, [i % 3 for i in range(35)])])
+@pytest.mark.parametrize("row_bytes", [4, 16, 124, 128, 496, 512, 516, 2048, 2064, 4128])
+@pytest.mark.parametrize("shift", [0, 4])
+def test_rows_copy(P, lens, row_bytes, shift):
+    import torch
+    from oracle import attention_oracle as orc
+    from paper_2605_15422_amd import binding as B
+    print("case rows", P, len(lens), row_bytes, shift, flush=True)
+    N, cu = len(lens), np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, w = int(cu[-1]), row_bytes // 4
+    x = np.random.default_rng(row_bytes + P).integers(0, 2**31, size=(P + T, w)).astype(np.int32)
+    std, _ = orc.replicated_layout(P, cu, x[:P], x[P:])
+    cu_dev = torch.from_numpy(cu).cuda()
+
+    def dev(rows, a=None):
+        t = torch.full((rows * w + shift // 4 + 8,), -5, dtype=torch.int32, device="cuda")
+        v = t[shift // 4:shift // 4 + rows * w]
+        if a is not None:
+            v.copy_(torch.from_numpy(np.ascontiguousarray(a).reshape(-1)))
+        return t, v
+
+    (_, packed), (lt, long_), (bt, back) = dev(P + T, x), dev(N * P + T), dev(P + T)
+    pos_l = torch.full((N * P + T,), -1, dtype=torch.int32, device="cuda")
+    pos_p = torch.full((P + T,), -1, dtype=torch.int32, device="cuda")
+    B.dualkv_replicate(N, P, T, cu_dev, row_bytes, packed, long_, pos_l)
+    B.dualkv_repack(N, P, T, cu_dev, row_bytes, long_, back, pos_p)
+    assert np.array_equal(long_.cpu().numpy().reshape(-1, w), std)
+    assert np.array_equal(back.cpu().numpy().reshape(-1, w), x)
+    assert np.array_equal(pos_l.cpu().numpy(), orc.position_ids_replicated(P, cu))
+    assert np.array_equal(pos_p.cpu().numpy(), orc.position_ids_single_prompt(P, cu))
+    for t in (lt, bt):   # nothing outside the rows is written
+        assert (t[:shift // 4] == -5).all() and (t[-(8 if shift == 0 else 7):] == -5).all()
