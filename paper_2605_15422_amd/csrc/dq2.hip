@@ -3,9 +3,9 @@
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
 //
-// Shape: 8 waves (two per SIMD), each owning one 32-row subtile with Q, dO fragments and the dQ^T
-// accumulator in registers; K and V tiles of 64 keys travel global -> LDS directly (global_load_lds, three
-// stages, two tiles ahead: no staging registers, which pays for a deeper operand prefetch) into swizzled LDS.  S^T = K Q^T and
+// Shape: 8 waves (two per SIMD; four where the row blocks are few, see prefer_four_waves), each owning one 32-row
+// subtile with Q, dO fragments and the dQ^T accumulator in registers; K and V tiles of 64 keys travel global -> LDS
+// directly (global_load_lds, three stages, two tiles ahead: no staging registers, which pays for a deeper operand prefetch) into swizzled LDS.  S^T = K Q^T and
 // dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T through LDS transpose
 // reads of the same row-major K tile.  A 64-key tile is consumed as two 32-key halves so only one
 // 32x32 S and dP tile is live at a time.
@@ -20,15 +20,15 @@
 
 namespace dkv {
 
-template <int D, bool LOCAL>
-__global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
-  constexpr int NT = 512, BN = 64;
+template <int D, int NW, bool LOCAL>
+__global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
+  constexpr int BN = 64;
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int TILE_BYTES = BN * RB;
   constexpr int NSTAGE = 3, STAGE_BYTES = 2 * TILE_BYTES;
-  constexpr int IPT = TILE_BYTES / 1024 / 8;   // 1 KB load instructions per wave, tile and tensor
+  constexpr int IPT = TILE_BYTES / 1024 / NW;  // 1 KB load instructions per wave, tile and tensor
   constexpr int RPI = 1024 / RB;               // rows per load instruction
-  constexpr int LPT = 2 * TILE_BYTES / 1024 / 8;   // per wave and tile
+  constexpr int LPT = 2 * TILE_BYTES / 1024 / NW;  // per wave and tile
   static_assert(kSplitRow<D> || LPT == 2 * IPT, "tile must split evenly over the waves");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSTAGE][K tile | V tile]
 
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   const u16* kd_base = p.kd.ptr + (int64_t)b.row_begin * p.kd.ts + (int64_t)b.hk * p.kd.hs;
   const u16* vd_base = p.vd.ptr + (int64_t)b.row_begin * p.vd.ts + (int64_t)b.hk * p.vd.hs;
   const int n_ctx_run = b.n_ctx - b.c0;
-  // global -> LDS tile loads: instruction j = wave + 8 t of a tile covers RPI key rows; lane l lands at LDS
+  // global -> LDS tile loads: instruction j = wave + NW t of a tile covers RPI key rows; lane l lands at LDS
   // chunk position l % CPR of row l / CPR of the instruction and fetches the chunk the swizzle stores there
   // (the swizzle has period 16 rows, so one offset serves every t).  Keys past the end of the region re-read
   // the last key: their scores are masked like any invisible key.
@@ -111,15 +111,16 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   // (token strides in bytes, read from the kernel arguments once: a scalar load inside the loop would make the
   // wave wait for every LDS read in flight as well)
   const int ktsb_c = (int)p.kc.ts * 2, ktsb_d = (int)p.kd.ts * 2, vtsb_c = (int)p.vc.ts * 2, vtsb_d = (int)p.vd.ts * 2;
-  // (head dim 96: twelve instructions per tensor, three consecutive ones per wave, waves 0-3 for K, 4-7 for V)
-  const u16 *myc_base = wave < 4 ? kc_base : vc_base, *myd_base = wave < 4 ? kd_base : vd_base;
-  const int mytsb_c = wave < 4 ? ktsb_c : vtsb_c, mytsb_d = wave < 4 ? ktsb_d : vtsb_d;
+  // (head dim 96: twelve instructions per tensor, consecutive ones per wave, the first half of the waves for K)
+  constexpr int HW = NW / 2;
+  const u16 *myc_base = wave < HW ? kc_base : vc_base, *myd_base = wave < HW ? kd_base : vd_base;
+  const int mytsb_c = wave < HW ? ktsb_c : vtsb_c, mytsb_d = wave < HW ? ktsb_d : vtsb_d;
   int ld_row[LPT], ld_off[LPT];
   if constexpr (kSplitRow<D>) {
-    static_assert(LPT == 3 && BN == 4 * kSplitRows<D>, "three instructions per wave");
+    static_assert(LPT % 3 == 0 && BN == HW * (LPT / 3) * kSplitRows<D>, "whole rows per wave");
 #pragma unroll
     for (int t = 0; t < LPT; ++t) {
-      ld_row[t] = (wave & 3) * kSplitRows<D> + split_row<D>(t, lane);
+      ld_row[t] = wave % HW * (LPT / 3) * kSplitRows<D> + split_row<D>(t, lane);
       ld_off[t] = (split_pos<D>(t, lane) ^ swz<D>(ld_row[t])) * 16;
     }
   }
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
       const u16* tb = uniform_ptr(reinterpret_cast<const u16*>(
           reinterpret_cast<const unsigned char*>(is_ctx ? myc_base : myd_base) + (int64_t)key0 * tsb));
       const int last = (is_ctx ? P : R) - key0 - 1;
-      const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * 3072;   // the V tile follows the K tile
+      const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * (LPT * 1024);   // the V tile follows the K tile
 #pragma unroll
       for (int t = 0; t < LPT; ++t)
         dma16(tb, __umul24((unsigned)min(ld_row[t], last), (unsigned)tsb) + ld_off[t], dst + t * 1024);
@@ -146,9 +147,9 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
     const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
-      const unsigned row = (unsigned)min(ld_row0 + t * 8 * RPI, last);
-      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * 8192);
-      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * 8192);
+      const unsigned row = (unsigned)min(ld_row0 + t * NW * RPI, last);
+      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * NW * 1024);
+      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * NW * 1024);
     }
   };
   // the tile consumed next must have landed; the LPT loads of the tile after it may stay in flight
@@ -271,25 +272,31 @@ __global__ __launch_bounds__(512) void dq2_kernel(const AttnParams p) {
   }
 }
 
-template <int D, bool LOCAL>
+template <int D, int NW, bool LOCAL>
 static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
-  fill_packing(p, 8);
+  fill_packing(p, NW);
   const size_t smem = 3 * 2 * 64 * 2 * D;
-  auto kern = dq2_kernel<D, LOCAL>;
-  hipError_t e = ensure_dynamic_lds<dq2_kernel<D, LOCAL>>(smem);
+  auto kern = dq2_kernel<D, NW, LOCAL>;
+  hipError_t e = ensure_dynamic_lds<dq2_kernel<D, NW, LOCAL>>(smem);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
   if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), smem, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NW * 64), smem, st, p);
   return hipGetLastError();
 }
 
-hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st) {
+template <int D>
+static hipError_t launch_dq2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
+  if (prefer_four_waves(p, 0.8)) return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
+  return local ? launch_dq2_t<D, 8, true>(p, st) : launch_dq2_t<D, 8, false>(p, st);
+}
+
+hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st) {
   switch (head_dim) {
-    case 64:  return local ? launch_dq2_t<64, true>(p, st) : launch_dq2_t<64, false>(p, st);
-    case 96:  return local ? launch_dq2_t<96, true>(p, st) : launch_dq2_t<96, false>(p, st);
-    case 128: return local ? launch_dq2_t<128, true>(p, st) : launch_dq2_t<128, false>(p, st);
+    case 64:  return launch_dq2_d<64>(p, st);
+    case 96:  return launch_dq2_d<96>(p, st);
+    case 128: return launch_dq2_d<128>(p, st);
   }
   return hipErrorInvalidValue;
 }

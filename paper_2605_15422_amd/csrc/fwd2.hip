@@ -4,14 +4,14 @@
 // are shared by all packed heads) and walks the two KV regions in logical order, prompt tiles then own-response tiles.
 // The scores are computed transposed, S^T = K Q^T, so that a lane owns one query row and exp(S^T) is already laid out
 // as the B operand of O^T += V^T P^T:
-//   * 8 waves (two per SIMD), each owning ONE 32-row subtile: Q fragments (B operands) and the O^T
-//     accumulator stay in registers (~200 VGPRs, no spills);
+//   * 8 waves (two per SIMD; four where the row blocks are few, see prefer_four_waves), each owning ONE 32-row
+//     subtile: Q fragments (B operands) and the O^T accumulator stay in registers (~200 VGPRs, no spills);
 //   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row so that both the
 //     16-byte K operand reads and the transposing V reads are bank-conflict free; V^T operands come
 //     from ds_read_b64_tr_b16 (LDS transpose read), so nothing is transposed on the way into LDS;
 //   * the tiles travel global -> LDS directly (global_load_lds) into two rings of four slots, K three
-//     tiles ahead (requested by waves 0-3) and V two (waves 4-7): no staging registers, no LDS stores, one
-//     barrier per tile;
+//     tiles ahead (requested by the first half of the waves) and V two (the second half): no staging
+//     registers, no LDS stores, one barrier per tile;
 //   * each wave runs a software pipeline over 32-key half tiles: while the VALU does the softmax of
 //     half g, the matrix pipe computes the scores of half g+1 and the P V product of half g-1.  Two
 //     waves per SIMD do not hide a wave's own MFMA -> softmax -> MFMA dependency chain on this chip
@@ -29,11 +29,9 @@
 
 namespace dkv {
 
-constexpr int kFwdWaves = 8;   // the K / V loader split below assumes eight waves
-
-template <int D>
+template <int D, int NWAVES>
 struct F2Cfg {
-  static constexpr int NW = kFwdWaves, NT = NW * 64, BN = 64;
+  static constexpr int NW = NWAVES, NT = NW * 64, BN = 64;
   static constexpr int KS = D / 16, DSUB = D / 32;
   static constexpr int RB = 2 * D;                 // row bytes
   static constexpr int CPR = D / 8;                // 16-byte chunks per row
@@ -45,9 +43,9 @@ struct F2Cfg {
   __device__ static __forceinline__ int fV(int row) { return D == 96 ? 0 : 4 * ((row / RPL) % (CPR / 4)); }
 };
 
-template <int D, bool LOCAL>
-__global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p) {
-  using C = F2Cfg<D>;
+template <int D, int NW, bool LOCAL>
+__global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
+  using C = F2Cfg<D, NW>;
   constexpr int BN = C::BN;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
   QBlock b;
@@ -107,7 +105,7 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   const int n_ctx_run = b.n_ctx - b.c0;
   constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
   constexpr int V_RING = NSTAGE * C::TILE_BYTES;
-  // the K tiles are requested by waves 0-3, the V tiles by waves 4-7: one address computation per wave and tile
+  // half of the waves request the K tiles, half the V tiles: one address computation per wave and tile
   constexpr int LW = C::NW / 2;                       // waves per tensor
   constexpr int IPT = C::TILE_BYTES / 1024 / LW;      // 1 KB load instructions per wave and tile
   constexpr int RPI = 1024 / C::RB;                   // rows per load instruction
@@ -121,10 +119,10 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows, each with an offset of its own)
   int ld_row[IPT], ld_coff[IPT];
   if constexpr (kSplitRow<D>) {
-    static_assert(IPT == 3 && C::BN == LW * kSplitRows<D>, "three instructions per wave");
+    static_assert(IPT % 3 == 0 && C::BN == LW * (IPT / 3) * kSplitRows<D>, "whole rows per wave");
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
-      ld_row[t] = lwave * kSplitRows<D> + split_row<D>(t, lane);
+      ld_row[t] = lwave * (IPT / 3) * kSplitRows<D> + split_row<D>(t, lane);
       ld_coff[t] = (split_pos<D>(t, lane) ^ (v_loader ? C::fV(ld_row[t]) : C::fK(ld_row[t]))) * 16;
     }
   }
@@ -150,8 +148,10 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
       const int r = min(ld_row0 + t * LW * RPI, last);
-      dma16(uniform_ptr(reinterpret_cast<const u16*>(tb)), (uint32_t)(__umul24((unsigned)r, (unsigned)tsb) + coff),
-            dst + t * LW * 1024);
+      // (four waves at head dim 128: the instructions of a wave are half a period of the K swizzle apart)
+      constexpr int FLIP = D == 128 && LW * RPI == 8 ? 128 : 0;
+      const int c = FLIP != 0 && which == 0 && (t & 1) ? coff ^ FLIP : coff;
+      dma16(uniform_ptr(reinterpret_cast<const u16*>(tb)), (uint32_t)(__umul24((unsigned)r, (unsigned)tsb) + c), dst + t * LW * 1024);
     }
   };
 
@@ -422,13 +422,13 @@ __global__ __launch_bounds__(kFwdWaves * 64) void fwd2_kernel(const AttnParams p
   }
 }
 
-template <int D, bool LOCAL>
+template <int D, int NW, bool LOCAL>
 static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
-  using C = F2Cfg<D>;
-  fill_packing(p, C::NW);
+  using C = F2Cfg<D, NW>;
+  fill_packing(p, NW);
   const size_t smem = 4 * 2 * C::TILE_BYTES;
-  auto kern = fwd2_kernel<D, LOCAL>;
-  hipError_t e = ensure_dynamic_lds<fwd2_kernel<D, LOCAL>>(smem);
+  auto kern = fwd2_kernel<D, NW, LOCAL>;
+  hipError_t e = ensure_dynamic_lds<fwd2_kernel<D, NW, LOCAL>>(smem);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
   if (nblk == 0) return hipSuccess;
@@ -436,12 +436,18 @@ static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st) {
+template <int D>
+static hipError_t launch_fwd2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
+  if (prefer_four_waves(p, 0.7)) return local ? launch_fwd2_t<D, 4, true>(p, st) : launch_fwd2_t<D, 4, false>(p, st);
+  return local ? launch_fwd2_t<D, 8, true>(p, st) : launch_fwd2_t<D, 8, false>(p, st);
+}
+
+hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st) {
   switch (head_dim) {
-    case 64:  return local ? launch_fwd2_t<64, true>(p, st) : launch_fwd2_t<64, false>(p, st);
-    case 96:  return local ? launch_fwd2_t<96, true>(p, st) : launch_fwd2_t<96, false>(p, st);
-    case 128: return local ? launch_fwd2_t<128, true>(p, st) : launch_fwd2_t<128, false>(p, st);
+    case 64:  return launch_fwd2_d<64>(p, st);
+    case 96:  return launch_fwd2_d<96>(p, st);
+    case 128: return launch_fwd2_d<128>(p, st);
   }
   return hipErrorInvalidValue;
 }
