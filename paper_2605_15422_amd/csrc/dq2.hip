@@ -3,7 +3,7 @@
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
 //
-// Shape: 8 waves (two per SIMD; four where the row blocks are few, see prefer_four_waves), each owning one 32-row
+// Shape: 8 waves (two per SIMD; four where the row blocks are few, see choose_waves), each owning one 32-row
 // subtile with Q, dO fragments and the dQ^T accumulator in registers; K and V tiles of 64 keys travel global -> LDS
 // directly (global_load_lds, three stages, two tiles ahead: no staging registers, which pays for a deeper operand prefetch) into swizzled LDS.  S^T = K Q^T and
 // dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T through LDS transpose
@@ -21,14 +21,15 @@
 namespace dkv {
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void dq2_kernel(const AttnParams p) {
   constexpr int BN = 64;
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int TILE_BYTES = BN * RB;
   constexpr int NSTAGE = 3, STAGE_BYTES = 2 * TILE_BYTES;
-  constexpr int IPT = TILE_BYTES / 1024 / NW;  // 1 KB load instructions per wave, tile and tensor
+  constexpr int LW = NW == 12 ? 8 : NW;          // waves that request tiles
+  constexpr int IPT = TILE_BYTES / 1024 / LW;  // 1 KB load instructions per wave, tile and tensor
   constexpr int RPI = 1024 / RB;               // rows per load instruction
-  constexpr int LPT = 2 * TILE_BYTES / 1024 / NW;  // per wave and tile
+  constexpr int LPT = 2 * TILE_BYTES / 1024 / LW;  // per wave and tile
   static_assert(kSplitRow<D> || LPT == 2 * IPT, "tile must split evenly over the waves");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSTAGE][K tile | V tile]
 
@@ -147,9 +148,9 @@ __global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
     const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
-      const unsigned row = (unsigned)min(ld_row0 + t * NW * RPI, last);
-      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * NW * 1024);
-      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * NW * 1024);
+      const unsigned row = (unsigned)min(ld_row0 + t * LW * RPI, last);
+      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * LW * 1024);
+      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * LW * 1024);
     }
   };
   // the tile consumed next must have landed; the LPT loads of the tile after it may stay in flight
@@ -158,8 +159,11 @@ __global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
     if (__builtin_expect(!newer_in_flight, 0)) wait_vm<0>();
   };
 
-  issue_loads(0, 0);
-  if (b.n_tiles > 1) issue_loads(1, 1);
+  const bool loader = LW == NW || wave < LW;
+  if (loader) {
+    issue_loads(0, 0);
+    if (b.n_tiles > 1) issue_loads(1, 1);
+  }
   wait_vm<0>();   // (also the stores of the row statistics: the waits of the main loop count loads only)
   __syncthreads();
 
@@ -173,7 +177,7 @@ __global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
   for (int it = 0; it < b.n_tiles; ++it) {
     // tile it+2 goes into the stage that tile it-1 left at the last barrier
     const int stage2 = stage == 0 ? 2 : stage - 1;
-    if (it + 2 < b.n_tiles) issue_loads(it + 2, stage2);
+    if (loader && it + 2 < b.n_tiles) issue_loads(it + 2, stage2);
 
     const unsigned char* Kb = smem + stage * STAGE_BYTES;
     const unsigned char* Vb = Kb + TILE_BYTES;
@@ -288,7 +292,11 @@ static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
 template <int D>
 static hipError_t launch_dq2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
-  if (prefer_four_waves(p, 0.8)) return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
+  switch (choose_waves(p, 0.8, D == 64 ? 1.32 : 0.0)) {
+    case 4: return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
+    case 12:
+      if constexpr (D == 64) return local ? launch_dq2_t<D, 12, true>(p, st) : launch_dq2_t<D, 12, false>(p, st);
+  }
   return local ? launch_dq2_t<D, 8, true>(p, st) : launch_dq2_t<D, 8, false>(p, st);
 }
 

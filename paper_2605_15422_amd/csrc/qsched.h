@@ -112,32 +112,37 @@ static inline void fill_packing(AttnParams& p, int nst) {
   p.MB = (p.max_rows + p.BMR - 1) / p.BMR;
 }
 
-// Four or eight waves in a workgroup of the head-dim 64 / 96 / 128 kernels?  A wave that has its SIMD to itself takes `alpha`
-// of the time per tile (0.7 forward, 0.8 dQ), so four waves give a CU less, but half as many rows make twice as many
-// workgroups, which pays where the chip would otherwise wait for its longest key walk.  Times in tiles of 64 keys, with
-// kStart for a workgroup's start and end: the longest walk, the total over 256 CUs, and whole rounds where all walks are
-// about alike.  Measured (eight -> four waves): 1 x 1021 rows, 32 / 8 heads, d = 128 (128 workgroups of eight) forward
-// 34.7 -> 25.2 us, dQ 42 -> 35; responses of 8 x <= 256 rows behind them (176) 47 -> 54 and 54 -> 74; 1 x 4111 rows, 16 / 4
-// heads, d = 96 (260) forward + dQ 0.25 -> 0.19 ms; 1 x 5059 rows, d = 128 (640) 238 -> 282 and 303 -> 391 us.
-static inline bool prefer_four_waves(const AttnParams& p, double alpha) {
+// How many waves in a workgroup of the head-dim 64 / 96 / 128 kernels?  Eight (two per SIMD) unless
+//   * four: a wave that has its SIMD to itself takes t4 of the time per tile (0.7 forward, 0.8 dQ).  A CU gets less done, but
+//     half the rows make twice as many workgroups, which pays where the chip would otherwise wait for its longest key walk;
+//   * twelve (t12 > 0: head dim 64, whose waves fit three to a SIMD): a tile takes 1.32 times as long for 1.5 times the rows;
+//     the softmax of this head dim takes more issue slots than its MFMAs, and a third wave fills gaps of the other two.
+// Times in tiles of 64 keys, with kStart for a workgroup's start and end: the longest walk, the total over 256 CUs, and whole
+// rounds where all walks are about alike.  Measured, eight -> four waves: 1 x 1021 rows, 32 / 8 heads, d = 128 (128 workgroups
+// of eight) forward 34.7 -> 25.2 us, dQ 42 -> 35; responses of 8 x <= 256 rows behind them (176) 47 -> 54 and 54 -> 74;
+// 1 x 4111 rows, 16 / 4 heads, d = 96 (260) forward + dQ 0.25 -> 0.19 ms; 1 x 5059 rows, d = 128 (640) 238 -> 282 and 303 ->
+// 391 us.  Eight -> twelve: responses of 8 x U(131, 2048) rows behind 4096, 32 / 8 heads, d = 64, forward 0.80 -> 0.70 ms, dQ
+// 0.92 -> 0.83 ms; the 4096 prompt rows alone 0.10 -> 0.13 and 0.12 -> 0.13 ms.
+static inline int choose_waves(const AttnParams& p, double t4, double t12) {
   constexpr double kStart = 3.0, kCus = 256.0;
-  AttnParams e = p;
-  fill_packing(e, 8);
   const double rows = (double)p.total / p.n_seqs;
-  const double wgs = (double)p.n_seqs * (int64_t)((rows + e.BMR - 1) / e.BMR) * e.HC * p.Hk;
   double avg = (p.ctx_len + rows / 2) / 64 + 0.5, longest = ((double)p.ctx_len + p.max_rows) / 64 + 1;
   if (p.window > 0) {
     const double most = (double)p.window / 64 + 2;
     avg = avg < most ? avg : most;
     longest = longest < most ? longest : most;
   }
-  auto time = [&](double n, double a) {
-    double t = n * (a * avg + kStart) / kCus;
-    if (avg > 0.75 * longest) t = (double)(int64_t)((n + kCus - 1) / kCus) * (a * avg + kStart);
-    const double chain = a * longest + kStart;
-    return t > chain ? t : chain;
+  auto time = [&](int waves, double per_tile) {
+    AttnParams e = p;
+    fill_packing(e, waves);
+    const double n = (double)p.n_seqs * (int64_t)((rows + e.BMR - 1) / e.BMR) * e.HC * p.Hk, each = per_tile * avg + kStart;
+    const double all = avg > 0.75 * longest ? (double)(int64_t)((n + kCus - 1) / kCus) * each : n * each / kCus;
+    const double chain = per_tile * longest + kStart;
+    return all > chain ? all : chain;
   };
-  return time(2 * wgs, alpha) < 0.97 * time(wgs, 1.0);
+  const double t8 = 0.97 * time(8, 1.0);
+  if (time(4, t4) < t8) return 4;
+  return t12 > 0 && time(12, t12) < t8 ? 12 : 8;
 }
 
 }  // namespace dkv
