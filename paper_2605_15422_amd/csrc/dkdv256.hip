@@ -35,7 +35,6 @@
 namespace dkv {
 namespace {
 
-enum : int { HDR_VALID = 1, HDR_ACTIVE = 2, HDR_MASK = 4 };
 template <int V>
 using IC = std::integral_constant<int, V>;
 

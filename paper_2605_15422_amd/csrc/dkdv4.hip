@@ -28,6 +28,11 @@
 // P = 4111, R ~ U(131, 2048), 16 / 4 heads: 0.88 + 0.35 ms (Call 2 + Call 1), against 1.95 + 0.82 ms for the kernel with
 // register staging, transposed copies and a barrier per phase that served this head dim before.
 //
+// Head dim 64 halves the MFMAs of a block but not its exponentials, and its waves need 168 registers at most: three fit on a
+// SIMD.  Two groups of four producers take two row blocks per interval, the four consumers accumulate both, one after the
+// other: half the barriers per block, and the softmax of one group runs beside the chains of the other.  Measured on N = 8,
+// P = 4096, R ~ U(131, 2048), 32 / 8 heads: Call 2 1.43 -> 1.34 ms, Call 1 0.237 -> 0.221 ms.
+//
 // The compiler does not know about the global -> LDS loads: the consumers count them themselves
 // (s_waitcnt vmcnt) before the barrier that publishes a row block, and no compiler-visible vector memory
 // load is issued inside the main loop (a compiler-placed wait would also wait for all blocks in flight).
@@ -40,25 +45,36 @@
 
 namespace dkv {
 
-enum : int { HDR_VALID = 1, HDR_ACTIVE = 2, HDR_MASK = 4 };
+
+// Producer groups: how many row blocks an interval takes.
+template <int D>
+constexpr int kGroups = D == 64 ? 2 : 1;
+template <int D>
+constexpr int kWaves = 4 * kGroups<D> + 4;
+template <int D>
+constexpr int kStages = kGroups<D> == 2 ? 8 : 6;   // LDS stages (row blocks)
 template <int V>
 using IC = std::integral_constant<int, V>;
 
 template <int D, bool LOCAL>
-__global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
+__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p) {
   constexpr int BN = 128, HB = 32;                 // keys per workgroup, query rows per block
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int HT_BYTES = HB * RB;                // one Q or dO row block
   constexpr int STAT_OFF = 2 * HT_BYTES;           // lse2[32] | D[32]
   constexpr int HDR_OFF = STAT_OFF + 256;          // 4 x {flags, row0, nvalid, -}
   constexpr int STAGE_BYTES = HDR_OFF + 64;
-  constexpr int NBUF = 6, AHEAD = NBUF - 1;        // row blocks requested ahead of the one being computed
+  constexpr int NPG = kGroups<D>, CW = 4 * NPG;    // row blocks per interval; the first consumer wave
+  constexpr int NBUF = kStages<D>, NIS = NBUF / NPG;   // stages: one row block each, NIS intervals in all
+  constexpr int AHEAD = NIS - 1;                   // intervals requested ahead of the one being computed
+  constexpr int IST_BYTES = NPG * STAGE_BYTES;
+  constexpr int HDR_GO = NPG == 1 ? HDR_VALID : HDR_RUN;
   constexpr int XCH_OFF = NBUF * STAGE_BYTES;
-  constexpr int XCH_BYTES = 16384;                 // [key subtile][P k-step 0,1 | dS k-step 0,1][lane] x 16 B
+  constexpr int XCH_BYTES = NPG * 16384;           // [row block][key subtile][P k-step 0,1 | dS k-step 0,1][lane] x 16 B
   constexpr int NIT = HT_BYTES / 1024;             // 1 KB load instructions per row block and tensor
   constexpr bool LOADER = kSplitRow<D>;            // one consumer wave makes all requests
   constexpr int IPB = LOADER ? 2 * NIT : 2 * NIT / 4;   // per requesting wave (Q and dO)
-  constexpr int LOAD_WAVE = 7, HDR_WAVE = LOADER ? LOAD_WAVE : 4, STAT_WAVE = 5;
+  constexpr int LOAD_WAVE = 7, STAT_WAVE = CW + 1;
   constexpr int RPI = 1024 / RB;                   // rows per load instruction
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -81,9 +97,10 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     region_len = p.cu ? (p.cu[seq_lo + 1] - key_row_begin) : p.total;
   }
 
-  if (wave < 4) {
+  if (wave < CW) {
     // ================================= producer ==============================================
     const float c = p.scale_log2;
+    const int pg = NPG == 1 ? 0 : wave >> 2;   // the row block of every interval that this wave takes
     const int my_key = key0 + kvs * 32 + l32;
     const u16 *kbase, *vbase;
     int64_t kts, vts;
@@ -119,24 +136,25 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     }
     // LDS addresses: two base registers per operand (stages 0-2 and 3-5) so that every access of the
     // unrolled loop is base + immediate offset (the offset field has 16 bits)
-    constexpr int HALF = (NBUF / 2) * STAGE_BYTES;
+    constexpr int NLO = NPG == 2 ? NIS : NIS / 2;   // interval stages within the 16-bit offset of one base register
+    constexpr int HALF = NLO * IST_BYTES;
     const unsigned char* frag_lo[KS];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) frag_lo[ks] = smem + tile_off<D>(l32, 2 * ks + hi);
+    for (int ks = 0; ks < KS; ++ks) frag_lo[ks] = smem + pg * STAGE_BYTES + tile_off<D>(l32, 2 * ks + hi);
     const unsigned char* frag_hi[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) frag_hi[ks] = frag_lo[ks] + HALF;
-    const unsigned char* stat_lo = smem + STAT_OFF + hi * 16;   // this lane's rows 8*(r/4) + 4*hi + r%4
+    const unsigned char* stat_lo = smem + pg * STAGE_BYTES + STAT_OFF + hi * 16;   // this lane's rows 8*(r/4) + 4*hi + r%4
     const unsigned char* stat_hi = stat_lo + HALF;
-    const unsigned char* hdr_lo = smem + HDR_OFF + kvs * 16;
+    const unsigned char* hdr_lo = smem + pg * STAGE_BYTES + HDR_OFF + kvs * 16;
     const unsigned char* hdr_hi = hdr_lo + HALF;
-    unsigned char* xw_lane = smem + XCH_OFF + kvs * 4096 + lane * 16;
+    unsigned char* xw_lane = smem + XCH_OFF + pg * 16384 + kvs * 4096 + lane * 16;
 
     bf16x8 qfr[KS];
     int flags, row0, nvalid;
     auto read_header = [&](auto Uc, u32x4& h) __attribute__((always_inline)) {
       constexpr int U = decltype(Uc)::value;
-      h = *reinterpret_cast<const u32x4*>((U < NBUF / 2 ? hdr_lo : hdr_hi) + (U % (NBUF / 2)) * STAGE_BYTES);
+      h = *reinterpret_cast<const u32x4*>((U < NLO ? hdr_lo : hdr_hi) + (U % NLO) * IST_BYTES);
     };
     // which = 0: Q fragments (read one interval early), 1: dO fragments (read at the start of their interval,
     // behind the S chain: keeping both sets across the barrier does not fit next to the K / V fragments)
@@ -144,14 +162,14 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       constexpr int U = decltype(Uc)::value;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        const unsigned char* b = U >= NBUF / 2 ? frag_hi[ks] : frag_lo[ks];
-        out[ks] = *reinterpret_cast<const bf16x8*>(b + (U % (NBUF / 2)) * STAGE_BYTES + decltype(which)::value * HT_BYTES);
+        const unsigned char* b = U >= NLO ? frag_hi[ks] : frag_lo[ks];
+        out[ks] = *reinterpret_cast<const bf16x8*>(b + (U % NLO) * IST_BYTES + decltype(which)::value * HT_BYTES);
       }
     };
     // row statistics of this lane's 16 rows (register r <-> row crow(r, hi)): which = 0 LSE*log2e, 1 D
     auto load_stat = [&](auto Uc, int which, float* out) __attribute__((always_inline)) {
       constexpr int U = decltype(Uc)::value;
-      const unsigned char* b = (U < NBUF / 2 ? stat_lo : stat_hi) + (U % (NBUF / 2)) * STAGE_BYTES + which * 128;
+      const unsigned char* b = (U < NLO ? stat_lo : stat_hi) + (U % NLO) * IST_BYTES + which * 128;
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
         const f32x4 v = *reinterpret_cast<const f32x4*>(b + r4 * 32);
@@ -162,8 +180,8 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
 
     // one interval: block h in stage U; returns false after the end of the schedule
     auto interval = [&](auto Uc) __attribute__((always_inline)) -> bool {
-      constexpr int U = decltype(Uc)::value, NU = (U + 1) % NBUF, XB = U & 1;
-      if (__builtin_expect(!(flags & HDR_VALID), 0)) {
+      constexpr int U = decltype(Uc)::value, NU = (U + 1) % NIS, XB = U & 1;
+      if (__builtin_expect(!(flags & HDR_GO), 0)) {
         __syncthreads();
         return false;
       }
@@ -251,232 +269,128 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       if (!interval(IC<1>{})) break;
       if (!interval(IC<2>{})) break;
       if (!interval(IC<3>{})) break;
-      if (!interval(IC<4>{})) break;
-      if (!interval(IC<5>{})) break;
+      if constexpr (NIS > 4) {
+        if (!interval(IC<4 % NIS>{})) break;
+        if (!interval(IC<5 % NIS>{})) break;
+      }
     }
   } else {
     // ================================= consumer ==============================================
-    const int jb = wave - 4;
+    const int jb = wave - CW;
     const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
     // ---- global -> LDS loads: instruction i = jb + 4 t of a row block covers RPI rows of Q (t < IPB/2) or
     // dO; lane l lands at LDS chunk position l % CPR of row (l / CPR) of the instruction, so it fetches the
     // chunk that the tile swizzle stores there (the swizzle has period 4 RPI rows: one offset serves all t).
-    const int G = own_sgpr(p.G);
-    const int q_ts = own_sgpr((int)p.q.ts), do_ts = own_sgpr((int)p.dout.ts);
-    const int64_t q_hs = own_sgpr(p.q.hs), do_hs = own_sgpr(p.dout.hs), total = own_sgpr((int64_t)p.total);
     const int ld_row0 = jb * RPI + lane / CPR;
     const int ld_coff = ((lane % CPR) ^ swz<D>(ld_row0)) * 16;
-    const uint32_t ld_lds = smem_addr + jb * 1024;
+    const uint32_t ld_lds = smem_addr + (LOADER ? 0 : jb * 1024);
+    const int q_tsb = own_sgpr((int)p.q.ts * 2), do_tsb = own_sgpr((int)p.dout.ts * 2);   // bytes per token
     // per-lane global offsets of this wave's load instructions for a block of 32 valid rows (a partial last
     // block clamps its rows instead: rare, computed on the spot)
     uint32_t voff_full[IPB];
-    int sp_row[3], sp_coff[3];   // (loader) row and byte offset of instructions t, t + 3, ... (16 rows apart)
-    if constexpr (LOADER) {
+    int ld_row[IPB / 2], ld_off[IPB / 2];   // row and byte offset within the row, the same for Q and dO
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        sp_row[t] = split_row<D>(t, lane);
-        sp_coff[t] = (split_pos<D>(t, lane) ^ swz<D>(sp_row[t])) * 16;
-      }
+    for (int t = 0; t < IPB / 2; ++t) {
+      ld_row[t] = LOADER ? split_row<D>(t, lane) : ld_row0 + t * 4 * RPI;
+      ld_off[t] = LOADER ? (split_pos<D>(t, lane) ^ swz<D>(ld_row[t])) * 16 : ld_coff;
     }
 #pragma unroll
-    for (int t = 0; t < IPB; ++t) {
-      if constexpr (LOADER) {
-        const int tt = t % NIT, row = sp_row[tt % 3] + tt / 3 * kSplitRows<D>;
-        voff_full[t] = (uint32_t)(row * (t < NIT ? q_ts : do_ts) * 2 + sp_coff[tt % 3]);
-        continue;
-      }
-      voff_full[t] = LOCAL ? 0u : (uint32_t)((ld_row0 + (t % (IPB / 2)) * 4 * RPI) * (t < IPB / 2 ? q_ts : do_ts) * 2 + ld_coff);
-    }
+    for (int t = 0; t < IPB; ++t)
+      voff_full[t] = (uint32_t)(ld_row[t % (IPB / 2)] * (t < IPB / 2 ? q_tsb : do_tsb) + ld_off[t % (IPB / 2)]);
     // row statistics: lanes 0-31 fetch LSE*log2e, lanes 32-63 fetch D; both arrays live in one workspace, D
     // first and LSE*log2e less than 4 GB behind it (checked by the launcher), so one scalar base plus an
-    // unsigned 32-bit lane offset addresses both
-    const float* stat_ptr = p.dvec;
+    // unsigned 32-bit lane offset addresses both (the loader of head dim 96 uses 64-bit lane addresses)
     const uint32_t stat_lane_off = hi ? 0u : (uint32_t)((const char*)p.lse2 - (const char*)p.dvec);
-    const float* stat_lane = hi ? p.dvec : p.lse2;   // (the loader uses 64-bit lane addresses)
+    const int64_t stat_lane = hi ? 0 : (const char*)p.lse2 - (const char*)p.dvec;
 
-    // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
-    // blocks of 32 that see at least one key of the tile, query heads of the group innermost.  All state is
-    // wave-uniform and advanced incrementally.
-    int seq = seq_lo, rb = 0, rb_end = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
-    const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
-    int64_t st_row = 0, st_cur = 0;
-    bool more = false;
-    uint32_t gflags = 0;   // wave 4, lanes 0-3: flags of key subtile `lane` for the current row group (loader: byte i of
-                           // a scalar: those of subtile i)
-    auto enter_group = [&]() __attribute__((always_inline)) {
-      row0 = rb * HB;
-      nvalid = min(HB, R - row0);
-      q_cur = q_row;
-      do_cur = do_row;
-      st_cur = st_row;
-      g = 0;
+    // ---- row-block schedule (kvsched.h); wave jb writes the headers of key subtile jb, the loader all four
+    RowWalk<HB> walk(p, hk, seq_hi);
+    const SubtileVis<LOCAL> vis(is_ctx, key0 + (LOADER ? 0 : jb * 32), P, W);
+    uint32_t flags = 0;   // of the current row block (the loader: byte i those of subtile i)
+    auto new_rows = [&]() __attribute__((always_inline)) {
+      flags = vis.flags(walk.row0, walk.nvalid, HB);
       if constexpr (LOADER) {
-        gflags = 0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int k_lo = key0 + i * 32, k_hi = k_lo + 31;
-          bool a, m;
-          if (is_ctx) {
-            a = !LOCAL || (k_hi > P + row0 - W);
-            m = LOCAL && (k_lo <= P + row0 + 31 - W);
-          } else {
-            a = k_lo <= row0 + 31;
-            m = k_hi > row0;
-            if (LOCAL) {
-              a = a && (k_hi > row0 - W);
-              m = m || (k_lo <= row0 + 31 - W);
-            }
-          }
-          m = m || nvalid < HB;
-          gflags |= (uint32_t)(HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0)) << (8 * i);
-        }
-      } else if (wave == HDR_WAVE) {
-        const int k_lo = key0 + (lane & 3) * 32, k_hi = k_lo + 31;
-        bool a, m;
-        if (is_ctx) {
-          a = !LOCAL || (k_hi > P + row0 - W);
-          m = LOCAL && (k_lo <= P + row0 + 31 - W);
-        } else {
-          a = k_lo <= row0 + 31;
-          m = k_hi > row0;
-          if (LOCAL) {
-            a = a && (k_hi > row0 - W);
-            m = m || (k_lo <= row0 + 31 - W);
-          }
-        }
-        m = m || nvalid < HB;
-        gflags = HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0);
+        for (int i = 1; i < 4; ++i) flags |= vis.flags(walk.row0 - i * 32, walk.nvalid, HB) << (8 * i);
       }
+      asm("" : "+s"(flags));
     };
-    // (response tiles have one sequence: only the first call has to know them)
+    // (response tiles have one sequence: only the first call has to know them; windowed tiles are short and not cut)
+    const int rows_lo = LOCAL ? 0 : kb.rb_lo * HB, rows_hi = LOCAL || kb.rb_hi == INT_MAX ? INT_MAX : kb.rb_hi * HB;
     auto init_seq = [&](auto first) __attribute__((always_inline)) {
-      // the offsets are loaded through the vector path: make their uniformity explicit
-      row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
-      R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
-      int rows = R;
+      const int Rs = walk.enter_seq(p);
+      int lo = 0, end;
       if (LOCAL ? is_ctx : !decltype(first)::value || is_ctx) {
         const int key_hi = min(P, key0 + BN) - 1;
-        if (LOCAL) rows = min(R, key_hi + W - P);
-        rb = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
-        rb_end = rows > 0 ? (rows + HB - 1) / HB : 0;
-        if (!LOCAL && seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
+        end = LOCAL ? min(Rs, key_hi + W - P) : Rs;
+        if (!LOCAL && decltype(first)::value) lo = rows_lo;
+        if (!LOCAL && walk.seq == seq_hi - 1) end = min(end, rows_hi);
       } else {
-        const int key_hi = min(R, key0 + BN) - 1;
-        if (LOCAL) rows = min(R, key_hi + W);
-        rb = LOCAL ? key0 / HB : max(key0 / HB, kb.rb_lo);   // (windowed tiles are short: their row blocks are not cut)
-        rb_end = LOCAL ? (rows + HB - 1) / HB : min((rows + HB - 1) / HB, kb.rb_hi);
+        const int key_hi = min(Rs, key0 + BN) - 1;
+        end = LOCAL ? min(Rs, key_hi + W) : min(Rs, rows_hi);
+        lo = max(key0, rows_lo);
       }
-      const int64_t grow = (int64_t)row_begin + rb * HB;
-      q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
-      do_row = uniform_ptr(p.dout.ptr + grow * do_ts + (int64_t)hk * G * do_hs);
-      st_row = (int64_t)hk * G * total + grow;
-    };
-    auto next_group = [&]() __attribute__((always_inline)) {
-      if (++rb < rb_end) {
-        q_row += (int64_t)HB * q_ts;
-        do_row += (int64_t)HB * do_ts;
-        st_row += HB;
-        enter_group();
-        return;
-      }
-      more = false;
-      while (++seq < seq_hi) {
-        init_seq(std::false_type{});
-        if (rb < rb_end) {
-          more = true;
-          enter_group();
-          return;
-        }
-      }
+      walk.enter_rows(p, lo, end);
+      new_rows();
     };
     uint32_t vbits = 0;   // bit i: block (request position - 1 - i) exists
     // requests the next block of the schedule (or marks the end) in stage IS (the loader: at stage_off) and advances the
     // schedule
     auto issue_block = [&](auto ISc, uint32_t stage_off = 0) __attribute__((always_inline)) {
       constexpr int IS = decltype(ISc)::value;
-      if (wave == HDR_WAVE && lane < 4) {
-        u32x4 h;
-        h.x = more ? (LOADER ? (gflags >> (8 * lane)) & 0xffu : gflags) : 0u;
-        h.y = (uint32_t)row0;
-        h.z = (uint32_t)nvalid;
-        h.w = 0u;
-        *reinterpret_cast<u32x4*>(smem + stage_off + IS * STAGE_BYTES + HDR_OFF + lane * 16) = h;
+      unsigned char* hdr = smem + stage_off + IS * STAGE_BYTES + HDR_OFF + (LOADER ? lane : jb) * 16;
+      if (__builtin_expect(!walk.more, 0)) {
+        vbits <<= 1;
+        // the second block of an interval runs (with nothing visible) if the first one exists
+        const uint32_t run = IS % NPG != 0 && (vbits & 2u) != 0 ? HDR_RUN : 0u;
+        if (lane < (LOADER ? 4 : 1)) *reinterpret_cast<u32x4*>(hdr) = u32x4{run, 0u, 0u, 0u};
+        return;
       }
-      vbits = (vbits << 1) | (more ? 1u : 0u);
-      if (__builtin_expect(more, 1)) {
-        const int last = nvalid - 1;   // rows past the end of the sequence re-read its last row
-        const u16* q_base = uniform_ptr(q_cur);
-        const u16* do_base = uniform_ptr(do_cur);
-        // (one branch for the whole block, not one per load)
-        if constexpr (LOADER) {
-          if (__builtin_expect(nvalid == HB, 1)) {
-            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
-              constexpr int t = decltype(Tc)::value;
-              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff_full[t], smem_addr + stage_off);
-            });
-          } else {
-            static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
-              constexpr int t = decltype(Tc)::value, tt = t % NIT;
-              const int row = sp_row[tt % 3] + tt / 3 * kSplitRows<D>;
-              const uint32_t voff =
-                  __umul24((unsigned)min(row, last), (unsigned)((t < NIT ? q_ts : do_ts) * 2)) + (uint32_t)sp_coff[tt % 3];
-              dma16_at<IS * STAGE_BYTES + t * 1024>(t < NIT ? q_base : do_base, voff, smem_addr + stage_off);
-            });
-          }
-        } else if (__builtin_expect(!LOCAL && nvalid == HB, 1)) {
-          static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
-            constexpr int t = decltype(Tc)::value;
-            dma16_at<IS * STAGE_BYTES + (t < IPB / 2 ? 0 : HT_BYTES) + (t % (IPB / 2)) * 4096>(
-                t < IPB / 2 ? q_base : do_base, voff_full[t], ld_lds);
-          });
-        } else {
-          static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
-            constexpr int t = decltype(Tc)::value;
-            constexpr bool is_q = t < IPB / 2;
-            const int row = ld_row0 + (t % (IPB / 2)) * 4 * RPI;
-            const uint32_t voff = __umul24((unsigned)min(row, last), (unsigned)((is_q ? q_ts : do_ts) * 2)) + ld_coff;
-            dma16_at<IS * STAGE_BYTES + (is_q ? 0 : HT_BYTES) + (t % (IPB / 2)) * 4096>(is_q ? q_base : do_base, voff, ld_lds);
-          });
-        }
-        if (LOADER) {
-          dma4_from<IS * STAGE_BYTES + STAT_OFF>(stat_lane + st_cur + min(l32, last), smem_addr + stage_off);
-        } else if (wave == STAT_WAVE) {
-          dma4_at<IS * STAGE_BYTES + STAT_OFF>(uniform_ptr(reinterpret_cast<const u16*>(stat_ptr + st_cur)),
-                                               stat_lane_off + (uint32_t)min(l32, last) * 4u, smem_addr);
-        }
-        if (__builtin_expect(++g < G, 1)) {
-          q_cur += q_hs;
-          do_cur += do_hs;
-          st_cur += total;
-        } else {
-          next_group();
-        }
+      vbits = (vbits << 1) | 1u;
+      if (lane < (LOADER ? 4 : 1)) {
+        const uint32_t fl = LOADER ? (flags >> (8 * lane)) & 0xffu : flags;
+        *reinterpret_cast<u32x4*>(hdr) = u32x4{fl | HDR_RUN, (uint32_t)walk.row0, (uint32_t)walk.nvalid, 0u};
       }
+      const int last = walk.nvalid - 1;   // rows past the end of the sequence re-read its last row
+      const void* const q_base = reinterpret_cast<const void*>(walk.q);
+      const void* const do_base = reinterpret_cast<const void*>(walk.dout);
+      auto load = [&](auto Tc, uint32_t voff) __attribute__((always_inline)) {
+        constexpr int t = decltype(Tc)::value;
+        constexpr int off = IS * STAGE_BYTES + (LOADER ? t * 1024 : (t < IPB / 2 ? 0 : HT_BYTES) + (t % (IPB / 2)) * 4096);
+        dma16_at<off>(t < IPB / 2 ? q_base : do_base, voff, ld_lds + stage_off);
+      };
+      // (one branch for the whole block, not one per load)
+      if (__builtin_expect(walk.nvalid == HB, 1)) {
+        static_for<IPB>([&](auto Tc) __attribute__((always_inline)) { load(Tc, voff_full[decltype(Tc)::value]); });
+      } else {
+        static_for<IPB>([&](auto Tc) __attribute__((always_inline)) {
+          constexpr int t = decltype(Tc)::value;
+          load(Tc, __umul24((unsigned)min(ld_row[t % (IPB / 2)], last), (unsigned)(t < IPB / 2 ? q_tsb : do_tsb)) +
+                       (uint32_t)ld_off[t % (IPB / 2)]);
+        });
+      }
+      if constexpr (LOADER)
+        dma4_from<IS * STAGE_BYTES + STAT_OFF>(reinterpret_cast<const char*>(walk.st) + stat_lane + min(l32, last) * 4,
+                                               smem_addr + stage_off);
+      else if (wave == STAT_WAVE)
+        dma4_at<IS * STAGE_BYTES + STAT_OFF>(reinterpret_cast<const void*>(walk.st), stat_lane_off + (uint32_t)min(l32, last) * 4u,
+                                             smem_addr);
+      if (__builtin_expect(!walk.step(new_rows), 0)) walk.next_seq([&]() __attribute__((always_inline)) { init_seq(std::false_type{}); });
     };
     // Block b is requested AHEAD blocks early and must have landed by the end of interval b - 2 (the
     // producer reads its operands one interval early): the three youngest blocks (IPB loads each per
     // wave; wave 5 issues one more, for it the bound is a little stricter) may stay in flight.  If the
     // newest request was the end mark, fewer loads are outstanding: wait for all of them.
     auto wait_loads = [&]() __attribute__((always_inline)) {
-      wait_vm<(AHEAD - 2) * (IPB + (LOADER ? 1 : 0))>();
+      wait_vm<(AHEAD - 2) * NPG * (IPB + (LOADER ? 1 : 0))>();
       if (__builtin_expect(!(vbits & 1u), 0)) wait_vm<0>();
     };
 
     if (!LOADER || wave == LOAD_WAVE) {
-      for (; seq < seq_hi; ++seq) {
-        init_seq(std::true_type{});
-        if (rb < rb_end) {
-          more = true;
-          enter_group();
-          break;
-        }
-      }
+      walk.start(seq_lo, [&]() __attribute__((always_inline)) { init_seq(std::true_type{}); },
+                 [&]() __attribute__((always_inline)) { init_seq(std::false_type{}); });
       if constexpr (!LOADER) {
-        issue_block(IC<0>{});
-        issue_block(IC<1>{});
-        issue_block(IC<2>{});
-        issue_block(IC<3>{});
-        issue_block(IC<4>{});
+        static_for<AHEAD * NPG>([&](auto Ic) __attribute__((always_inline)) { issue_block(Ic); });
         wait_loads();
       }
     }
@@ -514,19 +428,22 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
     const unsigned char* tr0 = smem + tr_off<D>(lane, hi * 4, dblk * 32);
     const unsigned char* tr1 = smem + tr_off<D>(lane, hi * 4 + 8, dblk * 32);
     const unsigned char* xr_lane = smem + XCH_OFF + k0 * 4096 + lane * 16;
-    bf16x8 tq[2], tdo[2];   // Q^T, dO^T operands of the row block accumulated next interval
+    bf16x8 tq[NPG][2], tdo[NPG][2];   // Q^T, dO^T operands of the row blocks accumulated next interval
     bool prev = false;      // (with a loader wave) block h - 1 exists
 
     // one interval: accumulates block h-1, reads the transposed operands of block h (stage U), requests
     // block h + AHEAD; returns false after the end of the schedule
     auto interval = [&](auto Uc) __attribute__((always_inline)) -> bool {
-      constexpr int U = decltype(Uc)::value, IS = (U + AHEAD) % NBUF, XB = (U + 1) & 1;
+      constexpr int U = decltype(Uc)::value, IS = (U + AHEAD) % NIS, XB = (U + 1) & 1;
+      constexpr int CUR = AHEAD * NPG + NPG - 1, PREV = CUR + NPG;   // bits of the first block of this and of the last interval
       // requests first: the producers' MFMAs run meanwhile, the consumers' follow them
       uint32_t hdr = 0;
       if constexpr (LOADER) hdr = *reinterpret_cast<const uint32_t*>(smem + HDR_OFF + U * STAGE_BYTES);
-      else issue_block(IC<IS>{});
-      if (LOADER ? prev : (vbits & (1u << (AHEAD + 1))) != 0) {
-        const unsigned char* xr = xr_lane + XB * XCH_BYTES;
+      else static_for<NPG>([&](auto Ec) __attribute__((always_inline)) { issue_block(IC<IS * NPG + decltype(Ec)::value>{}); });
+#pragma unroll
+      for (int e = 0; e < NPG; ++e) {
+        if (LOADER ? !prev : (vbits & (1u << (PREV - e))) == 0) continue;
+        const unsigned char* xr = xr_lane + XB * XCH_BYTES + e * 16384;
         // all P / -dS operands are requested before the first MFMA (left alone, the compiler reads one operand,
         // waits for it and issues one MFMA, sixteen LDS latencies in a row)
         bf16x8 pa[2][NK], dsa[2][NK];
@@ -542,17 +459,21 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
         for (int t2 = 0; t2 < 2; ++t2)
 #pragma unroll
           for (int i = 0; i < NK; ++i) {
-            dv[i] = mfma32(pa[t2][i], tdo[t2], dv[i]);
-            dk[i] = mfma32(dsa[t2][i], tq[t2], dk[i]);
+            dv[i] = mfma32(pa[t2][i], tdo[e][t2], dv[i]);
+            dk[i] = mfma32(dsa[t2][i], tq[e][t2], dk[i]);
           }
         __builtin_amdgcn_sched_barrier(0);
       }
-      const bool cur = LOADER ? (__builtin_amdgcn_readfirstlane((int)hdr) & HDR_VALID) != 0 : (vbits & (1u << AHEAD)) != 0;
-      if (__builtin_expect(cur, 1)) {
+      const bool cur = LOADER ? (__builtin_amdgcn_readfirstlane((int)hdr) & HDR_VALID) != 0 : (vbits & (1u << CUR)) != 0;
+#pragma unroll
+      for (int e = 0; e < NPG; ++e) {
+        if (__builtin_expect(e == 0 ? !cur : (vbits & (1u << (CUR - e))) == 0, 0)) continue;
+        constexpr int ST = U * IST_BYTES;
 #pragma unroll
         for (int t2 = 0; t2 < 2; ++t2) {
-          tdo[t2] = tr_pair(tr0 + U * STAGE_BYTES + HT_BYTES + t2 * 16 * RB, tr1 + U * STAGE_BYTES + HT_BYTES + t2 * 16 * RB);
-          tq[t2] = tr_pair(tr0 + U * STAGE_BYTES + t2 * 16 * RB, tr1 + U * STAGE_BYTES + t2 * 16 * RB);
+          const int at = ST + e * STAGE_BYTES + t2 * 16 * RB;
+          tdo[e][t2] = tr_pair(tr0 + at + HT_BYTES, tr1 + at + HT_BYTES);
+          tq[e][t2] = tr_pair(tr0 + at, tr1 + at);
         }
       }
       if constexpr (LOADER) prev = cur;
@@ -567,8 +488,10 @@ __global__ __launch_bounds__(512) void dkdv4_kernel(const AttnParams p) {
       if (!interval(IC<1>{})) break;
       if (!interval(IC<2>{})) break;
       if (!interval(IC<3>{})) break;
-      if (!interval(IC<4>{})) break;
-      if (!interval(IC<5>{})) break;
+      if constexpr (NIS > 4) {
+        if (!interval(IC<4 % NIS>{})) break;
+        if (!interval(IC<5 % NIS>{})) break;
+      }
     }
 
     // ---- epilogue: C layout -> lane owns head-dim column, register r owns key crow(r); the dK
@@ -613,14 +536,14 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  const size_t smem = 6 * (2 * 32 * 2 * D + 256 + 64) + 2 * 16384;
+  const size_t smem = kStages<D> * (2 * 32 * 2 * D + 256 + 64) + 2 * kGroups<D> * 16384;
   auto kern = dkdv4_kernel<D, LOCAL>;
   hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL>>(smem);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
                        (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
   if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), smem, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kWaves<D> * 64), smem, st, p);
   return hipGetLastError();
 }
 

@@ -119,4 +119,116 @@ __device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int 
   return true;
 }
 
+// Flags in a block's header, per 32-key subtile: the block exists; some of its (row, key) pairs are visible; some are not.
+// HDR_RUN: the first block of the interval exists.
+enum : int { HDR_VALID = 1, HDR_ACTIVE = 2, HDR_MASK = 4, HDR_RUN = 8 };
+
+// Visibility of a row block (first row row0, a multiple of HB <= 32) for the 32-key subtile that starts at k_lo: four
+// scalar bounds, so that a block costs a handful of scalar compares.
+template <bool LOCAL>
+struct SubtileVis {
+  int lo, act_hi, mask_lo;   // rows from lo on reach the subtile's first key; rows before act_hi still see its last one
+  bool ctx;
+  __device__ __forceinline__ SubtileVis(bool is_ctx, int k_lo, int P, int W) : lo(k_lo), ctx(is_ctx) {
+    const int shift = is_ctx ? P : 0;   // a row's logical position minus its index
+    act_hi = k_lo + 31 + W - shift;
+    mask_lo = k_lo + W - 31 - shift;
+  }
+  // (row0 minus 32 i gives the flags of the i-th next subtile)
+  __device__ __forceinline__ uint32_t flags(int row0, int nvalid, int HB) const {
+    bool a = ctx || row0 + HB > lo, m = nvalid < HB || (!ctx && row0 < lo + 31);
+    if (LOCAL) {
+      a = a && row0 < act_hi;
+      m = m || row0 >= mask_lo;
+    }
+    return (uint32_t)(HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0));
+  }
+};
+
+// Row-block schedule of a key tile (Alg. 1, "Q-row blocks in causal support of K_n"): the sequences of the tile, row blocks
+// of HB rows that see at least one of its keys, query heads of the KV group innermost.  It runs beside the MFMAs in the
+// waves that make the requests, so a step is straight-line scalar code: byte addresses advance by one of two precomputed
+// strides, and only another row block and the end of a sequence branch.  The empty asm statements keep the state in scalar
+// registers: left alone, the compiler moves row counts to vector registers, which the twelve-wave kernel does not have.
+template <int HB>
+struct RowWalk {
+  uint64_t q, dout, st;      // byte addresses of the block's first row of Q, dO and D (of its head)
+  int row0, nvalid, R, row_end, g, seq;
+  bool more;
+  const int hk, seq_hi, G;
+  int64_t q_head, q_row, do_head, do_row, st_head, st_row;   // strides to the next head / from the last head to the next block
+  int row_begin;
+
+  __device__ __forceinline__ static int64_t pin(int64_t v) {
+    asm("" : "+s"(v));
+    return v;
+  }
+  __device__ __forceinline__ RowWalk(const AttnParams& p, int hk_, int seq_hi_)
+      : q(0), dout(0), st(0), row0(0), nvalid(0), R(0), row_end(0), g(0), seq(0), more(false), hk(hk_), seq_hi(seq_hi_),
+        G(own_sgpr(p.G)), row_begin(0) {
+    q_head = pin(p.q.hs * 2);
+    q_row = pin(p.q.ts * (2 * HB) - q_head * (G - 1));
+    do_head = pin(p.dout.hs * 2);
+    do_row = pin(p.dout.ts * (2 * HB) - do_head * (G - 1));
+    st_head = pin((int64_t)p.total * 4);
+    st_row = pin(4 * HB - st_head * (G - 1));
+  }
+  __device__ __forceinline__ void keep() {
+    asm("" : "+s"(q), "+s"(dout), "+s"(st), "+s"(row0), "+s"(nvalid), "+s"(R), "+s"(row_end), "+s"(g), "+s"(seq));
+  }
+  // the rows of sequence `seq`; returns their number
+  __device__ __forceinline__ int enter_seq(const AttnParams& p) {
+    // the offsets are loaded through the vector path: make their uniformity explicit
+    row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
+    R = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin : p.total;
+    return R;
+  }
+  // its row blocks from row `first` (a multiple of HB) to before row `end`
+  __device__ __forceinline__ void enter_rows(const AttnParams& p, int first, int end) {
+    row0 = first;
+    row_end = end;
+    nvalid = min(HB, R - row0);
+    g = 0;
+    const int64_t grow = (int64_t)row_begin + first, h0 = (int64_t)hk * G;
+    q = reinterpret_cast<uint64_t>(p.q.ptr) + (uint64_t)(grow * p.q.ts + h0 * p.q.hs) * 2;
+    dout = reinterpret_cast<uint64_t>(p.dout.ptr) + (uint64_t)(grow * p.dout.ts + h0 * p.dout.hs) * 2;
+    st = reinterpret_cast<uint64_t>(p.dvec) + (uint64_t)(h0 * p.total + grow) * 4;
+    keep();
+  }
+  // one block on (new_rows() if that is another row block); false: past the last block of the sequence
+  template <typename F>
+  __device__ __forceinline__ bool step(F&& new_rows) {
+    const bool wrap = g + 1 == G;
+    q += wrap ? q_row : q_head;
+    dout += wrap ? do_row : do_head;
+    st += wrap ? st_row : st_head;
+    g = wrap ? 0 : g + 1;
+    row0 += wrap ? HB : 0;
+    nvalid = min(HB, R - row0);
+    keep();
+    if (wrap) new_rows();
+    return row0 < row_end;
+  }
+  template <typename F>
+  __device__ __forceinline__ void next_seq(F&& init_seq) {
+    more = false;
+    while (++seq < seq_hi) {
+      init_seq();
+      if (row0 < row_end) {
+        more = true;
+        return;
+      }
+    }
+  }
+  template <typename F, typename N>
+  __device__ __forceinline__ void start(int seq_lo, F&& init_first, N&& init_next) {
+    seq = seq_lo;
+    if (seq >= seq_hi) return;
+    init_first();
+    if (row0 < row_end) more = true;
+    else next_seq(init_next);
+  }
+};
+
+
 }  // namespace dkv
