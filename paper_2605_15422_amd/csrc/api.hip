@@ -233,14 +233,19 @@ hipError_t run_dkdv(const AttnParams& p, int d, hipStream_t st) {
 // The backward stages of one call over `rows` rows.  The dQ kernel holds the dO rows that D = rowsum(dO * O) needs, so it
 // runs first and forms D (and LSE in base-2 units) for the dK/dV kernel: one launch and one pass over dO less than with a
 // preprocess of its own (layer at N = 16, P = 8192, R = 1024, 32 / 8 heads, d = 128: 11.40 -> 11.33 ms; at d = 256, window
-// 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 5.21 -> 5.06 ms; one launch and 3 of 94 us at the smallest sizes).  The preprocess kernel serves calls without dQ, and calls whose dQ overwrites what the dK/dV
-// kernel has to read (dQ is written last then).
+// 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 5.21 -> 5.06 ms).  Calls that leave CUs idle run both kernels side by side
+// behind the preprocess (dkdv4.hip).  The preprocess also serves calls without dQ, and calls whose dQ overwrites what the
+// dK/dV kernel has to read (dQ is written last then).
 hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, hipStream_t st) {
   const bool do_dq = rows > 0 && !(flags & DUALKV_FLAG_SKIP_DQ), do_dkdv = !(flags & DUALKV_FLAG_SKIP_DKDV);
   const bool do_pre = rows > 0 && !(flags & DUALKV_FLAG_SKIP_PRE);
   hipError_t e = hipSuccess;
   if (do_pre && do_dq && !overlap(p.dq, p.q, rows, p.H, d) && !overlap(p.dq, p.dout, rows, p.H, d) &&
       !overlap(p.dq, p.o, rows, p.H, d)) {
+    if (do_dkdv && dkv::dkdv4_dq_fits(p, d)) {
+      if ((e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
+      return dkv::launch_dkdv4_dq(p, d, st);
+    }
     p.make_stats = 1;
     if ((e = run_dq(p, d, st)) != hipSuccess) return e;
     return do_dkdv ? run_dkdv(p, d, st) : hipSuccess;

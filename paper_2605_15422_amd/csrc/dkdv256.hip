@@ -83,7 +83,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
   const int W = p.window;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb)) return;
+  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, gridDim.x)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;

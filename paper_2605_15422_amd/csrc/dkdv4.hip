@@ -39,12 +39,12 @@
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
+#include "dq2.h"
 #include "kvsched.h"
 #include "launch.h"
 #include "tiles.h"
 
 namespace dkv {
-
 
 // Producer groups: how many row blocks an interval takes.
 template <int D>
@@ -56,8 +56,22 @@ constexpr int kStages = kGroups<D> == 2 ? 8 : 6;   // LDS stages (row blocks)
 template <int V>
 using IC = std::integral_constant<int, V>;
 
-template <int D, bool LOCAL>
-__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p) {
+constexpr int kDqWaves = 4;   // of the dQ workgroups in a launch of both
+
+// WITH_DQ: both backward kernels in one launch, for calls that do not fill the chip: n_kv dK/dV workgroups, then dQ workgroups
+// of four waves (dq2.h).  The two are independent once the row statistics are there, each is as long as its longest walk when
+// a CU has no second workgroup to do, and side by side they take the longer of the two instead of the sum.  Measured (backward call with its preprocess, two launches -> one):
+//   1 x 1021 rows, 16 / 4 heads, d = 128 (128 + 128 workgroups)                      72.2 -> 48.1 us; d = 64 49.0 -> 32.6
+//   1 x 1500 rows, 8 / 8 heads, d = 128 (96 + 96)                                    88.8 -> 51.4 us; d = 96 76.6 -> 48.7
+//   1 x 512 rows, 32 / 8 heads, d = 128 (64 + 128)                                   61.6 -> 47.2 us
+//   2 x <= 64 rows behind a prompt of 64, 8 / 2 heads, d = 128 (6 + 8)               33.8 -> 27.0 us; d = 64 25.2 -> 23.8
+template <int D, bool LOCAL, bool WITH_DQ>
+__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p, int n_kv) {
+  if (WITH_DQ && (int)blockIdx.x >= n_kv) {
+    if (threadIdx.x >= kDqWaves * 64) return;   // (waves that have ended do not take part in barriers)
+    dq2_workgroup<D, kDqWaves, LOCAL, false>(p, blockIdx.x - n_kv, gridDim.x - n_kv);
+    return;
+  }
   constexpr int BN = 128, HB = 32;                 // keys per workgroup, query rows per block
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int HT_BYTES = HB * RB;                // one Q or dO row block
@@ -85,7 +99,7 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
   const int W = p.window;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb)) return;
+  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, n_kv)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;
@@ -525,8 +539,12 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
   }
 }
 
-template <int D, bool LOCAL>
-static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
+template <int D>
+constexpr size_t kDkdv4Smem = kStages<D> * (2 * 32 * 2 * D + 256 + 64) + 2 * kGroups<D> * 16384;
+
+// Fills in the schedule fields of the parameters; number of workgroups.
+template <int D>
+static hipError_t prepare_dkdv4(AttnParams& p, int64_t& n_workgroups) {
   constexpr int BN = 128;
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
@@ -534,27 +552,56 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   if (p.n_row_split < 1) p.n_row_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
-      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
+       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  const size_t smem = kStages<D> * (2 * 32 * 2 * D + 256 + 64) + 2 * kGroups<D> * 16384;
-  auto kern = dkdv4_kernel<D, LOCAL>;
-  hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL>>(smem);
+  n_workgroups = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
+                 (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
+  return hipSuccess;
+}
+
+
+static int64_t dq_workgroups(AttnParams& p) {
+  fill_packing(p, kDqWaves);
+  return (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
+}
+
+template <int D, bool LOCAL, bool WITH_DQ>
+static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
+  int64_t n_kv;
+  hipError_t e = prepare_dkdv4<D>(p, n_kv);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(kWaves<D> * 64), smem, st, p);
+  const int64_t n = n_kv + (WITH_DQ ? dq_workgroups(p) : 0);
+  constexpr size_t smem = WITH_DQ && kDq2Smem<D> > kDkdv4Smem<D> ? kDq2Smem<D> : kDkdv4Smem<D>;
+  auto kern = dkdv4_kernel<D, LOCAL, WITH_DQ>;
+  if ((e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL, WITH_DQ>>(smem)) != hipSuccess) return e;
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kWaves<D> * 64), smem, st, p, (int)n_kv);
   return hipGetLastError();
 }
 
-hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) {
+template <bool WITH_DQ>
+static hipError_t launch_dkdv4_d(const AttnParams& p, int head_dim, hipStream_t st) {
   const bool local = p.window > 0;
   switch (head_dim) {
-    case 64:  return local ? launch_dkdv4_t<64, true>(p, st) : launch_dkdv4_t<64, false>(p, st);
-    case 96:  return local ? launch_dkdv4_t<96, true>(p, st) : launch_dkdv4_t<96, false>(p, st);
-    case 128: return local ? launch_dkdv4_t<128, true>(p, st) : launch_dkdv4_t<128, false>(p, st);
+    case 64:  return local ? launch_dkdv4_t<64, true, WITH_DQ>(p, st) : launch_dkdv4_t<64, false, WITH_DQ>(p, st);
+    case 96:  return local ? launch_dkdv4_t<96, true, WITH_DQ>(p, st) : launch_dkdv4_t<96, false, WITH_DQ>(p, st);
+    case 128: return local ? launch_dkdv4_t<128, true, WITH_DQ>(p, st) : launch_dkdv4_t<128, false, WITH_DQ>(p, st);
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<false>(p, head_dim, st); }
+hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<true>(p, head_dim, st); }
+
+// One launch where every workgroup of both kernels has one of the 256 CUs to itself: all calls measured there gained (1.02 to
+// 1.7 times, head dims 64, 96 and 128).  With more workgroups it goes either way, by how ragged the rows are: 320 + 224 (4 x
+// <= 512 rows behind 2048, 16 / 4 heads, d = 128) 179 -> 134 us, but 256 + 128 (1 x 2048 rows, 8 / 2 heads) 95 -> 105 us, 256 +
+// 256 (8 x <= 256 rows behind 1021, 16 / 4 heads) 91 -> 96 us, 192 + 192 (1 x 3000 rows, window 512, 8 / 8 heads) 75 -> 80 us:
+// the dQ loop is slower here (it shares its scalar registers with the other kernel's arguments) and needs the preprocess.
+bool dkdv4_dq_fits(AttnParams p, int head_dim) {
+  int64_t n_kv;
+  if (head_dim > 128 || prepare_dkdv4<128>(p, n_kv) != hipSuccess || dq2_waves(p, head_dim) != kDqWaves) return false;
+  return n_kv + dq_workgroups(p) <= 256;
 }
 
 }  // namespace dkv

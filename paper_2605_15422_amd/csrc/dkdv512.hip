@@ -61,7 +61,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
   const int l32 = lane & 31, hi = lane >> 5;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb)) return;
+  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, gridDim.x)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const A
   constexpr int BN = C::BN;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
   QBlock b;
-  if (!decode_qblock<BN>(p, b)) return;
+  if (!decode_qblock<BN>(p, b, blockIdx.x, gridDim.x)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;

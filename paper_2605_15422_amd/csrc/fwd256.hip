@@ -62,7 +62,7 @@ __global__ __launch_bounds__(512) void fwd256_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   QBlock b;
-  if (!decode_qblock<BN>(p, b)) return;
+  if (!decode_qblock<BN>(p, b, blockIdx.x, gridDim.x)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hi = lane >> 5;

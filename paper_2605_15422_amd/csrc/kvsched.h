@@ -41,10 +41,9 @@ __device__ __forceinline__ void row_block_at(const int32_t* cu, int s0, int s1, 
 }
 
 // false: the block owns no key (beyond its prompt or its response)
-__device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int HB, KVBlock& b) {
+__device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int HB, KVBlock& b, int bid, int nblk) {
   const int n_grp = p.grp ? p.n_groups : 1;
   const int ctx_blocks = n_grp * p.n_ctx_tiles * p.Hk * p.n_split;
-  int bid = blockIdx.x;
   b.rb_lo = 0;
   b.rb_hi = INT_MAX;
   if (bid < ctx_blocks) {
@@ -92,7 +91,7 @@ __device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int 
     // therefore given to the same XCD (block i takes tile (i % 8) * n / 8 + i / 8), where one fetch from memory then
     // serves many of them.  All tiles carry about the same work here, so the XCDs stay balanced; without a window the
     // work falls with the key index and the round-robin order is the balanced one.
-    const int chunk = ((int)gridDim.x - ctx_blocks) / 8;
+    const int chunk = (nblk - ctx_blocks) / 8;
     if (bid < chunk * 8) bid = (bid % 8) * chunk + bid / 8;
   }
   b.is_ctx = false;

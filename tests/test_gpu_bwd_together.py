@@ -1,0 +1,36 @@
+"""Backward calls with no more workgroups than CUs run dK/dV and dQ in one launch: bit for bit what the two kernels give in
+launches of their own, on both sides of the limit, around the 32-row and 128-key tiles, with a window, an empty response and
+several groups' worth of heads."""
+import numpy as np
+import pytest
+
+from paper_2605_15422_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("H,Hk,P,lens", [(2, 1, 1, [1]), (4, 2, 128, [33, 0, 129]), (8, 8, 1021, [128, 32, 31]), (16, 4, 1500, [300] * 4),
+                                         (32, 8, 130, [64] * 8), (32, 8, 130, [200] * 12), (6, 1, 0, [257, 5])])
+@pytest.mark.parametrize("window", [0, 70])
+def test_together_as_apart(d, H, Hk, P, lens, window):
+    import torch
+    from paper_2605_15422_amd import binding as B, runner
+    print("case together", d, H, Hk, P, len(lens), window, flush=True)
+    dg = B.upload(W.make_workload(W.Shape("together", len(lens), P, 0, 0, H, Hk, d, window, seed=90 + d), resp_lens=np.asarray(lens)))
+    out = []
+    for flags in ((0,), (B.FLAG_SKIP_DKDV, B.FLAG_SKIP_PRE | B.FLAG_SKIP_DQ)):
+        b = runner.alloc(dg)
+        runner.forward(dg, b, call1=P > 0)
+        for f in flags:
+            s = type(dg.shape_c).from_buffer_copy(bytes(dg.shape_c))
+            s.flags = f
+            B.dualkv_bwd(s, dg.do_d, b.o_d, b.lse_d, dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d, dg.cu_dev, dg.cu_host, b.dq_d,
+                         b.dk_c2, b.dv_c2, b.dk_d, b.dv_d, None, None, b.ws_bwd)
+            if P:
+                B.dualkv_ctx_bwd(s, dg.do_c, b.o_c, b.lse_c, dg.q_c, dg.k_c, dg.v_c, b.dq_c, b.dk_c1, b.dv_c1, None, None,
+                                 b.ws_ctx_bwd)
+        torch.cuda.synchronize()
+        out.append([b.dq_d, b.dk_d, b.dv_d] + ([b.dq_c, b.dk_c1, b.dv_c1] if P else []))
+    for x, y in zip(*out):
+        assert not torch.isnan(x).any() and torch.equal(x.view(torch.int16), y.view(torch.int16))
