@@ -1,6 +1,6 @@
 """Backward calls with no more workgroups than CUs run dK/dV and dQ in one launch: bit for bit what the two kernels give in
 launches of their own, on both sides of the limit, around the 32-row and 128-key tiles, with a window, an empty response and
-several groups' worth of heads."""
+several head counts."""
 import numpy as np
 import pytest
 
