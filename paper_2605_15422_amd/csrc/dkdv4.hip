@@ -594,14 +594,20 @@ hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { ret
 hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<true>(p, head_dim, st); }
 
 // One launch where every workgroup of both kernels has one of the 256 CUs to itself: all calls measured there gained (1.02 to
-// 1.7 times, head dims 64, 96 and 128).  With more workgroups it goes either way, by how ragged the rows are: 320 + 224 (4 x
-// <= 512 rows behind 2048, 16 / 4 heads, d = 128) 179 -> 134 us, but 256 + 128 (1 x 2048 rows, 8 / 2 heads) 95 -> 105 us, 256 +
-// 256 (8 x <= 256 rows behind 1021, 16 / 4 heads) 91 -> 96 us, 192 + 192 (1 x 3000 rows, window 512, 8 / 8 heads) 75 -> 80 us:
-// the dQ loop is slower here (it shares its scalar registers with the other kernel's arguments) and needs the preprocess.
+// 1.7 times, head dims 64, 96 and 128).  With more workgroups what can be won are the tails, against a dQ loop that is slower
+// here (it shares its scalar registers with the other kernel's arguments) and the preprocess.  Up to 2.5 workgroups a CU there is
+// such a tail where the responses are long for their prompt, since a response's tiles carry work that falls from the first to the
+// last; a long prompt's tiles are cut into full rounds of even parts.  Measured over 110 drawn calls with such responses: those
+// whose launches changed became 1.02 to 1.56 times faster, none slower: 2 x U(206, 654) behind 807, 12 / 4 heads, d = 128, 104 ->
+// 69 us; 5 x U(369, 431) behind 1158, 8 / 2 heads, d = 128, 119 -> 99.  The other side: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128,
+// 107 -> 115 us, 2 x U(74, 105) behind 3540, 32 / 8 heads 163 -> 176; causal rows alone, 1 x 2048, 8 / 2 heads 95 -> 105; window 512,
+// 1 x 3000, 8 / 8 heads 75 -> 80; 776 + 704 workgroups (8 x U(500, 1500) behind 300, 8 / 8 heads), d = 96, 142 -> 160.
 bool dkdv4_dq_fits(AttnParams p, int head_dim) {
   int64_t n_kv;
   if (head_dim > 128 || prepare_dkdv4<128>(p, n_kv) != hipSuccess || dq2_waves(p, head_dim) != kDqWaves) return false;
-  return n_kv + dq_workgroups(p) <= 256;
+  const int64_t n = n_kv + dq_workgroups(p);
+  if (p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs) return n <= 640;
+  return n <= 256;
 }
 
 }  // namespace dkv

@@ -1,5 +1,5 @@
-"""Backward calls with no more workgroups than CUs run dK/dV and dQ in one launch: bit for bit what the two kernels give in
-launches of their own, on both sides of the limit, around the 32-row and 128-key tiles, with a window, an empty response and
+"""Backward calls with few workgroups run dK/dV and dQ in one launch: bit for bit what the two kernels give in launches of
+their own, on both sides of the limits, around the 32-row and 128-key tiles, with a window, an empty response and
 several head counts."""
 import numpy as np
 import pytest
@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("d", [64, 96, 128])
 @pytest.mark.parametrize("H,Hk,P,lens", [(2, 1, 1, [1]), (4, 2, 128, [33, 0, 129]), (8, 8, 1021, [128, 32, 31]), (16, 4, 1500, [300] * 4),
-                                         (32, 8, 130, [64] * 8), (32, 8, 130, [200] * 12), (6, 1, 0, [257, 5])])
+                                         (32, 8, 130, [64] * 8), (32, 8, 130, [200] * 12), (8, 2, 700, [300, 1, 523]),
+                                         (8, 2, 300, [700] * 5 + [90]), (6, 1, 0, [257, 5])])
 @pytest.mark.parametrize("window", [0, 70])
 def test_together_as_apart(d, H, Hk, P, lens, window):
     import torch
