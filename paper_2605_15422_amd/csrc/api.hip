@@ -144,33 +144,6 @@ int ctx_parts(const dualkv_shape* s, const Groups& g, bool accum) {
   return best;
 }
 
-// How the row blocks of Call 1's key tiles are cut into parts for several workgroups (see decode_kvblock), where the
-// gradients are added into fp32 accumulators anyway.  The first tile sees every row block and the last one a single one, so a
-// prompt with too few tiles for the chip waits for its first tiles: a tile is cut into parts of about 3/4 of what a CU gets
-// on average, but not below kPartMin intervals, where the start and the atomic epilogue of a part outweigh it.  Prompts whose
-// longest tile is within a quarter of that average are left alone.  Layers of N = 8, P = 4096, R ~ U(131, 2048): 32 / 8
-// heads, d = 64 3.31 -> 3.23 ms, 16 / 4 heads, d = 96 2.23 -> 2.04; 1/2 or 1 instead of 3/4: 3.30 / 3.25 and 2.10 / 2.07.
-constexpr int kPartMin = 32;
-struct RowSplit {
-  int n = 1, len = 0;   // at most n parts of at most len row blocks
-};
-
-RowSplit ctx_row_split(const dualkv_shape* s, const Groups& g = Groups()) {
-  RowSplit r;
-  const int bn = dkv::dkdv_key_tile(s->head_dim), hb = s->head_dim == 512 ? 16 : 32;
-  const int64_t P = s->ctx_len, G = s->n_q_heads / s->n_kv_heads;
-  if (P == 0 || s->window > 0) return r;   // (a windowed tile sees few row blocks)
-  const int64_t n_seqs = g.n > 0 ? (g.total_ctx + P - 1) / P : 1;   // (prompts of the largest size that fill the rows)
-  const int64_t longest = (P + hb - 1) / hb * G, tiles = (P + bn - 1) / bn;
-  const double per_cu = (double)((longest + 1) / 2) * (double)(tiles * n_seqs * s->n_kv_heads) / 256.0;
-  if ((double)longest <= 1.25 * per_cu || longest < 2 * kPartMin) return r;
-  double len = per_cu * 0.75;
-  if (len < kPartMin) len = kPartMin;
-  r.len = (int)((len + (double)G - 1) / (double)G);
-  r.n = (int)((longest / G + r.len - 1) / r.len);
-  return r;
-}
-
 struct BwdWorkspace {
   size_t dvec_off, dvec_bytes, lse2_off, acc_off, acc_bytes, seqctx_off, seqctx_bytes, total;
 };
@@ -401,9 +374,6 @@ int ctx_bwd_impl(const dualkv_shape* shape, dualkv_tin do_c, dualkv_tin o_c, con
   } else {
     p.dkd_acc = dk_c_acc32;
     p.dvd_acc = dv_c_acc32;
-    const RowSplit split = ctx_row_split(shape, groups);
-    p.n_row_split = split.n;
-    p.row_split_len = split.len;
   }
   p.lse = const_cast<float*>(lse_c);
   p.dvec = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.dvec_off);

@@ -143,8 +143,6 @@ struct AttnParams {
   // KV-stationary kernel
   int n_ctx_tiles, n_dec_tiles;          // per sequence upper bound for dec
   int n_split;                           // ctx tiles: the sequence loop is cut in n_split parts
-  int n_row_split, row_split_len;        // response-region tiles that add into fp32 accumulators: the row blocks of a tile
-                                         // are cut into parts of at most row_split_len, at most n_row_split (1: not cut)
 };
 
 // A scalar kernel argument in scalar registers of its own.  The arguments arrive in blocks of up to sixteen registers;

@@ -421,8 +421,8 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       } else {
         const int key_hi = min(R, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W);
-        rb = LOCAL ? key0 / HB : max(key0 / HB, kb.rb_lo);   // (windowed tiles are short: their row blocks are not cut)
-        rb_end = LOCAL ? (rows + HB - 1) / HB : min((rows + HB - 1) / HB, kb.rb_hi);
+        rb = key0 / HB;
+        rb_end = (rows + HB - 1) / HB;
       }
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
@@ -780,7 +780,6 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
-  if (p.n_row_split < 1) p.n_row_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 192 does not)
   if (!Cfg<D>::LOADER && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
@@ -788,7 +787,7 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
   hipError_t e = ensure_dynamic_lds<dkdv256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
+                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
   if (nblk == 0) return hipSuccess;
   auto kern = dkdv256_kernel<D, LOCAL>;
   hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), Cfg<D>::SMEM_BYTES, st, p);

@@ -341,8 +341,8 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
         if (!LOCAL && walk.seq == seq_hi - 1) end = min(end, rows_hi);
       } else {
         const int key_hi = min(Rs, key0 + BN) - 1;
-        end = LOCAL ? min(Rs, key_hi + W) : min(Rs, rows_hi);
-        lo = max(key0, rows_lo);
+        end = LOCAL ? min(Rs, key_hi + W) : Rs;
+        lo = key0;
       }
       walk.enter_rows(p, lo, end);
       new_rows();
@@ -549,13 +549,12 @@ static hipError_t prepare_dkdv4(AttnParams& p, int64_t& n_workgroups) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
-  if (p.n_row_split < 1) p.n_row_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
        reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
   n_workgroups = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                 (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
+                 (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
   return hipSuccess;
 }
 

@@ -364,8 +364,8 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
         rb_end = R > 0 ? (R + HB - 1) / HB : 0;
         if (seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
       } else {
-        rb = max(key0 / HB, kb.rb_lo);
-        rb_end = min((R + HB - 1) / HB, kb.rb_hi);
+        rb = key0 / HB;
+        rb_end = (R + HB - 1) / HB;
       }
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
@@ -553,7 +553,6 @@ hipError_t launch_dkdv512(const AttnParams& p0, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
   p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
   if (p.n_split < 1) p.n_split = 1;
-  if (p.n_row_split < 1) p.n_row_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset
   if (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32))
@@ -561,7 +560,7 @@ hipError_t launch_dkdv512(const AttnParams& p0, hipStream_t st) {
   hipError_t e = ensure_dynamic_lds<dkdv512_kernel>(SMEM_BYTES);
   if (e != hipSuccess) return e;
   const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk * p.n_row_split;
+                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
   if (nblk == 0) return hipSuccess;
   hipLaunchKernelGGL(dkdv512_kernel, dim3((unsigned)nblk), dim3(512), SMEM_BYTES, st, p);
   return hipGetLastError();

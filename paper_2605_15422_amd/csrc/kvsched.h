@@ -96,9 +96,7 @@ __device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int 
   }
   b.is_ctx = false;
   b.hk = bid % p.Hk;
-  int t = bid / p.Hk;
-  const int part = t % p.n_row_split;
-  t /= p.n_row_split;
+  const int t = bid / p.Hk;
   b.key0 = (t % p.n_dec_tiles) * BN;
   b.seq_lo = t / p.n_dec_tiles;
   b.seq_hi = b.seq_lo + 1;
@@ -106,16 +104,7 @@ __device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int 
   b.ctx_off = 0;
   const int rb0 = p.cu ? p.cu[b.seq_lo] : 0;
   const int Rs = p.cu ? (p.cu[b.seq_lo + 1] - rb0) : p.total;
-  if (b.key0 >= Rs) return false;
-  if (p.n_row_split > 1) {
-    // The row blocks that see the tile (no window here), cut evenly.  Every part adds its gradient into the fp32 accumulators.
-    const int lo = b.key0 / HB, n = (Rs + HB - 1) / HB - lo;
-    const int parts = min(p.n_row_split, (n + p.row_split_len - 1) / p.row_split_len);
-    if (part >= parts) return false;
-    b.rb_lo = __builtin_amdgcn_readfirstlane(lo + n * part / parts);   // (n < 2^27, part < 16)
-    b.rb_hi = __builtin_amdgcn_readfirstlane(lo + n * (part + 1) / parts);
-  }
-  return true;
+  return b.key0 < Rs;
 }
 
 // Flags in a block's header, per 32-key subtile: the block exists; some of its (row, key) pairs are visible; some are not.
