@@ -219,11 +219,11 @@ hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, hipStream
       if ((e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
       return dkv::launch_dkdv4_dq(p, d, st);
     }
-    p.make_stats = 1;
     if ((e = run_dq(p, d, st)) != hipSuccess) return e;
     return do_dkdv ? run_dkdv(p, d, st) : hipSuccess;
   }
   if (do_pre && (e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
+  p.o.ptr = nullptr;   // the row statistics are given
   if (do_dkdv && (e = run_dkdv(p, d, st)) != hipSuccess) return e;
   return do_dq ? run_dq(p, d, st) : hipSuccess;
 }

@@ -121,7 +121,6 @@ struct AttnParams {
   float* lse;                            // (H, total) fwd: written, bwd: read
   float* dvec;                           // (H, total) D = rowsum(dO * O), bwd only
   float* lse2;                           // (H, total) LSE * log2(e), written with D
-  int make_stats;                        // dQ kernels: form D from dO and O and write dvec / lse2 (else dvec is read)
   float* dkc_acc;                        // optional fp32 (P, Hk, d) accumulators (atomic adds)
   float* dvc_acc;
   float* dkd_acc;                        // optional fp32 (rows, Hk, d) accumulators for response-region keys
@@ -143,6 +142,12 @@ struct AttnParams {
   // KV-stationary kernel
   int n_ctx_tiles, n_dec_tiles;          // per sequence upper bound for dec
   int n_split;                           // ctx tiles: the sequence loop is cut in n_split parts
+
+  // dQ kernels: D is formed from dO and O and written with LSE * log2(e), unless the row statistics are given (o.ptr nullptr).
+  // Not a field: one more argument word shifts the blocks that the others arrive in, and the head-dim 512 dK/dV kernel, short of
+  // scalar registers, then spills two and a half times as many (backward of Call 2 at N = 8, P = 1136, R ~ U(100, 400), 16 / 16
+  // heads: 530 us; as it is, 515).
+  __host__ __device__ bool make_stats() const { return o.ptr != nullptr; }
 };
 
 // A scalar kernel argument in scalar registers of its own.  The arguments arrive in blocks of up to sixteen registers;

@@ -354,15 +354,13 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
       m = m || nvalid < HB;
       gflags = HDR_VALID | (a ? HDR_ACTIVE : 0) | (m ? HDR_MASK : 0);
     };
-    // (response tiles have one sequence: only the first call has to know them)
-    auto init_seq = [&](auto first) __attribute__((always_inline)) {
+    auto init_seq = [&]() __attribute__((always_inline)) {
       // the offsets are loaded through the vector path: make their uniformity explicit
       row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
       R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
-      if (!decltype(first)::value || is_ctx) {
-        rb = decltype(first)::value ? kb.rb_lo : 0;
+      if (is_ctx) {
+        rb = 0;
         rb_end = R > 0 ? (R + HB - 1) / HB : 0;
-        if (seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
       } else {
         rb = key0 / HB;
         rb_end = (R + HB - 1) / HB;
@@ -382,7 +380,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
       }
       more = false;
       while (++seq < seq_hi) {
-        init_seq(std::false_type{});
+        init_seq();
         if (rb < rb_end) {
           more = true;
           enter_group();
@@ -442,7 +440,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
     };
 
     for (; seq < seq_hi; ++seq) {
-      init_seq(std::true_type{});
+      init_seq();
       if (rb < rb_end) {
         more = true;
         enter_group();

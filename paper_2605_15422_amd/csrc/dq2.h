@@ -23,7 +23,7 @@ namespace dkv {
 // waves of a workgroup of the kernel that dQ has to itself
 inline int dq2_waves(const AttnParams& p, int head_dim) { return choose_waves(p, 0.8, head_dim == 64 ? 1.32 : 0.0); }
 
-// workgroup `bid` of `nblk`; STATS: it may have to form the row statistics (p.make_stats)
+// workgroup `bid` of `nblk`; STATS: it may have to form the row statistics (p.make_stats())
 template <int D, int NW, bool LOCAL, bool STATS>
 __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int nblk) {
   constexpr int BN = 64;
@@ -62,7 +62,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
       dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
     }
     lse2 = p.lse[(int64_t)head * p.total + grow] * LOG2E;
-    if (STATS && p.make_stats) {
+    if (STATS && p.make_stats()) {
       const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + hi * 8;
       bf16x8 of[KS];
 #pragma unroll

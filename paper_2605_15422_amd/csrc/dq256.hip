@@ -85,7 +85,7 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
         dof[ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 16);
       }
       lse2 = p.lse[(int64_t)head * p.total + grow] * LOG2E;
-      if (p.make_stats) {
+      if (p.make_stats()) {
         const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + hi * 8;
         float t[KS];
         constexpr int GRP = 4;   // (at most GRP operands of O next to the Q and dO fragments)
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(512) void dq256_kernel(const AttnParams p) {
       }
       __syncthreads();
     }
-    if (p.make_stats && hi == 0 && row < R) {
+    if (p.make_stats() && hi == 0 && row < R) {
       const int64_t at = (int64_t)head * p.total + b.row_begin + row;
       p.dvec[at] = -negd;
       p.lse2[at] = lse2;

@@ -64,16 +64,19 @@ __device__ __forceinline__ bool decode_kvblock(const AttnParams& p, int BN, int 
       s1 = p.grp[4 * g + 3];
     }
     if (b.key0 >= b.P) return false;
-    b.seq_lo = s0;
-    b.seq_hi = s1;
-    if (p.n_split == 1) return true;   // (an unsplit tile without rows still has to write its zeros)
-    if (p.window > 0 || p.cu == nullptr) {
-      // with a window a tile sees few rows of each sequence: whole sequences
+    if (HB < 32 || p.window > 0 || p.cu == nullptr) {
+      // Whole sequences: with a window a tile sees few rows of each one, and the head-dim 512 kernel (HB = 16) has no scalar
+      // registers left for the bounds of its first and last one.
       const int n = s1 - s0;
       b.seq_lo = s0 + (int)((int64_t)n * split / p.n_split);
       b.seq_hi = s0 + (int)((int64_t)n * (split + 1) / p.n_split);
-      return b.seq_lo < b.seq_hi;      // a part without rows adds nothing to the accumulators
+      // a part without sequences adds nothing to the accumulators; an unsplit tile still has to write its zeros
+      if (p.n_split > 1 && b.seq_lo == b.seq_hi) return false;
+      return true;
     }
+    b.seq_lo = s0;
+    b.seq_hi = s1;
+    if (p.n_split == 1) return true;
     // the rows of all sequences, cut evenly at row blocks
     const int rows = p.cu[s1] - p.cu[s0];
     int seq_end, rb_end;
