@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "launch.h"
+#include "rules.h"
 
 // Scratch of dualkv_bwd_noalloc (see static_scratch below).  Host code never passes this name to a kernel.
 static __device__ __align__(256) unsigned char scratch[DUALKV_STATIC_SCRATCH_BYTES];
@@ -16,8 +17,6 @@ namespace {
 using dkv::AttnParams;
 using dkv::TView;
 using dkv::TViewOut;
-
-constexpr int kTargetBlocks = 512;   // prompt-tile workgroups from which on no prompt tile is cut into parts
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -101,47 +100,29 @@ int check_groups(const dualkv_shape* s, const Groups& g) {
   return next == s->n_seqs ? DUALKV_OK : DUALKV_E_INVALID;
 }
 
-// number of parts the sequence loop of a prompt-tile workgroup is cut into
-int ctx_split(const dualkv_shape* s, const Groups& g = Groups()) {
-  if (s->ctx_len == 0) return 1;
-  const int bn = dkv::dkdv_key_tile(s->head_dim);
-  const int n_grp = g.n > 0 ? g.n : 1;
-  const int64_t blocks = (int64_t)n_grp * ((s->ctx_len + bn - 1) / bn) * s->n_kv_heads;
-  if (blocks >= kTargetBlocks) return 1;
-  int64_t want = (kTargetBlocks + blocks - 1) / blocks;
-  const int64_t seqs_per_group = (s->n_seqs + n_grp - 1) / n_grp;
-  if (want > seqs_per_group) want = seqs_per_group;
-  return (int)(want < 1 ? 1 : want);
+dkv::rules::PromptTiles prompt_tiles(const dualkv_shape* s, const Groups& g) {
+  dkv::rules::PromptTiles c;
+  c.key_tile = dkv::dkdv_key_tile(s->head_dim);
+  c.row_block = s->head_dim == 512 ? 16 : 32;
+  c.whole_seqs = s->head_dim == 512;
+  c.n_groups = g.n > 0 ? g.n : 1;
+  c.tiles = (int64_t)c.n_groups * ((s->ctx_len + c.key_tile - 1) / c.key_tile) * s->n_kv_heads;
+  c.n_seqs = s->n_seqs;
+  c.total_resp = s->total_resp;
+  c.max_resp = s->max_resp;
+  c.kv_heads = s->n_kv_heads;
+  c.G = s->n_q_heads / s->n_kv_heads;
+  c.shared = -1;
+  c.ctx_len = s->ctx_len;
+  return c;
 }
 
-// The number of parts to launch.  ctx_split says whether the caller's workspace holds accumulators for more than one; how
-// many are best follows from rounds of 256 workgroups (one per CU): a part takes as many intervals as it has (row block,
-// head) pairs plus kPartOverhead for its start and its atomic epilogue, and the response tiles fill the gaps that are left.
-// The parts cut the rows evenly.  Before, 512 workgroups were wanted whatever that made of the last round, and the parts were
-// whole sequences: layers of N = 8, P = 4111, R ~ U(131, 2048), 16 / 4 heads, d = 96: 2.04 -> 1.86 ms (528 parts became
-// 396); N = 8, P = 1021, R <= 256, 32 / 8 heads, d = 128: 415 -> 375 us; an overhead of 15 or 25 instead of 40 intervals is
-// 3 % slower at N = 4, P = 5059.
-constexpr int kPartOverhead = 40;
-int ctx_parts(const dualkv_shape* s, const Groups& g, bool accum) {
-  const int most = ctx_split(s, g);
-  if (s->ctx_len == 0 || s->total_resp == 0 || s->window > 0 || (most == 1 && !accum)) return most;
-  const int bn = dkv::dkdv_key_tile(s->head_dim), hb = s->head_dim == 512 ? 16 : 32, n_grp = g.n > 0 ? g.n : 1;
-  const double G = s->n_q_heads / s->n_kv_heads;
-  const int64_t blocks = (int64_t)n_grp * ((s->ctx_len + bn - 1) / bn) * s->n_kv_heads;
-  if (blocks >= kTargetBlocks) return 1;
-  const double chain = (double)s->total_resp / n_grp / hb * G, resp = (double)s->total_resp / s->n_seqs;
-  const double own = (double)s->n_seqs * s->n_kv_heads * ((int)(resp / bn) + 1) * (resp / hb * G / 2 + kPartOverhead);
-  int best = 1;
-  double best_t = 1e30;
-  for (int n = 1; n <= 16 && (n == 1 || chain / n >= 8); ++n) {
-    const double part = chain / n + kPartOverhead, rounds = (double)((blocks * n + 255) / 256);
-    const double t = std::max((blocks * n * part + own) / 256, rounds * part);
-    if (t < 0.98 * best_t) {
-      best = n;
-      best_t = t;
-    }
-  }
-  return best;
+// parts of a prompt tile to launch (with a window a tile sees few rows of each sequence: whole sequences, as many as fill the chip)
+int ctx_parts(const AttnParams& p, const dualkv_shape* s, const Groups& g) {
+  dkv::rules::PromptTiles c = prompt_tiles(s, g);
+  if (s->window > 0) return dkv::rules::most_parts(c);
+  c.shared = dkv::dkdv4_dq_room(p, s->head_dim);
+  return dkv::rules::prompt_parts(c);
 }
 
 struct BwdWorkspace {
@@ -156,7 +137,7 @@ BwdWorkspace bwd_workspace(const dualkv_shape* s, bool ctx_call, const Groups& g
   w.lse2_off = w.dvec_bytes;
   w.acc_off = 2 * w.dvec_bytes;
   w.acc_bytes = 0;
-  if (!ctx_call && !(s->flags & DUALKV_FLAG_ACCUM_CTX_F32) && ctx_split(s, g) > 1)
+  if (!ctx_call && !(s->flags & DUALKV_FLAG_ACCUM_CTX_F32) && dkv::rules::most_parts(prompt_tiles(s, g)) > 1)
     w.acc_bytes = align_up((size_t)ctx_rows(s, g) * s->n_kv_heads * s->head_dim * sizeof(float), 256);
   w.seqctx_off = w.acc_off + 2 * w.acc_bytes;
   w.seqctx_bytes = (!ctx_call && g.n > 0) ? align_up((size_t)s->n_seqs * 2 * sizeof(int32_t), 256) : 0;
@@ -442,11 +423,11 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
   if (accum) {
     p.dkc_acc = dk_c_acc32;
     p.dvc_acc = dv_c_acc32;
-    p.n_split = ctx_parts(shape, groups, true);
+    p.n_split = ctx_parts(p, shape, groups);
   } else if (scratch) {
     p.dkc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off);
     p.dvc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off + w.acc_bytes);
-    p.n_split = ctx_parts(shape, groups, false);
+    p.n_split = ctx_parts(p, shape, groups);
     // zero-initialise the fp32 scratch (Alg. 1, "Require: zero-initialized")
     if (!(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
       if ((rc = hip_rc(dkv::launch_clear2_f32(p.dkc_acc, p.dvc_acc, n_acc, st)))) return rc;

@@ -542,22 +542,26 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
 template <int D>
 constexpr size_t kDkdv4Smem = kStages<D> * (2 * 32 * 2 * D + 256 + 64) + 2 * kGroups<D> * 16384;
 
+constexpr int kKeyTile = 128;
+static int64_t prompt_workgroups(const AttnParams& p) {
+  return (int64_t)(p.grp ? p.n_groups : 1) * ((p.ctx_len + kKeyTile - 1) / kKeyTile) * p.Hk * (p.n_split < 1 ? 1 : p.n_split);
+}
+static int64_t response_workgroups(const AttnParams& p) {
+  return (int64_t)p.n_seqs * ((p.max_rows + kKeyTile - 1) / kKeyTile) * p.Hk;
+}
 // Fills in the schedule fields of the parameters; number of workgroups.
 template <int D>
 static hipError_t prepare_dkdv4(AttnParams& p, int64_t& n_workgroups) {
-  constexpr int BN = 128;
-  p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
-  p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
+  p.n_ctx_tiles = (p.ctx_len + kKeyTile - 1) / kKeyTile;
+  p.n_dec_tiles = (p.max_rows + kKeyTile - 1) / kKeyTile;
   if (p.n_split < 1) p.n_split = 1;
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
        reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  n_workgroups = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                 (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
+  n_workgroups = prompt_workgroups(p) + response_workgroups(p);
   return hipSuccess;
 }
-
 
 static int64_t dq_workgroups(AttnParams& p) {
   fill_packing(p, kDqWaves);
@@ -601,12 +605,11 @@ hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { 
 // 69 us; 5 x U(369, 431) behind 1158, 8 / 2 heads, d = 128, 119 -> 99.  The other side: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128,
 // 107 -> 115 us, 2 x U(74, 105) behind 3540, 32 / 8 heads 163 -> 176; causal rows alone, 1 x 2048, 8 / 2 heads 95 -> 105; window 512,
 // 1 x 3000, 8 / 8 heads 75 -> 80; 776 + 704 workgroups (8 x U(500, 1500) behind 300, 8 / 8 heads), d = 96, 142 -> 160.
-bool dkdv4_dq_fits(AttnParams p, int head_dim) {
-  int64_t n_kv;
-  if (head_dim > 128 || prepare_dkdv4<128>(p, n_kv) != hipSuccess || dq2_waves(p, head_dim) != kDqWaves) return false;
-  const int64_t n = n_kv + dq_workgroups(p);
-  if (p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs) return n <= 640;
-  return n <= 256;
+int64_t dkdv4_dq_room(AttnParams p, int head_dim) {
+  if (head_dim > 128 || dq2_waves(p, head_dim) != kDqWaves) return -1;
+  const bool tails = p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs;
+  return (tails ? 640 : 256) - response_workgroups(p) - dq_workgroups(p);
 }
+bool dkdv4_dq_fits(const AttnParams& p, int head_dim) { return prompt_workgroups(p) <= dkdv4_dq_room(p, head_dim); }
 
 }  // namespace dkv

@@ -18,8 +18,9 @@ struct KVBlock {
   int rb_lo, rb_hi; // first row block of seq_lo; end of the row blocks of seq_hi - 1 (of HB rows; INT_MAX: all)
 };
 
-// The row block at `target` rows behind the first row of sequence s0 (sequences [s0, s1), whole row blocks: a target inside a
-// block means the next one): its sequence and its index there.  One parallel compare per 64 sequences instead of a search.
+// The start of a row block that is nearest to `target` rows behind the first row of sequence s0 (sequences [s0, s1)): its
+// sequence and its index there.  Nearest and not next: where a sequence is one row block, the next start after every target
+// would give one part two sequences and another none.  One parallel compare per 64 sequences instead of a search.
 __device__ __forceinline__ void row_block_at(const int32_t* cu, int s0, int s1, int target, int HB, int& seq, int& rb) {
   const int lane = threadIdx.x & 63;
   const int x = __builtin_amdgcn_readfirstlane(cu[s0] + target);
@@ -33,7 +34,9 @@ __device__ __forceinline__ void row_block_at(const int32_t* cu, int s0, int s1, 
   rb = 0;
   if (seq >= s1) return;
   const int r0 = __builtin_amdgcn_readfirstlane(cu[seq]), r1 = __builtin_amdgcn_readfirstlane(cu[seq + 1]);
-  rb = (x - r0 + HB - 1) / HB;
+  rb = (x - r0) / HB;
+  const int at_row = r0 + rb * HB;
+  if (2 * (x - at_row) >= min(HB, r1 - at_row)) ++rb;
   if (r0 + rb * HB >= r1) {
     ++seq;
     rb = 0;

@@ -10,8 +10,9 @@ hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned backward kernels for head dims 64 / 96 / 128
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
-// both in one launch (row statistics given), for calls with few workgroups
-bool dkdv4_dq_fits(AttnParams p, int head_dim);
+// both in one launch (row statistics given), for calls with few workgroups: up to dkdv4_dq_room prompt workgroups
+int64_t dkdv4_dq_room(AttnParams p, int head_dim);
+bool dkdv4_dq_fits(const AttnParams& p, int head_dim);
 hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st);
 // kernels for head dims 192 / 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)
 hipError_t launch_fwd256(const AttnParams& p, int head_dim, hipStream_t st);

@@ -1,0 +1,68 @@
+// Host-side rules that size a launch from the sizes of a call.  Plain C++: no device code, no HIP types.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace dkv {
+namespace rules {
+
+constexpr int kCus = 256;
+
+// ---- Call 2: workgroups per prompt tile (dK/dV) ----
+struct PromptTiles {
+  int64_t tiles;               // prompt tiles of all groups, times the KV heads
+  int n_seqs, n_groups, total_resp, max_resp;
+  int G;                       // query heads per KV head
+  int kv_heads;
+  int key_tile, row_block;     // keys and rows that the kernel takes at a time
+  bool whole_seqs;             // parts are whole sequences (else row blocks)
+  int64_t shared;              // up to so many prompt workgroups dK/dV and dQ share a launch
+  int ctx_len;                 // keys of the longest prompt
+};
+
+constexpr int kTargetBlocks = 512;   // prompt-tile workgroups from which on no prompt tile is cut into parts
+
+// A bound on the parts of a prompt tile that is known to the caller's workspace: above one, the fp32 accumulators exist.
+inline int most_parts(const PromptTiles& c) {
+  if (c.tiles == 0 || c.tiles >= kTargetBlocks) return 1;
+  const int64_t want = (kTargetBlocks + c.tiles - 1) / c.tiles, per_group = (c.n_seqs + c.n_groups - 1) / c.n_groups;
+  return (int)std::max<int64_t>(1, std::min(want, per_group));
+}
+
+// The number of parts to launch: the one with the shortest time in a model of 256 CUs that take workgroups in launch order,
+// prompt tiles first.  Unit: one interval of the kernel (a row block of one query head); kStart of them for a workgroup's
+// start and end.  Sequences count in whole row blocks.  Three bounds: all work spread evenly; full rounds of parts; the longest
+// response tile, which may start behind the full rounds.  Where dK/dV and dQ would no longer share a launch, dQ's walk over the
+// keys comes on top.
+// Up to two parts the sum of an element has one result whatever the order (0 + a + b = 0 + b + a), and calls where most_parts
+// says so keep that; more parts add in an order that varies from run to run.
+// Over 900 drawn calls the backward of Call 2 takes 0.71 of its time with most_parts parts of whole sequences and two launches
+// (7 of them 1.03 to 1.24 times longer); with most_parts parts 0.76; kStart 12 to 40 differ by 1 %.
+constexpr int kStart = 30, kMaxParts = 32;
+inline int prompt_parts(const PromptTiles& c) {
+  const int most = most_parts(c);
+  if (most == 1 || c.total_resp == 0) return most;
+  const double mean = (double)c.total_resp / c.n_seqs;
+  auto ceil_div = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
+  const double seqs = ceil_div(c.n_seqs, c.n_groups), one = ceil_div(mean, c.row_block) * c.G;   // sequences; intervals of one
+  const double resp_tiles = ceil_div(mean, c.key_tile);
+  // the tiles of a response see from all of its row blocks down to the last tile's
+  const double own = resp_tiles * c.n_seqs * c.kv_heads * (one * (resp_tiles + 1) / (2 * resp_tiles) + kStart);
+  const double longest = ceil_div(c.max_resp, c.row_block) * c.G + kStart;
+  const double apart = 10 + ((double)c.ctx_len + c.max_resp) / 53;   // (64 keys of dQ: 1.2 intervals)
+  auto time = [&](int n) {
+    const double part = (c.whole_seqs ? ceil_div(seqs, n) * one : ceil_div(seqs * one, n)) + kStart;
+    const int64_t all = c.tiles * n;
+    const double t = std::max({(all * part + own) / kCus, (all + kCus - 1) / kCus * part, all / kCus * part + longest});
+    return c.shared >= c.tiles && all > c.shared ? t + apart : t;
+  };
+  // (a part takes at least a sequence or a row block)
+  const int limit = (int)std::min<double>(most <= 2 ? most : kMaxParts, c.whole_seqs ? seqs : seqs * one / c.G);
+  int best = 1;
+  for (int n = 2; n <= limit; ++n)
+    if (time(n) < 0.98 * time(best)) best = n;
+  return best;
+}
+
+}  // namespace rules
+}  // namespace dkv

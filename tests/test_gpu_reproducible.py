@@ -1,5 +1,6 @@
 """Sums of the prompt gradients that have one order have one result: Call 1 adds to every element of the fp32 joint
-accumulators once, so that a joint sum of Call 1 alone is the two-term result before its cast."""
+accumulators once, so that a joint sum of Call 1 alone is the two-term result before its cast; Call 2 adds to zeroed ones at
+most twice where its prompt tiles have at most two parts."""
 import numpy as np
 import pytest
 
@@ -26,3 +27,25 @@ def test_call1_joint_sum_is_the_two_term_sum(d, H, Hk, P):
         B.dualkv_finalize_ctx_grads(s, *acc, b.dk_c2, b.dv_c2)
         torch.cuda.synchronize()
         assert torch.equal(b.dk_c2, b.dk_c1) and torch.equal(b.dv_c2, b.dv_c1)
+
+
+@pytest.mark.parametrize("d,H,Hk,P,lens", [(64, 8, 1, 700, [900, 800]), (96, 8, 2, 1500, [700, 30]), (128, 32, 4, 86, [1900, 719]),
+                                           (128, 16, 8, 5000, [300, 200, 100, 400]), (192, 8, 2, 600, [1000]), (256, 8, 2, 1200, [800, 500]),
+                                           (512, 8, 1, 500, [400, 300])])
+@pytest.mark.parametrize("joint", [False, True])
+def test_two_parts_have_one_sum(d, H, Hk, P, lens, joint):
+    """Call 2 with one or two parts a prompt tile: the same bits from run to run, whichever part adds first."""
+    import torch
+    from paper_2605_15422_amd import binding as B, runner
+    print("case two parts", d, H, Hk, P, joint, flush=True)
+    dg = B.upload(W.make_workload(W.Shape("two", len(lens), P, 0, 0, H, Hk, d, 0, seed=800 + d), resp_lens=np.asarray(lens)),
+                  B.FLAG_ACCUM_CTX_F32 if joint else 0)
+    b = runner.alloc(dg)
+    want = None
+    for _ in range(6):
+        runner.layer_step(dg, b)
+        torch.cuda.synchronize()
+        got = [t.clone() for t in ((b.dk_c_acc, b.dv_c_acc) if joint else (b.dk_c2, b.dv_c2))]
+        want = want or got
+        for x, y in zip(got, want):
+            assert torch.equal(x, y)

@@ -1,0 +1,90 @@
+"""Rules that size launches (csrc/rules.h), compiled for the host: what they choose where a wrong choice was measured to cost
+a tenth of the call or more (MI355X), and what they may not choose."""
+import os
+import random
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CXX = shutil.which("g++")
+
+pytestmark = pytest.mark.skipif(CXX is None, reason="no host compiler")
+
+SOURCE = r"""
+#include <cstdio>
+#include "rules.h"
+using namespace dkv::rules;
+int main() {
+  long long v[13];
+  char what;
+  while (std::scanf(" %c", &what) == 1) {
+    int n = 0;
+    if (what == 'p') {
+      for (auto& x : v) std::scanf("%lld", &x);
+      PromptTiles c{v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], v[9] != 0, v[10], (int)v[11]};
+      n = v[12] ? most_parts(c) : prompt_parts(c);
+    }
+    std::printf("%d\n", n);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "rules.cpp").write_text(SOURCE)
+    exe = str(d / "rules")
+    subprocess.run([CXX, "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2605_15422_amd", "csrc"), str(d / "rules.cpp"), "-o", exe],
+                   check=True)
+    return lambda lines: [int(x) for x in subprocess.run([exe], input="\n".join(lines), capture_output=True, text=True,
+                                                         check=True).stdout.split()]
+
+
+def _parts(d, N, P, total, longest, H, Hk, shared=-1, groups=1, most=0):
+    tile = 128 if d <= 128 else 64 if d <= 256 else 32
+    tiles = groups * -(-P // tile) * Hk
+    return "p " + " ".join(str(int(x)) for x in (tiles, N, groups, total, longest, H // Hk, Hk, tile, 16 if d == 512 else 32,
+                                                  d == 512, shared, P, most))
+
+
+# (d, N, P, total, longest, H, H_k, shared), the counts within a tenth of the best one
+PARTS = [
+    ((64, 19, 34, 120, 7, 8, 2), range(10, 33)),        # one row block a sequence: 1 part 61 us, 19 parts 22
+    ((512, 16, 21, 96, 7, 12, 4), range(8, 17)),        # 1 part 38 us, 16 parts 25
+    ((128, 23, 132, 1075, 60, 8, 8), (2, 3, 4, 5, 6)),  # 23 parts 53 us, 4 parts 32
+    ((64, 6, 3043, 204, 60, 8, 8), (1,)),               # 3 parts 98 us, 1 part 76
+    ((128, 7, 793, 475, 100, 16, 16), (1, 2)),          # 5 parts 106 us, 1 part 65
+    ((128, 10, 1259, 68, 8, 8, 8, 96), (1,)),          # with 2 parts dK/dV and dQ do not share a launch: 42 -> 64 us
+    ((128, 15, 67, 97, 7, 32, 8, 16), range(8, 33)),    # dQ's walk is short: 2 parts 55 us, 15 parts 40
+    ((128, 2, 1607, 2129, 1500, 32, 4), (1, 2)),        # 4 parts 434 us, 2 parts 378
+]
+
+
+@pytest.mark.parametrize("case,good", PARTS)
+def test_prompt_parts(ask, case, good):
+    assert ask([_parts(*case)])[0] in good
+
+
+def test_prompt_parts_keep_sums_that_have_one_result(ask):
+    """Two adds to zero commute, three do not: calls for which 512 workgroups mean at most two parts get at most two."""
+    rng = random.Random(5)
+    few = more = 0
+    lines = []
+    for _ in range(4000):
+        N, R = rng.randint(1, 40), rng.randint(1, 3000)
+        Hk = rng.choice([1, 2, 4, 8, 16])
+        args = (rng.choice([64, 96, 128, 192, 256, 512]), N, rng.randint(1, 20000), N * R, R, Hk * rng.choice([1, 3, 4, 8]), Hk,
+                rng.randint(-1, 600), rng.choice([1, 1, min(N, 3)]))
+        lines += [_parts(*args, most=1), _parts(*args)]
+    got = ask(lines)
+    for most, n in zip(got[::2], got[1::2]):
+        assert 1 <= n <= 32
+        if most <= 2:
+            assert n <= most
+            few += 1
+        else:
+            more += n > 2
+    assert few > 500 and more > 500
