@@ -319,6 +319,16 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     const int G = keep(p.G);
     const int q_ts = keep((int)p.q.ts), do_ts = keep((int)p.dout.ts);
     const int64_t q_hs = keep(p.q.hs), do_hs = keep(p.dout.hs), total = keep((int64_t)p.total);
+    auto keep_ptr = [](auto own, auto v) __attribute__((always_inline)) {
+      if constexpr (decltype(own)::value) return reinterpret_cast<decltype(v)>(own_sgpr(reinterpret_cast<int64_t>(v)));
+      else return v;
+    };
+    // (the schedule's pointers, where their argument blocks were spilled for them: scalar spills of the head-dim 256 kernel
+    // without a window 3506 -> 1103 lane accesses, of the head-dim 192 kernel with one 1138 -> 404)
+    constexpr std::bool_constant<!LOCAL && !LOADER> own_rows{};
+    constexpr std::bool_constant<LOADER> own_cu{};
+    const u16 *const q_ptr = keep_ptr(own_rows, p.q.ptr), *const do_ptr = keep_ptr(own_rows, p.dout.ptr);
+    const int32_t* const cu = keep_ptr(own_cu, p.cu);
     const int ld_row0 = jb * RPI + lane / CPR;
     const int ld_coff = ((lane % CPR) ^ swz<D>(ld_row0)) * 16;
     const uint32_t ld_lds = smem_addr + jb * 1024;
@@ -409,8 +419,8 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     // (response tiles have one sequence: only the first call has to know them)
     auto init_seq = [&](auto first) __attribute__((always_inline)) {
       // the offsets are loaded through the vector path: make their uniformity explicit
-      row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
-      R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
+      row_begin = cu ? __builtin_amdgcn_readfirstlane(cu[seq]) : 0;
+      R = cu ? (__builtin_amdgcn_readfirstlane(cu[seq + 1]) - row_begin) : p.total;
       int rows = R;
       if (LOCAL ? is_ctx : !decltype(first)::value || is_ctx) {
         const int key_hi = min(P, key0 + BN) - 1;
@@ -425,8 +435,8 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
         rb_end = (rows + HB - 1) / HB;
       }
       const int64_t grow = (int64_t)row_begin + rb * HB;
-      q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
-      do_row = uniform_ptr(p.dout.ptr + grow * do_ts + (int64_t)hk * G * do_hs);
+      q_row = uniform_ptr(q_ptr + grow * q_ts + (int64_t)hk * G * q_hs);
+      do_row = uniform_ptr(do_ptr + grow * do_ts + (int64_t)hk * G * do_hs);
       st_row = (int64_t)hk * G * total + grow;
       if (LOCAL) {
         rb_lo = rb;
