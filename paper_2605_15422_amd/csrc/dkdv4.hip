@@ -606,7 +606,7 @@ hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { 
 // 107 -> 115 us, 2 x U(74, 105) behind 3540, 32 / 8 heads 163 -> 176; causal rows alone, 1 x 2048, 8 / 2 heads 95 -> 105; window 512,
 // 1 x 3000, 8 / 8 heads 75 -> 80; 776 + 704 workgroups (8 x U(500, 1500) behind 300, 8 / 8 heads), d = 96, 142 -> 160.
 int64_t dkdv4_dq_room(AttnParams p, int head_dim) {
-  if (head_dim > 128 || dq2_waves(p, head_dim) != kDqWaves) return -1;
+  if (head_dim > 128 || choose_waves(p, head_dim, true, true) != kDqWaves) return -1;
   const bool tails = p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs;
   return (tails ? 640 : 256) - response_workgroups(p) - dq_workgroups(p);
 }

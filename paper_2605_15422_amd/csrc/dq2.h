@@ -3,8 +3,8 @@
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
 //
-// Shape: 8 waves (two per SIMD; four where the row blocks are few, see choose_waves), each owning one 32-row
-// subtile with Q, dO fragments and the dQ^T accumulator in registers; K and V tiles of 64 keys travel global -> LDS
+// Shape: 4 waves where two workgroups fit a CU (head dims 64 and 96), else 8, two per SIMD, or 4 by the rule of
+// row_block_waves (rules.h); each owns one 32-row subtile with Q, dO fragments and the dQ^T accumulator in registers; K and V tiles of 64 keys travel global -> LDS
 // directly (global_load_lds, three stages, two tiles ahead: no staging registers, which pays for a deeper operand prefetch) into swizzled LDS.  S^T = K Q^T and
 // dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T through LDS transpose
 // reads of the same row-major K tile.  A 64-key tile is consumed as two 32-key halves so only one
@@ -20,9 +20,6 @@
 
 namespace dkv {
 
-// waves of a workgroup of the kernel that dQ has to itself
-inline int dq2_waves(const AttnParams& p, int head_dim) { return choose_waves(p, 0.8, head_dim == 64 ? 1.32 : 0.0); }
-
 // workgroup `bid` of `nblk`; STATS: it may have to form the row statistics (p.make_stats())
 template <int D, int NW, bool LOCAL, bool STATS>
 __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int nblk) {
@@ -30,10 +27,9 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int TILE_BYTES = BN * RB;
   constexpr int NSTAGE = 3, STAGE_BYTES = 2 * TILE_BYTES;
-  constexpr int LW = NW == 12 ? 8 : NW;          // waves that request tiles
-  constexpr int IPT = TILE_BYTES / 1024 / LW;  // 1 KB load instructions per wave, tile and tensor
+  constexpr int IPT = TILE_BYTES / 1024 / NW;  // 1 KB load instructions per wave, tile and tensor
   constexpr int RPI = 1024 / RB;               // rows per load instruction
-  constexpr int LPT = 2 * TILE_BYTES / 1024 / LW;  // per wave and tile
+  constexpr int LPT = 2 * TILE_BYTES / 1024 / NW;  // per wave and tile
   static_assert(kSplitRow<D> || LPT == 2 * IPT, "tile must split evenly over the waves");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // [NSTAGE][K tile | V tile]
 
@@ -152,9 +148,9 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     const uint32_t dst = smem_addr + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
     for (int t = 0; t < IPT; ++t) {
-      const unsigned row = (unsigned)min(ld_row0 + t * LW * RPI, last);
-      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * LW * 1024);
-      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * LW * 1024);
+      const unsigned row = (unsigned)min(ld_row0 + t * NW * RPI, last);
+      dma16(kb, __umul24(row, (unsigned)ktsb) + ld_coff, dst + t * NW * 1024);
+      dma16(vb, __umul24(row, (unsigned)vtsb) + ld_coff, dst + TILE_BYTES + t * NW * 1024);
     }
   };
   // the tile consumed next must have landed; the LPT loads of the tile after it may stay in flight
@@ -163,11 +159,8 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     if (__builtin_expect(!newer_in_flight, 0)) wait_vm<0>();
   };
 
-  const bool loader = LW == NW || wave < LW;
-  if (loader) {
-    issue_loads(0, 0);
-    if (b.n_tiles > 1) issue_loads(1, 1);
-  }
+  issue_loads(0, 0);
+  if (b.n_tiles > 1) issue_loads(1, 1);
   wait_vm<0>();   // (also the stores of the row statistics: the waits of the main loop count loads only)
   __syncthreads();
 
@@ -181,7 +174,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   for (int it = 0; it < b.n_tiles; ++it) {
     // tile it+2 goes into the stage that tile it-1 left at the last barrier
     const int stage2 = stage == 0 ? 2 : stage - 1;
-    if (loader && it + 2 < b.n_tiles) issue_loads(it + 2, stage2);
+    if (it + 2 < b.n_tiles) issue_loads(it + 2, stage2);
 
     const unsigned char* Kb = smem + stage * STAGE_BYTES;
     const unsigned char* Vb = Kb + TILE_BYTES;

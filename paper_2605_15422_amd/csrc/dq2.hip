@@ -5,7 +5,7 @@
 namespace dkv {
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void dq2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
   dq2_workgroup<D, NW, LOCAL, true>(p, blockIdx.x, gridDim.x);
 }
 
@@ -25,12 +25,8 @@ static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
 template <int D>
 static hipError_t launch_dq2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
-  switch (dq2_waves(p, D)) {
-    case 4: return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
-    case 12:
-      if constexpr (D == 64) return local ? launch_dq2_t<D, 12, true>(p, st) : launch_dq2_t<D, 12, false>(p, st);
-  }
-  return local ? launch_dq2_t<D, 8, true>(p, st) : launch_dq2_t<D, 8, false>(p, st);
+  if (choose_waves(p, D, true) == 8) return local ? launch_dq2_t<D, 8, true>(p, st) : launch_dq2_t<D, 8, false>(p, st);
+  return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
 }
 
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st) {

@@ -4,8 +4,8 @@
 // are shared by all packed heads) and walks the two KV regions in logical order, prompt tiles then own-response tiles.
 // The scores are computed transposed, S^T = K Q^T, so that a lane owns one query row and exp(S^T) is already laid out
 // as the B operand of O^T += V^T P^T:
-//   * 8 waves (two per SIMD; four where the row blocks are few, see choose_waves), each owning ONE 32-row
-//     subtile: Q fragments (B operands) and the O^T accumulator stay in registers (~200 VGPRs, no spills);
+//   * 4 waves at head dim 64 (two workgroups fit a CU), else 8, two per SIMD, or 4 by the rule of
+//     row_block_waves (rules.h); each owns ONE 32-row subtile: Q fragments (B operands) and the O^T accumulator stay in registers (~200 VGPRs, no spills);
 //   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row so that both the
 //     16-byte K operand reads and the transposing V reads are bank-conflict free; V^T operands come
 //     from ds_read_b64_tr_b16 (LDS transpose read), so nothing is transposed on the way into LDS;
@@ -44,7 +44,7 @@ struct F2Cfg {
 };
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   using C = F2Cfg<D, NW>;
   constexpr int BN = C::BN;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
@@ -106,13 +106,13 @@ __global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const A
   constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
   constexpr int V_RING = NSTAGE * C::TILE_BYTES;
   // half of the waves request the K tiles, half the V tiles: one address computation per wave and tile
-  constexpr int LW = C::NW == 12 ? 4 : C::NW / 2;     // waves per tensor (of twelve waves, four request nothing)
+  constexpr int LW = C::NW / 2;                       // waves per tensor
   constexpr int IPT = C::TILE_BYTES / 1024 / LW;      // 1 KB load instructions per wave and tile
   constexpr int RPI = 1024 / C::RB;                   // rows per load instruction
   static_assert(IPT >= 1 && C::TILE_BYTES % (1024 * LW) == 0, "tile must split evenly over the waves");
   const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
   const int lwave = wave % LW;
-  const bool v_loader = wave >= LW, loader = wave < 2 * LW;
+  const bool v_loader = wave >= LW;
   const int ld_row0 = lwave * RPI + lane / C::CPR;
   const int ld_kcoff = ((lane % C::CPR) ^ C::fK(ld_row0)) * 16;
   const int ld_vcoff = ((lane % C::CPR) ^ C::fV(ld_row0)) * 16;
@@ -335,8 +335,7 @@ __global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const A
   };
 
   // ---- prologue: K0 V0 K1 V1 K2 requested, everything landed and published, scores of the first half
-  if (!loader) {
-  } else if (v_loader) {
+  if (v_loader) {
     issue_tile(0, 1);
     if (b.n_tiles > 1) issue_tile(1, 1);
   } else {
@@ -365,9 +364,7 @@ __global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const A
     // barrier that ended tile it-1
     const bool more = it + 3 < b.n_tiles;
     bool issued;
-    if (!loader) {
-      issued = true;
-    } else if (v_loader) {
+    if (v_loader) {
       issued = it + 2 < b.n_tiles;
       if (issued) issue_tile(it + 2, 1);
     } else {
@@ -403,8 +400,6 @@ __global__ __launch_bounds__(NW * 64, NW == 12 ? 3 : 2) void fwd2_kernel(const A
   const float l = xor32_sum(l_sum);
   const float inv = 1.0f / l;
   unsigned char* ot = smem + wave * 32 * C::RB;
-  if (C::NW == 12 && wave >= 8)   // (the K ring has room for eight waves; the V slots but that of the last tile are free, too)
-    ot = smem + V_RING + ((b.n_tiles + (wave - 8) / 2) & (NSTAGE - 1)) * C::TILE_BYTES + (wave & 1) * 32 * C::RB;
   auto oswz = [](int r) { return D == 96 ? swz<96>(r) : r & (C::CPR - 1); };
 #pragma unroll
   for (int ds = 0; ds < C::DSUB; ++ds)
@@ -444,12 +439,9 @@ static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
 template <int D>
 static hipError_t launch_fwd2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
-  switch (choose_waves(p, 0.7, D == 64 ? 1.32 : 0.0)) {
-    case 4: return local ? launch_fwd2_t<D, 4, true>(p, st) : launch_fwd2_t<D, 4, false>(p, st);
-    case 12:
-      if constexpr (D == 64) return local ? launch_fwd2_t<D, 12, true>(p, st) : launch_fwd2_t<D, 12, false>(p, st);
-  }
-  return local ? launch_fwd2_t<D, 8, true>(p, st) : launch_fwd2_t<D, 8, false>(p, st);
+  if constexpr (D != 64)   // (which takes four always)
+    if (choose_waves(p, D, false) == 8) return local ? launch_fwd2_t<D, 8, true>(p, st) : launch_fwd2_t<D, 8, false>(p, st);
+  return local ? launch_fwd2_t<D, 4, true>(p, st) : launch_fwd2_t<D, 4, false>(p, st);
 }
 
 hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st) {

@@ -3,6 +3,7 @@
 // the logical position space (prompt positions 0..P-1, then P + r; Sec. 3.1 and App. F of the paper).
 #pragma once
 #include "common.h"
+#include "rules.h"
 
 namespace dkv {
 
@@ -96,53 +97,19 @@ __device__ __forceinline__ bool tile_active(bool is_ctx, int key0, int rmin, int
 }
 
 
-// Head packing of one workgroup that owns `nst` 32-row subtiles: GP query heads of the KV group share
-// the staged K/V tiles, each with RSH consecutive subtiles (BMR rows).
+// Head packing of one workgroup that owns `nst` 32-row subtiles (rules.h)
 static inline void fill_packing(AttnParams& p, int nst) {
-  int a = p.G, b = nst;
-  while (b) {
-    const int t = a % b;
-    a = b;
-    b = t;
-  }
-  p.GP = a;
-  p.RSH = nst / p.GP;
+  const rules::Packing k = rules::pack_heads(p.G, nst);
+  p.GP = k.heads;
+  p.RSH = k.subtiles;
   p.BMR = p.RSH * 32;
   p.HC = p.G / p.GP;
   p.MB = (p.max_rows + p.BMR - 1) / p.BMR;
 }
 
-// How many waves in a workgroup of the head-dim 64 / 96 / 128 kernels?  Eight (two per SIMD) unless
-//   * four: a wave that has its SIMD to itself takes t4 of the time per tile (0.7 forward, 0.8 dQ).  A CU gets less done, but
-//     half the rows make twice as many workgroups, which pays where the chip would otherwise wait for its longest key walk;
-//   * twelve (t12 > 0: head dim 64, whose waves fit three to a SIMD): a tile takes 1.32 times as long for 1.5 times the rows;
-//     the softmax of this head dim takes more issue slots than its MFMAs, and a third wave fills gaps of the other two.
-// Times in tiles of 64 keys, with kStart for a workgroup's start and end: the longest walk, the total over 256 CUs, and whole
-// rounds where all walks are about alike.  Measured, eight -> four waves: 1 x 1021 rows, 32 / 8 heads, d = 128 (128 workgroups
-// of eight) forward 34.7 -> 25.2 us, dQ 42 -> 35; responses of 8 x <= 256 rows behind them (176) 47 -> 54 and 54 -> 74;
-// 1 x 4111 rows, 16 / 4 heads, d = 96 (260) forward + dQ 0.25 -> 0.19 ms; 1 x 5059 rows, d = 128 (640) 238 -> 282 and 303 ->
-// 391 us.  Eight -> twelve: responses of 8 x U(131, 2048) rows behind 4096, 32 / 8 heads, d = 64, forward 0.80 -> 0.70 ms, dQ
-// 0.92 -> 0.83 ms; the 4096 prompt rows alone 0.10 -> 0.13 and 0.12 -> 0.13 ms.
-static inline int choose_waves(const AttnParams& p, double t4, double t12) {
-  constexpr double kStart = 3.0, kCus = 256.0;
-  const double rows = (double)p.total / p.n_seqs;
-  double avg = (p.ctx_len + rows / 2) / 64 + 0.5, longest = ((double)p.ctx_len + p.max_rows) / 64 + 1;
-  if (p.window > 0) {
-    const double most = (double)p.window / 64 + 2;
-    avg = avg < most ? avg : most;
-    longest = longest < most ? longest : most;
-  }
-  auto time = [&](int waves, double per_tile) {
-    AttnParams e = p;
-    fill_packing(e, waves);
-    const double n = (double)p.n_seqs * (int64_t)((rows + e.BMR - 1) / e.BMR) * e.HC * p.Hk, each = per_tile * avg + kStart;
-    const double all = avg > 0.75 * longest ? (double)(int64_t)((n + kCus - 1) / kCus) * each : n * each / kCus;
-    const double chain = per_tile * longest + kStart;
-    return all > chain ? all : chain;
-  };
-  const double t8 = 0.97 * time(8, 1.0);
-  if (time(4, t4) < t8) return 4;
-  return t12 > 0 && time(12, t12) < t8 ? 12 : 8;
+static inline int choose_waves(const AttnParams& p, int head_dim, bool dq, bool shared = false) {
+  const rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk};
+  return rules::row_block_waves(c, head_dim == 64 || (head_dim == 96 && dq), dq, shared);
 }
 
 }  // namespace dkv

@@ -64,5 +64,57 @@ inline int prompt_parts(const PromptTiles& c) {
   return best;
 }
 
+// ---- Forward and dQ of head dims 64 / 96 / 128: waves in a workgroup ----
+// Head packing of one workgroup that owns `nst` 32-row subtiles: `heads` query heads of the KV group share the staged K / V
+// tiles, each with `subtiles` consecutive subtiles.
+struct Packing {
+  int heads, subtiles;
+};
+inline Packing pack_heads(int G, int nst) {
+  int a = G, b = nst;
+  while (b) {
+    const int t = a % b;
+    a = b;
+    b = t;
+  }
+  return {a, nst / a};
+}
+
+struct RowBlocks {
+  int n_seqs, longest;     // sequences, rows of the longest one
+  int ctx_len;             // prompt keys in front of them
+  bool window;
+  int G, kv_heads;
+};
+
+// Four waves or eight?  A wave that has its SIMD to itself takes 0.7 of the time per tile, and half the rows make twice as many
+// workgroups; but where only one workgroup fits a CU, four waves get less done on it than two per SIMD.  So four
+//   * where the LDS has room for two workgroups of four (`pair`: head dim 64, and dQ of head dim 96): 0.71 to 0.89 of the time of
+//     eight over 1160 calls, at most 1.09;
+//   * where every workgroup has a CU to itself, counted with the longest sequence: row blocks that other sequences do not have are
+//     dispatched, too, and displace some (22 x U(93, 135) rows behind 392, 8 / 8 heads, d = 128, 232 of 352 with rows: 25 -> 32 us);
+//   * forward, where eight would not make fewer workgroups, since half of them have no rows: 0.75 of the time;
+//   * for one or two causal sequences past a short prompt up to 600 workgroups: the longest walks start first and the short ones
+//     fill the gaps (d = 128, 1 x 10746 rows, 336 workgroups: 248 -> 185 us; 1 x 10723, 672: 288 -> 304).  With a window all walks
+//     are alike (1 x 1229 rows, window 918, 32 / 4 heads, 312 workgroups: 39 -> 56 us); with more sequences the long walks of the
+//     last one start late (23 x U(73, 496) rows behind 4793, 4 / 2 heads: 147 -> 194 us).
+// dQ: eight also where half of them have no rows; the other four run like four alone, and eight request the tiles (20 x 20 rows
+// behind 4283, 8 / 8 heads, d = 128: 93 us with four, 90 with eight).  But a launch that dK/dV shares takes four (`shared`).
+// Over 3400 forward and dQ calls of 19 us and more the choice takes 0.83 of the time of eight and 1.01 of that of the better one.
+inline int64_t row_block_count(const RowBlocks& c, int waves) {
+  const Packing k = pack_heads(c.G, waves);
+  const int64_t rows = 32 * k.subtiles;
+  return c.n_seqs * ((c.longest + rows - 1) / rows) * (c.G / k.heads) * c.kv_heads;
+}
+inline int row_block_waves(const RowBlocks& c, bool pair, bool dq, bool shared) {
+  const int64_t n = row_block_count(c, 4);
+  if (n <= kCus) {
+    const Packing k = pack_heads(c.G, 8);
+    return dq && !shared && std::min(k.subtiles, (c.longest + 31) / 32) * k.heads <= 4 ? 8 : 4;
+  }
+  if (pair || (!dq && n == row_block_count(c, 8))) return 4;
+  return c.n_seqs <= 2 && !c.window && 4 * (int64_t)c.ctx_len <= c.longest && n <= 600 ? 4 : 8;
+}
+
 }  // namespace rules
 }  // namespace dkv

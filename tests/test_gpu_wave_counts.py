@@ -1,6 +1,6 @@
-"""The head-dim 64 / 96 / 128 forward and dQ kernels run four, eight or (head dim 64) twelve waves in a workgroup, chosen
-by the number of row blocks: row counts around the 32-row subtiles and the 64-key tiles, with and without a window, every
-packing of query heads into twelve subtiles."""
+"""The head-dim 64 / 96 / 128 forward and dQ kernels run four or eight waves in a workgroup, chosen by the number of row
+blocks: row counts around the 32-row subtiles and the 64-key tiles, with and without a window, and enough rows of one
+length, head dim 64, to keep every CU busy several times over."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,7 @@ import parity_util as PU
 pytestmark = pytest.mark.gpu
 
 FEW = [33, 64, 1, 0, 97]                                            # a handful of workgroups: four waves
-# enough rows of one length that twelve waves (head dim 64) win: packings of 1, 2, 3, 4 and 8 heads a KV head
+# 1, 2, 3, 4 and 8 heads a KV head, packed into four waves or, three, each by itself
 LONG = [(1, 1, [4000, 4000]), (2, 1, [3200, 3100, 33]), (3, 1, [2200, 2100]), (4, 1, [1600] * 3), (8, 1, [800] * 3 + [31])]
 MANY = [(13 * i) % 71 for i in range(200)] + [31, 32, 33, 63, 64, 65, 129]   # more than the 256 CUs: eight
 

@@ -26,6 +26,10 @@ int main() {
       PromptTiles c{v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], v[9] != 0, v[10], (int)v[11]};
       n = v[12] ? most_parts(c) : prompt_parts(c);
     }
+    if (what == 'w') {
+      for (int i = 0; i < 9; ++i) std::scanf("%lld", &v[i]);
+      n = row_block_waves({(int)v[0], (int)v[1], (int)v[2], v[3] != 0, (int)v[4], (int)v[5]}, v[6] != 0, v[7] != 0, v[8] != 0);
+    }
     std::printf("%d\n", n);
   }
 }
@@ -88,3 +92,39 @@ def test_prompt_parts_keep_sums_that_have_one_result(ask):
         else:
             more += n > 2
     assert few > 500 and more > 500
+
+
+# (d, dQ, N, longest, P, window, H, H_k), waves, what they save
+WAVES = [
+    ((128, 0, 1, 1021, 0, 0, 32, 8), 4),         # forward 35 -> 25 us
+    ((128, 0, 22, 135, 392, 0, 8, 8), 8),        # four: 25 -> 32 us
+    ((128, 1, 22, 135, 392, 0, 8, 8), 8),        # four: 26 -> 38
+    ((128, 0, 22, 127, 392, 0, 8, 8), 4),        # 23 -> 18: every sequence is one row block of four waves
+    ((128, 0, 24, 119, 5407, 0, 16, 16), 4),     # 309 -> 195: and one of eight, half of them without rows
+    ((128, 0, 18, 253, 139, 0, 8, 1), 8),        # four: 19 -> 27
+    ((128, 1, 18, 253, 139, 0, 8, 1), 8),        # four: 23 -> 32
+    ((128, 0, 1, 1229, 0, 918, 32, 4), 8),       # four: 39 -> 56
+    ((128, 0, 1, 1475, 0, 0, 32, 8), 4),         # 42 -> 31, more than a workgroup a CU
+    ((128, 0, 1, 10746, 0, 0, 4, 2), 4),         # 248 -> 185
+    ((128, 0, 2, 3478, 753, 0, 8, 8), 4),        # 124 -> 98
+    ((128, 0, 1, 10723, 0, 0, 8, 8), 8),         # four: 288 -> 304
+    ((128, 1, 23, 496, 4793, 0, 4, 2), 8),       # four: 176 -> 243
+    ((128, 1, 20, 26, 4283, 0, 8, 8), 8),        # four: 88 -> 92
+    ((64, 0, 37, 296, 10, 0, 32, 4), 4),         # eight: 40 -> 47
+    ((64, 0, 31, 314, 2722, 0, 16, 4), 4),       # eight: 156 -> 178
+    ((64, 1, 39, 1040, 500, 0, 32, 8), 4),       # eight: 588 -> 775
+    ((96, 0, 34, 12, 2797, 0, 32, 4), 8),        # four: 74 -> 102
+    ((96, 1, 34, 40, 2797, 0, 32, 4), 4),
+    ((128, 0, 16, 1024, 8192, 0, 32, 8), 8),
+]
+
+
+@pytest.mark.parametrize("case,waves", WAVES)
+def test_row_block_waves(ask, case, waves):
+    d, dq, N, longest, P, window, H, Hk = case
+    pair = d == 64 or (d == 96 and dq)
+    assert ask(["w " + " ".join(map(str, (N, longest, P, window, H // Hk, Hk, int(pair), dq, 0)))]) == [waves]
+
+
+def test_a_shared_launch_takes_four_waves(ask):
+    assert ask(["w 20 26 0 0 1 8 0 1 1", "w 1 1 0 0 1 1 0 1 1"]) == [4, 4]
