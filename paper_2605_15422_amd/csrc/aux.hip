@@ -162,14 +162,12 @@ hipError_t launch_convert2_ctx(const float* acc0, const TViewOut& out0, const fl
 // Layout copies between the standard packing (Eq. 1) and the single-prompt packing (Eq. 5); rows are opaque records of 4- or
 // 16-byte units.  All three kernels are bound by memory once enough of it is in flight.
 //   * repack, long rows: driven by the destination rows, TPR threads a row, source row by binary search in cu_seqlens;
-//   * replicate, long rows: driven by the source rows, so that a prompt row is read once and written kCopies times from
+//   * replicate, long rows: driven by the source rows, so that a prompt row is read once and written 16 times from
 //     registers, where a gather read it again for every copy;
 //   * short rows (token ids, labels): a workgroup per row spends its life in the binary search; one lane takes one unit.
 // 16 x (8192 + 1024) rows of 8 KB: replicate 335 -> 265 us (5.3 TB/s, the rate of a plain copy), repack 77 -> 70 us; of 4
 // bytes: replicate 118 -> 4.9 us, repack 14 -> 4.7 us.
 // ---------------------------------------------------------------------------------------------
-constexpr int kCopies = 16;   // copies of a prompt row that one workgroup writes
-
 // the last sequence s with base * s + cu[s] <= x (x >= 0, cu[0] == 0)
 __device__ __forceinline__ int find_seq(const int32_t* cu, int n_seqs, int64_t base, int64_t x) {
   int lo = 0, hi = n_seqs;
@@ -213,56 +211,72 @@ __global__ __launch_bounds__(256) void short_rows_kernel(bool to_packed, int n_s
   if (pos_ids != nullptr && unit == 0) pos_ids[drow] = pos;
 }
 
-// NT: the copy is larger than the last-level cache, nothing of it is found there again
-template <typename VEC, int TPR, bool NT>
-__global__ __launch_bounds__(256) void repack_rows_kernel(int n_seqs, int P, int64_t drows, const int32_t* __restrict__ cu,
-                                                          int64_t row_vecs, const VEC* __restrict__ src, VEC* __restrict__ dst,
-                                                          int32_t* __restrict__ pos_ids) {
-  const int64_t drow = (int64_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
-  if (drow >= drows) return;
-  const int t = threadIdx.x % TPR;
-  int pos;
-  const VEC* s = src + standard_row(cu, n_seqs, P, drow, pos) * row_vecs;
-  VEC* d = dst + drow * row_vecs;
+// a workgroup's or a wave's row, in a scalar register: the search in cu_seqlens takes scalar loads then (53 x 506 + 20099 rows of
+// 4 KB, repack: 29.5 us with vector loads, 25.0 with scalar ones)
+template <int TPR>
+__device__ __forceinline__ int64_t row_index() {
+  static_assert(TPR == 64 || TPR == 256);
+  if constexpr (TPR == 256) return blockIdx.x;
+  else return (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+}
+
+// (four units in flight a thread: 6 x 725 + 56 rows of 64 KB, repack: 16.8 us with two, 16.4 with four)
+template <bool NT, int TPR, typename VEC>
+__device__ __forceinline__ void copy_row(const VEC* s, VEC* d, int64_t row_vecs, int t) {
   auto load = [](const VEC* p) { return NT ? __builtin_nontemporal_load(p) : *p; };
   auto store = [](VEC v, VEC* p) {
     if (NT) __builtin_nontemporal_store(v, p);
     else *p = v;
   };
   int64_t i = t;
+  for (; i + 3 * TPR < row_vecs; i += 4 * TPR) {
+    const VEC a = load(s + i), b = load(s + i + TPR), c = load(s + i + 2 * TPR), e = load(s + i + 3 * TPR);
+    store(a, d + i);
+    store(b, d + i + TPR);
+    store(c, d + i + 2 * TPR);
+    store(e, d + i + 3 * TPR);
+  }
   for (; i + TPR < row_vecs; i += 2 * TPR) {
     const VEC a = load(s + i), b = load(s + i + TPR);
     store(a, d + i);
     store(b, d + i + TPR);
   }
   if (i < row_vecs) store(load(s + i), d + i);
+}
+
+// NT: the copy is larger than the last-level cache, nothing of it is found there again
+template <typename VEC, int TPR, bool NT>
+__global__ __launch_bounds__(256) void repack_rows_kernel(int n_seqs, int P, int64_t drows, const int32_t* __restrict__ cu,
+                                                          int64_t row_vecs, const VEC* __restrict__ src, VEC* __restrict__ dst,
+                                                          int32_t* __restrict__ pos_ids) {
+  const int64_t drow = row_index<TPR>();
+  if (drow >= drows) return;
+  const int t = threadIdx.x % TPR;
+  int pos;
+  const VEC* s = src + standard_row(cu, n_seqs, P, drow, pos) * row_vecs;
+  copy_row<NT, TPR>(s, dst + drow * row_vecs, row_vecs, t);
   if (pos_ids != nullptr && t == 0) pos_ids[drow] = pos;
 }
 
 template <typename VEC, int TPR>
-__global__ __launch_bounds__(256) void replicate_rows_kernel(int n_seqs, int P, int total_resp, const int32_t* __restrict__ cu,
-                                                             int64_t row_vecs, const VEC* __restrict__ src,
-                                                             VEC* __restrict__ dst, int32_t* __restrict__ pos_ids) {
-  // items: the P prompt rows for every group of kCopies sequences, then the response rows
-  int64_t item = (int64_t)blockIdx.x * (256 / TPR) + threadIdx.x / TPR;
+__global__ __launch_bounds__(256) void replicate_rows_kernel(int n_seqs, int P, int total_resp, int copies, int64_t prompt_items,
+                                                             const int32_t* __restrict__ cu, int64_t row_vecs,
+                                                             const VEC* __restrict__ src, VEC* __restrict__ dst,
+                                                             int32_t* __restrict__ pos_ids) {
+  // items: the P prompt rows for every group of `copies` sequences, then the response rows
+  const int64_t item = row_index<TPR>();
   const int t = threadIdx.x % TPR;
-  const int64_t prompt_items = (int64_t)P * ((n_seqs + kCopies - 1) / kCopies);
-  int64_t srow;
-  int s0, s1, pos;
-  if (item < prompt_items) {
-    srow = item % P;
-    s0 = (int)(item / P) * kCopies;
-    s1 = min(n_seqs, s0 + kCopies);
-    pos = (int)srow;
-  } else {
-    item -= prompt_items;
-    if (item >= total_resp) return;
-    srow = P + item;
-    s0 = find_seq(cu, n_seqs, 0, item);
-    s1 = s0 + 1;
-    pos = P + (int)(item - cu[s0]);
+  if (item >= prompt_items) {
+    const int64_t x = item - prompt_items;
+    if (x >= total_resp) return;
+    const int q = find_seq(cu, n_seqs, 0, x);
+    const int64_t drow = (int64_t)(q + 1) * P + x;
+    copy_row<false, TPR>(src + (P + x) * row_vecs, dst + drow * row_vecs, row_vecs, t);
+    if (pos_ids != nullptr && t == 0) pos_ids[drow] = P + (int)(x - cu[q]);
+    return;
   }
-  const VEC* s = src + srow * row_vecs;
+  const int pos = (int)(item % P), s0 = (int)(item / P) * copies, s1 = min(n_seqs, s0 + copies);
+  const VEC* s = src + (int64_t)pos * row_vecs;
   auto row_of = [&](int q) { return (int64_t)q * P + cu[q] + pos; };
   int64_t i = t;
   for (; i + TPR < row_vecs; i += 2 * TPR) {
@@ -300,9 +314,10 @@ static hipError_t launch_rows_copy_t(bool to_packed, int n_seqs, int P, int T, c
     if (wide) return launch(repack_rows_kernel<VEC, 256, false>, drows, 1, n_seqs, P, drows, cu, row_vecs, s, d, pos_ids);
     return launch(repack_rows_kernel<VEC, 64, false>, drows, 4, n_seqs, P, drows, cu, row_vecs, s, d, pos_ids);
   }
-  const int64_t items = (int64_t)P * ((n_seqs + kCopies - 1) / kCopies) + T;
-  if (wide) return launch(replicate_rows_kernel<VEC, 256>, items, 1, n_seqs, P, T, cu, row_vecs, s, d, pos_ids);
-  return launch(replicate_rows_kernel<VEC, 64>, items, 4, n_seqs, P, T, cu, row_vecs, s, d, pos_ids);
+  const int copies = 16;
+  const int64_t prompt_items = (int64_t)P * ((n_seqs + copies - 1) / copies), items = prompt_items + T;
+  if (wide) return launch(replicate_rows_kernel<VEC, 256>, items, 1, n_seqs, P, T, copies, prompt_items, cu, row_vecs, s, d, pos_ids);
+  return launch(replicate_rows_kernel<VEC, 64>, items, 4, n_seqs, P, T, copies, prompt_items, cu, row_vecs, s, d, pos_ids);
 }
 
 hipError_t launch_rows_copy(bool to_packed, int n_seqs, int ctx_len, int total_resp, const int32_t* cu,

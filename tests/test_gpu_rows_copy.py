@@ -39,3 +39,32 @@ def test_rows_copy(P, lens, row_bytes, shift):
     assert np.array_equal(pos_p.cpu().numpy(), orc.position_ids_single_prompt(P, cu))
     for t in (lt, bt):   # nothing outside the rows is written
         assert (t[:shift // 4] == -5).all() and (t[-(8 if shift == 0 else 7):] == -5).all()
+
+
+def device_check(N, P, lens, row_bytes, shift=0):
+    """Both copies against gathers by torch on the device; 4-byte units where `shift` moves the bases by 4 bytes."""
+    import torch
+    from paper_2605_15422_amd import binding as B
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, w = int(cu[-1]), row_bytes // 4
+    idx = np.concatenate([np.concatenate([np.arange(P), P + np.arange(cu[i], cu[i + 1])]) for i in range(N)])
+    cu_dev = torch.from_numpy(cu).cuda()
+
+    def dev(rows):
+        return torch.full((rows * w + shift // 4,), -5, dtype=torch.int32, device="cuda")[shift // 4:]
+
+    packed, long_, back = dev(P + T), dev(N * P + T), dev(P + T)
+    packed.copy_(torch.randint(0, 2**31 - 1, (packed.numel(),), dtype=torch.int32, device="cuda"))
+    B.dualkv_replicate(N, P, T, cu_dev, row_bytes, packed, long_)
+    assert torch.equal(long_.view(-1, w), packed.view(-1, w)[torch.from_numpy(idx).cuda()])
+    B.dualkv_repack(N, P, T, cu_dev, row_bytes, long_, back)
+    assert torch.equal(back, packed)
+
+
+@pytest.mark.parametrize("units", [255, 256, 257, 511, 513, 768, 769, 1024, 1025, 2305])
+@pytest.mark.parametrize("unit_bytes", [4, 16])
+def test_long_rows(units, unit_bytes):
+    """Around one, two, three and four units of each of the 256 threads of a row."""
+    print("case long rows", units, unit_bytes, flush=True)
+    device_check(5, 7, [3, 0, 9, 1, 4], units * unit_bytes)
+    device_check(3, 2, [1, 40, 0], units * unit_bytes, shift=4)
