@@ -3,6 +3,7 @@
 // the standard packing (Eq. 1) and the single-prompt packing (Eq. 5).
 #include "common.h"
 #include "launch.h"
+#include "rules.h"
 
 namespace dkv {
 
@@ -162,8 +163,8 @@ hipError_t launch_convert2_ctx(const float* acc0, const TViewOut& out0, const fl
 // Layout copies between the standard packing (Eq. 1) and the single-prompt packing (Eq. 5); rows are opaque records of 4- or
 // 16-byte units.  All three kernels are bound by memory once enough of it is in flight.
 //   * repack, long rows: driven by the destination rows, TPR threads a row, source row by binary search in cu_seqlens;
-//   * replicate, long rows: driven by the source rows, so that a prompt row is read once and written 16 times from
-//     registers, where a gather read it again for every copy;
+//   * replicate, long rows: driven by the source rows, so that a prompt row is read once and written up to 16 times from
+//     registers, where a gather read it again for every copy (replicate_copies);
 //   * short rows (token ids, labels): a workgroup per row spends its life in the binary search; one lane takes one unit.
 // 16 x (8192 + 1024) rows of 8 KB: replicate 335 -> 265 us (5.3 TB/s, the rate of a plain copy), repack 77 -> 70 us; of 4
 // bytes: replicate 118 -> 4.9 us, repack 14 -> 4.7 us.
@@ -314,7 +315,7 @@ static hipError_t launch_rows_copy_t(bool to_packed, int n_seqs, int P, int T, c
     if (wide) return launch(repack_rows_kernel<VEC, 256, false>, drows, 1, n_seqs, P, drows, cu, row_vecs, s, d, pos_ids);
     return launch(repack_rows_kernel<VEC, 64, false>, drows, 4, n_seqs, P, drows, cu, row_vecs, s, d, pos_ids);
   }
-  const int copies = 16;
+  const int copies = rules::replicate_copies(n_seqs, P, T);
   const int64_t prompt_items = (int64_t)P * ((n_seqs + copies - 1) / copies), items = prompt_items + T;
   if (wide) return launch(replicate_rows_kernel<VEC, 256>, items, 1, n_seqs, P, T, copies, prompt_items, cu, row_vecs, s, d, pos_ids);
   return launch(replicate_rows_kernel<VEC, 64>, items, 4, n_seqs, P, T, copies, prompt_items, cu, row_vecs, s, d, pos_ids);

@@ -68,3 +68,11 @@ def test_long_rows(units, unit_bytes):
     print("case long rows", units, unit_bytes, flush=True)
     device_check(5, 7, [3, 0, 9, 1, 4], units * unit_bytes)
     device_check(3, 2, [1, 40, 0], units * unit_bytes, shift=4)
+
+
+@pytest.mark.parametrize("P,N", [(8, 35), (40, 14), (36, 35), (75, 35), (130, 35), (260, 17), (4300, 1)])
+@pytest.mark.parametrize("row_bytes", [512, 2064])
+def test_copies_of_a_prompt_row(P, N, row_bytes):
+    """1, 2, 4, 8 and 16 copies per workgroup, sequences that they do not divide, a wave and a workgroup per row."""
+    print("case copies", P, N, row_bytes, flush=True)
+    device_check(N, P, [i % 3 for i in range(N)], row_bytes)

@@ -30,6 +30,10 @@ int main() {
       for (int i = 0; i < 9; ++i) std::scanf("%lld", &v[i]);
       n = row_block_waves({(int)v[0], (int)v[1], (int)v[2], v[3] != 0, (int)v[4], (int)v[5]}, v[6] != 0, v[7] != 0, v[8] != 0);
     }
+    if (what == 'r') {
+      for (int i = 0; i < 3; ++i) std::scanf("%lld", &v[i]);
+      n = replicate_copies(v[0], v[1], v[2]);
+    }
     std::printf("%d\n", n);
   }
 }
@@ -128,3 +132,10 @@ def test_row_block_waves(ask, case, waves):
 
 def test_a_shared_launch_takes_four_waves(ask):
     assert ask(["w 20 26 0 0 1 8 0 1 1", "w 1 1 0 0 1 1 0 1 1"]) == [4, 4]
+
+
+# (N, P, T), copies of a prompt row per workgroup of the replicating copy
+@pytest.mark.parametrize("case,copies", [((16, 8192, 16384), 16), ((23, 29, 138), 2), ((16, 64, 264), 4), ((4, 32, 27), 1),
+                                         ((1, 100000, 0), 16), ((0, 0, 0), 1), ((2**31 - 1, 2**31 - 1, 0), 16)])
+def test_replicate_copies(ask, case, copies):
+    assert ask(["r %d %d %d" % case]) == [copies]
