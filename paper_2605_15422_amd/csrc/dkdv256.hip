@@ -796,12 +796,12 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
     return hipErrorInvalidValue;
   hipError_t e = ensure_dynamic_lds<dkdv256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split +
-                       (int64_t)p.n_seqs * p.n_dec_tiles * p.Hk;
-  if (nblk == 0) return hipSuccess;
+  const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
   auto kern = dkdv256_kernel<D, LOCAL>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), Cfg<D>::SMEM_BYTES, st, p);
-  return hipGetLastError();
+  return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

@@ -549,20 +549,6 @@ static int64_t prompt_workgroups(const AttnParams& p) {
 static int64_t response_workgroups(const AttnParams& p) {
   return (int64_t)p.n_seqs * ((p.max_rows + kKeyTile - 1) / kKeyTile) * p.Hk;
 }
-// Fills in the schedule fields of the parameters; number of workgroups.
-template <int D>
-static hipError_t prepare_dkdv4(AttnParams& p, int64_t& n_workgroups) {
-  p.n_ctx_tiles = (p.ctx_len + kKeyTile - 1) / kKeyTile;
-  p.n_dec_tiles = (p.max_rows + kKeyTile - 1) / kKeyTile;
-  if (p.n_split < 1) p.n_split = 1;
-  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
-  if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
-       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
-    return hipErrorInvalidValue;
-  n_workgroups = prompt_workgroups(p) + response_workgroups(p);
-  return hipSuccess;
-}
-
 static int64_t dq_workgroups(AttnParams& p) {
   fill_packing(p, kDqWaves);
   return (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
@@ -570,16 +556,28 @@ static int64_t dq_workgroups(AttnParams& p) {
 
 template <int D, bool LOCAL, bool WITH_DQ>
 static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
-  int64_t n_kv;
-  hipError_t e = prepare_dkdv4<D>(p, n_kv);
-  if (e != hipSuccess) return e;
-  const int64_t n = n_kv + (WITH_DQ ? dq_workgroups(p) : 0);
+  p.n_ctx_tiles = (p.ctx_len + kKeyTile - 1) / kKeyTile;
+  p.n_dec_tiles = (p.max_rows + kKeyTile - 1) / kKeyTile;
+  if (p.n_split < 1) p.n_split = 1;
+  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
+  if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
+       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
+    return hipErrorInvalidValue;
   constexpr size_t smem = WITH_DQ && kDq2Smem<D> > kDkdv4Smem<D> ? kDq2Smem<D> : kDkdv4Smem<D>;
   auto kern = dkdv4_kernel<D, LOCAL, WITH_DQ>;
-  if ((e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL, WITH_DQ>>(smem)) != hipSuccess) return e;
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kWaves<D> * 64), smem, st, p, (int)n_kv);
-  return hipGetLastError();
+  const hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL, WITH_DQ>>(smem);
+  if (e != hipSuccess) return e;
+  constexpr int threads = kWaves<D> * 64;
+  if constexpr (WITH_DQ) {   // (few workgroups: dkdv4_dq_fits)
+    const unsigned n_kv = (unsigned)(prompt_workgroups(p) + response_workgroups(p)), n = n_kv + (unsigned)dq_workgroups(p);
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv);
+    return hipGetLastError();
+  }
+  return launch_key_tiles(p, prompt_workgroups(p), (int64_t)p.n_dec_tiles * p.Hk, threads, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, q, (int)n);
+    return hipGetLastError();
+  });
 }
 
 template <bool WITH_DQ>

@@ -16,10 +16,10 @@ static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
   auto kern = dq2_kernel<D, NW, LOCAL>;
   hipError_t e = ensure_dynamic_lds<dq2_kernel<D, NW, LOCAL>>(smem);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(NW * 64), smem, st, p);
-  return hipGetLastError();
+  return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, NW * 64, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(NW * 64), smem, st, q);
+    return hipGetLastError();
+  });
 }
 
 template <int D>

@@ -367,10 +367,10 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
   auto kern = dq256_kernel<D, LOCAL>;
   hipError_t e = ensure_dynamic_lds<dq256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(512), Cfg<D>::SMEM_BYTES, st, p);
-  return hipGetLastError();
+  return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

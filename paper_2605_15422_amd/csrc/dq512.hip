@@ -279,10 +279,10 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
   fill_packing(p, NSUB);
   hipError_t e = ensure_dynamic_lds<dq512_kernel<LOCAL>>(SMEM_BYTES);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(dq512_kernel<LOCAL>, dim3((unsigned)nblk), dim3(512), SMEM_BYTES, st, p);
-  return hipGetLastError();
+  return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(dq512_kernel<LOCAL>, dim3(n), dim3(512), SMEM_BYTES, st, q);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace

@@ -430,10 +430,10 @@ static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
   auto kern = fwd2_kernel<D, NW, LOCAL>;
   hipError_t e = ensure_dynamic_lds<fwd2_kernel<D, NW, LOCAL>>(smem);
   if (e != hipSuccess) return e;
-  const int64_t nblk = (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(C::NT), smem, st, p);
-  return hipGetLastError();
+  return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, C::NT, [&](const AttnParams& q, unsigned n) {
+    hipLaunchKernelGGL(kern, dim3(n), dim3(C::NT), smem, st, q);
+    return hipGetLastError();
+  });
 }
 
 template <int D>

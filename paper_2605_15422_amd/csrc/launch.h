@@ -47,4 +47,37 @@ inline hipError_t ensure_dynamic_lds(size_t bytes) {
   return once;
 }
 
+// HIP takes fewer than 2^32 work items a launch.  Row blocks or key tiles count with the longest sequence, so that a call with many
+// sequences and a long one may need more of them: its sequences go out in several launches of per_seq workgroups each.
+template <typename F>
+inline hipError_t launch_sequences(const AttnParams& p, int64_t per_seq, int threads, F launch) {
+  if (per_seq == 0) return hipSuccess;
+  const int64_t fit = ((int64_t)1 << 32) / threads - 1, step = fit > per_seq ? fit / per_seq : 1;
+  hipError_t e = hipSuccess;
+  for (int64_t s = 0; s < p.n_seqs && e == hipSuccess; s += step) {
+    AttnParams q = p;
+    q.n_seqs = (int)(p.n_seqs - s < step ? p.n_seqs - s : step);
+    if (s) q.cu += s;
+    if (s && q.seq_ctx) q.seq_ctx += 2 * s;
+    e = launch(q, (unsigned)(q.n_seqs * per_seq));
+  }
+  return e;
+}
+// dK/dV: the prompt tiles of all sequences belong to the first launch, which then is one of its own
+template <typename F>
+inline hipError_t launch_key_tiles(const AttnParams& p, int64_t prompt, int64_t per_seq, int threads, F launch) {
+  const int64_t n = prompt + p.n_seqs * per_seq;
+  if (n == 0) return hipSuccess;
+  if (n < ((int64_t)1 << 32) / threads) return launch(p, (unsigned)n);
+  AttnParams q = p;
+  if (prompt) {
+    q.n_dec_tiles = 0;
+    hipError_t e = launch(q, (unsigned)prompt);
+    if (e != hipSuccess) return e;
+    q.n_dec_tiles = p.n_dec_tiles;
+  }
+  q.n_ctx_tiles = 0;
+  return launch_sequences(q, per_seq, threads, launch);
+}
+
 }  // namespace dkv
