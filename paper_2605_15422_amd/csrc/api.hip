@@ -209,12 +209,14 @@ hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, hipStream
   return do_dq ? run_dq(p, d, st) : hipSuccess;
 }
 
-void base_params(AttnParams& p, const dualkv_shape* s) {
+// `positions`: logical positions that the call can have
+void base_params(AttnParams& p, const dualkv_shape* s, int64_t positions) {
   p = AttnParams{};
   p.H = s->n_q_heads;
   p.Hk = s->n_kv_heads;
   p.G = s->n_q_heads / s->n_kv_heads;
-  p.window = s->window > 0 ? s->window : 0;
+  // (a wider window sees the same keys; the kernels add it to key indexes in 32 bits)
+  p.window = s->window > 0 ? (int)std::min<int64_t>(s->window, std::max<int64_t>(positions, 1)) : 0;
   p.scale = resolve_scale(s);
   p.scale_log2 = p.scale * dkv::LOG2E;
   p.n_split = 1;
@@ -264,7 +266,7 @@ int ctx_fwd_impl(const dualkv_shape* shape, dualkv_tin q_c, dualkv_tin k_c, dual
   if (cu_bytes > 0 && reinterpret_cast<uintptr_t>(workspace) % 16) return DUALKV_E_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   AttnParams p;
-  base_params(p, shape);
+  base_params(p, shape, shape->ctx_len);
   p.q = view(q_c);
   p.kd = view(k_c);
   p.vd = view(v_c);
@@ -295,7 +297,7 @@ int fwd_impl(const dualkv_shape* shape, dualkv_tin q_d, dualkv_tin k_c, dualkv_t
   if (seqctx_bytes > 0 && reinterpret_cast<uintptr_t>(workspace) % 16) return DUALKV_E_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   AttnParams p;
-  base_params(p, shape);
+  base_params(p, shape, (int64_t)shape->ctx_len + shape->max_resp);
   p.q = view(q_d);
   p.kc = view(k_c);
   p.vc = view(v_c);
@@ -340,7 +342,7 @@ int ctx_bwd_impl(const dualkv_shape* shape, dualkv_tin do_c, dualkv_tin o_c, con
   hipStream_t st = static_cast<hipStream_t>(stream);
 
   AttnParams p;
-  base_params(p, shape);
+  base_params(p, shape, shape->ctx_len);
   p.q = view(q_c);
   p.kd = view(k_c);
   p.vd = view(v_c);
@@ -398,7 +400,7 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
   const int64_t n_acc = (int64_t)P * shape->n_kv_heads * d;
 
   AttnParams p;
-  base_params(p, shape);
+  base_params(p, shape, (int64_t)shape->ctx_len + shape->max_resp);
   p.q = view(q_d);
   p.kc = view(k_c);
   p.vc = view(v_c);
