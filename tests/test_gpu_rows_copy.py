@@ -76,3 +76,10 @@ def test_copies_of_a_prompt_row(P, N, row_bytes):
     """1, 2, 4, 8 and 16 copies per workgroup, sequences that they do not divide, a wave and a workgroup per row."""
     print("case copies", P, N, row_bytes, flush=True)
     device_check(N, P, [i % 3 for i in range(N)], row_bytes)
+
+
+@pytest.mark.parametrize("shift", [0, 4])
+def test_copies_larger_than_the_cache(shift):
+    """Source and destination of 160 MB each: the variant that bypasses the caches, in 16- and 4-byte units."""
+    print("case large copy", shift, flush=True)
+    device_check(4, 4000, [4000, 0, 5000, 7001], 8192, shift)
