@@ -15,9 +15,10 @@
 //     transpose reads.  The producers' exponentials overlap the consumers' MFMAs.
 //   * the consumers also walk the row-block schedule (a few scalar operations per block) and issue the
 //     global -> LDS loads (global_load_lds: Q, dO, LSE*log2e, D never pass through registers) five row
-//     blocks ahead; wave 4 leaves a 16-byte header per key subtile in the stage (valid / active / mask flags,
-//     first row, row count), which is all a producer needs to know about the schedule.
-//   * the main loop is unrolled over the six LDS stages, so every LDS address is an immediate offset;
+//     blocks ahead; each of them leaves the 16-byte header of one key subtile in the stage (valid / active /
+//     mask flags, first row, row count), which is all a producer needs to know about the schedule.
+//   * the main loop is unrolled over the LDS stages (six; eight at head dim 64), so every LDS address is an
+//     immediate offset;
 //     every LDS operand is read one interval before its use, across the single barrier per row block.
 //
 // Head dim 96 has three 32-wide head-dim blocks for the four consumer waves.  Three of them own a block each and do

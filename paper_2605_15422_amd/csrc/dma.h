@@ -26,13 +26,6 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
                : "s"(lds_addr), "v"(voff), "s"(sbase)
                : "memory", "m0");
 }
-// 64 lanes x 4 bytes: global address = sbase + voff (per lane), LDS address = lds_addr + 4 * lane.
-__device__ __forceinline__ void dma4(const void* sbase, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(sbase)
-               : "memory", "m0");
-}
 // The same with the LDS address given as a wave-uniform base plus a compile-time offset, added into M0 inside the
 // statement.  In a loop unrolled over LDS stages every load has a different constant address; given as one value,
 // the compiler computes all of them ahead of the loop, runs out of scalar registers and reloads each from a spill
