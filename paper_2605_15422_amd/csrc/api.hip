@@ -186,8 +186,8 @@ hipError_t run_dkdv(const AttnParams& p, int d, hipStream_t st) {
 
 // The backward stages of one call over `rows` rows.  The dQ kernel holds the dO rows that D = rowsum(dO * O) needs, so it
 // runs first and forms D (and LSE in base-2 units) for the dK/dV kernel: one launch and one pass over dO less than with a
-// preprocess of its own (layer at N = 16, P = 8192, R = 1024, 32 / 8 heads, d = 128: 11.40 -> 11.33 ms; at d = 256, window
-// 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 5.21 -> 5.06 ms).  Calls that leave CUs idle run both kernels side by side
+// preprocess of its own (layer at N = 16, P = 8192, R = 1024, 32 / 8 heads, d = 128: 11.40 -> 11.33 ms, no more than runs differ;
+// at d = 256, window 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 2 to 3 %).  Calls that leave CUs idle run both kernels side by side
 // behind the preprocess (dkdv4.hip).  The preprocess also serves calls without dQ, and calls whose dQ overwrites what the
 // dK/dV kernel has to read (dQ is written last then).
 hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, hipStream_t st) {

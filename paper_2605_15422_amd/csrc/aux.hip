@@ -166,7 +166,7 @@ hipError_t launch_convert2_ctx(const float* acc0, const TViewOut& out0, const fl
 //   * replicate, long rows: driven by the source rows, so that a prompt row is read once and written up to 16 times from
 //     registers, where a gather read it again for every copy (replicate_copies);
 //   * short rows (token ids, labels): a workgroup per row spends its life in the binary search; one lane takes one unit.
-// 16 x (8192 + 1024) rows of 8 KB: replicate 335 -> 265 us (5.3 TB/s, the rate of a plain copy), repack 77 -> 70 us; of 4
+// 16 x (8192 + 1024) rows of 8 KB: replicate 335 -> 260 us (5.4 TB/s, the rate of a plain copy), repack 77 -> 65 us; of 4
 // bytes: replicate 118 -> 4.9 us, repack 14 -> 4.7 us.
 // ---------------------------------------------------------------------------------------------
 // the last sequence s with base * s + cu[s] <= x (x >= 0, cu[0] == 0)

@@ -1,6 +1,6 @@
 """GPU parity of dK/dV tiles whose row blocks are cut into parts for several workgroups (few key tiles, many row blocks and
-heads): Call 1 and Call 2 with the fp32 joint accumulation, against the fp64 oracle; parts that end inside a sequence, empty
-sequences, a single sequence, groups of unequal prompts."""
+heads): Call 2 (Call 1's are never cut) with the fp32 joint accumulation, against the fp64 oracle; parts that end inside a
+sequence, empty sequences, a single sequence, groups of unequal prompts."""
 import numpy as np
 import pytest
 
@@ -19,6 +19,17 @@ def test_joint_accumulation_in_parts(d, P, lens):
     shape = W.Shape("parts", len(lens), P, 0, 0, 8, 1, d, 0, seed=6000 + d + P)
     wl = W.make_workload(shape, resp_lens=np.asarray(lens))
     PU.bounded_parity(wl, flags=B.FLAG_ACCUM_CTX_F32)
+
+
+@pytest.mark.parametrize("d", [64, 96, 128, 192, 256, 512])
+@pytest.mark.parametrize("accum", [False, True])
+def test_more_than_sixteen_parts(d, accum):
+    """Sixty short sequences behind one key tile: thirty parts and more."""
+    from paper_2605_15422_amd import binding as B
+    print("case many parts", d, accum, flush=True)
+    lens = [(7 * i) % 90 for i in range(60)]
+    wl = W.make_workload(W.Shape("parts", len(lens), 31, 0, 0, 8, 1, d, 0, seed=6500 + d), resp_lens=np.asarray(lens))
+    PU.bounded_parity(wl, flags=B.FLAG_ACCUM_CTX_F32 if accum else 0)
 
 
 def test_groups_in_parts():
