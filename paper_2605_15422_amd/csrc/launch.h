@@ -1,6 +1,7 @@
 // Host-side launch entry points of the kernel translation units.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include "common.h"
 
 namespace dkv {
@@ -56,26 +57,30 @@ inline hipError_t launch_sequences(const AttnParams& p, int64_t per_seq, int thr
   hipError_t e = hipSuccess;
   for (int64_t s = 0; s < p.n_seqs && e == hipSuccess; s += step) {
     AttnParams q = p;
-    q.n_seqs = (int)(p.n_seqs - s < step ? p.n_seqs - s : step);
+    q.n_seqs = (int)std::min(step, p.n_seqs - s);
     if (s) q.cu += s;
     if (s && q.seq_ctx) q.seq_ctx += 2 * s;
     e = launch(q, (unsigned)(q.n_seqs * per_seq));
   }
   return e;
 }
-// dK/dV: the prompt tiles of all sequences belong to the first launch, which then is one of its own
+// dK/dV: the prompt tiles go out by groups (they see all sequences of theirs), then the response tiles
 template <typename F>
 inline hipError_t launch_key_tiles(const AttnParams& p, int64_t prompt, int64_t per_seq, int threads, F launch) {
-  const int64_t n = prompt + p.n_seqs * per_seq;
+  const int64_t n = prompt + p.n_seqs * per_seq, fit = ((int64_t)1 << 32) / threads - 1;
   if (n == 0) return hipSuccess;
-  if (n < ((int64_t)1 << 32) / threads) return launch(p, (unsigned)n);
+  if (n <= fit) return launch(p, (unsigned)n);
   AttnParams q = p;
-  if (prompt) {
-    q.n_dec_tiles = 0;
-    hipError_t e = launch(q, (unsigned)prompt);
+  q.n_dec_tiles = 0;
+  const int n_groups = p.grp ? p.n_groups : 1;
+  const int64_t per_group = prompt / n_groups, step = fit > per_group ? fit / std::max<int64_t>(per_group, 1) : 1;
+  for (int64_t g = 0; prompt && g < n_groups; g += step) {
+    q.n_groups = (int)std::min(step, n_groups - g);
+    if (p.grp) q.grp = p.grp + 4 * g;
+    const hipError_t e = launch(q, (unsigned)(q.n_groups * per_group));
     if (e != hipSuccess) return e;
-    q.n_dec_tiles = p.n_dec_tiles;
   }
+  q = p;
   q.n_ctx_tiles = 0;
   return launch_sequences(q, per_seq, threads, launch);
 }

@@ -31,3 +31,24 @@ def test_many_empty_sequences(d, window):
             assert (x.double() - y.double()).norm() <= 2.0**-8 * y.double().norm()
         else:
             assert not torch.isnan(x).any() and torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
+@pytest.mark.parametrize("d", [64, 256])
+def test_many_empty_groups(d):
+    """Prompt tiles, too: every group gets as many as the longest prompt."""
+    import torch
+    import test_gpu_groups as G
+    specs = [(40, [3, 70]), (65536, [33, 0, 5]), (1, []), (129, [64])]
+    at = [7, 8190, 10922, 16399]   # where they stand among 16400 groups
+    _, packed, table, cu = G._build(specs, 1, 1, d, 0, seed=23)
+    many = np.zeros((16400, 4), np.int32)
+    many[at] = table
+    for g in range(len(many)):
+        if g and g not in at:   # no prompt rows, no sequences
+            many[g] = many[g - 1, 0] + many[g - 1, 1], 0, many[g - 1, 3], many[g - 1, 3]
+    out = []
+    for t in (many, table):
+        print("case many groups", d, len(t), flush=True)
+        out.append(G._run_groups([(65536, [])] * len(t), packed, t, cu, 1, 1, d, 0, 0)[1])
+    for k, x in out[0].items():
+        assert not torch.isnan(x).any() and torch.equal(x.view(torch.int16), out[1][k].view(torch.int16)), k
