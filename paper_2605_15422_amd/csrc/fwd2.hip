@@ -206,7 +206,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   auto operand = [&](const unsigned char* Kh, const unsigned char* Vh, int i) __attribute__((always_inline)) {
     return i < NS ? k_operand(Kh, i) : v_operand(Vh, i - NS);
   };
-  float thr = (m_ref + 8.0f) / c;   // an (unscaled) row maximum above this moves the reference
   // (plain C: the compiler must see these reads of MFMA results to place the wait states they need)
   auto lane_max = [&](const f32x16& v) __attribute__((always_inline)) {
     float m = fmaxf(fmaxf(v[0], v[1]), v[2]);
@@ -214,8 +213,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     for (int r = 3; r < 15; r += 2) m = fmaxf(fmaxf(m, v[r]), v[r + 1]);
     return fmaxf(m, v[15]);
   };
-  // mx: on entry the maximum of this lane's 16 scores in `sc` before masking, on exit that of `sn`
-  auto step = [&](bool masked, float& mx, f32x16& sc, f32x16& sn, bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
+  auto step = [&](bool masked, f32x16& sc, f32x16& sn, bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
                   const unsigned char* Kn, const unsigned char* Vp, const unsigned char* Kn2, const unsigned char* Vn2,
                   bool is_ctx, int keyh0) __attribute__((always_inline)) {
     if (masked) {
@@ -237,30 +235,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
         sc[r] = vis ? sc[r] : -INFINITY;
       }
     }
-    // Row maximum of this lane's 16 scores (the partner lane l ^ 32 holds the other 16 of the row; its own
-    // test below covers them: the branch is taken if ANY lane exceeds the threshold).  It was formed in the
-    // shadow of the previous step's last MFMAs; only a masked half tile has to form it again.
-    if (masked) mx = lane_max(sc);
-    // rescale lazily: keep the reference maximum until some row's maximum outgrows it by 2^8.  The product of
-    // the previous half was formed against the old reference, so it is accumulated before the rescale (and
-    // the slots below then add a product with P = 0).
-    if (__any(mx > thr)) {
-      mx = xor32_max(mx) * c;
-      pv_half(Vp, pprev);
-      pprev[0] = __builtin_bit_cast(bf16x8, zero4);
-      pprev[1] = __builtin_bit_cast(bf16x8, zero4);
-      const float mn = fmaxf(m_ref, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m_ref - mn);
-      m_ref = mn;
-      thr = (m_ref + 8.0f) / c;
-      l_sum *= alpha;
-#pragma unroll
-      for (int ds = 0; ds < C::DSUB; ++ds)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[ds][r] *= alpha;
-    }
-    // (the exponentials below must not be computed ahead of the branch above)
-    asm volatile("" : "+v"(m_ref));
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 ob[NSLOT];
 #pragma unroll
@@ -320,15 +294,30 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
             asm volatile("" : "+v"(ls0));
           }
         }
-        if (g == NG - 1 && q == 1) {
-          // the scores of the next half are complete: their maximum, needed at the top of the next step
-          mx = lane_max(sn);
-          asm volatile("" : "+v"(mx));
-        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    l_sum += ls0 + ls1;
+    float ls = ls0 + ls1;
+    // rescale lazily
+    if (__builtin_expect(__any(!(ls < 256.0f)), 0)) {
+      const float mn = fmaxf(m_ref, xor32_max(lane_max(sc)) * c);
+      const float alpha = __builtin_amdgcn_exp2f(m_ref - mn);
+      m_ref = mn;
+      l_sum *= alpha;
+#pragma unroll
+      for (int ds = 0; ds < C::DSUB; ++ds)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[ds][r] *= alpha;
+      ls = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        const float e0 = __builtin_amdgcn_exp2f(sc[r] * c - m_ref), e1 = __builtin_amdgcn_exp2f(sc[r + 1] * c - m_ref);
+        ls += e0 + e1;
+        pw[r >> 1] = pack2_bf16(e0, e1);
+      }
+    }
+    asm volatile("" : "+v"(m_ref));
+    l_sum += ls;
     u32x4 w0 = {pw[0], pw[1], pw[2], pw[3]}, w1 = {pw[4], pw[5], pw[6], pw[7]};
     pcur[0] = __builtin_bit_cast(bf16x8, w0);
     pcur[1] = __builtin_bit_cast(bf16x8, w1);
@@ -354,7 +343,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   pB[0] = __builtin_bit_cast(bf16x8, zero4);
   pB[1] = __builtin_bit_cast(bf16x8, zero4);
   s_half(smem, sA);
-  float mxs = lane_max(sA);
   bf16x8 pre[LEAD];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0, V with P = 0
 #pragma unroll
   for (int i = 0; i < LEAD; ++i) pre[i] = operand(smem + 32 * C::RB, smem + V_RING + 32 * C::RB, i);
@@ -383,8 +371,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     // tiles that can hold an invisible (row, key) pair for this wave: the partial last prompt tile, response
     // tiles from the diagonal (or the end of the sequence) on; windowed runs mask every tile
     const bool masked = always_masked || (is_ctx ? kt == ctx_masked : kt >= dec_masked);
-    step(masked, mxs, sA, sB, pB, pA, pre, Kt + 32 * C::RB, Vp, Kn, Vt, is_ctx, key0);
-    step(masked, mxs, sB, sA, pA, pB, pre, Kn, Vt, Kn + 32 * C::RB, Vt + 32 * C::RB, is_ctx, key0 + 32);
+    step(masked, sA, sB, pB, pA, pre, Kt + 32 * C::RB, Vp, Kn, Vt, is_ctx, key0);
+    step(masked, sB, sA, pA, pB, pre, Kn, Vt, Kn + 32 * C::RB, Vt + 32 * C::RB, is_ctx, key0 + 32);
     // tiles it+2 (K) and it+1 (V) must have landed; the loads requested at the top of this tile may stay in flight
     if (issued) wait_vm<IPT>();
     else wait_vm<0>();
