@@ -32,6 +32,13 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// v_mfma_f32_16x16x32_bf16: A lane l holds row l % 16, B lane l column l % 16, both k = 8*(l/16) .. 8*(l/16)+7; C lane l holds
+// column l % 16, register r (0..3) row 4*(l/16) + r.  Two C tiles of 16 rows are the 32-deep K-indexed operand of the next
+// MFMA (lane group g holds rows 4g..4g+3 and 16+4g..16+4g+3).
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
   f32x2 v = {a, b};
   bf16x2 r = __builtin_convertvector(v, bf16x2);

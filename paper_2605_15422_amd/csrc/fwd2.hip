@@ -4,22 +4,27 @@
 // are shared by all packed heads) and walks the two KV regions in logical order, prompt tiles then own-response tiles.
 // The scores are computed transposed, S^T = K Q^T, so that a lane owns one query row and exp(S^T) is already laid out
 // as the B operand of O^T += V^T P^T:
-//   * 4 waves at head dim 64 (two workgroups fit a CU), else 8, two per SIMD, or 4 by the rule of
-//     row_block_waves (rules.h); each owns ONE 32-row subtile: Q fragments (B operands) and the O^T accumulator stay in registers (~200 VGPRs, no spills);
-//   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row so that both the
-//     16-byte K operand reads and the transposing V reads are bank-conflict free; V^T operands come
-//     from ds_read_b64_tr_b16 (LDS transpose read), so nothing is transposed on the way into LDS;
-//   * the tiles travel global -> LDS directly (global_load_lds) into two rings of four slots, K three
-//     tiles ahead (requested by the first half of the waves) and V two (the second half): no staging
-//     registers, no LDS stores, one barrier per tile;
-//   * each wave runs a software pipeline over 32-key half tiles: while the VALU does the softmax of
-//     half g, the matrix pipe computes the scores of half g+1 and the P V product of half g-1.  Two
-//     waves per SIMD do not hide a wave's own MFMA -> softmax -> MFMA dependency chain on this chip
-//     (their phases drift together at every barrier); interleaving independent work inside one
-//     instruction stream does.
-// Head dim 96 takes twelve slots per step instead of sixteen and tiles of un-padded 192-byte rows (tiles.h).  On N = 8,
-// P = 4111, R ~ U(131, 2048), 16 / 4 heads it runs 0.41 + 0.13 ms (Call 2 + Call 1), against 0.68 + 0.20 ms for the
-// unpipelined kernel with register staging that served this head dim before.
+//   * 4 waves at head dim 64 (two workgroups fit a CU), else 8, two per SIMD, or 4 by the rule of row_block_waves (rules.h);
+//     each owns 32 query rows, two halves of 16: Q fragments (B operands) and the O^T accumulator stay in registers;
+//   * the 16x16x32 MFMA, each K or V operand read from LDS feeding the two halves.  These kernels run into the card's power
+//     limit, not into its matrix rate: with all inputs zero the 32x32x16 form of this kernel took 16.0 ms for 16 x U(1024, 2048)
+//     behind 32768, 32 / 4 heads, d = 128, and 20.5 with normal ones.  On normal values a bare loop of 16x16x32 MFMAs reaches
+//     2040 TFLOP/s, one of 32x32x16 1775 (2460 both on zeros), and a loop with this kernel's operand reads and softmax
+//     1466 against 1344;
+//   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row (tiles.h) so that both the 16-byte K
+//     operand reads and the transposing V reads are bank-conflict free; V^T operands come from ds_read_b64_tr_b16
+//     (LDS transpose read), so nothing is transposed on the way into LDS;
+//   * the tiles travel global -> LDS directly (global_load_lds) into two rings of four slots, K three tiles ahead (requested
+//     by the first half of the waves) and V two (the second half): no staging registers, no LDS stores, one barrier per tile;
+//     the loop is unrolled over the slots, so that every operand address is a register plus an immediate;
+//   * each wave runs a software pipeline over 32-key half tiles: while the VALU does the softmax of half g, the matrix pipe
+//     computes the scores of half g+1 and the P V product of half g-1.  Two waves per SIMD do not hide a wave's own MFMA ->
+//     softmax -> MFMA dependency chain on this chip (their phases drift together at every barrier); interleaving
+//     independent work inside one instruction stream does;
+//   * no row maximum per half tile: the reference of the exponentials moves when a sum of probabilities says so.
+// Measured against the same kernel on 32x32x16 MFMAs with a row maximum and addresses formed per tile: 16 x 1024 rows behind 8192,
+// 32 / 8 heads, d = 128 2.15 -> 1.91 ms (1224 TFLOP/s); 8 x U(131, 2048) behind 4096, d = 64 650 -> 585 us, d = 96 (16 / 4 heads)
+// 371 -> 308 us.
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
@@ -32,19 +37,16 @@ namespace dkv {
 template <int D, int NWAVES>
 struct F2Cfg {
   static constexpr int NW = NWAVES, NT = NW * 64, BN = 64;
-  static constexpr int KS = D / 16, DSUB = D / 32;
+  static constexpr int KS = D / 32, DB = D / 16;   // k-steps of a score, 16-wide head-dim blocks
   static constexpr int RB = 2 * D;                 // row bytes
   static constexpr int CPR = D / 8;                // 16-byte chunks per row
-  static constexpr int RPL = CPR < 16 ? 16 / CPR : 1;   // rows per 256-byte bank line
   static constexpr int TILE_BYTES = BN * RB;
-  // (head dim 96: four consecutive 192-byte rows lie on different quarters of the bank line by themselves, which is all
-  // that the transpose reads of V need)
-  __device__ static __forceinline__ int fK(int row) { return D == 96 ? swz<96>(row) : (row / RPL) % CPR; }
-  __device__ static __forceinline__ int fV(int row) { return D == 96 ? 0 : 4 * ((row / RPL) % (CPR / 4)); }
+  static constexpr bool ALONE = NW == 4 && D != 64;   // one wave per SIMD (the rings leave no room for a second workgroup)
+  static constexpr int DIST = ALONE ? 2 : 1;          // groups of slots from an operand's request to its use
 };
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_kernel(const AttnParams p) {
   using C = F2Cfg<D, NW>;
   constexpr int BN = C::BN;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
@@ -52,353 +54,291 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   if (!decode_qblock<BN>(p, b, blockIdx.x, gridDim.x)) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int i16 = lane & 15, lg = lane >> 4;
   const int P = b.P, R = b.R, W = p.window;
   const float c = p.scale_log2;
 
   const int head = b.hk * p.G + b.hc * p.GP + wave / p.RSH;
   const int row0 = b.blk_row0 + (wave % p.RSH) * 32;
-  const int row = row0 + l32;
   const bool wave_valid = row0 < R;
 
-  bf16x8 qf[C::KS];
+  bf16x8 qf[2][C::KS];   // rows row0 + i16 and row0 + 16 + i16
   {
-    const int r = min(row, R - 1);
-    const u16* qp = p.q.ptr + (int64_t)(b.row_begin + r) * p.q.ts + (int64_t)head * p.q.hs + hi * 8;
+    const u16* qp = p.q.ptr + (int64_t)b.row_begin * p.q.ts + (int64_t)head * p.q.hs + kgrp16<D>(lg) * 8;
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 16);
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ++ks)
+        qf[h][ks] = *reinterpret_cast<const bf16x8*>(qp + (int64_t)min(row0 + 16 * h + i16, R - 1) * p.q.ts + ks * 32);
     // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : : "v"(qf[ks]));
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : : "v"(qf[h][ks]));
   }
 
-  f32x16 oacc[C::DSUB];
+  f32x4 oacc[2][C::DB];
 #pragma unroll
-  for (int ds = 0; ds < C::DSUB; ++ds)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[ds][r] = 0.f;
-  float m_ref = NEG_BIG, l_sum = 0.f;
+    for (int db = 0; db < C::DB; ++db) oacc[h][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_ref[2] = {NEG_BIG, NEG_BIG}, l_sum[2] = {0.f, 0.f};
 
-  // ---- per-lane LDS offsets (bytes, relative to a tile base)
-  int koff[C::KS];          // K operand: row l32 (+32*half), chunk 2*ks+hi
-#pragma unroll
-  for (int ks = 0; ks < C::KS; ++ks) koff[ks] = l32 * C::RB + (((2 * ks + hi) ^ C::fK(l32)) << 4);
-  int voff[C::DSUB];        // V transpose read: row (lane%16)/4 (+ key base), 4 head-dim values at 16*((lane/16)%2)+4*(lane%4)
-  {
-    const int r16 = lane & 15, g = (lane >> 4) & 1;
-    const int vrow = hi * 4 + (r16 >> 2);
-#pragma unroll
-    for (int ds = 0; ds < C::DSUB; ++ds) {
-      const int dcol = ds * 32 + g * 16 + (r16 & 3) * 4;
-      voff[ds] = vrow * C::RB + ((((dcol >> 3)) ^ C::fV(vrow)) << 4) + ((dcol >> 2) & 1) * 8;
-    }
-  }
-
-  // ---- global -> LDS tile loads: instruction j = lwave + LW t of a tile covers RPI key rows; lane l lands at
-  // LDS chunk position l % CPR of row l / CPR of the instruction and fetches the chunk the swizzle stores
-  // there (both swizzles have a period that divides LW RPI rows, so one offset per tensor serves every t).
-  // Keys past the end of the region re-read the last key: their scores are masked like any invisible key.
-  const u16* kc_base = p.kc.ptr + (int64_t)b.ctx_off * p.kc.ts + (int64_t)b.hk * p.kc.hs;
-  const u16* vc_base = p.vc.ptr + (int64_t)b.ctx_off * p.vc.ts + (int64_t)b.hk * p.vc.hs;
-  const u16* kd_base = p.kd.ptr + (int64_t)b.row_begin * p.kd.ts + (int64_t)b.hk * p.kd.hs;
-  const u16* vd_base = p.vd.ptr + (int64_t)b.row_begin * p.vd.ts + (int64_t)b.hk * p.vd.hs;
-  const int n_ctx_run = b.n_ctx - b.c0;
   constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
   constexpr int V_RING = NSTAGE * C::TILE_BYTES;
-  // half of the waves request the K tiles, half the V tiles: one address computation per wave and tile
-  constexpr int LW = C::NW / 2;                       // waves per tensor
-  constexpr int IPT = C::TILE_BYTES / 1024 / LW;      // 1 KB load instructions per wave and tile
-  constexpr int RPI = 1024 / C::RB;                   // rows per load instruction
-  static_assert(IPT >= 1 && C::TILE_BYTES % (1024 * LW) == 0, "tile must split evenly over the waves");
-  const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
-  const int lwave = wave % LW;
-  const bool v_loader = wave >= LW;
-  const int ld_row0 = lwave * RPI + lane / C::CPR;
-  const int ld_kcoff = ((lane % C::CPR) ^ C::fK(ld_row0)) * 16;
-  const int ld_vcoff = ((lane % C::CPR) ^ C::fV(ld_row0)) * 16;
-  // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows, each with an offset of its own)
-  int ld_row[IPT], ld_coff[IPT];
-  if constexpr (kSplitRow<D>) {
-    static_assert(IPT % 3 == 0 && C::BN == LW * (IPT / 3) * kSplitRows<D>, "whole rows per wave");
+  // ---- per-lane LDS addresses in slot 0.  The loop is unrolled over the slots, so that all others are immediate offsets.
+  const unsigned char* kadr[C::KS];   // K operand of k-step ks
 #pragma unroll
-    for (int t = 0; t < IPT; ++t) {
-      ld_row[t] = lwave * (IPT / 3) * kSplitRows<D> + split_row<D>(t, lane);
-      ld_coff[t] = (split_pos<D>(t, lane) ^ (v_loader ? C::fV(ld_row[t]) : C::fK(ld_row[t]))) * 16;
-    }
-  }
-  // which = 0: K tile `it` into the K ring, 1: V tile `it` into the V ring (slot it % 4)
-  const int tsb_c[2] = {(int)p.kc.ts * 2, (int)p.vc.ts * 2}, tsb_d[2] = {(int)p.kd.ts * 2, (int)p.vd.ts * 2};
-  auto issue_tile = [&](int it, int which) __attribute__((always_inline)) {
-    const bool is_ctx = it < n_ctx_run;
-    const int kt = is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run;
-    const int tsb = is_ctx ? tsb_c[which] : tsb_d[which];   // bytes per token
-    const u16* base = is_ctx ? (which ? vc_base : kc_base) : (which ? vd_base : kd_base);
-    const unsigned char* tb = reinterpret_cast<const unsigned char*>(base) + (int64_t)(kt * BN) * tsb;
-    const int last = (is_ctx ? P : R) - kt * BN - 1;
-    const uint32_t slot_addr = smem_addr + which * V_RING + (it & (NSTAGE - 1)) * C::TILE_BYTES;
-    if constexpr (kSplitRow<D>) {
+  for (int ks = 0; ks < C::KS; ++ks) kadr[ks] = smem + frag16_off<D>(lane, ks);
+  const unsigned char* vadr[C::DB];   // V^T operand of head-dim block db
 #pragma unroll
-      for (int t = 0; t < IPT; ++t)
-        dma16(uniform_ptr(reinterpret_cast<const u16*>(tb)),
-              (uint32_t)(__umul24((unsigned)min(ld_row[t], last), (unsigned)tsb) + ld_coff[t]), slot_addr + (lwave * IPT + t) * 1024);
-      return;
-    }
-    const uint32_t dst = slot_addr + lwave * 1024;
-    const int coff = which ? ld_vcoff : ld_kcoff;
-#pragma unroll
-    for (int t = 0; t < IPT; ++t) {
-      const int r = min(ld_row0 + t * LW * RPI, last);
-      // (four waves at head dim 128: the instructions of a wave are half a period of the K swizzle apart)
-      constexpr int FLIP = D == 128 && LW * RPI == 8 ? 128 : 0;
-      const int c = FLIP != 0 && which == 0 && (t & 1) ? coff ^ FLIP : coff;
-      dma16(uniform_ptr(reinterpret_cast<const u16*>(tb)), (uint32_t)(__umul24((unsigned)r, (unsigned)tsb) + c), dst + t * LW * 1024);
-    }
-  };
+  for (int db = 0; db < C::DB; ++db) vadr[db] = smem + V_RING + tr16_off<D>(lane, db);
+
+  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
+  const int n_ctx_run = b.n_ctx - b.c0;
 
   // ---- the three pieces of work of a 32-key half tile
-  // S^T half = K_half Q^T
-  auto s_half = [&](const unsigned char* Kh, f32x16& s) __attribute__((always_inline)) {
+  // S^T half = K_half Q^T: tile 2 h + kh holds keys 16 kh .. 16 kh + 15 of rows 16 h .. 16 h + 15
+  auto s_half = [&](int kh0, f32x4 (&s)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+    for (int i = 0; i < 4; ++i) s[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < C::KS; ++ks) {
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(Kh + koff[ks]);
-      s = mfma32(a, qf[ks], s);
-    }
+    for (int ks = 0; ks < C::KS; ++ks)
+#pragma unroll
+      for (int kh = 0; kh < 2; ++kh) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(kadr[ks] + kh0 + kh * 16 * C::RB);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) s[2 * h + kh] = mfma16(a, qf[h][ks], s[2 * h + kh]);
+      }
   };
   // O^T += V_half^T P_half^T
-  auto pv_half = [&](const unsigned char* Vh, const bf16x8 (&pp)[2]) __attribute__((always_inline)) {
+  auto pv_half = [&](int v0, const bf16x8 (&pp)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      const unsigned char* vrow = Vh + t2 * 16 * C::RB;
+    for (int db = 0; db < C::DB; ++db) {
+      const bf16x8 a = tr16_pair<D>(vadr[db] + v0);
 #pragma unroll
-      for (int ds = 0; ds < C::DSUB; ++ds) {
-        const bf16x8 a = tr_pair(vrow + voff[ds], vrow + 8 * C::RB + voff[ds]);
-        oacc[ds] = mfma32(a, pp[t2], oacc[ds]);
-      }
+      for (int h = 0; h < 2; ++h) oacc[h][db] = mfma16(a, pp[h], oacc[h][db]);
     }
   };
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
   // One step of the software pipeline: the softmax of half tile g (scores in `sc`) runs on the VALU while the
   // matrix pipe computes the scores of half g+1 (into `sn`) and accumulates the P V product of half g-1
-  // (`pprev`); the three are independent.  Measured on this chip, a SIMD issues one VALU-class instruction
-  // (MFMA included) per ~5 cycles over all its waves, so a 32-cycle MFMA hides about six of them if independent
-  // ones are next in the stream; the softmax needs 4.5 per MFMA at d = 128.  The step consists of
-  // NSLOT slots of {one MFMA, the softmax of 16 / NSLOT scores} in groups of four.  All operand reads of a
-  // group are requested at the start of the previous group, and a group's MFMAs consume their operands in the
-  // reverse of the request order, so one wait per group covers them all; the softmax of a score is spread
-  // over three slots so that no instruction of a slot depends on another one of the same slot.  Fences keep
-  // the compiler from regrouping.  The operands of the first group are requested by the previous step
-  // (`pre`), those of the next step's first group here.
-  constexpr int NS = C::KS, NPV = 2 * C::DSUB, NSLOT = NS + NPV, LEAD = 4, NG = NSLOT / LEAD;
+  // (`pprev`); the three are independent.  A SIMD issues one VALU-class instruction (MFMA included) per ~5 cycles over all its
+  // waves.  The step consists of NSLOT slots of {two MFMAs that share an operand from LDS, the softmax of 16 / NSLOT scores}
+  // in groups of four.  All operand reads of a group are requested at the start of the previous group (of the last but one
+  // where a wave has its SIMD to itself), and a group's MFMAs consume their operands in the reverse of the request order,
+  // so one wait per group covers them all; the softmax of a score is spread over three slots so that no instruction of a
+  // slot depends on another one of the same slot.  Fences keep the compiler from regrouping.  The operands of the first
+  // groups are requested by the previous step (`pre`), those of the next step's first groups here.
+  constexpr int NS = 2 * C::KS, NPV = C::DB, NSLOT = NS + NPV, LEAD = 4, NG = NSLOT / LEAD, PRE = LEAD * C::DIST;
   constexpr int EPS = (16 + NSLOT - 1) / NSLOT;   // most scores per slot
   static_assert(NS == NPV && NSLOT <= 16 && NSLOT % LEAD == 0, "slot layout");
   // the sixteen scores of a lane are spread evenly over the slots: slot i finishes scores [sc0(i), sc0(i + 1))
   auto sc0 = [](int i) constexpr { return i < NSLOT ? 16 * i / NSLOT : 16; };
-  auto k_operand = [&](const unsigned char* Kh, int ks) __attribute__((always_inline)) {
-    return *reinterpret_cast<const bf16x8*>(Kh + koff[ks]);
+  // slot i < NS: scores of key half i % 2, k-step i / 2; slot NS + j: products of head-dim block j
+  // (k0, v0: the half tile's offset in the ring)
+  auto operand = [&](int k0, int v0, int i) __attribute__((always_inline)) {
+    if (i < NS) return *reinterpret_cast<const bf16x8*>(kadr[i >> 1] + k0 + (i & 1) * 16 * C::RB);
+    return tr16_pair<D>(vadr[i - NS] + v0);
   };
-  auto v_operand = [&](const unsigned char* Vh, int j) __attribute__((always_inline)) {
-    const unsigned char* vrow = Vh + (j / C::DSUB) * 16 * C::RB;
-    return tr_pair(vrow + voff[j % C::DSUB], vrow + 8 * C::RB + voff[j % C::DSUB]);
-  };
-  // slot i < NS: score MFMA of k-step i; slot NS + j: product MFMA j
-  auto operand = [&](const unsigned char* Kh, const unsigned char* Vh, int i) __attribute__((always_inline)) {
-    return i < NS ? k_operand(Kh, i) : v_operand(Vh, i - NS);
-  };
-  // (plain C: the compiler must see these reads of MFMA results to place the wait states they need)
-  auto lane_max = [&](const f32x16& v) __attribute__((always_inline)) {
-    float m = fmaxf(fmaxf(v[0], v[1]), v[2]);
+  // score e = 8 h + 4 kh + r of a lane: row 16 h + i16, key 16 kh + 4 lg + r
+  auto step = [&](bool masked, f32x4 (&sc)[4], f32x4 (&sn)[4], bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[PRE],
+                  int Kn, int Vp, int Kn2, int Vn2, int it, int half) __attribute__((always_inline)) {
+    if (LOCAL ? masked : __builtin_expect(masked, 0)) {
+      const bool is_ctx = it < n_ctx_run;
+      const int keyh0 = (is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run) * BN + half * 32;
+      // visible keys of a row: lo < key < lim (indices inside the region)
 #pragma unroll
-    for (int r = 3; r < 15; r += 2) m = fmaxf(fmaxf(m, v[r]), v[r + 1]);
-    return fmaxf(m, v[15]);
-  };
-  auto step = [&](bool masked, f32x16& sc, f32x16& sn, bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
-                  const unsigned char* Kn, const unsigned char* Vp, const unsigned char* Kn2, const unsigned char* Vn2,
-                  bool is_ctx, int keyh0) __attribute__((always_inline)) {
-    if (masked) {
-      // visible keys of this lane's row: lo < key < lim (indices inside the region)
-      int lim, lo = -1;
-      if (is_ctx) {
-        lim = P;
-        if (LOCAL) lo = P + row - W;
-      } else {
-        lim = min(row + 1, R);
-        if (LOCAL) lo = row - W;
-      }
-      lim -= keyh0 + 4 * hi;
-      lo -= keyh0 + 4 * hi;
+      for (int h = 0; h < 2; ++h) {
+        const int row = row0 + 16 * h + i16;
+        int lim, lo = -1;
+        if (is_ctx) {
+          lim = P;
+          if (LOCAL) lo = P + row - W;
+        } else {
+          lim = min(row + 1, R);
+          if (LOCAL) lo = row - W;
+        }
+        lim -= keyh0 + 4 * lg;
+        lo -= keyh0 + 4 * lg;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int k = 8 * (r >> 2) + (r & 3);
-        const bool vis = LOCAL ? (k < lim && k > lo) : (k < lim);
-        sc[r] = vis ? sc[r] : -INFINITY;
+        for (int e = 0; e < 8; ++e) {
+          const int k = 16 * (e >> 2) + (e & 3);
+          const bool vis = LOCAL ? (k < lim && k > lo) : (k < lim);
+          sc[2 * h + (e >> 2)][e & 3] = vis ? sc[2 * h + (e >> 2)][e & 3] : -INFINITY;
+        }
       }
     }
+    auto score = [&](int e) __attribute__((always_inline)) { return sc[e >> 2][e & 3]; };
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 ob[NSLOT];
 #pragma unroll
-    for (int i = 0; i < LEAD; ++i) ob[i] = pre[i];
+    for (int i = 0; i < PRE; ++i) ob[i] = pre[i];
     uint32_t pw[8];
     float tv[16], ev[16];
-    float ls0 = 0.f, ls1 = 0.f;
+    float ls[2] = {0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < sc0(2); ++e) tv[e] = sc[e] * c - m_ref;
+    for (int e = 0; e < sc0(2); ++e) tv[e] = score(e) * c - m_ref[e >> 3];
 #pragma unroll
     for (int e = 0; e < sc0(1); ++e) ev[e] = __builtin_amdgcn_exp2f(tv[e]);
-    bool first_s = true;
+    bool first_s[2] = {true, true};
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
 #pragma unroll
       for (int q = 0; q < LEAD; ++q) {
         const int i = g * LEAD + (LEAD - 1 - q);   // reverse of the request order
-        if (i >= NS) {
-          const int j = i - NS;
-          oacc[j % C::DSUB] = mfma32(ob[i], pprev[j / C::DSUB], oacc[j % C::DSUB]);
-        } else if (first_s) {
-          f32x16 z;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) z[r] = 0.f;
-          sn = mfma32(ob[i], qf[i], z);
-          first_s = false;
-        } else {
-          sn = mfma32(ob[i], qf[i], sn);
-        }
+        auto mm = [&](int h) __attribute__((always_inline)) {
+          if (i >= NS) oacc[h][i - NS] = mfma16(ob[i], pprev[h], oacc[h][i - NS]);
+          else sn[2 * h + (i & 1)] = mfma16(ob[i], qf[h][i >> 1], first_s[i & 1] ? f32x4{0.f, 0.f, 0.f, 0.f} : sn[2 * h + (i & 1)]);
+        };
+        const int n = g * LEAD + q;
+        mm(0);
         if (q == 0) {
-          // request the next group's operands (the next step's first group at the end)
+          // request the operands of a later group (of the next step's first ones at the end)
 #pragma unroll
           for (int n = 0; n < LEAD; ++n) {
-            const int i2 = (g + 1) * LEAD + n;
+            const int i2 = (g + C::DIST) * LEAD + n;
             if (i2 < NSLOT) ob[i2] = operand(Kn, Vp, i2);
-            else pre[n] = operand(Kn2, Vn2, n);
+            else pre[i2 - NSLOT] = operand(Kn2, Vn2, i2 - NSLOT);
           }
         }
 #pragma unroll
         for (int j = 0; j < EPS; ++j) {
-          const int n = g * LEAD + q, e2 = sc0(n + 2) + j, e1 = sc0(n + 1) + j, e = sc0(n) + j;
-          if (e2 < sc0(n + 3)) {
-            tv[e2] = sc[e2] * c - m_ref;
-            asm volatile("" : "+v"(tv[e2]));   // (keeps this slot's softmax work inside the slot)
-          }
+          const int e2 = sc0(n + 2) + j, e1 = sc0(n + 1) + j;
           if (e1 < sc0(n + 2)) {
             ev[e1] = __builtin_amdgcn_exp2f(tv[e1]);
-            asm volatile("" : "+v"(ev[e1]));
+            asm volatile("" : "+v"(ev[e1]));   // (keeps this slot's softmax work inside the slot)
           }
-          if (e >= sc0(n + 1)) {
-          } else if (e & 1) {
-            ls1 += ev[e];
+          if (e2 < sc0(n + 3)) {
+            tv[e2] = score(e2) * c - m_ref[e2 >> 3];
+            asm volatile("" : "+v"(tv[e2]));
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        mm(1);
+        if (i < NS) first_s[i & 1] = false;
+#pragma unroll
+        for (int j = 0; j < EPS; ++j) {
+          const int e = sc0(n) + j;
+          if (e >= sc0(n + 1)) continue;
+          ls[e >> 3] += ev[e];
+          if (e & 1) {
             pw[e >> 1] = pack2_bf16(ev[e - 1], ev[e]);
-            asm volatile("" : "+v"(pw[e >> 1]), "+v"(ls1));
+            asm volatile("" : "+v"(pw[e >> 1]), "+v"(ls[e >> 3]));
           } else {
-            ls0 += ev[e];
-            asm volatile("" : "+v"(ls0));
+            asm volatile("" : "+v"(ls[e >> 3]));
           }
         }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    float ls = ls0 + ls1;
-    // rescale lazily
-    if (__builtin_expect(__any(!(ls < 256.0f)), 0)) {
-      const float mn = fmaxf(m_ref, xor32_max(lane_max(sc)) * c);
-      const float alpha = __builtin_amdgcn_exp2f(m_ref - mn);
-      m_ref = mn;
-      l_sum *= alpha;
+    // The reference of a row's exponentials moves lazily: it is kept until the probabilities of a half tile in some lane sum up
+    // to more than 2^8 (or to infinity).  They are then formed again from the scores, against the row's new maximum.  The products of
+    // the half before are complete and rescaled with the rest.
+    if (__builtin_expect(__any(!(fmaxf(ls[0], ls[1]) < 256.0f)), 0)) {
 #pragma unroll
-      for (int ds = 0; ds < C::DSUB; ++ds)
+      for (int h = 0; h < 2; ++h) {
+        float mx = score(8 * h);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[ds][r] *= alpha;
-      ls = 0.f;
+        for (int e = 1; e < 8; ++e) mx = fmaxf(mx, score(8 * h + e));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float mn = fmaxf(m_ref[h], mx * c);
+        const float alpha = __builtin_amdgcn_exp2f(m_ref[h] - mn);
+        m_ref[h] = mn;
+        l_sum[h] *= alpha;
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const float e0 = __builtin_amdgcn_exp2f(sc[r] * c - m_ref), e1 = __builtin_amdgcn_exp2f(sc[r + 1] * c - m_ref);
-        ls += e0 + e1;
-        pw[r >> 1] = pack2_bf16(e0, e1);
+        for (int db = 0; db < C::DB; ++db) oacc[h][db] *= alpha;
+        ls[h] = 0.f;
+#pragma unroll
+        for (int e = 8 * h; e < 8 * h + 8; e += 2) {
+          const float e0 = __builtin_amdgcn_exp2f(score(e) * c - mn), e1 = __builtin_amdgcn_exp2f(score(e + 1) * c - mn);
+          ls[h] += e0 + e1;
+          pw[e >> 1] = pack2_bf16(e0, e1);
+        }
       }
     }
-    asm volatile("" : "+v"(m_ref));
-    l_sum += ls;
+    asm volatile("" : "+v"(m_ref[0]), "+v"(m_ref[1]));
+    l_sum[0] += ls[0];
+    l_sum[1] += ls[1];
     u32x4 w0 = {pw[0], pw[1], pw[2], pw[3]}, w1 = {pw[4], pw[5], pw[6], pw[7]};
     pcur[0] = __builtin_bit_cast(bf16x8, w0);
     pcur[1] = __builtin_bit_cast(bf16x8, w1);
   };
 
-  // ---- prologue: K0 V0 K1 V1 K2 requested, everything landed and published, scores of the first half
-  if (v_loader) {
-    issue_tile(0, 1);
-    if (b.n_tiles > 1) issue_tile(1, 1);
-  } else {
-    issue_tile(0, 0);
-    if (b.n_tiles > 1) issue_tile(1, 0);
-    if (b.n_tiles > 2) issue_tile(2, 0);
-  }
+  // ---- prologue: K0 V0 K1 V1 K2 requested, everything landed and published, scores of the first half.  The first step multiplies
+  // P = 0 with the second half of V slot 3: whatever is there has to be finite.
+  loader.request(0);
+  loader.request(1);
+  if (!loader.v) loader.request(2);
+  const u32x4 zero4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int i = tid; i < 32 * C::CPR; i += C::NT)
+    *reinterpret_cast<u32x4*>(smem + V_RING + 3 * C::TILE_BYTES + 32 * C::RB + i * 16) = zero4;
   wait_vm<0>();
   __syncthreads();
 
+  // tiles that can hold an invisible (row, key) pair for this wave: the partial last prompt tile, response tiles from the diagonal
+  // (or the end of the sequence) on; windowed runs mask every tile
   const bool always_masked = LOCAL || !wave_valid;
-  const int ctx_masked = (P % BN) ? b.n_ctx - 1 : -1;
-  const int dec_masked = min(row0 + 1, R) / BN;
-  f32x16 sA, sB;
+  const int ctx_masked = (P % BN) && n_ctx_run > 0 ? n_ctx_run - 1 : -1;
+  const int dec_masked = n_ctx_run - b.d0 + min(row0 + 1, R) / BN;
+  f32x4 sA[4], sB[4];
   bf16x8 pA[2], pB[2];
   pB[0] = __builtin_bit_cast(bf16x8, zero4);
   pB[1] = __builtin_bit_cast(bf16x8, zero4);
-  s_half(smem, sA);
-  bf16x8 pre[LEAD];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0, V with P = 0
+  constexpr int T = C::TILE_BYTES, HT = 32 * C::RB;
+  s_half(0, sA);
+  bf16x8 pre[PRE];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0
 #pragma unroll
-  for (int i = 0; i < LEAD; ++i) pre[i] = operand(smem + 32 * C::RB, smem + V_RING + 32 * C::RB, i);
+  for (int i = 0; i < PRE; ++i) pre[i] = operand(HT, 3 * T + HT, i);
 
-  for (int it = 0; it < b.n_tiles; ++it) {
-    // K tile it+3 replaces K tile it-1, V tile it+2 replaces V tile it-2: both were last read before the
-    // barrier that ended tile it-1
-    const bool more = it + 3 < b.n_tiles;
-    bool issued;
-    if (v_loader) {
-      issued = it + 2 < b.n_tiles;
-      if (issued) issue_tile(it + 2, 1);
-    } else {
-      issued = more;
-      if (issued) issue_tile(it + 3, 0);
-    }
-
-    const int slot = it & (NSTAGE - 1), slot_n = (it + 1) & (NSTAGE - 1), slot_p = (it > 0 ? it - 1 : 0) & (NSTAGE - 1);
-    const unsigned char* Kt = smem + slot * C::TILE_BYTES;
-    const unsigned char* Kn = smem + slot_n * C::TILE_BYTES;
-    const unsigned char* Vt = smem + V_RING + slot * C::TILE_BYTES;
-    const unsigned char* Vp = smem + V_RING + slot_p * C::TILE_BYTES + 32 * C::RB;
-    const bool is_ctx = it < n_ctx_run;
-    const int kt = is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run;
-    const int key0 = kt * BN;
-    // tiles that can hold an invisible (row, key) pair for this wave: the partial last prompt tile, response
-    // tiles from the diagonal (or the end of the sequence) on; windowed runs mask every tile
-    const bool masked = always_masked || (is_ctx ? kt == ctx_masked : kt >= dec_masked);
-    step(masked, sA, sB, pB, pA, pre, Kt + 32 * C::RB, Vp, Kn, Vt, is_ctx, key0);
-    step(masked, sB, sA, pA, pB, pre, Kn, Vt, Kn + 32 * C::RB, Vt + 32 * C::RB, is_ctx, key0 + 32);
+  int it = 0;
+  // tile `it` in slot U; false: it was the last one
+  auto tile = [&](auto Uc) __attribute__((always_inline)) -> bool {
+    constexpr int U = decltype(Uc)::value, UN = (U + 1) % NSTAGE, UP = (U + NSTAGE - 1) % NSTAGE;
+    // K tile it+3 replaces K tile it-1, V tile it+2 replaces V tile it-2: both were last read before the barrier that ended
+    // tile it-1
+    const bool issued = loader.request(loader.v ? (U + 2) % NSTAGE : UP);
+    const bool masked = always_masked || it == ctx_masked || it >= dec_masked;
+    step(masked, sA, sB, pB, pA, pre, U * T + HT, UP * T + HT, UN * T, U * T, it, 0);
+    step(masked, sB, sA, pA, pB, pre, UN * T, U * T, UN * T + HT, U * T + HT, it, 1);
     // tiles it+2 (K) and it+1 (V) must have landed; the loads requested at the top of this tile may stay in flight
-    if (issued) wait_vm<IPT>();
+    if (__builtin_expect(issued, 1)) wait_vm<decltype(loader)::IPT>();
     else wait_vm<0>();
     __syncthreads();
+    return ++it < b.n_tiles;
+  };
+  while (true) {
+    if (!tile(std::integral_constant<int, 0>{})) break;
+    if (!tile(std::integral_constant<int, 1>{})) break;
+    if (!tile(std::integral_constant<int, 2>{})) break;
+    if (!tile(std::integral_constant<int, 3>{})) break;
   }
   // the product of the last half tile
-  pv_half(smem + V_RING + ((b.n_tiles - 1) & (NSTAGE - 1)) * C::TILE_BYTES + 32 * C::RB, pB);
+  pv_half(((b.n_tiles - 1) & (NSTAGE - 1)) * T + HT, pB);
 
   // ---- epilogue: lane owns a query row, register r the head-dim column crow(r) of a 32-column block.  Stored from
   // here a row would leave in 16-byte pieces, 32 rows per instruction.  The wave's normalised 32 x D tile goes through
   // LDS instead: its own 32 rows of the K ring (free since the last barrier: only V is read after it; 16-byte chunks
   // XOR-swizzled by the row), read back as whole rows.  Wave-private: no barrier.
-  const float l = xor32_sum(l_sum);
-  const float inv = 1.0f / l;
   unsigned char* ot = smem + wave * 32 * C::RB;
   auto oswz = [](int r) { return D == 96 ? swz<96>(r) : r & (C::CPR - 1); };
 #pragma unroll
-  for (int ds = 0; ds < C::DSUB; ++ds)
+  for (int h = 0; h < 2; ++h) {
+    float l = l_sum[h];
+    l += __shfl_xor(l, 16);
+    l = xor32_sum(l);
+    const float inv = 1.0f / l;
+    const int tr = 16 * h + i16, row = row0 + tr;
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
+    for (int db = 0; db < C::DB; ++db) {
       u32x2 w;
-      w.x = pack2_bf16(oacc[ds][r4 * 4 + 0] * inv, oacc[ds][r4 * 4 + 1] * inv);
-      w.y = pack2_bf16(oacc[ds][r4 * 4 + 2] * inv, oacc[ds][r4 * 4 + 3] * inv);
-      *reinterpret_cast<u32x2*>(ot + l32 * C::RB + (((ds * 4 + r4) ^ oswz(l32)) << 4) + hi * 8) = w;
+      w.x = pack2_bf16(oacc[h][db][0] * inv, oacc[h][db][1] * inv);
+      w.y = pack2_bf16(oacc[h][db][2] * inv, oacc[h][db][3] * inv);
+      *reinterpret_cast<u32x2*>(ot + tr * C::RB + (((db * 2 + (lg >> 1)) ^ oswz(tr)) << 4) + (lg & 1) * 8) = w;
     }
-  if (hi == 0 && row < R) p.lse[(int64_t)head * p.total + b.row_begin + row] = (m_ref + log2f(l)) * LN2;
+    if (lg == 0 && row < R) p.lse[(int64_t)head * p.total + b.row_begin + row] = (m_ref[h] + log2f(l)) * LN2;
+  }
 #pragma unroll
   for (int i = 0; i < C::CPR / 2; ++i) {   // 64 of the tile's 32 CPR chunks per store instruction
     const int tr = (i * 64 + lane) / C::CPR, chunk = (i * 64 + lane) % C::CPR;

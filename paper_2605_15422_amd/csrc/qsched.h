@@ -3,7 +3,9 @@
 // the logical position space (prompt positions 0..P-1, then P + r; Sec. 3.1 and App. F of the paper).
 #pragma once
 #include "common.h"
+#include "dma.h"
 #include "rules.h"
+#include "tiles.h"
 
 namespace dkv {
 
@@ -96,6 +98,73 @@ __device__ __forceinline__ bool tile_active(bool is_ctx, int key0, int rmin, int
   return act;
 }
 
+
+// Global -> LDS loads of the 64-key tiles of a row block's schedule, in order (head dims 64, 96, 128).  Half of the workgroup's waves
+// request the K tiles, half the V tiles; a wave keeps the address of its next tile, the keys of the region from there on and the
+// lane offsets of a full tile, so that a request is a handful of scalar instructions.  Instruction t of a wave covers 1 KB of its
+// rows; lane l lands at LDS chunk position l % CPR of its row and fetches the chunk that the swizzle stores there.  Keys past the
+// end of a region re-read the last key: their scores are masked like any invisible key.
+template <int D, int NW>
+struct TileLoader {
+  static constexpr int BN = 64, CPR = D / 8, TILE_BYTES = BN * 2 * D;
+  static constexpr int LW = NW / 2;                            // waves per tensor
+  static constexpr int IPT = TILE_BYTES / 1024 / LW;           // load instructions per wave and tile
+  static constexpr int RPI = 1024 / (2 * D);                   // whole rows per instruction (not at head dim 96)
+  static constexpr int STEP = kSplitRow<D> ? 1024 : LW * 1024;   // bytes from one instruction of a wave to the next
+  static_assert(IPT >= 1 && TILE_BYTES % (1024 * LW) == 0, "tile must split evenly over the waves");
+  static_assert(!kSplitRow<D> || (IPT % 3 == 0 && BN == LW * (IPT / 3) * kSplitRows<D>), "whole rows per wave");
+  const AttnParams& p;
+  const QBlock& b;
+  const int lane, lwave;
+  const bool v;                // this wave requests V tiles
+  const uint32_t lds;
+  uint64_t ptr = 0;
+  int keys = 0, tsb = 0, left;   // keys of the region from the next tile on, bytes per token, tiles to request
+  uint32_t voff[IPT];
+
+  // the V ring lies v_ring bytes behind the K ring at `smem`
+  __device__ __forceinline__ TileLoader(const AttnParams& p_, const QBlock& b_, int wave, int lane_, const unsigned char* smem, int v_ring)
+      : p(p_), b(b_), lane(lane_), lwave(wave % LW), v(wave >= LW),
+        lds((uint32_t)reinterpret_cast<uintptr_t>(smem) + (wave >= LW ? v_ring : 0) + wave % LW * (kSplitRow<D> ? IPT * 1024 : 1024)),
+        left(b_.n_tiles) {
+    if (b.c0 < b.n_ctx) enter(p.kc, p.vc, (int64_t)b.ctx_off + b.c0 * BN, b.P - b.c0 * BN);
+  }
+  __device__ __forceinline__ int row(int t) const {
+    // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows)
+    if constexpr (kSplitRow<D>) return lwave * (IPT / 3) * kSplitRows<D> + split_row<D>(t, lane);
+    else return lwave * RPI + lane / CPR + t * LW * RPI;
+  }
+  __device__ __forceinline__ int col(int t) const {
+    return ((kSplitRow<D> ? split_pos<D>(t, lane) : lane % CPR) ^ swz16<D>(row(t))) * 16;
+  }
+  __device__ __forceinline__ void enter(const TView& tk, const TView& tv, int64_t first, int n) {
+    const TView& x = v ? tv : tk;
+    tsb = (int)x.ts * 2;
+    keys = n;
+    ptr = reinterpret_cast<uint64_t>(uniform_ptr(x.ptr + first * x.ts + (int64_t)b.hk * x.hs));
+#pragma unroll
+    for (int t = 0; t < IPT; ++t) voff[t] = (uint32_t)(__umul24((unsigned)row(t), (unsigned)tsb) + col(t));
+  }
+  // requests this wave's next tile into ring slot `slot`; false: there is none
+  __device__ __forceinline__ bool request(uint32_t slot) {
+    if (left == 0) return false;
+    --left;
+    if (__builtin_expect(keys <= 0, 0)) enter(p.kd, p.vd, (int64_t)b.row_begin + b.d0 * BN, b.R - b.d0 * BN);
+    const void* const base = reinterpret_cast<const void*>(ptr);
+    const uint32_t dst = lds + slot * TILE_BYTES;
+    if (__builtin_expect(keys >= BN, 1)) {
+      static_for<IPT>([&](auto Tc) __attribute__((always_inline)) { dma16_at<decltype(Tc)::value * STEP>(base, voff[decltype(Tc)::value], dst); });
+    } else {
+      static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(Tc)::value;
+        dma16_at<t * STEP>(base, (uint32_t)(__umul24((unsigned)min(row(t), keys - 1), (unsigned)tsb) + col(t)), dst);
+      });
+    }
+    ptr += (uint64_t)(uint32_t)tsb * BN;
+    keys -= BN;
+    return true;
+  }
+};
 
 // Head packing of one workgroup that owns `nst` 32-row subtiles (rules.h)
 static inline void fill_packing(AttnParams& p, int nst) {

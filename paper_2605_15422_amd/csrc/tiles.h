@@ -73,4 +73,37 @@ __device__ __forceinline__ bf16x8 tr_pair(const unsigned char* a0, const unsigne
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// ---- tiles read by the 16x16x32 MFMA (head dims 64, 96, 128).  A row operand is row l % 16, 64-byte k-step ks, of which lane group
+// g = l / 16 takes chunk kgrp16<D>(g) (both operands of a product alike); a transpose read takes rows 4 g .. 4 g + 3 (+ 16) and 16
+// columns.  A 16-byte read is served in groups of sixteen lanes {0-3, 12-15, 20-23, 24-27}, {4-11, 16-19, 28-31}, + 32; an 8-byte
+// transpose read in halves of the wave.  This swizzle and choice of chunks keeps both free of bank conflicts (all rows of eight
+// consecutive ones on different pairs of chunks for the latter; checked by enumeration).
+template <int D>
+__device__ __forceinline__ int swz16(int row) {
+  static_assert(D == 64 || D == 96 || D == 128, "");
+  const int pair = D == 128 ? row & 7 : D == 64 ? (row >> 1) & 3 : (row >> 2) & 1;
+  return 2 * pair | ((row >> 3) & 1);
+}
+template <int D>
+__device__ __forceinline__ int kgrp16(int g) {
+  return D == 96 ? (g == 0 ? 0 : g == 1 ? 3 : g - 1) : ((g & 1) << 1) | (g >> 1);
+}
+// byte offset of this lane's row operand of k-step ks, rows 0-15
+template <int D>
+__device__ __forceinline__ int frag16_off(int lane, int ks) {
+  const int row = lane & 15;
+  return row * (2 * D) + (((4 * ks + kgrp16<D>(lane >> 4)) ^ swz16<D>(row)) << 4);
+}
+// byte offset of this lane's transpose read of rows 0-15, columns 16 db .. 16 db + 15
+template <int D>
+__device__ __forceinline__ int tr16_off(int lane, int db) {
+  const int row = 4 * (lane >> 4) + ((lane & 15) >> 2), col = 16 * db + (lane & 3) * 4;
+  return row * (2 * D) + (((col >> 3) ^ swz16<D>(row)) << 4) + ((col >> 2) & 1) * 8;
+}
+// transpose reads of rows 0-15 and 16-31 -> the 32-deep operand of a 16-column block
+template <int D>
+__device__ __forceinline__ bf16x8 tr16_pair(const unsigned char* a) {
+  return tr_pair(a, a + 16 * 2 * D);
+}
+
 }  // namespace dkv
