@@ -41,12 +41,10 @@ struct F2Cfg {
   static constexpr int RB = 2 * D;                 // row bytes
   static constexpr int CPR = D / 8;                // 16-byte chunks per row
   static constexpr int TILE_BYTES = BN * RB;
-  static constexpr bool ALONE = NW == 4 && D != 64;   // one wave per SIMD (the rings leave no room for a second workgroup)
-  static constexpr int DIST = ALONE ? 2 : 1;          // groups of slots from an operand's request to its use
 };
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   using C = F2Cfg<D, NW>;
   constexpr int BN = C::BN;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
@@ -124,12 +122,11 @@ __global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_ker
   // matrix pipe computes the scores of half g+1 (into `sn`) and accumulates the P V product of half g-1
   // (`pprev`); the three are independent.  A SIMD issues one VALU-class instruction (MFMA included) per ~5 cycles over all its
   // waves.  The step consists of NSLOT slots of {two MFMAs that share an operand from LDS, the softmax of 16 / NSLOT scores}
-  // in groups of four.  All operand reads of a group are requested at the start of the previous group (of the last but one
-  // where a wave has its SIMD to itself), and a group's MFMAs consume their operands in the reverse of the request order,
-  // so one wait per group covers them all; the softmax of a score is spread over three slots so that no instruction of a
+  // in groups of four.  All operand reads of a group are requested at the start of the previous group, and a group's MFMAs consume their operands
+  // in the reverse of the request order, so one wait per group covers them all; the softmax of a score is spread over three slots so that no instruction of a
   // slot depends on another one of the same slot.  Fences keep the compiler from regrouping.  The operands of the first
-  // groups are requested by the previous step (`pre`), those of the next step's first groups here.
-  constexpr int NS = 2 * C::KS, NPV = C::DB, NSLOT = NS + NPV, LEAD = 4, NG = NSLOT / LEAD, PRE = LEAD * C::DIST;
+  // group are requested by the previous step (`pre`), those of the next step's first group here.
+  constexpr int NS = 2 * C::KS, NPV = C::DB, NSLOT = NS + NPV, LEAD = 4, NG = NSLOT / LEAD;
   constexpr int EPS = (16 + NSLOT - 1) / NSLOT;   // most scores per slot
   static_assert(NS == NPV && NSLOT <= 16 && NSLOT % LEAD == 0, "slot layout");
   // the sixteen scores of a lane are spread evenly over the slots: slot i finishes scores [sc0(i), sc0(i + 1))
@@ -141,7 +138,7 @@ __global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_ker
     return tr16_pair<D>(vadr[i - NS] + v0);
   };
   // score e = 8 h + 4 kh + r of a lane: row 16 h + i16, key 16 kh + 4 lg + r
-  auto step = [&](bool masked, f32x4 (&sc)[4], f32x4 (&sn)[4], bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[PRE],
+  auto step = [&](bool masked, f32x4 (&sc)[4], f32x4 (&sn)[4], bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
                   int Kn, int Vp, int Kn2, int Vn2, int it, int half) __attribute__((always_inline)) {
     if (LOCAL ? masked : __builtin_expect(masked, 0)) {
       const bool is_ctx = it < n_ctx_run;
@@ -172,7 +169,7 @@ __global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_ker
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 ob[NSLOT];
 #pragma unroll
-    for (int i = 0; i < PRE; ++i) ob[i] = pre[i];
+    for (int i = 0; i < LEAD; ++i) ob[i] = pre[i];
     uint32_t pw[8];
     float tv[16], ev[16];
     float ls[2] = {0.f, 0.f};
@@ -193,12 +190,12 @@ __global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_ker
         const int n = g * LEAD + q;
         mm(0);
         if (q == 0) {
-          // request the operands of a later group (of the next step's first ones at the end)
+          // request the next group's operands (the next step's first group at the end)
 #pragma unroll
           for (int n = 0; n < LEAD; ++n) {
-            const int i2 = (g + C::DIST) * LEAD + n;
+            const int i2 = (g + 1) * LEAD + n;
             if (i2 < NSLOT) ob[i2] = operand(Kn, Vp, i2);
-            else pre[i2 - NSLOT] = operand(Kn2, Vn2, i2 - NSLOT);
+            else pre[n] = operand(Kn2, Vn2, n);
           }
         }
 #pragma unroll
@@ -288,9 +285,9 @@ __global__ __launch_bounds__(NW * 64, F2Cfg<D, NW>::ALONE ? 1 : 2) void fwd2_ker
   pB[1] = __builtin_bit_cast(bf16x8, zero4);
   constexpr int T = C::TILE_BYTES, HT = 32 * C::RB;
   s_half(0, sA);
-  bf16x8 pre[PRE];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0
+  bf16x8 pre[LEAD];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0
 #pragma unroll
-  for (int i = 0; i < PRE; ++i) pre[i] = operand(HT, 3 * T + HT, i);
+  for (int i = 0; i < LEAD; ++i) pre[i] = operand(HT, 3 * T + HT, i);
 
   int it = 0;
   // tile `it` in slot U; false: it was the last one
