@@ -95,7 +95,7 @@ __device__ __forceinline__ float dot8_bf16(bf16x8 a, bf16x8 b) {
 template <int N>
 __device__ __forceinline__ float butterfly_sum(float (&t)[N]) {
   constexpr int top = N <= 4 ? 2 : N <= 8 ? 4 : 8;
-  static_assert(N > 2 && N <= 16, "");
+  static_assert(N >= 2 && N <= 16, "");
 #pragma unroll
   for (int h = top; h >= 1; h >>= 1)
 #pragma unroll

@@ -50,6 +50,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
   QBlock b;
   if (!decode_qblock<BN>(p, b, blockIdx.x, gridDim.x)) return;
+  make_uniform(b);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, lg = lane >> 4;
@@ -59,6 +60,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   const int head = b.hk * p.G + b.hc * p.GP + wave / p.RSH;
   const int row0 = b.blk_row0 + (wave % p.RSH) * 32;
   const bool wave_valid = row0 < R;
+
+  // (the first tiles are requested ahead of Q: one latency for both)
+  constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
+  constexpr int V_RING = NSTAGE * C::TILE_BYTES;
+  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
+  loader.request(0);
+  loader.request(1);
 
   bf16x8 qf[2][C::KS];   // rows row0 + i16 and row0 + 16 + i16
   {
@@ -82,8 +90,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     for (int db = 0; db < C::DB; ++db) oacc[h][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_ref[2] = {NEG_BIG, NEG_BIG}, l_sum[2] = {0.f, 0.f};
 
-  constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
-  constexpr int V_RING = NSTAGE * C::TILE_BYTES;
   // ---- per-lane LDS addresses in slot 0.  The loop is unrolled over the slots, so that all others are immediate offsets.
   const unsigned char* kadr[C::KS];   // K operand of k-step ks
 #pragma unroll
@@ -92,7 +98,6 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
 #pragma unroll
   for (int db = 0; db < C::DB; ++db) vadr[db] = smem + V_RING + tr16_off<D>(lane, db);
 
-  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
   const int n_ctx_run = b.n_ctx - b.c0;
 
   // ---- the three pieces of work of a 32-key half tile
@@ -262,16 +267,14 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     pcur[1] = __builtin_bit_cast(bf16x8, w1);
   };
 
-  // ---- prologue: K0 V0 K1 V1 K2 requested, everything landed and published, scores of the first half.  The first step multiplies
+  // ---- prologue: K0 V0 K1 V1 landed and published, K2 requested, scores of the first half.  The first step multiplies
   // P = 0 with the second half of V slot 3: whatever is there has to be finite.
-  loader.request(0);
-  loader.request(1);
-  if (!loader.v) loader.request(2);
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = tid; i < 32 * C::CPR; i += C::NT)
     *reinterpret_cast<u32x4*>(smem + V_RING + 3 * C::TILE_BYTES + 32 * C::RB + i * 16) = zero4;
   wait_vm<0>();
+  if (!loader.v) loader.request(2);
   __syncthreads();
 
   // tiles that can hold an invisible (row, key) pair for this wave: the partial last prompt tile, response tiles from the diagonal

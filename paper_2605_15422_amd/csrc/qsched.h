@@ -99,6 +99,19 @@ __device__ __forceinline__ bool tile_active(bool is_ctx, int key0, int rmin, int
 }
 
 
+// The offsets of a block are loaded through the vector path: make their uniformity explicit.
+__device__ __forceinline__ void make_uniform(QBlock& b) {
+  b.row_begin = __builtin_amdgcn_readfirstlane(b.row_begin);
+  b.R = __builtin_amdgcn_readfirstlane(b.R);
+  b.P = __builtin_amdgcn_readfirstlane(b.P);
+  b.ctx_off = __builtin_amdgcn_readfirstlane(b.ctx_off);
+  b.c0 = __builtin_amdgcn_readfirstlane(b.c0);
+  b.n_ctx = __builtin_amdgcn_readfirstlane(b.n_ctx);
+  b.d0 = __builtin_amdgcn_readfirstlane(b.d0);
+  b.n_dec = __builtin_amdgcn_readfirstlane(b.n_dec);
+  b.n_tiles = __builtin_amdgcn_readfirstlane(b.n_tiles);
+}
+
 // Global -> LDS loads of the 64-key tiles of a row block's schedule, in order (head dims 64, 96, 128).  Half of the workgroup's waves
 // request the K tiles, half the V tiles; a wave keeps the address of its next tile, the keys of the region from there on and the
 // lane offsets of a full tile, so that a request is a handful of scalar instructions.  Instruction t of a wave covers 1 KB of its
@@ -111,23 +124,36 @@ struct TileLoader {
   static constexpr int IPT = TILE_BYTES / 1024 / LW;           // load instructions per wave and tile
   static constexpr int RPI = 1024 / (2 * D);                   // whole rows per instruction (not at head dim 96)
   static constexpr int STEP = kSplitRow<D> ? 1024 : LW * 1024;   // bytes from one instruction of a wave to the next
+  // the lane offsets repeat after NV instructions (the swizzle after 16 rows), GROUP rows further on
+  static constexpr int NV = kSplitRow<D> ? 3 : LW * RPI % 16 == 0 ? 1 : 2, GROUP = kSplitRow<D> ? 16 : NV * LW * RPI;
+  static_assert(IPT % NV == 0 && GROUP % 16 == 0, "");
   static_assert(IPT >= 1 && TILE_BYTES % (1024 * LW) == 0, "tile must split evenly over the waves");
   static_assert(!kSplitRow<D> || (IPT % 3 == 0 && BN == LW * (IPT / 3) * kSplitRows<D>), "whole rows per wave");
-  const AttnParams& p;
-  const QBlock& b;
   const int lane, lwave;
   const bool v;                // this wave requests V tiles
-  const uint32_t lds;
-  uint64_t ptr = 0;
-  int keys = 0, tsb = 0, left;   // keys of the region from the next tile on, bytes per token, tiles to request
-  uint32_t voff[IPT];
+  uint32_t lds;
+  uint64_t ptr, own_ptr;       // next tile; first one of the response
+  int keys, tsb, left;         // keys of the region from the next tile on, bytes per token, tiles to request
+  int own_keys, own_tsb;
+  uint32_t voff[NV];
 
   // the V ring lies v_ring bytes behind the K ring at `smem`
-  __device__ __forceinline__ TileLoader(const AttnParams& p_, const QBlock& b_, int wave, int lane_, const unsigned char* smem, int v_ring)
-      : p(p_), b(b_), lane(lane_), lwave(wave % LW), v(wave >= LW),
-        lds((uint32_t)reinterpret_cast<uintptr_t>(smem) + (wave >= LW ? v_ring : 0) + wave % LW * (kSplitRow<D> ? IPT * 1024 : 1024)),
-        left(b_.n_tiles) {
-    if (b.c0 < b.n_ctx) enter(p.kc, p.vc, (int64_t)b.ctx_off + b.c0 * BN, b.P - b.c0 * BN);
+  __device__ __forceinline__ TileLoader(const AttnParams& p, const QBlock& b, int wave, int lane_, const unsigned char* smem, int v_ring)
+      : lane(lane_), lwave(wave % LW), v(wave >= LW),
+        left(b.n_tiles) {
+    lds = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(smem) + (v ? v_ring : 0) +
+                                         lwave * (kSplitRow<D> ? IPT * 1024 : 1024));
+    const TView own = v ? p.vd : p.kd, ctx = v ? p.vc : p.kc;
+    own_ptr = first_tile(own, (int64_t)b.row_begin + b.d0 * BN, b.hk);
+    own_tsb = (int)own.ts * 2;
+    own_keys = b.R - b.d0 * BN;
+    ptr = first_tile(ctx, (int64_t)b.ctx_off + b.c0 * BN, b.hk);
+    tsb = (int)ctx.ts * 2;
+    keys = b.c0 < b.n_ctx ? b.P - b.c0 * BN : 0;
+    lane_offsets();
+  }
+  __device__ __forceinline__ static uint64_t first_tile(const TView& x, int64_t row, int hk) {
+    return reinterpret_cast<uint64_t>(uniform_ptr(x.ptr + row * x.ts + (int64_t)hk * x.hs));
   }
   __device__ __forceinline__ int row(int t) const {
     // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows)
@@ -137,27 +163,33 @@ struct TileLoader {
   __device__ __forceinline__ int col(int t) const {
     return ((kSplitRow<D> ? split_pos<D>(t, lane) : lane % CPR) ^ swz16<D>(row(t))) * 16;
   }
-  __device__ __forceinline__ void enter(const TView& tk, const TView& tv, int64_t first, int n) {
-    const TView& x = v ? tv : tk;
-    tsb = (int)x.ts * 2;
-    keys = n;
-    ptr = reinterpret_cast<uint64_t>(uniform_ptr(x.ptr + first * x.ts + (int64_t)b.hk * x.hs));
+  __device__ __forceinline__ void lane_offsets() {
 #pragma unroll
-    for (int t = 0; t < IPT; ++t) voff[t] = (uint32_t)(__umul24((unsigned)row(t), (unsigned)tsb) + col(t));
+    for (int t = 0; t < NV; ++t) voff[t] = (uint32_t)(__umul24((unsigned)row(t), (unsigned)tsb) + col(t));
   }
   // requests this wave's next tile into ring slot `slot`; false: there is none
   __device__ __forceinline__ bool request(uint32_t slot) {
     if (left == 0) return false;
     --left;
-    if (__builtin_expect(keys <= 0, 0)) enter(p.kd, p.vd, (int64_t)b.row_begin + b.d0 * BN, b.R - b.d0 * BN);
-    const void* const base = reinterpret_cast<const void*>(ptr);
-    const uint32_t dst = lds + slot * TILE_BYTES;
+    if (__builtin_expect(keys <= 0, 0)) {
+      ptr = own_ptr;
+      tsb = own_tsb;
+      keys = own_keys;
+      lane_offsets();
+    }
+    // (uniform, but not always in scalar registers, which the requests need)
+    const uint64_t base = reinterpret_cast<uint64_t>(uniform_ptr(reinterpret_cast<const u16*>(ptr)));
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds + slot * TILE_BYTES);
+    const int step = __builtin_amdgcn_readfirstlane(GROUP * tsb);
     if (__builtin_expect(keys >= BN, 1)) {
-      static_for<IPT>([&](auto Tc) __attribute__((always_inline)) { dma16_at<decltype(Tc)::value * STEP>(base, voff[decltype(Tc)::value], dst); });
+      static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
+        constexpr int t = decltype(Tc)::value;
+        dma16_at<t * STEP>(reinterpret_cast<const void*>(base + (uint32_t)(t / NV * step)), voff[t % NV], dst);
+      });
     } else {
       static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
         constexpr int t = decltype(Tc)::value;
-        dma16_at<t * STEP>(base, (uint32_t)(__umul24((unsigned)min(row(t), keys - 1), (unsigned)tsb) + col(t)), dst);
+        dma16_at<t * STEP>(reinterpret_cast<const void*>(base), (uint32_t)(__umul24((unsigned)min(row(t), keys - 1), (unsigned)tsb) + col(t)), dst);
       });
     }
     ptr += (uint64_t)(uint32_t)tsb * BN;
