@@ -9,9 +9,13 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdualkv.so")
-SOURCES = ["api.hip", "fwd2.hip", "dq2.hip", "dkdv4.hip", "fwd256.hip", "dq256.hip", "dkdv256.hip", "dkdv512.hip", "dq512.hip", "fwd512.hip", "aux.hip"]
+SOURCES = ["api.hip", "fwd2.hip", "dq2.hip", "dkdv4.hip", "dkdvw.hip", "fwd256.hip", "dq256.hip", "dkdv256.hip", "dkdv512.hip", "dq512.hip", "fwd512.hip", "aux.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-munsafe-fp-atomics",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-Wno-inline-asm"]
+
+# Register allocation of the wide dK/dV kernel: its accumulators and operands fill the register file, and in the allocator's default
+# order they are moved between registers (30 moves a step at head dim 128) or spilled inside the loop.
+FILE_FLAGS = {"dkdvw.hip": ["-mllvm", "-greedy-regclass-priority-trumps-globalness=1"]}
 
 
 def _hipcc() -> str:
@@ -29,7 +33,7 @@ def build(verbose: bool = True, extra_flags=()) -> str:
 
     def compile_one(src):
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
-        cmd = [hipcc, *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, *FILE_FLAGS.get(src, ()), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))

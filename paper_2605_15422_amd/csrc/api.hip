@@ -118,11 +118,21 @@ dkv::rules::PromptTiles prompt_tiles(const dualkv_shape* s, const Groups& g) {
 }
 
 // parts of a prompt tile to launch (with a window a tile sees few rows of each sequence: whole sequences, as many as fill the chip)
-int ctx_parts(const AttnParams& p, const dualkv_shape* s, const Groups& g) {
+// and whether the kernel of which two workgroups share a CU takes the call's dK/dV
+struct CtxParts {
+  int n;
+  bool pair;
+};
+CtxParts ctx_parts(const AttnParams& p, const dualkv_shape* s, const Groups& g) {
   dkv::rules::PromptTiles c = prompt_tiles(s, g);
-  if (s->window > 0) return dkv::rules::most_parts(c);
+  if (s->window > 0) return {dkv::rules::most_parts(c), false};
   c.shared = dkv::dkdv4_dq_room(p, s->head_dim);
-  return dkv::rules::prompt_parts(c);
+  const int n = dkv::rules::prompt_parts(c);
+  if (s->head_dim == 96 || s->head_dim == 128) {
+    const int pair = dkv::rules::prompt_parts(c, true);
+    if (dkv::rules::pair_tiles(c, n, pair)) return {pair, true};
+  }
+  return {n, false};
 }
 
 struct BwdWorkspace {
@@ -178,7 +188,8 @@ hipError_t run_dq(const AttnParams& p, int d, hipStream_t st) {
   if (d <= 256) return dkv::launch_dq256(p, d, st);
   return dkv::launch_dq512(p, st);
 }
-hipError_t run_dkdv(const AttnParams& p, int d, hipStream_t st) {
+hipError_t run_dkdv(const AttnParams& p, int d, bool pair, hipStream_t st) {
+  if (pair) return dkv::launch_dkdvw(p, d, st);
   if (d <= 128) return dkv::launch_dkdv4(p, d, st);
   if (d <= 256) return dkv::launch_dkdv256(p, d, st);
   return dkv::launch_dkdv512(p, st);
@@ -190,22 +201,22 @@ hipError_t run_dkdv(const AttnParams& p, int d, hipStream_t st) {
 // at d = 256, window 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 2 to 3 %).  Calls that leave CUs idle run both kernels side by side
 // behind the preprocess (dkdv4.hip).  The preprocess also serves calls without dQ, and calls whose dQ overwrites what the
 // dK/dV kernel has to read (dQ is written last then).
-hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, hipStream_t st) {
+hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, bool pair, hipStream_t st) {
   const bool do_dq = rows > 0 && !(flags & DUALKV_FLAG_SKIP_DQ), do_dkdv = !(flags & DUALKV_FLAG_SKIP_DKDV);
   const bool do_pre = rows > 0 && !(flags & DUALKV_FLAG_SKIP_PRE);
   hipError_t e = hipSuccess;
   if (do_pre && do_dq && !overlap(p.dq, p.q, rows, p.H, d) && !overlap(p.dq, p.dout, rows, p.H, d) &&
       !overlap(p.dq, p.o, rows, p.H, d)) {
-    if (do_dkdv && dkv::dkdv4_dq_fits(p, d)) {
+    if (do_dkdv && !pair && dkv::dkdv4_dq_fits(p, d)) {
       if ((e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
       return dkv::launch_dkdv4_dq(p, d, st);
     }
     if ((e = run_dq(p, d, st)) != hipSuccess) return e;
-    return do_dkdv ? run_dkdv(p, d, st) : hipSuccess;
+    return do_dkdv ? run_dkdv(p, d, pair, st) : hipSuccess;
   }
   if (do_pre && (e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
   p.o.ptr = nullptr;   // the row statistics are given
-  if (do_dkdv && (e = run_dkdv(p, d, st)) != hipSuccess) return e;
+  if (do_dkdv && (e = run_dkdv(p, d, pair, st)) != hipSuccess) return e;
   return do_dq ? run_dq(p, d, st) : hipSuccess;
 }
 
@@ -362,7 +373,7 @@ int ctx_bwd_impl(const dualkv_shape* shape, dualkv_tin do_c, dualkv_tin o_c, con
   p.dvec = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.dvec_off);
   p.lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.lse2_off);
   if ((rc = bind_ctx_groups(p, shape, groups, static_cast<char*>(workspace) + w.total, st))) return rc;
-  return hip_rc(run_bwd(p, shape->flags, P, d, st));
+  return hip_rc(run_bwd(p, shape->flags, P, d, false, st));
 }
 
 
@@ -422,14 +433,15 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
   if ((rc = bind_groups(p, groups, shape->n_seqs, static_cast<char*>(workspace) + w.seqctx_off, st))) return rc;
 
   const bool scratch = !accum && w.acc_bytes > 0;
+  const CtxParts parts = ctx_parts(p, shape, groups);   // (one part where there are no fp32 sums to add to)
   if (accum) {
     p.dkc_acc = dk_c_acc32;
     p.dvc_acc = dv_c_acc32;
-    p.n_split = ctx_parts(p, shape, groups);
+    p.n_split = parts.n;
   } else if (scratch) {
     p.dkc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off);
     p.dvc_acc = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.acc_off + w.acc_bytes);
-    p.n_split = ctx_parts(p, shape, groups);
+    p.n_split = parts.n;
     // zero-initialise the fp32 scratch (Alg. 1, "Require: zero-initialized")
     if (!(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
       if ((rc = hip_rc(dkv::launch_clear2_f32(p.dkc_acc, p.dvc_acc, n_acc, st)))) return rc;
@@ -438,7 +450,7 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
     p.dkc = view(dk_c);
     p.dvc = view(dv_c);
   }
-  if ((rc = hip_rc(run_bwd(p, shape->flags, T, d, st)))) return rc;
+  if ((rc = hip_rc(run_bwd(p, shape->flags, T, d, parts.pair, st)))) return rc;
   if (scratch && !(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
     // Stage 2 (Alg. 2): cast the accumulated prompt gradients once
     if ((rc = hip_rc(dkv::launch_convert2_ctx(p.dkc_acc, view(dk_c), p.dvc_acc, view(dv_c), P, p.Hk, d, st)))) return rc;

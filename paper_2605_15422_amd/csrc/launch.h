@@ -11,6 +11,8 @@ hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st);
 // tuned backward kernels for head dims 64 / 96 / 128
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
+// dK/dV of Call 2 at head dims 96 and 128 without a window, two workgroups a CU
+hipError_t launch_dkdvw(const AttnParams& p, int head_dim, hipStream_t st);
 // both in one launch (row statistics given), for calls with few workgroups: up to dkdv4_dq_room prompt workgroups
 int64_t dkdv4_dq_room(AttnParams p, int head_dim);
 bool dkdv4_dq_fits(const AttnParams& p, int head_dim);

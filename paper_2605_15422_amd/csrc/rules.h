@@ -39,29 +39,66 @@ inline int most_parts(const PromptTiles& c) {
 // Over 900 drawn calls the backward of Call 2 takes 0.71 of its time with most_parts parts of whole sequences and two launches
 // (7 of them 1.03 to 1.24 times longer); with most_parts parts 0.76; kStart 12 to 40 differ by 1 %.
 constexpr int kStart = 30, kMaxParts = 32;
-inline int prompt_parts(const PromptTiles& c) {
-  const int most = most_parts(c);
-  if (most == 1 || c.total_resp == 0) return most;
+
+struct PromptWork {
+  double seqs, one;     // sequences of a group; intervals of one
+  double own, longest;  // all response tiles; the longest one
+};
+inline double ceil_div(double a, double b) { return (double)(int64_t)((a + b - 1) / b); }
+inline PromptWork prompt_work(const PromptTiles& c) {
+  PromptWork w;
   const double mean = (double)c.total_resp / c.n_seqs;
-  auto ceil_div = [](double a, double b) { return (double)(int64_t)((a + b - 1) / b); };
-  const double seqs = ceil_div(c.n_seqs, c.n_groups), one = ceil_div(mean, c.row_block) * c.G;   // sequences; intervals of one
+  w.seqs = ceil_div(c.n_seqs, c.n_groups);
+  w.one = ceil_div(mean, c.row_block) * c.G;
   const double resp_tiles = ceil_div(mean, c.key_tile);
   // the tiles of a response see from all of its row blocks down to the last tile's
-  const double own = resp_tiles * c.n_seqs * c.kv_heads * (one * (resp_tiles + 1) / (2 * resp_tiles) + kStart);
-  const double longest = ceil_div(c.max_resp, c.row_block) * c.G + kStart;
+  w.own = resp_tiles * c.n_seqs * c.kv_heads * (w.one * (resp_tiles + 1) / (2 * resp_tiles) + kStart);
+  w.longest = ceil_div(c.max_resp, c.row_block) * c.G + kStart;
+  return w;
+}
+// intervals of one of n parts of a prompt tile
+inline double part_work(const PromptTiles& c, const PromptWork& w, int n) {
+  return (c.whole_seqs ? ceil_div(w.seqs, n) * w.one : ceil_div(w.seqs * w.one, n)) + kStart;
+}
+// Time of all tiles with n parts.  `pair`: the kernel of which two workgroups share a CU (kPair: the time of an interval of each
+// of them then, kAlone: of one that has the CU to itself).
+constexpr double kPair = 1.72, kAlone = 1.27;
+inline double parts_time(const PromptTiles& c, const PromptWork& w, int n, bool pair) {
+  const double part = part_work(c, w, n);
+  const int64_t all = c.tiles * n;
+  if (pair) {
+    const int64_t full = all / (2 * kCus), rest = all % (2 * kCus);
+    const double last = rest == 0 ? 0 : rest <= kCus ? kAlone * part : kPair * part;
+    return std::max({(all * part + w.own) * (kPair / 2) / kCus, full * kPair * part + last, full * kPair * part + kPair * w.longest});
+  }
+  return std::max({(all * part + w.own) / kCus, (all + kCus - 1) / kCus * part, all / kCus * part + w.longest});
+}
+
+inline int prompt_parts(const PromptTiles& c, bool pair = false) {
+  const int most = most_parts(c);
+  if (most == 1 || c.total_resp == 0) return most;
+  const PromptWork w = prompt_work(c);
   const double apart = 10 + ((double)c.ctx_len + c.max_resp) / 53;   // (64 keys of dQ: 1.2 intervals)
   auto time = [&](int n) {
-    const double part = (c.whole_seqs ? ceil_div(seqs, n) * one : ceil_div(seqs * one, n)) + kStart;
-    const int64_t all = c.tiles * n;
-    const double t = std::max({(all * part + own) / kCus, (all + kCus - 1) / kCus * part, all / kCus * part + longest});
-    return c.shared >= c.tiles && all > c.shared ? t + apart : t;
+    const double t = parts_time(c, w, n, pair);
+    return c.shared >= c.tiles && c.tiles * n > c.shared ? t + apart : t;
   };
   // (a part takes at least a sequence or a row block)
-  const int limit = (int)std::min<double>(most <= 2 ? most : kMaxParts, c.whole_seqs ? seqs : seqs * one / c.G);
+  const int limit = (int)std::min<double>(most <= 2 ? most : kMaxParts, c.whole_seqs ? w.seqs : w.seqs * w.one / c.G);
   int best = 1;
   for (int n = 2; n <= limit; ++n)
     if (time(n) < 0.98 * time(best)) best = n;
   return best;
+}
+
+// dK/dV at head dims 96 and 128, no window, one prompt: two workgroups a CU (dkdvw.hip) with `pair_parts` parts, or one with `parts`?
+// Two get more done on a full chip but each is slower, and a long response tile that starts behind the prompt tiles is then late.  So
+// where three quarters of the work are prompt tiles and the model says that they fill their rounds.
+inline bool pair_tiles(const PromptTiles& c, int parts, int pair_parts) {
+  if (c.total_resp == 0 || c.tiles == 0 || c.n_groups > 1 || c.tiles * parts <= c.shared) return false;
+  const PromptWork w = prompt_work(c);
+  const double prompt = c.tiles * pair_parts * part_work(c, w, pair_parts);
+  return prompt >= 3 * w.own && parts_time(c, w, pair_parts, true) <= parts_time(c, w, parts, false);
 }
 
 // ---- Forward and dQ of head dims 64 / 96 / 128: waves in a workgroup ----

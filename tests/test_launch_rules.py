@@ -21,10 +21,10 @@ int main() {
   char what;
   while (std::scanf(" %c", &what) == 1) {
     int n = 0;
-    if (what == 'p') {
+    if (what == 'p' || what == 'k') {
       for (auto& x : v) std::scanf("%lld", &x);
       PromptTiles c{v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], v[9] != 0, v[10], (int)v[11]};
-      n = v[12] ? most_parts(c) : prompt_parts(c);
+      n = what == 'k' ? pair_tiles(c, prompt_parts(c), prompt_parts(c, true)) : v[12] ? most_parts(c) : prompt_parts(c);
     }
     if (what == 'w') {
       for (int i = 0; i < 9; ++i) std::scanf("%lld", &v[i]);
@@ -96,6 +96,33 @@ def test_prompt_parts_keep_sums_that_have_one_result(ask):
         else:
             more += n > 2
     assert few > 500 and more > 500
+
+
+# (d, N, P, total, longest, H, H_k, shared), two dK/dV workgroups a CU?
+PAIRS = [
+    ((128, 16, 8192, 16384, 1024, 32, 8), 1),       # 4.12 -> 3.70 ms
+    ((96, 8, 4111, 7300, 1680, 16, 4), 1),          # 699 -> 590 us
+    ((96, 5, 11889, 132, 31, 32, 8), 1),            # 136 -> 108
+    ((128, 1, 3577, 3577, 3577, 12, 4), 0),         # 271 -> 364
+    ((128, 7, 71, 13933, 2878, 8, 8), 0),           # responses: 263 -> 316
+    ((128, 4, 2567, 4300, 1829, 4, 2), 0),          # 116 -> 140
+    ((96, 7, 4639, 581, 118, 4, 2), 0),             # 44 -> 48
+    ((128, 1, 3999, 101, 101, 4, 2), 0),            # 64 workgroups: 22 -> 23
+    ((128, 16, 8192, 16384, 1024, 32, 8, 4000), 0),  # dQ shares the launch
+    ((128, 4, 0, 4000, 1000, 32, 8), 0),
+    ((128, 4, 8192, 0, 0, 32, 8), 0),
+    # the sizes of test_gpu_dkdv_pair.py
+    ((128, 8, 1537, 655, 300, 64, 32), 1),
+    ((96, 8, 1537, 655, 300, 64, 32), 1),
+    ((128, 6, 4097, 1199, 515, 8, 4), 1),
+    ((96, 6, 4097, 1199, 515, 8, 4), 1),
+]
+
+
+@pytest.mark.parametrize("case,pair", PAIRS)
+def test_pair_tiles(ask, case, pair):
+    line = _parts(*case)
+    assert ask(["k" + line[1:]]) == [pair]
 
 
 # (d, dQ, N, longest, P, window, H, H_k), waves, what they save
