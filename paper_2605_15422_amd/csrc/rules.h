@@ -93,12 +93,15 @@ inline int prompt_parts(const PromptTiles& c, bool pair = false) {
 
 // dK/dV at head dims 96 and 128, no window, one prompt: two workgroups a CU (dkdvw.hip) with `pair_parts` parts, or one with `parts`?
 // Two get more done on a full chip but each is slower, and a long response tile that starts behind the prompt tiles is then late.  So
-// where three quarters of the work are prompt tiles and the model says that they fill their rounds.
+// where three quarters of the work are prompt tiles and the model says that they fill their rounds, with a margin unless nearly all of
+// it is.  70 drawn calls behind prompts of 1000 and more, d = 96 and 128: the 42 that go here take 0.67 to 1.007 of their time, in the mean 0.89;
+// without the margin 6 x U(1870, 2474) behind 9832, 32 / 4 heads 4.44 -> 4.70 ms.
 inline bool pair_tiles(const PromptTiles& c, int parts, int pair_parts) {
   if (c.total_resp == 0 || c.tiles == 0 || c.n_groups > 1 || c.tiles * parts <= c.shared) return false;
   const PromptWork w = prompt_work(c);
   const double prompt = c.tiles * pair_parts * part_work(c, w, pair_parts);
-  return prompt >= 3 * w.own && parts_time(c, w, pair_parts, true) <= parts_time(c, w, parts, false);
+  const double margin = prompt >= 10 * w.own ? 1.0 : 0.97;
+  return prompt >= 3 * w.own && parts_time(c, w, pair_parts, true) <= margin * parts_time(c, w, parts, false);
 }
 
 // ---- Forward and dQ of head dims 64 / 96 / 128: waves in a workgroup ----

@@ -109,6 +109,7 @@ PAIRS = [
     ((96, 7, 4639, 581, 118, 4, 2), 0),             # 44 -> 48
     ((128, 1, 3999, 101, 101, 4, 2), 0),            # 64 workgroups: 22 -> 23
     ((128, 16, 8192, 16384, 1024, 32, 8, 4000), 0),  # dQ shares the launch
+    ((128, 6, 9832, 13032, 2474, 32, 4), 0),        # 4.44 -> 4.70 ms
     ((128, 4, 0, 4000, 1000, 32, 8), 0),
     ((128, 4, 8192, 0, 0, 32, 8), 0),
     # the sizes of test_gpu_dkdv_pair.py
