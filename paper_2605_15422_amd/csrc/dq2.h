@@ -60,38 +60,48 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   bf16x8 qf[2][KS], dof[2][KS];   // rows row0 + i16 and row0 + 16 + i16
   float lse2[2];
   f32x4 negd[2];                  // accumulator image of -D: this lane's query row in all four registers
+  {
+    // all loads of both halves before the first use of one (half by half, short walks took 1.2 us longer)
+    const bool stats = STATS && p.make_stats();
+    bf16x8 of[2][KS];
+    float dvec[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int row = row0 + 16 * h + i16;
-    const int64_t grow = b.row_begin + min(row, R - 1);
-    const u16* qp = p.q.ptr + grow * p.q.ts + (int64_t)head * p.q.hs + kgrp16<D>(lg) * 8;
-    const u16* dop = p.dout.ptr + grow * p.dout.ts + (int64_t)head * p.dout.hs + kgrp16<D>(lg) * 8;
+    for (int h = 0; h < 2; ++h) {
+      const int64_t grow = b.row_begin + min(row0 + 16 * h + i16, R - 1);
+      const u16* qp = p.q.ptr + grow * p.q.ts + (int64_t)head * p.q.hs + kgrp16<D>(lg) * 8;
+      const u16* dop = p.dout.ptr + grow * p.dout.ts + (int64_t)head * p.dout.hs + kgrp16<D>(lg) * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      qf[h][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 32);
-      dof[h][ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 32);
+      for (int ks = 0; ks < KS; ++ks) {
+        qf[h][ks] = *reinterpret_cast<const bf16x8*>(qp + ks * 32);
+        dof[h][ks] = *reinterpret_cast<const bf16x8*>(dop + ks * 32);
+      }
+      lse2[h] = p.lse[(int64_t)head * p.total + grow];
+      if (stats) {
+        const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + kgrp16<D>(lg) * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) of[h][ks] = *reinterpret_cast<const bf16x8*>(op + ks * 32);
+      } else {
+        dvec[h] = p.dvec[(int64_t)head * p.total + grow];
+      }
     }
-    lse2[h] = p.lse[(int64_t)head * p.total + grow] * LOG2E;
-    float dvec;
-    if (STATS && p.make_stats()) {
-      const u16* op = p.o.ptr + grow * p.o.ts + (int64_t)head * p.o.hs + kgrp16<D>(lg) * 8;
-      bf16x8 of[KS];
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) of[ks] = *reinterpret_cast<const bf16x8*>(op + ks * 32);
-      float t[KS];
+    for (int h = 0; h < 2; ++h) {
+      lse2[h] *= LOG2E;
+      if (stats) {
+        float t[KS];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) t[ks] = dot8_bf16(dof[h][ks], of[ks]);   // chunk 4 ks + kgrp16(lg)
-      dvec = butterfly_sum(t);
-      dvec += __shfl_xor(dvec, D == 96 ? 48 : 16);   // the chunk two further, then the next one (kgrp16)
-      dvec = xor32_sum(dvec);
-    } else {
-      dvec = p.dvec[(int64_t)head * p.total + grow];
+        for (int ks = 0; ks < KS; ++ks) t[ks] = dot8_bf16(dof[h][ks], of[h][ks]);   // chunk 4 ks + kgrp16(lg)
+        dvec[h] = butterfly_sum(t);
+        dvec[h] += __shfl_xor(dvec[h], D == 96 ? 48 : 16);   // the chunk two further, then the next one (kgrp16)
+        dvec[h] = xor32_sum(dvec[h]);
+      }
+      negd[h] = f32x4{-dvec[h], -dvec[h], -dvec[h], -dvec[h]};
+      // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qf[h][ks]), "v"(dof[h][ks]));
+      asm volatile("" : : "v"(lse2[h]), "v"(dvec[h]));
     }
-    negd[h] = f32x4{-dvec, -dvec, -dvec, -dvec};
-    // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : : "v"(qf[h][ks]), "v"(dof[h][ks]));
-    asm volatile("" : : "v"(lse2[h]), "v"(dvec));
   }
 
   f32x4 dqacc[2][DB];
