@@ -527,7 +527,7 @@ def main():
            256: ("fwd256_kernel", "dq256_kernel", "dkdv256_kernel"),
            512: ("fwd512_kernel", "dq512_kernel", "dkdv512_kernel")}.get(d, ("fwd_kernel", "dq_kernel", "dkdv_kernel"))
     kernel_names = {"ctx_fwd": fam[0] + " (Call 1)", "fwd": fam[0] + " (Call 2)",
-                    "bwd_dkdv": fam[2] + " (Call 2)", "bwd_dq": fam[1] + " (Call 2)",
+                    "bwd_dkdv": fam[2] + (" or dkdvw_kernel" if d in (96, 128) else "") + " (Call 2)", "bwd_dq": fam[1] + " (Call 2)",
                     "ctx_bwd_dkdv": fam[2] + " (Call 1)", "ctx_bwd_dq": fam[1] + " (Call 1)"}
     roofline = {"bound": "mfma", "kernel": kernel_names[dom], "achieved": round(achieved, 2),
                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),

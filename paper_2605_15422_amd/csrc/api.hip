@@ -128,7 +128,8 @@ CtxParts ctx_parts(const AttnParams& p, const dualkv_shape* s, const Groups& g) 
   if (s->window > 0) return {dkv::rules::most_parts(c), false};
   c.shared = dkv::dkdv4_dq_room(p, s->head_dim);
   const int n = dkv::rules::prompt_parts(c);
-  if (s->head_dim == 96 || s->head_dim == 128) {
+  // (two terms: a call for several groups and one for each of them give the same bits)
+  if ((s->head_dim == 96 || s->head_dim == 128) && (s->flags & DUALKV_FLAG_ACCUM_CTX_F32)) {
     const int pair = dkv::rules::prompt_parts(c, true);
     if (dkv::rules::pair_tiles(c, n, pair)) return {pair, true};
   }

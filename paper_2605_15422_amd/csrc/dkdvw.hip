@@ -1,4 +1,5 @@
-// dK / dV of Call 2 at head dims 96 and 128 where the prompt tiles fill the chip: a wave does all the work of its keys.
+// dK / dV of Call 2 at head dims 96 and 128, prompt gradients added to fp32 sums, where the prompt tiles fill the chip: a wave does all
+// the work of its keys.
 //
 // One workgroup of four waves owns a 128-key tile of one KV head (ownership, parts and gradients as in dkdv4.hip), each wave 32 keys: it
 // keeps K and -V operands and the fp32 dK, dV of its keys in registers and forms S, D - dP, P, -dS, dV += P^T dO and -dK += (-dS)^T Q
@@ -425,7 +426,7 @@ static hipError_t launch_dkdvw_t(AttnParams p, hipStream_t st) {
   });
 }
 hipError_t launch_dkdvw(const AttnParams& p, int head_dim, hipStream_t st) {
-  if (p.window > 0) return hipErrorInvalidValue;
+  if (p.window > 0 || p.dkc_acc == nullptr || p.dvc_acc == nullptr) return hipErrorInvalidValue;
   switch (head_dim) {
     case 96: return launch_dkdvw_t<96>(p, st);
     case 128: return launch_dkdvw_t<128>(p, st);

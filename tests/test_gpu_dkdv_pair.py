@@ -1,6 +1,6 @@
 """GPU parity of the dK/dV kernel of which two workgroups share a CU (head dims 96 and 128, many prompt tiles; test_launch_rules.py
 checks that these sizes go there): a last prompt tile of one key, responses around its 32-row blocks and 128-key tiles, empty ones,
-whole tiles and tiles in three parts that end inside a sequence, both forms of the prompt gradients, views of a packed projection."""
+whole tiles and tiles in three parts that end inside a sequence, views of a packed projection."""
 import numpy as np
 import pytest
 
@@ -26,7 +26,8 @@ def test_pair(d, size):
     keys = [(i, j) for i, R in enumerate(lens) for j in range(R)]
     want = {hk: orc.key_columns_call2(x["q_d"], x["k_c"], x["v_c"], x["k_d"], x["v_d"], wl.cu_seqlens, wl.scale, x["do_d"], hk,
                                       np.arange(P), keys) for hk in (0, 1, Hk - 1)}
-    for mode, flags in (("one", B.FLAG_ACCUM_CTX_F32), ("two", 0), ("packed", 0)):
+    flags = B.FLAG_ACCUM_CTX_F32
+    for mode in ("plain", "packed"):
         print("case pair", d, size, mode, flush=True)
         dg = B.upload(wl, flags)
         if mode == "packed":
@@ -38,8 +39,8 @@ def test_pair(d, size):
         torch.cuda.synchronize()
         rep = []
         for hk, (dk_c, dv_c, dk_d, dv_d) in want.items():
-            PU.compare("dK_c", PU.to_f64((b.dk_c_acc if flags else b.dk_c2)[:, hk]), dk_c, rep)
-            PU.compare("dV_c", PU.to_f64((b.dv_c_acc if flags else b.dv_c2)[:, hk]), dv_c, rep)
+            PU.compare("dK_c", PU.to_f64(b.dk_c_acc[:, hk]), dk_c, rep)
+            PU.compare("dV_c", PU.to_f64(b.dv_c_acc[:, hk]), dv_c, rep)
             PU.compare("dK_d", PU.to_f64(b.dk_d[:, hk]), dk_d, rep)
             PU.compare("dV_d", PU.to_f64(b.dv_d[:, hk]), dv_d, rep)
         print("\n".join(rep), flush=True)
