@@ -114,6 +114,7 @@ dkv::rules::PromptTiles prompt_tiles(const dualkv_shape* s, const Groups& g) {
   c.G = s->n_q_heads / s->n_kv_heads;
   c.shared = -1;
   c.ctx_len = s->ctx_len;
+  c.head_dim = s->head_dim;
   return c;
 }
 

@@ -18,6 +18,7 @@ struct PromptTiles {
   bool whole_seqs;             // parts are whole sequences (else row blocks)
   int64_t shared;              // up to so many prompt workgroups dK/dV and dQ share a launch
   int ctx_len;                 // keys of the longest prompt
+  int head_dim = 128;
 };
 
 constexpr int kTargetBlocks = 512;   // prompt-tile workgroups from which on no prompt tile is cut into parts
@@ -43,6 +44,7 @@ constexpr int kStart = 30, kMaxParts = 32;
 struct PromptWork {
   double seqs, one;     // sequences of a group; intervals of one
   double own, longest;  // all response tiles; the longest one
+  double resp_tiles;    // their number
 };
 inline double ceil_div(double a, double b) { return (double)(int64_t)((a + b - 1) / b); }
 inline PromptWork prompt_work(const PromptTiles& c) {
@@ -50,9 +52,10 @@ inline PromptWork prompt_work(const PromptTiles& c) {
   const double mean = (double)c.total_resp / c.n_seqs;
   w.seqs = ceil_div(c.n_seqs, c.n_groups);
   w.one = ceil_div(mean, c.row_block) * c.G;
-  const double resp_tiles = ceil_div(mean, c.key_tile);
+  const double tiles = ceil_div(mean, c.key_tile);
+  w.resp_tiles = tiles * c.n_seqs * c.kv_heads;
   // the tiles of a response see from all of its row blocks down to the last tile's
-  w.own = resp_tiles * c.n_seqs * c.kv_heads * (w.one * (resp_tiles + 1) / (2 * resp_tiles) + kStart);
+  w.own = w.resp_tiles * (w.one * (tiles + 1) / (2 * tiles) + kStart);
   w.longest = ceil_div(c.max_resp, c.row_block) * c.G + kStart;
   return w;
 }
@@ -60,16 +63,21 @@ inline PromptWork prompt_work(const PromptTiles& c) {
 inline double part_work(const PromptTiles& c, const PromptWork& w, int n) {
   return (c.whole_seqs ? ceil_div(w.seqs, n) * w.one : ceil_div(w.seqs * w.one, n)) + kStart;
 }
-// Time of all tiles with n parts.  `pair`: the kernel of which two workgroups share a CU (kPair: the time of an interval of each
-// of them then, kAlone: of one that has the CU to itself).
-constexpr double kPair = 1.72, kAlone = 1.27;
+// Time of all tiles with n parts.  `pair`: the kernel of which two workgroups share a CU (pair_interval: the time of an interval of
+// each of them then, kAlone: of one that has the CU to itself; in a full round a start and end lie beside the other one's work).  The
+// longest response tile may start behind the full rounds.
+constexpr double kAlone = 1.27;
+inline double pair_interval(const PromptTiles& c) { return c.head_dim == 96 ? 1.65 : 1.78; }
 inline double parts_time(const PromptTiles& c, const PromptWork& w, int n, bool pair) {
   const double part = part_work(c, w, n);
   const int64_t all = c.tiles * n;
   if (pair) {
     const int64_t full = all / (2 * kCus), rest = all % (2 * kCus);
-    const double last = rest == 0 ? 0 : rest <= kCus ? kAlone * part : kPair * part;
-    return std::max({(all * part + w.own) * (kPair / 2) / kCus, full * kPair * part + last, full * kPair * part + kPair * w.longest});
+    const double kPair = pair_interval(c);
+    const double rounds = full * (kPair * (part - kStart) + kStart);
+    const double last = rest == 0 ? 0 : (rest <= kCus ? kAlone : kPair) * part;
+    const double late = (rest + w.resp_tiles <= kCus ? kAlone : kPair) * w.longest;
+    return std::max({(all * part + w.own) * (kPair / 2) / kCus, rounds + last, rounds + late});
   }
   return std::max({(all * part + w.own) / kCus, (all + kCus - 1) / kCus * part, all / kCus * part + w.longest});
 }
@@ -93,15 +101,15 @@ inline int prompt_parts(const PromptTiles& c, bool pair = false) {
 
 // dK/dV at head dims 96 and 128, no window, one prompt: two workgroups a CU (dkdvw.hip) with `pair_parts` parts, or one with `parts`?
 // Two get more done on a full chip but each is slower, and a long response tile that starts behind the prompt tiles is then late.  So
-// where three quarters of the work are prompt tiles and the model says that they fill their rounds, with a margin unless nearly all of
-// it is.  70 drawn calls behind prompts of 1000 and more, d = 96 and 128: the 42 that go here take 0.67 to 1.007 of their time, in the mean 0.89;
-// without the margin 6 x U(1870, 2474) behind 9832, 32 / 4 heads 4.44 -> 4.70 ms.
+// where three quarters of the work are prompt tiles and the model says that they fill their rounds.  Both measured for 583 calls behind
+// prompts of 300 to 40000, d = 96 and 128: those that go here take 0.68 to 1.02 of their time (runs of equal kernels differ by
+// 0.015), all 583 together 0.924.  With one pair_interval of 1.72 for both head dims (0.929) calls of 2 to 2.75 rounds of 256 long parts
+// went here, too, and lost at d = 128: 16 x 1024 rows behind 10240, 32 / 8 heads 5.67 -> 5.80 ms, behind 11264 5.56 -> 5.78.
 inline bool pair_tiles(const PromptTiles& c, int parts, int pair_parts) {
   if (c.total_resp == 0 || c.tiles == 0 || c.n_groups > 1 || c.tiles * parts <= c.shared) return false;
   const PromptWork w = prompt_work(c);
   const double prompt = c.tiles * pair_parts * part_work(c, w, pair_parts);
-  const double margin = prompt >= 10 * w.own ? 1.0 : 0.97;
-  return prompt >= 3 * w.own && parts_time(c, w, pair_parts, true) <= margin * parts_time(c, w, parts, false);
+  return prompt >= 3 * w.own && parts_time(c, w, pair_parts, true) <= parts_time(c, w, parts, false);
 }
 
 // ---- Forward and dQ of head dims 64 / 96 / 128: waves in a workgroup ----

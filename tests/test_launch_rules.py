@@ -17,13 +17,15 @@ SOURCE = r"""
 #include "rules.h"
 using namespace dkv::rules;
 int main() {
-  long long v[13];
+  long long v[14];
   char what;
   while (std::scanf(" %c", &what) == 1) {
     int n = 0;
     if (what == 'p' || what == 'k') {
-      for (auto& x : v) std::scanf("%lld", &x);
+      for (int i = 0; i < 13; ++i) std::scanf("%lld", &v[i]);
+      if (what == 'k') std::scanf("%lld", &v[13]);
       PromptTiles c{v[0], (int)v[1], (int)v[2], (int)v[3], (int)v[4], (int)v[5], (int)v[6], (int)v[7], (int)v[8], v[9] != 0, v[10], (int)v[11]};
+      if (what == 'k') c.head_dim = (int)v[13];
       n = what == 'k' ? pair_tiles(c, prompt_parts(c), prompt_parts(c, true)) : v[12] ? most_parts(c) : prompt_parts(c);
     }
     if (what == 'w') {
@@ -110,6 +112,14 @@ PAIRS = [
     ((128, 1, 3999, 101, 101, 4, 2), 0),            # 64 workgroups: 22 -> 23
     ((128, 16, 8192, 16384, 1024, 32, 8, 4000), 0),  # dQ shares the launch
     ((128, 6, 9832, 13032, 2474, 32, 4), 0),        # 4.44 -> 4.70 ms
+    # two and a quarter to two and three quarters rounds of 256 are as many of 512: three of the one against one full and one half
+    # of the other, which at d = 128 is slower
+    ((128, 16, 9216, 16384, 1024, 32, 8), 0),       # 5.70 -> 5.78 ms
+    ((128, 16, 10240, 16384, 1024, 32, 4), 0),      # 5.65 -> 5.75
+    ((128, 9, 19149, 18400, 2443, 12, 4), 0),       # 4.99 -> 5.07
+    ((128, 8, 17500, 16384, 2048, 16, 4), 0),       # 5.60 -> 5.69
+    ((96, 16, 8660, 6500, 489, 32, 8), 1),          # 1.90 -> 1.80
+    ((128, 8, 3072, 8192, 1024, 8, 2), 0),          # 308 -> 331 us in nine parts
     ((128, 4, 0, 4000, 1000, 32, 8), 0),
     ((128, 4, 8192, 0, 0, 32, 8), 0),
     # the sizes of test_gpu_dkdv_pair.py
@@ -123,7 +133,7 @@ PAIRS = [
 @pytest.mark.parametrize("case,pair", PAIRS)
 def test_pair_tiles(ask, case, pair):
     line = _parts(*case)
-    assert ask(["k" + line[1:]]) == [pair]
+    assert ask(["k" + line[1:] + " %d" % case[0]]) == [pair]
 
 
 # (d, dQ, N, longest, P, window, H, H_k), waves, what they save
