@@ -61,12 +61,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   const int row0 = b.blk_row0 + (wave % p.RSH) * 32;
   const bool wave_valid = row0 < R;
 
-  // (the first tiles are requested ahead of Q: one latency for both)
   constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
   constexpr int V_RING = NSTAGE * C::TILE_BYTES;
-  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
-  loader.request(0);
-  loader.request(1);
 
   bf16x8 qf[2][C::KS];   // rows row0 + i16 and row0 + 16 + i16
   {
@@ -76,12 +72,17 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
 #pragma unroll
       for (int ks = 0; ks < C::KS; ++ks)
         qf[h][ks] = *reinterpret_cast<const bf16x8*>(qp + (int64_t)min(row0 + 16 * h + i16, R - 1) * p.q.ts + ks * 32);
-    // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : : "v"(qf[h][ks]));
   }
+  // (the first tiles are requested under the loads of Q, which leave first: behind 16 to 32 KB of tiles they are late)
+  __builtin_amdgcn_sched_barrier(0);
+  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
+  loader.request(0);
+  loader.request(1);
+  // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int ks = 0; ks < C::KS; ++ks) asm volatile("" : : "v"(qf[h][ks]));
 
   f32x4 oacc[2][C::DB];
 #pragma unroll
@@ -143,33 +144,54 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     return tr16_pair<D>(vadr[i - NS] + v0);
   };
   // score e = 8 h + 4 kh + r of a lane: row 16 h + i16, key 16 kh + 4 lg + r
-  auto step = [&](bool masked, f32x4 (&sc)[4], f32x4 (&sn)[4], bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
-                  int Kn, int Vp, int Kn2, int Vn2, int it, int half) __attribute__((always_inline)) {
-    if (LOCAL ? masked : __builtin_expect(masked, 0)) {
-      const bool is_ctx = it < n_ctx_run;
-      const int keyh0 = (is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run) * BN + half * 32;
-      // visible keys of a row: lo < key < lim (indices inside the region)
+  auto mask = [&](f32x4 (&sc)[4], int it, int half) __attribute__((always_inline)) {
+    const bool is_ctx = it < n_ctx_run;
+    const int keyh0 = (is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run) * BN + half * 32;
+    // visible keys of a row: lo < key < lim (indices inside the region)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int row = row0 + 16 * h + i16;
-        int lim, lo = -1;
-        if (is_ctx) {
-          lim = P;
-          if (LOCAL) lo = P + row - W;
-        } else {
-          lim = min(row + 1, R);
-          if (LOCAL) lo = row - W;
-        }
-        lim -= keyh0 + 4 * lg;
-        lo -= keyh0 + 4 * lg;
+    for (int h = 0; h < 2; ++h) {
+      const int row = row0 + 16 * h + i16;
+      int lim, lo = -1;
+      if (is_ctx) {
+        lim = P;
+        if (LOCAL) lo = P + row - W;
+      } else {
+        lim = min(row + 1, R);
+        if (LOCAL) lo = row - W;
+      }
+      lim -= keyh0 + 4 * lg;
+      if (!LOCAL) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int k = 16 * (e >> 2) + (e & 3);
-          const bool vis = LOCAL ? (k < lim && k > lo) : (k < lim);
-          sc[2 * h + (e >> 2)][e & 3] = vis ? sc[2 * h + (e >> 2)][e & 3] : -INFINITY;
+          sc[2 * h + (e >> 2)][e & 3] = k < lim ? sc[2 * h + (e >> 2)][e & 3] : -INFINITY;
         }
+        continue;
+      }
+      // both bounds: bit k of a word says whether this lane's key k is visible (two instructions a score instead of four: 1024 rows,
+      // window 256, 32 / 8 heads, d = 128 14.6 -> 13.3 us; 8 x U(300, 900) behind 2000, window 512, 16 / 4 heads, d = 96 50.5 -> 46.0)
+      lo -= keyh0 + 4 * lg;
+      const uint32_t bits = (~0u << min(max(lo + 1, 0), 31)) & (0x0fffffu >> (20 - min(max(lim, 0), 20)));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = 16 * (e >> 2) + (e & 3);
+        const float x = sc[2 * h + (e >> 2)][e & 3];   // (the bits of a vector's element are taken from a copy)
+        const uint32_t see = (uint32_t)((int32_t)(bits << (31 - k)) >> 31);
+        sc[2 * h + (e >> 2)][e & 3] = __builtin_bit_cast(float, (see & __builtin_bit_cast(uint32_t, x)) | (~see & 0xff800000u));
       }
     }
+  };
+  // the maximum of half h's scores over the four lanes that hold a row
+  auto row_max = [&](const f32x4 (&sc)[4], int h) __attribute__((always_inline)) {
+    float mx = sc[2 * h][0];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[2 * h + (e >> 2)][e & 3]);
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    return xor32_max(mx);
+  };
+  auto step = [&](bool masked, f32x4 (&sc)[4], f32x4 (&sn)[4], bf16x8 (&pprev)[2], bf16x8 (&pcur)[2], bf16x8 (&pre)[LEAD],
+                  int Kn, int Vp, int Kn2, int Vn2, int it, int half) __attribute__((always_inline)) {
+    if (LOCAL ? masked : __builtin_expect(masked, 0)) mask(sc, it, half);
     auto score = [&](int e) __attribute__((always_inline)) { return sc[e >> 2][e & 3]; };
     __builtin_amdgcn_sched_barrier(0);
     bf16x8 ob[NSLOT];
@@ -239,12 +261,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     if (__builtin_expect(__any(!(fmaxf(ls[0], ls[1]) < 256.0f)), 0)) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        float mx = score(8 * h);
-#pragma unroll
-        for (int e = 1; e < 8; ++e) mx = fmaxf(mx, score(8 * h + e));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float mn = fmaxf(m_ref[h], mx * c);
+        const float mn = fmaxf(m_ref[h], row_max(sc, h) * c);
         const float alpha = __builtin_amdgcn_exp2f(m_ref[h] - mn);
         m_ref[h] = mn;
         l_sum[h] *= alpha;
@@ -267,14 +284,14 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     pcur[1] = __builtin_bit_cast(bf16x8, w1);
   };
 
-  // ---- prologue: K0 V0 K1 V1 landed and published, K2 requested, scores of the first half.  The first step multiplies
+  // ---- prologue: K0 V0 K1 V1 landed and published, scores of the first half, K2 requested.  The first step multiplies
   // P = 0 with the second half of V slot 3: whatever is there has to be finite.
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
-  for (int i = tid; i < 32 * C::CPR; i += C::NT)
-    *reinterpret_cast<u32x4*>(smem + V_RING + 3 * C::TILE_BYTES + 32 * C::RB + i * 16) = zero4;
+  for (int i = 0; i < 32 * C::CPR; i += C::NT)
+    if (32 * C::CPR % C::NT == 0 || i + tid < 32 * C::CPR)
+      *reinterpret_cast<u32x4*>(smem + V_RING + 3 * C::TILE_BYTES + 32 * C::RB + (i + tid) * 16) = zero4;
   wait_vm<0>();
-  if (!loader.v) loader.request(2);
   __syncthreads();
 
   // tiles that can hold an invisible (row, key) pair for this wave: the partial last prompt tile, response tiles from the diagonal
@@ -288,9 +305,15 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   pB[1] = __builtin_bit_cast(bf16x8, zero4);
   constexpr int T = C::TILE_BYTES, HT = 32 * C::RB;
   s_half(0, sA);
+  // The first reference is the maximum of the first half tile.  Left at its start value, every wave would form its first sixteen
+  // probabilities twice, the second time out of line: 4 x 128 rows behind 256, 4 / 2 heads, d = 64 9.05 -> 8.73 us.
+  if (always_masked || ctx_masked == 0 || dec_masked <= 0) mask(sA, 0, 0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h) m_ref[h] = fmaxf(m_ref[h], row_max(sA, h) * c);
   bf16x8 pre[LEAD];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0
 #pragma unroll
   for (int i = 0; i < LEAD; ++i) pre[i] = operand(HT, 3 * T + HT, i);
+  if (!loader.v) loader.request(2);
 
   int it = 0;
   // tile `it` in slot U; false: it was the last one
@@ -300,7 +323,7 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     // tile it-1
     const bool issued = loader.request(loader.v ? (U + 2) % NSTAGE : UP);
     const bool masked = always_masked || it == ctx_masked || it >= dec_masked;
-    step(masked, sA, sB, pB, pA, pre, U * T + HT, UP * T + HT, UN * T, U * T, it, 0);
+    step(masked && it > 0, sA, sB, pB, pA, pre, U * T + HT, UP * T + HT, UN * T, U * T, it, 0);
     step(masked, sB, sA, pA, pB, pre, UN * T, U * T, UN * T + HT, U * T + HT, it, 1);
     // tiles it+2 (K) and it+1 (V) must have landed; the loads requested at the top of this tile may stay in flight
     if (__builtin_expect(issued, 1)) wait_vm<decltype(loader)::IPT>();
