@@ -155,6 +155,12 @@ struct AttnParams {
   __host__ __device__ bool make_stats() const { return o.ptr != nullptr; }
 };
 
+// A value whose origin the compiler does not see: what is formed from it is neither hoisted out of a loop into registers nor shared.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // A scalar kernel argument in scalar registers of its own.  The arguments arrive in blocks of up to sixteen registers;
 // a value used inside a loop keeps its whole block alive, and when scalar registers run short the block is spilled and
 // reloaded as a whole for it.  The copy ends the block's life here.

@@ -105,10 +105,6 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
     l_row[t] = ld_row(t);
     l_col[t] = ld_col(t);
   }
-  auto opaque = [](int v) __attribute__((always_inline)) {   // (what is formed from it is not hoisted out of the loop into registers)
-    asm volatile("" : "+v"(v));
-    return v;
-  };
   // load instruction t of the next row block, into the stage at `st` bytes of both rings
   auto load = [&](uint32_t st, auto Tc) __attribute__((always_inline)) {
     constexpr int t = decltype(Tc)::value;

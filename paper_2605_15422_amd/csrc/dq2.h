@@ -110,15 +110,21 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
 #pragma unroll
     for (int db = 0; db < DB; ++db) dqacc[h][db] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // per-lane LDS addresses in slot 0; the loop is unrolled over the slots, so that all others are immediate offsets
-  const unsigned char *kadr[KS], *vadr[KS], *tadr[DB];
+  // Per-lane LDS addresses in slot 0; the loop is unrolled over the slots, so that all others are immediate offsets.  At head dim 128,
+  // where the registers are full, one address of each kind: k-steps and column blocks differ in bits that the swizzle flips and not in the rows.
+  constexpr bool ONE = D == 128;
+  const uint32_t smem_addr = (uint32_t)reinterpret_cast<uintptr_t>(smem);
+  uint32_t kadr[ONE ? 1 : KS], vadr[ONE ? 1 : KS], tadr[ONE ? 1 : DB];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    kadr[ks] = smem + frag16_off<D>(lane, ks);
+  for (int ks = 0; ks < (ONE ? 1 : KS); ++ks) {
+    kadr[ks] = smem_addr + frag16_off<D>(lane, ks);
     vadr[ks] = kadr[ks] + V_RING;
   }
 #pragma unroll
-  for (int db = 0; db < DB; ++db) tadr[db] = smem + tr16_off<D>(lane, db);
+  for (int db = 0; db < (ONE ? 1 : DB); ++db) tadr[db] = smem_addr + tr16_off<D>(lane, db);
+  auto k_at = [&](int ks) __attribute__((always_inline)) { return ONE ? kadr[0] ^ (ks * 64) : kadr[ONE ? 0 : ks]; };
+  auto v_at = [&](int ks) __attribute__((always_inline)) { return ONE ? vadr[0] ^ (ks * 64) : vadr[ONE ? 0 : ks]; };
+  auto t_at = [&](int db) __attribute__((always_inline)) { return ONE ? tadr[0] ^ (db * 32) : tadr[ONE ? 0 : db]; };
 
   const int n_ctx_run = b.n_ctx - b.c0;
   wait_vm<0>();
@@ -134,7 +140,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   bf16x8 ko[2 * KS];
   auto load_k = [&](int at) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2 * KS; ++i) ko[i] = *reinterpret_cast<const bf16x8*>(kadr[i % KS] + at + i / KS * 16 * RB);
+    for (int i = 0; i < 2 * KS; ++i) ko[i] = lds_frag(k_at(i % KS) + at + i / KS * 16 * RB);
   };
   // One half tile (32 keys) at offset `at` of both rings, whose K operands are in `ko`; requests those of the next half at `next`.
   // For each half h of the rows: S^T = K Q^T, dP^T - D = V dO^T - D (accumulator initialised to -D), dS^T = P (dP^T - D),
@@ -146,6 +152,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     float ev[16];        // score e = 8 h + 4 kh + r: key 16 kh + 4 lg + r
     bf16x8 vo[2 * KS], kt[DB], ds[2];
     uint32_t dw[8];
+    static_assert(DB == 2 * KS, "");
     constexpr int NM = 2 * KS, EPM = (8 + NM - 1) / NM;   // MFMAs of a chain pair, most scores beside one of them
     auto exps = [&](int h, int i) __attribute__((always_inline)) {   // beside MFMA i
 #pragma unroll
@@ -170,18 +177,22 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     };
     auto mask = [&](int h) __attribute__((always_inline)) {
       if (__builtin_expect(masked, 0)) {
-        const int row = row0 + 16 * h + i16;
-        int lim = (is_ctx ? P : min(row + 1, R)) - key0 - 4 * lg, lo = -1;
-        if (LOCAL) lo = (is_ctx ? P : 0) + row - W - key0 - 4 * lg;
+        const int l = opaque(lane), row = row0 + 16 * h + (l & 15), k0 = key0 + 4 * (l >> 4);   // (formed here: no registers in between)
+        const int lim = (is_ctx ? P : min(row + 1, R)) - k0, lo = (is_ctx ? P : 0) + row - W - k0;
+        // bit k of a word says whether this lane's key k is visible
+        uint32_t bits = 0x0fffffu >> (20 - min(max(lim, 0), 20));
+        if (LOCAL) bits &= ~0u << min(max(lo + 1, 0), 31);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           const int k = 16 * (e >> 2) + (e & 3);
-          if (!(LOCAL ? (k < lim && k > lo) : (k < lim))) ev[8 * h + e] = 0.f;
+          const uint32_t see = (uint32_t)((int32_t)(bits << (31 - k)) >> 31);
+          ev[8 * h + e] = __builtin_bit_cast(float, see & __builtin_bit_cast(uint32_t, ev[8 * h + e]));
         }
       }
     };
+    if (ONE) asm volatile("" : "+v"(kadr[0]), "+v"(vadr[0]), "+v"(tadr[0]));   // (what is formed from them is not kept in registers)
 #pragma unroll
-    for (int i = 0; i < NM; ++i) vo[i] = *reinterpret_cast<const bf16x8*>(vadr[i % KS] + at + i / KS * 16 * RB);
+    for (int i = 0; i < NM; ++i) vo[i] = lds_frag(v_at(i % KS) + at + i / KS * 16 * RB);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -191,8 +202,9 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
         if (h == 1) exps(0, i);
         __builtin_amdgcn_sched_barrier(0);
       }
+    // the first half of K^T; the other half where V operands have been used
 #pragma unroll
-    for (int db = 0; db < DB; ++db) kt[db] = tr16_pair<D>(tadr[db] + at);
+    for (int db = 0; db < DB / 2; ++db) kt[db] = lds_tr16<D>(t_at(db) + at);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -200,8 +212,12 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         dp[2 * h + i / KS] = mfma16(vo[i], dof[h][i % KS], i % KS ? dp[2 * h + i / KS] : negd[h]);
-        if (h == 0) exps(1, i);
-        else products(0, i);
+        if (h == 0) {
+          exps(1, i);
+        } else {
+          if (i % 2 == 0) kt[DB / 2 + i / 2] = lds_tr16<D>(t_at(DB / 2 + i / 2) + at);
+          products(0, i);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }

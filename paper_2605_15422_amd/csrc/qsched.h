@@ -155,17 +155,17 @@ struct TileLoader {
   __device__ __forceinline__ static uint64_t first_tile(const TView& x, int64_t row, int hk) {
     return reinterpret_cast<uint64_t>(uniform_ptr(x.ptr + row * x.ts + (int64_t)hk * x.hs));
   }
-  __device__ __forceinline__ int row(int t) const {
+  __device__ __forceinline__ int row(int t, int l) const {
     // (head dim 96: a wave's three instructions are consecutive, together its sixteen rows)
-    if constexpr (kSplitRow<D>) return lwave * (IPT / 3) * kSplitRows<D> + split_row<D>(t, lane);
-    else return lwave * RPI + lane / CPR + t * LW * RPI;
+    if constexpr (kSplitRow<D>) return lwave * (IPT / 3) * kSplitRows<D> + split_row<D>(t, l);
+    else return lwave * RPI + l / CPR + t * LW * RPI;
   }
-  __device__ __forceinline__ int col(int t) const {
-    return ((kSplitRow<D> ? split_pos<D>(t, lane) : lane % CPR) ^ swz16<D>(row(t))) * 16;
+  __device__ __forceinline__ int col(int t, int l) const {
+    return ((kSplitRow<D> ? split_pos<D>(t, l) : l % CPR) ^ swz16<D>(row(t, l))) * 16;
   }
   __device__ __forceinline__ void lane_offsets() {
 #pragma unroll
-    for (int t = 0; t < NV; ++t) voff[t] = (uint32_t)(__umul24((unsigned)row(t), (unsigned)tsb) + col(t));
+    for (int t = 0; t < NV; ++t) voff[t] = (uint32_t)(__umul24((unsigned)row(t, lane), (unsigned)tsb) + col(t, lane));
   }
   // requests this wave's next tile into ring slot `slot`; false: there is none
   __device__ __forceinline__ bool request(uint32_t slot) {
@@ -187,9 +187,10 @@ struct TileLoader {
         dma16_at<t * STEP>(reinterpret_cast<const void*>(base + (uint32_t)(t / NV * step)), voff[t % NV], dst);
       });
     } else {
+      const int l = opaque(lane);   // (rows and columns formed here: no registers in between)
       static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
         constexpr int t = decltype(Tc)::value;
-        dma16_at<t * STEP>(reinterpret_cast<const void*>(base), (uint32_t)(__umul24((unsigned)min(row(t), keys - 1), (unsigned)tsb) + col(t)), dst);
+        dma16_at<t * STEP>(reinterpret_cast<const void*>(base), (uint32_t)(__umul24((unsigned)min(row(t, l), keys - 1), (unsigned)tsb) + col(t, l)), dst);
       });
     }
     ptr += (uint64_t)(uint32_t)tsb * BN;

@@ -105,5 +105,13 @@ template <int D>
 __device__ __forceinline__ bf16x8 tr16_pair(const unsigned char* a) {
   return tr_pair(a, a + 16 * 2 * D);
 }
+// the same by LDS address: a row operand; the operand of a transpose read
+__device__ __forceinline__ bf16x8 lds_frag(uint32_t a) { return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(a); }
+template <int D>
+__device__ __forceinline__ bf16x8 lds_tr16(uint32_t a) {
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)a);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(a + 16 * 2 * D));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
 
 }  // namespace dkv
