@@ -27,7 +27,7 @@ namespace dkv {
 
 // Ring slots per tensor: with four the K tiles travel three tiles ahead, with three (head dim 96: two workgroups a CU) two.
 template <int D>
-constexpr int kDq2Stages = D == 96 ? 3 : 4;
+constexpr int kDq2Stages = rules::dq_ring_slots(D);
 
 // workgroup `bid` of `nblk`; STATS: it may have to form the row statistics (p.make_stats())
 template <int D, int NW, bool LOCAL, bool STATS>

@@ -5,7 +5,7 @@
 namespace dkv {
 
 template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, 2) void dq2_kernel(const AttnParams p) {
+__global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void dq2_kernel(const AttnParams p) {
   dq2_workgroup<D, NW, LOCAL, true>(p, blockIdx.x, gridDim.x);
 }
 

@@ -164,6 +164,10 @@ inline int row_block_waves(const RowBlocks& c, bool pair, bool dq, bool shared) 
   return c.n_seqs <= 2 && !c.window && 4 * (int64_t)c.ctx_len <= c.longest && n <= 600 ? 4 : 8;
 }
 
+// K and V tiles that a dQ workgroup of four waves has room for, head dims 64 / 96 / 128.  Three at d = 64, so that three workgroups fit the LDS
+// of a CU (their registers do, too): with four and two workgroups dQ of 8 x U(131, 2048) behind 4096, 32 / 8 heads takes 730 us instead of 686.
+constexpr int dq_ring_slots(int head_dim) { return head_dim == 128 ? 4 : 3; }
+
 // Copies of a prompt row that one workgroup of the replicating copy writes.  More of them read the row less often; but one
 // workgroup then writes for longer than its share of the whole copy takes, and the few that there are keep the others waiting.
 // So no more than the rows that a CU has to write: 23 x 29 + 138 rows of 64 KB take 31 us with 16 copies and 13 with 2, 16 x 64 + 270

@@ -57,6 +57,12 @@ def test_no_spills_and_one_register_file(kernels, d, local):
         assert (k[".vgpr_spill_count"], k[".private_segment_fixed_size"], k.get(".agpr_count", 0)) == (0, 0, 0), k[".name"]
 
 
+@pytest.mark.parametrize("local", ["true", "false"])
+def test_three_dq_workgroups_on_a_cu(kernels, local):
+    """Head dim 64: three waves a SIMD share its 512 registers, in units of eight"""
+    assert kernels["dq2_kernel<64, 4, %s>" % local][".vgpr_count"] <= 168
+
+
 @pytest.mark.parametrize("d", [64, 96, 128])
 @pytest.mark.parametrize("local", ["true", "false"])
 def test_shared_launch(kernels, d, local):

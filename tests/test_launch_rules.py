@@ -36,6 +36,10 @@ int main() {
       for (int i = 0; i < 3; ++i) std::scanf("%lld", &v[i]);
       n = replicate_copies(v[0], v[1], v[2]);
     }
+    if (what == 'd') {
+      std::scanf("%lld", &v[0]);
+      n = dq_ring_slots((int)v[0]);
+    }
     std::printf("%d\n", n);
   }
 }
@@ -134,6 +138,13 @@ PAIRS = [
 def test_pair_tiles(ask, case, pair):
     line = _parts(*case)
     assert ask(["k" + line[1:] + " %d" % case[0]]) == [pair]
+
+
+@pytest.mark.parametrize("d,per_cu", [(64, 3), (96, 2), (128, 1)])
+def test_dq_rings_fit_the_lds(ask, d, per_cu):
+    """As many workgroups as their registers let on a CU (test_kernel_registers.py): 160 KB for K and V tiles of 64 keys."""
+    slots, = ask(["d %d" % d])
+    assert slots >= 3 and per_cu * slots * 2 * 64 * 2 * d <= 160 * 1024
 
 
 # (d, dQ, N, longest, P, window, H, H_k), waves, what they save
