@@ -12,6 +12,7 @@ The dense fp64 oracle is too slow at these sizes, so each config is checked thre
      non-zero only on a seeded set of rows: dK / dV of sampled prompt keys and response keys of one KV head then
      depend on those rows only, and are compared with the oracle's column evaluation (all sequences contribute
      to the shared prompt keys);
+     both also with the prompt gradients added to the fp32 joint sums, as bench.py times them, at head dims 64 to 128;
   3. identities that hold for the full dense-gradient outputs at any size: sum_j dV_j = sum_rows dO
      (softmax rows sum to one), sum_j dK_j = 0 (rows of dS sum to zero), <q,dq> = <k,dk> (scale symmetry),
      per KV head, over prompt + response keys of Call 2 and over the prompt keys of Call 1.
@@ -57,6 +58,27 @@ def _sample_rows(rng, wl, n):
         if lens[i] > 0:
             out.add((i, int(rng.integers(0, lens[i]))))
     return sorted(out)[:max(n, 1)] if len(out) > n else sorted(out)
+
+
+def _joint(dg, bufs):
+    """Call 2's backward with the prompt gradients in fp32 sums (bench.py's default): sums of dK_c and dV_c, dK_d, dV_d."""
+    import torch
+    from paper_2605_15422_amd import binding as B
+    s = type(dg.shape_c).from_buffer_copy(bytes(dg.shape_c))
+    s.flags |= B.FLAG_ACCUM_CTX_F32
+    acc = [torch.empty(dg.k_c.shape, dtype=torch.float32, device="cuda") for _ in range(2)]
+    out = [torch.full(dg.k_d.shape, float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    ws = torch.full((max(16, B.dualkv_workspace_bytes(s, B.OP_BWD)),), 0xFF, dtype=torch.uint8, device="cuda")
+    dq = torch.empty_like(bufs.dq_d)
+    B.dualkv_zero_ctx_grads(s, *acc)
+    B.dualkv_bwd(s, dg.do_d, bufs.o_d, bufs.lse_d, dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d, dg.cu_dev, dg.cu_host, dq, None, None, *out, *acc, ws)
+    torch.cuda.synchronize()
+    return (*acc, *out)
+
+
+def _compare_joint(dg, bufs, kv, ctx_keys, didx, want, mark, rep):
+    for name, got, at, ref in zip(("dK_c32", "dV_c32", "dK_d32", "dV_d32"), _joint(dg, bufs), (ctx_keys, ctx_keys, didx, didx), want):
+        PU.compare(name + mark, PU.to_f64(got[at, kv]), ref, rep)
 
 
 # the five benchmark configs, plus two shapes of the paper-shape sweeps: a Tab. 1 point with N = 28 sequences and the
@@ -172,6 +194,7 @@ def test_full_size(name):
             didx = [int(cu[i]) + j for (i, j) in dec_keys]
             PU.compare("dK_d*", PU.to_f64(bufs.dk_d[didx, kv]), dk_dd, rep)
             PU.compare("dV_d*", PU.to_f64(bufs.dv_d[didx, kv]), dv_dd, rep)
+            _compare_joint(dg, bufs, kv, ctx_keys, didx, (dk_c, dv_c, dk_dd, dv_dd), "*", rep)
 
         # ---- 2b. sparse upstream gradient -> key columns of one KV head
         _say("  sparse-gradient backward")
@@ -206,6 +229,8 @@ def test_full_size(name):
         didx = [int(cu[i]) + j for (i, j) in dec_keys]
         PU.compare("dK_d", PU.to_f64(bufs.dk_d[didx, kv]), dk_dd, rep)
         PU.compare("dV_d", PU.to_f64(bufs.dv_d[didx, kv]), dv_dd, rep)
+        if d <= 128:
+            _compare_joint(dg2, bufs, kv, ctx_keys, didx, (dk_c, dv_c, dk_dd, dv_dd), "", rep)
         # Call 1: the prompt as a single sequence without a shared prefix
         cu1 = np.array([0, P], dtype=np.int32)
         e = np.zeros((0, 1, d))

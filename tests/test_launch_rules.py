@@ -131,6 +131,8 @@ PAIRS = [
     ((96, 8, 1537, 655, 300, 64, 32), 1),
     ((128, 6, 4097, 1199, 515, 8, 4), 1),
     ((96, 6, 4097, 1199, 515, 8, 4), 1),
+    *(((d, N, P, total, longest, H, Hk), 1) for d in (96, 128)
+      for N, P, total, longest, H, Hk in ((4, 4097, 534, 301, 8, 8), (4, 9001, 262, 129, 12, 4), (4, 4097, 534, 301, 32, 8), (3, 8100, 198, 100, 32, 4))),
 ]
 
 
