@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
   constexpr int IPB = LOADER ? 2 * NIT : 2 * NIT / 4;   // per requesting wave (Q and dO)
   constexpr int LOAD_WAVE = 7, STAT_WAVE = CW + 1;
   constexpr int RPI = 1024 / RB;                   // rows per load instruction
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // (as the dQ part needs it)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

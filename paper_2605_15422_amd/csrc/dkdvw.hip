@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
   constexpr bool SPLIT = kSplitRow<D>;             // head dim 96: waves 0 and 1 request Q, 2 and 3 dO
   constexpr int IPB = 2 * HT / 1024 / 4;           // load instructions per wave and row block
   constexpr int RPI = 1024 / RB;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // (addresses are formed by XOR)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -36,7 +36,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   constexpr int KS = D / 32, DB = D / 16, RB = 2 * D, CPR = D / 8;
   constexpr int T = BN * RB, HT = 32 * RB;         // bytes of a tile, of half a tile
   constexpr int NSTAGE = kDq2Stages<D>, V_RING = NSTAGE * T;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring | V ring
+  extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // K ring | V ring (aligned: addresses are formed by XOR)
 
   QBlock b;
   if (!decode_qblock<BN>(p, b, bid, nblk)) return;
