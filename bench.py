@@ -27,18 +27,18 @@ TRAFFIC_TABLE = os.path.join(ROOT, "profiles", "hbm_traffic_table.txt")
 
 
 def measured_traffic(config, stage):
-    """HBM bytes per launch (read + written) of one stage's kernel, from the tracked table of rocprofv3 --pmc
-    FETCH_SIZE / WRITE_SIZE results (already scaled by the copy-kernel calibration stated in that file); None if the
-    table has no line for it."""
+    """HBM bytes per launch (read + written) of one stage's kernel and that kernel's name, from the tracked table of rocprofv3
+    --pmc FETCH_SIZE / WRITE_SIZE results (already scaled by the copy-kernel calibration stated in that file; fp32 joint
+    accumulation); None, None if the table has no line for it."""
     try:
         with open(TRAFFIC_TABLE) as f:
             for ln in f:
                 w = ln.split()
-                if len(w) >= 3 and not ln.startswith("#") and w[0] == config and w[1] == stage:
-                    return int(w[2])
+                if len(w) >= 6 and not ln.startswith("#") and w[0] == config and w[1] == stage:
+                    return int(w[2]), w[5]
     except OSError:
         pass
-    return None
+    return None, None
 
 
 def _events(n):
@@ -523,16 +523,15 @@ def main():
     dom = max(kern_flops, key=lambda n: stage[n])
     achieved = kern_flops[dom] / (stage[dom] * 1e-3) / 1e12 if stage[dom] > 0 else 0.0
     # the kernel symbols that serve this head dim (as the rocprofv3 kernel trace names them)
-    fam = {64: ("fwd2_kernel", "dq2_kernel", "dkdv4_kernel"), 128: ("fwd2_kernel", "dq2_kernel", "dkdv4_kernel"),
-           256: ("fwd256_kernel", "dq256_kernel", "dkdv256_kernel"),
-           512: ("fwd512_kernel", "dq512_kernel", "dkdv512_kernel")}.get(d, ("fwd_kernel", "dq_kernel", "dkdv_kernel"))
-    kernel_names = {"ctx_fwd": fam[0] + " (Call 1)", "fwd": fam[0] + " (Call 2)",
-                    "bwd_dkdv": fam[2] + (" or dkdvw_kernel" if d in (96, 128) else "") + " (Call 2)", "bwd_dq": fam[1] + " (Call 2)",
-                    "ctx_bwd_dkdv": fam[2] + " (Call 1)", "ctx_bwd_dq": fam[1] + " (Call 1)"}
-    roofline = {"bound": "mfma", "kernel": kernel_names[dom], "achieved": round(achieved, 2),
-                "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
-                "traffic": measured_traffic(args.config, dom), "kernel_ms": round(stage[dom], 4),
-                "algorithmic_flops_per_launch": kern_flops[dom]}
+    small, mid = ("fwd2_kernel", "dq2_kernel", "dkdv4_kernel"), ("fwd256_kernel", "dq256_kernel", "dkdv256_kernel")
+    fam = {64: small, 96: small, 128: small, 192: mid, 256: mid, 512: ("fwd512_kernel", "dq512_kernel", "dkdv512_kernel")}[d]
+    # (which of the two dK/dV kernels of head dims 96 and 128 takes Call 2 is the library's choice: recorded with the traffic)
+    two = " or dkdvw_kernel" if d in (96, 128) and not args.two_terms and shape.window == 0 else ""
+    stage_kernel = {"ctx_fwd": fam[0], "fwd": fam[0], "bwd_dkdv": fam[2] + two, "bwd_dq": fam[1], "ctx_bwd_dkdv": fam[2], "ctx_bwd_dq": fam[1]}
+    traffic, recorded = (None, None) if args.two_terms else measured_traffic(args.config, dom)
+    roofline = {"bound": "mfma", "kernel": "%s (Call %d)" % (recorded or stage_kernel[dom], 1 if dom.startswith("ctx_") else 2),
+                "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
+                "traffic": traffic, "kernel_ms": round(stage[dom], 4), "algorithmic_flops_per_launch": kern_flops[dom]}
 
     tflops = fl["layer"] / (ms * 1e-3) / 1e12
     out = {
