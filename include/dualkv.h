@@ -30,6 +30,11 @@
  *     the *_groups entry points, or one call sequence per group captured in a HIP graph.
  *   - Outputs are fully overwritten.  The only exception are the fp32
  *     accumulators in DUALKV_FLAG_ACCUM_CTX_F32 mode, which are added into.
+ *   - The kernels that serve a call are chosen by its sizes, flags and number of groups; all meet the same precision, but the
+ *     order of their sums differs.  So the bits of a result are those of one kind of call: the response gradients dK_d, dV_d
+ *     of a call with DUALKV_FLAG_ACCUM_CTX_F32 may differ in their last bits from those of the same call without the flag, and
+ *     from those of a *_groups call that holds the group beside others.  Without the flag a *_groups call gives the bits of the
+ *     calls for each group (prompt gradients: where neither has to add its parts of a prompt tile atomically).
  *   - Every entry point returns DUALKV_OK or a negative error code; arguments are
  *     validated on the host before anything is launched.  No exceptions, no abort.
  *   - Semantics fixed here: diagonal inclusive; GQA map kv_head = q_head / (H/H_k);
@@ -175,8 +180,9 @@ int dualkv_finalize_ctx_grads(const dualkv_shape* shape, const float* dk_c_acc32
  * (optional, may be NULL): host copy, used only to validate (sequence ranges partition [0, n_seqs) in order, prompts
  * inside [0, total_ctx) and, for the ctx calls, packed back to back in group order).  Layouts of the other arguments
  * as in the single-group calls with P replaced by total_ctx: lse_c is (H, total_ctx), dk_c / dv_c and the fp32
- * accumulators are (total_ctx, H_k, d).  Each call runs the kernels of its single-group counterpart once for all
- * groups (plus one tiny index kernel), instead of once per group.  Workspace: dualkv_groups_workspace_bytes (the forward calls need a small one too).
+ * accumulators are (total_ctx, H_k, d).  Each call runs its kernels once for all groups (plus one tiny index kernel),
+ * instead of once per group; they are those of the single-group counterpart, except that the dK/dV kernel that some single
+ * calls with DUALKV_FLAG_ACCUM_CTX_F32 use serves no call with several groups.  Workspace: dualkv_groups_workspace_bytes (the forward calls need a small one too).
  * dualkv_zero_ctx_grads / dualkv_finalize_ctx_grads serve the accumulators of all groups when given a shape whose
  * ctx_len is total_ctx. */
 typedef struct dualkv_group {

@@ -1,7 +1,8 @@
 """GPU parity of the dK/dV kernel of which two workgroups share a CU (head dims 96 and 128, many prompt tiles; test_launch_rules.py
 checks that these sizes go there): a last prompt tile of one key, responses around its 32-row blocks and 128-key tiles, empty ones,
 whole tiles and tiles in parts that end inside a sequence, one to eight query heads per KV head, views of a packed projection; the
-routes of a call with one group, of given row statistics and of sums that hold something already; the largest token stride."""
+routes of a call with one group, of given row statistics and of sums that hold something already; the calls that the other
+kernel takes; the largest token stride."""
 import numpy as np
 import pytest
 
@@ -118,6 +119,49 @@ def test_pair_routes(d):
     B.dualkv_bwd_groups(dg.shape_c, torch.from_numpy(table).cuda(), table, P, *args, ws)
     torch.cuda.synchronize()
     check("one group", (*acc, *out))
+
+
+# dkdv4 takes the same work without the joint sums, and with a second group beside it; both sides round sums in another order to bf16, half
+# a unit (2^-9) each
+@pytest.mark.parametrize("d", [96, 128])
+def test_pair_and_other_kernel_agree(d):
+    import torch
+    from paper_2605_15422_amd import binding as B
+    print("case pair other kernel", d, flush=True)
+    dg, b = _group(d, "G1", B.FLAG_ACCUM_CTX_F32)
+    want = _backward(dg, b)
+
+    def check(got):
+        for x, y in zip(got, want):
+            assert (x.double() - y.double()).norm() <= 2.0**-8 * y.double().norm()
+
+    two = type(dg.shape_c).from_buffer_copy(bytes(dg.shape_c))
+    two.flags = 0
+    out = [torch.empty_like(x) for x in (dg.k_c, dg.k_c, dg.k_d, dg.k_d)]
+    ws = torch.full((B.dualkv_workspace_bytes(two, B.OP_BWD),), 0xFF, dtype=torch.uint8, device="cuda")
+    B.dualkv_bwd(two, dg.do_d, b.o_d, b.lse_d, dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d, dg.cu_dev, dg.cu_host, b.dq_d, *out, None, None, ws)
+    torch.cuda.synchronize()
+    check(out)
+
+    # the group twice
+    N, P, T = dg.shape_c.n_seqs, dg.shape_c.ctx_len, dg.shape_c.total_resp
+    table = np.asarray([(0, P, 0, N), (P, P, N, 2 * N)], dtype=np.int32)
+    cu = np.concatenate([dg.cu_host, dg.cu_host[1:] + T]).astype(np.int32)
+    both = type(dg.shape_c).from_buffer_copy(bytes(dg.shape_c))
+    both.n_seqs, both.total_resp = 2 * N, 2 * T
+
+    def twice(x):
+        return torch.cat([x, x])
+
+    acc = [torch.zeros((2 * P, *dg.k_c.shape[1:]), dtype=torch.float32, device="cuda") for _ in range(2)]
+    out = [torch.empty_like(twice(dg.k_d)) for _ in range(2)]
+    ws = torch.full((B.dualkv_groups_workspace_bytes(both, 2, 2 * P, B.OP_BWD),), 0xFF, dtype=torch.uint8, device="cuda")
+    B.dualkv_bwd_groups(both, torch.from_numpy(table).cuda(), table, 2 * P, *(twice(x) for x in (dg.do_d, b.o_d)), torch.cat([b.lse_d] * 2, dim=1).contiguous(),
+                        *(twice(x) for x in (dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d)), torch.from_numpy(cu).cuda(), cu, torch.empty_like(twice(b.dq_d)), None, None,
+                        *out, *acc, ws)
+    torch.cuda.synchronize()
+    for g in range(2):
+        check([x[g * P:(g + 1) * P] for x in acc] + [x[g * T:(g + 1) * T] for x in out])
 
 
 @pytest.mark.parametrize("d", [96, 128])
