@@ -1,6 +1,6 @@
 // Shared device helpers for the gfx950 shared-prompt attention kernels.
 //
-// MFMA conventions used everywhere (v_mfma_f32_32x32x16_bf16, wave64):
+// MFMA conventions (wave64).  v_mfma_f32_32x32x16_bf16 (dK/dV, head dims 192 and up; 16x16x32 beside mfma16 below):
 //   A operand (M x K = 32 x 16): lane l holds row  i = l % 32, k = 8*(l/32) .. 8*(l/32)+7
 //   B operand (K x N = 16 x 32): lane l holds col  j = l % 32, k = 8*(l/32) .. 8*(l/32)+7
 //   C/D       (M x N = 32 x 32): lane l holds col  j = l % 32, and register r (0..15) holds

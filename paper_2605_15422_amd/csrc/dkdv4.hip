@@ -61,11 +61,13 @@ constexpr int kDqWaves = 4;   // of the dQ workgroups in a launch of both
 
 // WITH_DQ: both backward kernels in one launch, for calls that do not fill the chip: n_kv dK/dV workgroups, then dQ workgroups
 // of four waves (dq2.h).  The two are independent once the row statistics are there, each is as long as its longest walk when
-// a CU has no second workgroup to do, and side by side they take the longer of the two instead of the sum.  Measured (backward call with its preprocess, two launches -> one):
-//   1 x 1021 rows, 16 / 4 heads, d = 128 (128 + 128 workgroups)                      72.2 -> 48.1 us; d = 64 49.0 -> 32.6
-//   1 x 1500 rows, 8 / 8 heads, d = 128 (96 + 96)                                    88.8 -> 51.4 us; d = 96 76.6 -> 48.7
-//   1 x 512 rows, 32 / 8 heads, d = 128 (64 + 128)                                   61.6 -> 47.2 us
-//   2 x <= 64 rows behind a prompt of 64, 8 / 2 heads, d = 128 (6 + 8)               33.8 -> 27.0 us; d = 64 25.2 -> 23.8
+// a CU has no second workgroup to do, and side by side they take the longer of the two instead of the sum.  Measured (backward call,
+// captured in graphs, two launches -> one with its preprocess):
+//   1 x 1021 rows, 16 / 16 heads, d = 128 (128 + 128 workgroups)                     69.7 -> 43.7 us; d = 64 45.5 -> 29.0
+//   1 x 1021 rows, 16 / 4 heads, d = 128 (32 + 128)                                  143.5 -> 117.8 us; d = 64 94.1 -> 77.1
+//   1 x 1500 rows, 8 / 8 heads, d = 128 (96 + 96)                                    90.0 -> 53.0 us; d = 96 75.9 -> 51.5
+//   1 x 512 rows, 32 / 8 heads, d = 128 (32 + 128)                                   84.3 -> 69.3 us
+//   2 x <= 64 rows behind a prompt of 64, 8 / 2 heads, d = 128 (6 + 8)               31.8 -> 25.1 us; d = 64 24.5 -> 24.0
 template <int D, bool LOCAL, bool WITH_DQ>
 __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p, int n_kv) {
   if (WITH_DQ && (int)blockIdx.x >= n_kv) {
@@ -596,14 +598,14 @@ hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { ret
 hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<true>(p, head_dim, st); }
 
 // One launch where every workgroup of both kernels has one of the 256 CUs to itself: all calls measured there gained (1.02 to
-// 1.7 times, head dims 64, 96 and 128).  With more workgroups what can be won are the tails, against a dQ loop that is slower
-// here (it shares its scalar registers with the other kernel's arguments) and the preprocess.  Up to 2.5 workgroups a CU there is
+// 1.7 times, head dims 64, 96 and 128).  With more workgroups what can be won are the tails, against the preprocess.  Up to 2.5 workgroups a CU there is
 // such a tail where the responses are long for their prompt, since a response's tiles carry work that falls from the first to the
 // last; a long prompt's tiles are cut into full rounds of even parts.  Measured over 110 drawn calls with such responses: those
-// whose launches changed became 1.02 to 1.56 times faster, none slower: 2 x U(206, 654) behind 807, 12 / 4 heads, d = 128, 104 ->
-// 69 us; 5 x U(369, 431) behind 1158, 8 / 2 heads, d = 128, 119 -> 99.  The other side: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128,
-// 107 -> 115 us, 2 x U(74, 105) behind 3540, 32 / 8 heads 163 -> 176; causal rows alone, 1 x 2048, 8 / 2 heads 95 -> 105; window 512,
-// 1 x 3000, 8 / 8 heads 75 -> 80; 776 + 704 workgroups (8 x U(500, 1500) behind 300, 8 / 8 heads), d = 96, 142 -> 160.
+// whose launches changed became 1.02 to 1.56 times faster, none slower: 2 x U(206, 654) behind 807, 12 / 4 heads, d = 128, 103 ->
+// 69 us; 5 x U(369, 431) behind 1158, 8 / 2 heads, d = 128, 112 -> 84.  The other side: 776 + 704 workgroups (8 x U(500, 1500) behind 300,
+// 8 / 8 heads), d = 96, 149 -> 167 us; nothing to be won: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128 113.5 -> 114.0, 2 x U(74, 105) behind
+// 3540, 32 / 8 heads 161 -> 161, window 512, 1 x 3000, 8 / 8 heads 68.0 -> 66.7.  Causal rows alone stay at one a CU, where one launch for
+// 256 + 256 workgroups would be the better one, too (1 x 2048, 16 / 16 heads, d = 128 117 -> 82 us, d = 64 76 -> 54).
 int64_t dkdv4_dq_room(AttnParams p, int head_dim) {
   if (head_dim > 128 || choose_waves(p, head_dim, true, true) != kDqWaves) return -1;
   const bool tails = p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs;

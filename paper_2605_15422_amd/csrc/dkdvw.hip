@@ -3,8 +3,8 @@
 //
 // One workgroup of four waves owns a 128-key tile of one KV head (ownership, parts and gradients as in dkdv4.hip), each wave 32 keys: it
 // keeps K and -V operands and the fp32 dK, dV of its keys in registers and forms S, D - dP, P, -dS, dV += P^T dO and -dK += (-dS)^T Q
-// itself.  Nothing but Q and dO passes through LDS: dkdv4's roles hand P and -dS over there, at a barrier that ties the waves of
-// a SIMD together.  Two workgroups share a CU (256 registers a wave, at most 80 KB of LDS each), so that one wave's softmax and waits
+// itself.  P and -dS never pass through LDS, where dkdv4's roles hand them over at a barrier that ties the waves of a SIMD together: it holds
+// Q, dO, the row statistics and at head dim 128 a part of -V.  Two workgroups share a CU (256 registers a wave, at most 80 KB of LDS each), so that one wave's softmax and waits
 // are beside the other's MFMAs.  16x16x32 MFMAs, as in the forward kernel: more work in the card's power.
 //   * A row block of 32 rows is two halves h of 16: S(0) | D - dP(0), exponentials of 0 | S(1), -dS of 0 | D - dP(1), exponentials
 //     of 1 | dV, -dS of 1 | dK.  P and -dS of both halves are the 32-deep operand of dV and dK without leaving registers (common.h).

@@ -3,7 +3,7 @@
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
 //
-// Shape: 4 waves where two workgroups fit a CU (head dims 64 and 96), else 8, two per SIMD, or 4 by the rule of
+// Shape: 4 waves where two or three workgroups fit a CU (head dims 96 and 64), else 8, two per SIMD, or 4 by the rule of
 // row_block_waves (rules.h); each owns 32 rows, two halves of 16, with Q, dO fragments and the dQ^T accumulator in registers; K and
 // V tiles of 64 keys travel global -> LDS directly (global_load_lds, two or three tiles ahead: no staging registers) into
 // two rings of swizzled tiles.  S^T = K Q^T and dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T
@@ -11,11 +11,8 @@
 // 16x16x32 MFMAs, as in the forward kernel (fwd2.hip): more work in the card's power than with 32x32x16, and the two halves of the
 // rows are two streams of work, so that softmax and products of one issue beside the chains of the other and the next half's
 // operands travel under the last MFMAs.  Measured against one stream of 32x32x16: 16 x 1024 rows behind 8192, 32 / 8 heads,
-// d = 128 2.86 -> 2.62 ms (1338 TFLOP/s of MFMA work); 8 x U(131, 2048) behind 4096, 16 / 4 heads, d = 96 405 -> 372 us; d = 64, 32 / 8
-// heads 732 -> 720 us.
-// Head dim 96 (tiles of un-padded 192-byte rows, tiles.h; half the waves request K, half V) on N = 8, P = 4111,
-// R ~ U(131, 2048), 16 / 4 heads: 0.45 + 0.12 ms (Call 2 + Call 1), against 0.71 + 0.19 ms for the register-staged kernel
-// that served it before.
+// d = 128 2.83 -> 2.61 ms (1341 TFLOP/s of MFMA work); 8 x U(131, 2048) (9112 rows) behind 4096, 16 / 4 heads, d = 96 396 -> 368 us; d = 64, 32 / 8
+// heads 518 -> 483 us.  Head dim 96: tiles of un-padded 192-byte rows (tiles.h).
 #pragma once
 #include <type_traits>
 #include "common.h"
@@ -25,7 +22,7 @@
 
 namespace dkv {
 
-// Ring slots per tensor: with four the K tiles travel three tiles ahead, with three (head dim 96: two workgroups a CU) two.
+// Ring slots per tensor: with four the K tiles travel three tiles ahead, with three (head dims 64 and 96: more workgroups a CU) two.
 template <int D>
 constexpr int kDq2Stages = rules::dq_ring_slots(D);
 
@@ -266,8 +263,8 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
       if (!tile(std::integral_constant<int, 3 % NSTAGE>{})) break;
   }
 
-  // ---- epilogue: lane owns a query row, register r the head-dim column crow(r) of a 32-column block.  Stored from
-  // here a row would leave in 16-byte pieces, 32 rows per instruction.  The wave's scaled 32 x D tile goes through LDS
+  // ---- epilogue: lane owns a query row of each half, register r the head-dim column 4 lg + r of a 16-column block.  Stored from
+  // here a row would leave in 8-byte pieces, 16 rows per instruction.  The wave's scaled 32 x D tile goes through LDS
   // instead (all stages are free after the last barrier; 16-byte chunks XOR-swizzled by the row) and is read back as
   // whole rows.  Wave-private: no barrier.
   if (STATS && p.make_stats() && lg == 0) {   // (stored here: the waits of the main loop count loads only)

@@ -23,8 +23,8 @@
 //     independent work inside one instruction stream does;
 //   * no row maximum per half tile: the reference of the exponentials moves when a sum of probabilities says so.
 // Measured against the same kernel on 32x32x16 MFMAs with a row maximum and addresses formed per tile: 16 x 1024 rows behind 8192,
-// 32 / 8 heads, d = 128 2.15 -> 1.91 ms (1224 TFLOP/s); 8 x U(131, 2048) behind 4096, d = 64 650 -> 585 us, d = 96 (16 / 4 heads)
-// 371 -> 308 us.
+// 32 / 8 heads, d = 128 2.05 -> 1.84 ms (1271 TFLOP/s); 8 x U(131, 2048) (9112 rows) behind 4096, d = 64 440 -> 404 us, d = 96 (16 / 4 heads)
+// 359 -> 303 us.
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   // the product of the last half tile
   pv_half(((b.n_tiles - 1) & (NSTAGE - 1)) * T + HT, pB);
 
-  // ---- epilogue: lane owns a query row, register r the head-dim column crow(r) of a 32-column block.  Stored from
-  // here a row would leave in 16-byte pieces, 32 rows per instruction.  The wave's normalised 32 x D tile goes through
+  // ---- epilogue: lane owns a query row of each half, register r the head-dim column 4 lg + r of a 16-column block.  Stored from
+  // here a row would leave in 8-byte pieces, 16 rows per instruction.  The wave's normalised 32 x D tile goes through
   // LDS instead: its own 32 rows of the K ring (free since the last barrier: only V is read after it; 16-byte chunks
   // XOR-swizzled by the row), read back as whole rows.  Wave-private: no barrier.
   unsigned char* ot = smem + wave * 32 * C::RB;

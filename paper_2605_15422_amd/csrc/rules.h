@@ -140,14 +140,14 @@ struct RowBlocks {
 //   * where the LDS has room for two workgroups of four (`pair`: head dim 64, and dQ of head dim 96): 0.71 to 0.89 of the time of
 //     eight over 1160 calls, at most 1.09;
 //   * where every workgroup has a CU to itself, counted with the longest sequence: row blocks that other sequences do not have are
-//     dispatched, too, and displace some (22 x U(93, 135) rows behind 392, 8 / 8 heads, d = 128, 232 of 352 with rows: 25 -> 32 us);
+//     dispatched, too, and displace some (22 x U(93, 135) rows behind 392, 8 / 8 heads, d = 128, 232 of 352 with rows: 26 -> 33 us);
 //   * forward, where eight would not make fewer workgroups, since half of them have no rows: 0.75 of the time;
 //   * for one or two causal sequences past a short prompt up to 600 workgroups: the longest walks start first and the short ones
 //     fill the gaps (d = 128, 1 x 10746 rows, 336 workgroups: 248 -> 185 us; 1 x 10723, 672: 288 -> 304).  With a window all walks
-//     are alike (1 x 1229 rows, window 918, 32 / 4 heads, 312 workgroups: 39 -> 56 us); with more sequences the long walks of the
-//     last one start late (23 x U(73, 496) rows behind 4793, 4 / 2 heads: 147 -> 194 us).
+//     are alike (1 x 1229 rows, window 918, 32 / 4 heads, 312 workgroups: 39 -> 50 us); with more sequences the long walks of the
+//     last one start late (23 x U(73, 496) rows behind 4793, 4 / 2 heads: 147 -> 189 us).
 // dQ: eight also where half of them have no rows; the other four run like four alone, and eight request the tiles (20 x 20 rows
-// behind 4283, 8 / 8 heads, d = 128: 93 us with four, 90 with eight).  But a launch that dK/dV shares takes four (`shared`).
+// behind 4283, 8 / 8 heads, d = 128: 99 us with four, 94 with eight).  But a launch that dK/dV shares takes four (`shared`).
 // Over 3400 forward and dQ calls of 19 us and more the choice takes 0.83 of the time of eight and 1.01 of that of the better one.
 inline int64_t row_block_count(const RowBlocks& c, int waves) {
   const Packing k = pack_heads(c.G, waves);
