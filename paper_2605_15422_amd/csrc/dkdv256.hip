@@ -362,9 +362,9 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     const float* stat_lane = hi ? p.dvec : p.lse2;   // (the loader uses 64-bit lane addresses)
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
-    // blocks of 32 that see at least one key of the tile, query heads of the group innermost.  All state is
-    // wave-uniform and advanced incrementally.
-    // With a window the order is sequences, heads, row blocks: neighbouring key tiles then read a given (head, row
+    // blocks of 32 that see at least one key of the tile, from the last one down (RowWalk in kvsched.h), query heads of the
+    // group innermost.  All state is wave-uniform and advanced incrementally.
+    // With a window the order is sequences, heads, row blocks upwards: neighbouring key tiles then read a given (head, row
     // block) two intervals apart instead of 2 G, close enough for the second one to find it in the L2 (a tile reads
     // only the W + BN rows behind its keys, and without that reuse every tile fetches them from memory again).
     int seq = seq_lo, rb = 0, rb_lo = 0, rb_end = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
@@ -425,21 +425,21 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       if (LOCAL ? is_ctx : !decltype(first)::value || is_ctx) {
         const int key_hi = min(P, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W - P);
-        rb = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
+        rb_lo = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
         rb_end = rows > 0 ? (rows + HB - 1) / HB : 0;
         if (!LOCAL && seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
       } else {
         const int key_hi = min(R, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W);
-        rb = key0 / HB;
+        rb_lo = key0 / HB;
         rb_end = (rows + HB - 1) / HB;
       }
+      rb = LOCAL ? rb_lo : rb_end - 1;
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(q_ptr + grow * q_ts + (int64_t)hk * G * q_hs);
       do_row = uniform_ptr(do_ptr + grow * do_ts + (int64_t)hk * G * do_hs);
       st_row = (int64_t)hk * G * total + grow;
       if (LOCAL) {
-        rb_lo = rb;
         g = 0;
         q_cur = q_row;
         do_cur = do_row;
@@ -447,17 +447,17 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       }
     };
     auto next_group = [&]() __attribute__((always_inline)) {
-      if (++rb < rb_end) {
-        q_row += (int64_t)HB * q_ts;
-        do_row += (int64_t)HB * do_ts;
-        st_row += HB;
+      if (!LOCAL && --rb >= rb_lo) {
+        q_row -= (int64_t)HB * q_ts;
+        do_row -= (int64_t)HB * do_ts;
+        st_row -= HB;
         enter_group();
         return;
       }
       more = false;
       while (++seq < seq_hi) {
         init_seq(std::false_type{});
-        if (rb < rb_end) {
+        if (rb_lo < rb_end) {
           more = true;
           enter_group();
           return;
@@ -547,7 +547,6 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
             st_cur = st_row;
             enter_group();
           } else {
-            rb = rb_end - 1;   // (next_group steps past the last row block: on to the next sequence)
             next_group();
           }
         } else {
@@ -587,7 +586,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     if (!LOADER || wave == LOAD_WAVE) {
       for (; seq < seq_hi; ++seq) {
         init_seq(std::true_type{});
-        if (rb < rb_end) {
+        if (rb_lo < rb_end) {
           more = true;
           enter_group();
           break;

@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
     const int64_t stat_lane = hi ? 0 : (const char*)p.lse2 - (const char*)p.dvec;
 
     // ---- row-block schedule (kvsched.h); wave jb writes the headers of key subtile jb, the loader all four
-    RowWalk<HB> walk(p, hk, seq_hi);
+    RowWalk<HB, false> walk(p, hk, seq_hi);
     const SubtileVis<LOCAL> vis(is_ctx, key0 + (LOADER ? 0 : jb * 32), P, W);
     uint32_t flags = 0;   // of the current row block (the loader: byte i those of subtile i)
     auto new_rows = [&]() __attribute__((always_inline)) {

@@ -331,9 +331,9 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
     const float* stat_ptr = p.dvec;
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
-    // blocks of 16 that see at least one key of the tile, query heads of the group innermost.  All state is
-    // wave-uniform and advanced incrementally.
-    int seq = seq_lo, rb = 0, rb_end = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
+    // blocks of 16 that see at least one key of the tile, from the last one down (RowWalk in kvsched.h), query heads of the
+    // group innermost.  All state is wave-uniform and advanced incrementally.
+    int seq = seq_lo, rb = 0, rb_first = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
     const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
     int64_t st_row = 0, st_cur = 0;
     bool more = false;
@@ -359,29 +359,28 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
       row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
       R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
       if (is_ctx) {
-        rb = 0;
-        rb_end = R > 0 ? (R + HB - 1) / HB : 0;
+        rb_first = 0;
       } else {
-        rb = key0 / HB;
-        rb_end = (R + HB - 1) / HB;
+        rb_first = key0 / HB;
       }
+      rb = (R + HB - 1) / HB - 1;   // (below rb_first: none)
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
       do_row = uniform_ptr(p.dout.ptr + grow * do_ts + (int64_t)hk * G * do_hs);
       st_row = (int64_t)hk * G * total + grow;
     };
     auto next_group = [&]() __attribute__((always_inline)) {
-      if (++rb < rb_end) {
-        q_row += (int64_t)HB * q_ts;
-        do_row += (int64_t)HB * do_ts;
-        st_row += HB;
+      if (--rb >= rb_first) {
+        q_row -= (int64_t)HB * q_ts;
+        do_row -= (int64_t)HB * do_ts;
+        st_row -= HB;
         enter_group();
         return;
       }
       more = false;
       while (++seq < seq_hi) {
         init_seq();
-        if (rb < rb_end) {
+        if (rb >= rb_first) {
           more = true;
           enter_group();
           return;
@@ -441,7 +440,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
 
     for (; seq < seq_hi; ++seq) {
       init_seq();
-      if (rb < rb_end) {
+      if (rb >= rb_first) {
         more = true;
         enter_group();
         break;

@@ -75,13 +75,13 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
   const int q_tsb = own_sgpr((int)p.q.ts * 2), do_tsb = own_sgpr((int)p.dout.ts * 2);   // bytes per token
   const uint32_t ld_lds = smem_addr + (SPLIT ? (wave >> 1) * DO_RING + (wave & 1) * 16 * RB : wave * 1024);
   const int64_t stat_gap = (const char*)p.lse2 - (const char*)p.dvec;   // lanes 0-31 fetch LSE*log2e, lanes 32-63 D
-  RowWalk<HB> walk(p, hk, seq_hi);
+  RowWalk<HB, true> walk(p, hk, seq_hi);
   uint32_t flags = 0;
   auto ld_row = [&](int t) __attribute__((always_inline)) { return SPLIT ? (wave & 1) * 16 + split_row<D>(t, lane) : wave * RPI + lane / CPR; };
   auto ld_col = [&](int t) __attribute__((always_inline)) {
     return ((SPLIT ? split_pos<D>(t, lane) : lane % CPR) ^ swz16<D>(ld_row(t))) * 16;
   };
-  int row_step = HB, live = HDR_VALID | HDR_MASK;   // 0 past the end
+  int row_step = walk.DIR, live = HDR_VALID | HDR_MASK;   // 0 past the end
   auto new_rows = [&]() __attribute__((always_inline)) {
     flags = live & (HDR_VALID | (walk.nvalid < HB || (!is_ctx && walk.row0 < wkey0 + KEYS - 1) ? HDR_MASK : 0));
   };
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
     const uint64_t q = walk.q + (wrap ? walk.q_row : walk.q_head), dout = walk.dout + (wrap ? walk.do_row : walk.do_head),
                    st = walk.st + (wrap ? walk.st_row : walk.st_head);
     const int row0 = walk.row0 + (wrap ? row_step : 0);
-    if (__builtin_expect(row0 >= walk.row_end, 0)) {
+    if (__builtin_expect(!walk.within(row0), 0)) {
       const uint64_t lq = walk.q, ldo = walk.dout, lst = walk.st;
       const int lrow0 = walk.row0, R = walk.R;
       walk.next_seq([&]() __attribute__((always_inline)) { init_seq(std::false_type{}); });
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
         walk.row0 = lrow0;
         walk.R = R;
         walk.q_head = walk.q_row = walk.do_head = walk.do_row = walk.st_head = walk.st_row = 0;
-        walk.row_end = INT_MAX;
+        walk.row_end = INT_MIN;
         live = row_step = 0;
       }
     } else {
