@@ -566,7 +566,7 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
        reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  constexpr size_t smem = WITH_DQ && kDq2Smem<D> > kDkdv4Smem<D> ? kDq2Smem<D> : kDkdv4Smem<D>;
+  constexpr size_t smem = WITH_DQ && kDq2Smem<D, kDqWaves> > kDkdv4Smem<D> ? kDq2Smem<D, kDqWaves> : kDkdv4Smem<D>;
   auto kern = dkdv4_kernel<D, LOCAL, WITH_DQ>;
   const hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL, WITH_DQ>>(smem);
   if (e != hipSuccess) return e;
@@ -607,7 +607,7 @@ hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { 
 // 3540, 32 / 8 heads 161 -> 161, window 512, 1 x 3000, 8 / 8 heads 68.0 -> 66.7.  Causal rows alone stay at one a CU, where one launch for
 // 256 + 256 workgroups would be the better one, too (1 x 2048, 16 / 16 heads, d = 128 117 -> 82 us, d = 64 76 -> 54).
 int64_t dkdv4_dq_room(AttnParams p, int head_dim) {
-  if (head_dim > 128 || choose_waves(p, head_dim, true, true) != kDqWaves) return -1;
+  if (head_dim > 128 || choose_waves(p, head_dim, true, true).n != kDqWaves) return -1;
   const bool tails = p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs;
   return (tails ? 640 : 256) - response_workgroups(p) - dq_workgroups(p);
 }

@@ -3,8 +3,8 @@
 // evaluated per query block over all its visible key tiles (prompt tiles, then own-response tiles), so
 // dQ is accumulated in registers and written once: no fp32 dQ scratch, no atomics, no convert pass.
 //
-// Shape: 4 waves where two or three workgroups fit a CU (head dims 96 and 64), else 8, two per SIMD, or 4 by the rule of
-// row_block_waves (rules.h); each owns 32 rows, two halves of 16, with Q, dO fragments and the dQ^T accumulator in registers; K and
+// Shape: 4 waves, two workgroups a CU (three at head dim 64), or 8, two per SIMD, by the rule of row_block_waves (rules.h); each
+// owns 32 rows, two halves of 16, with Q, dO fragments and the dQ^T accumulator in registers; K and
 // V tiles of 64 keys travel global -> LDS directly (global_load_lds, two or three tiles ahead: no staging registers) into
 // two rings of swizzled tiles.  S^T = K Q^T and dP^T = V dO^T take 16-byte row operands from LDS; dQ^T += K^T dS^T takes K^T
 // through LDS transpose reads of the same row-major K tile.  A 64-key tile is consumed as two 32-key halves.
@@ -22,9 +22,11 @@
 
 namespace dkv {
 
-// Ring slots per tensor: with four the K tiles travel three tiles ahead, with three (head dims 64 and 96: more workgroups a CU) two.
-template <int D>
-constexpr int kDq2Stages = rules::dq_ring_slots(D);
+// Ring slots of K and V: with four the K tiles travel three tiles ahead, with three two; with two slots the V tiles travel one ahead.
+template <int D, int NW>
+constexpr int kDq2Stages = rules::dq_ring_slots(D, NW);
+template <int D, int NW>
+constexpr int kDq2VStages = rules::dq_v_slots(D, NW);
 
 // workgroup `bid` of `nblk`; STATS: it may have to form the row statistics (p.make_stats())
 template <int D, int NW, bool LOCAL, bool STATS>
@@ -32,7 +34,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   constexpr int BN = 64;
   constexpr int KS = D / 32, DB = D / 16, RB = 2 * D, CPR = D / 8;
   constexpr int T = BN * RB, HT = 32 * RB;         // bytes of a tile, of half a tile
-  constexpr int NSTAGE = kDq2Stages<D>, V_RING = NSTAGE * T;
+  constexpr int NSTAGE = kDq2Stages<D, NW>, NVST = kDq2VStages<D, NW>, V_RING = NSTAGE * T;
   extern __shared__ __attribute__((aligned(256))) unsigned char smem[];   // K ring | V ring (aligned: addresses are formed by XOR)
 
   QBlock b;
@@ -48,11 +50,11 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   const int row0 = b.blk_row0 + (wave % p.RSH) * 32;
   const bool wave_valid = row0 < R;
 
-  // (the first tiles are requested ahead of Q and dO: one latency for both)
+  // (the first tiles are requested ahead of Q and dO: one latency for both; with two slots the second V tile is requested by tile 0)
   TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
   constexpr int IPT = decltype(loader)::IPT;
   loader.request(0);
-  loader.request(1);
+  if (NVST > 2 || !loader.v) loader.request(1);
 
   bf16x8 qf[2][KS], dof[2][KS];   // rows row0 + i16 and row0 + 16 + i16
   float lse2[2];
@@ -139,12 +141,12 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
 #pragma unroll
     for (int i = 0; i < 2 * KS; ++i) ko[i] = lds_frag(k_at(i % KS) + at + i / KS * 16 * RB);
   };
-  // One half tile (32 keys) at offset `at` of both rings, whose K operands are in `ko`; requests those of the next half at `next`.
+  // One half tile (32 keys) at offset `at` of the K ring and `atv` of the V ring, whose K operands are in `ko`; requests those of the next half at `next`.
   // For each half h of the rows: S^T = K Q^T, dP^T - D = V dO^T - D (accumulator initialised to -D), dS^T = P (dP^T - D),
   // dQ^T += K^T dS^T.  The exponentials of h = 0 issue beside the score MFMAs of h = 1, those of h = 1 beside the dP MFMAs of
   // h = 0, and so on.  Two sets of operand registers: V is requested under the score MFMAs, K^T under the dP MFMAs (where K was),
   // the next half's K under the dQ MFMAs (where V was).
-  auto half_tile = [&](bool masked, int at, int next, bool is_ctx, int key0) __attribute__((always_inline)) {
+  auto half_tile = [&](bool masked, int at, int atv, int next, bool is_ctx, int key0) __attribute__((always_inline)) {
     f32x4 s[4], dp[4];   // tile 2 h + kh: keys 16 kh .. of rows 16 h ..
     float ev[16];        // score e = 8 h + 4 kh + r: key 16 kh + 4 lg + r
     bf16x8 vo[2 * KS], kt[DB], ds[2];
@@ -189,7 +191,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     };
     if (ONE) asm volatile("" : "+v"(kadr[0]), "+v"(vadr[0]), "+v"(tadr[0]));   // (what is formed from them is not kept in registers)
 #pragma unroll
-    for (int i = 0; i < NM; ++i) vo[i] = lds_frag(v_at(i % KS) + at + i / KS * 16 * RB);
+    for (int i = 0; i < NM; ++i) vo[i] = lds_frag(v_at(i % KS) + atv + i / KS * 16 * RB);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -236,21 +238,21 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   load_k(0);
   // tile `it` in slot U; false: it was the last one
   auto tile = [&](auto Uc) __attribute__((always_inline)) -> bool {
-    constexpr int U = decltype(Uc)::value, UN = (U + 1) % NSTAGE;
-    // the K tile requested goes into the slot that tile it-1 left at the last barrier, the V tile (two ahead) into its or an older one
-    const bool issued = loader.request(NSTAGE == 4 && loader.v ? (U + 2) % NSTAGE : (U + NSTAGE - 1) % NSTAGE);
+    constexpr int N = decltype(Uc)::value, U = N % NSTAGE, UN = (U + 1) % NSTAGE, UV = N % NVST;
+    // the K tile requested goes into the slot that tile it-1 left at the last barrier, the V tile (two ahead, or one) into its or an older one
+    const bool issued = loader.request(NVST == 2 && loader.v ? (UV + 1) % 2 : NSTAGE == 4 && loader.v ? (U + 2) % NSTAGE : (U + NSTAGE - 1) % NSTAGE);
     const bool plain = !(never_plain || it == ctx_masked || it >= dec_masked);
     const bool is_ctx = it < n_ctx_run;
     const int key0 = (is_ctx ? b.c0 + it : b.d0 + it - n_ctx_run) * BN;
     static_for<2>([&](auto Hc) __attribute__((always_inline)) {
-      constexpr int H = decltype(Hc)::value, at = U * T + H * HT, next = H ? UN * T : U * T + HT;
+      constexpr int H = decltype(Hc)::value, at = U * T + H * HT, atv = UV * T + H * HT, next = H ? UN * T : U * T + HT;
       const int k0 = key0 + H * 32;
       const bool active = plain || (wave_valid && tile_active<LOCAL, 32>(is_ctx, k0, row0, row0 + 31, P, W) && k0 < (is_ctx ? P : R));
-      if (__builtin_expect(active, 1)) half_tile(!plain && tile_needs_mask<LOCAL, 32>(is_ctx, k0, row0, P, R, W), at, next, is_ctx, k0);
+      if (__builtin_expect(active, 1)) half_tile(!plain && tile_needs_mask<LOCAL, 32>(is_ctx, k0, row0, P, R, W), at, atv, next, is_ctx, k0);
       else load_k(next);
     });
     // the next tile's V and the K tile after it must have landed
-    if (__builtin_expect(issued && (NSTAGE == 4 || loader.v), 1)) wait_vm<IPT>();
+    if (__builtin_expect(issued && NVST > 2 && (NSTAGE == 4 || loader.v), 1)) wait_vm<IPT>();
     else wait_vm<0>();
     __syncthreads();
     return ++it < b.n_tiles;
@@ -259,8 +261,12 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
     if (!tile(std::integral_constant<int, 0>{})) break;
     if (!tile(std::integral_constant<int, 1>{})) break;
     if (!tile(std::integral_constant<int, 2>{})) break;
-    if constexpr (NSTAGE > 3)
-      if (!tile(std::integral_constant<int, 3 % NSTAGE>{})) break;
+    if constexpr (NSTAGE > 3 || NVST == 2)
+      if (!tile(std::integral_constant<int, 3>{})) break;
+    if constexpr (NVST == 2) {
+      if (!tile(std::integral_constant<int, 4>{})) break;
+      if (!tile(std::integral_constant<int, 5>{})) break;
+    }
   }
 
   // ---- epilogue: lane owns a query row of each half, register r the head-dim column 4 lg + r of a 16-column block.  Stored from
@@ -299,7 +305,7 @@ __device__ __forceinline__ void dq2_workgroup(const AttnParams& p, int bid, int 
   }
 }
 
-template <int D>
-constexpr size_t kDq2Smem = kDq2Stages<D> * 2 * 64 * 2 * D;
+template <int D, int NW>
+constexpr size_t kDq2Smem = (kDq2Stages<D, NW> + kDq2VStages<D, NW>) * 64 * 2 * D;
 
 }  // namespace dkv

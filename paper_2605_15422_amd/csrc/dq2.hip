@@ -10,11 +10,12 @@ __global__ __launch_bounds__(NW * 64, D == 64 && NW == 4 ? 3 : 2) void dq2_kerne
 }
 
 template <int D, int NW, bool LOCAL>
-static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
+static hipError_t launch_dq2_t(AttnParams p, bool pair, hipStream_t st) {
   fill_packing(p, NW);
-  const size_t smem = kDq2Smem<D>;
+  constexpr size_t alone = 96 << 10;   // (of a CU's 160 KB: one workgroup)
+  const size_t smem = pair ? kDq2Smem<D, NW> : std::max(kDq2Smem<D, NW>, alone);
   auto kern = dq2_kernel<D, NW, LOCAL>;
-  hipError_t e = ensure_dynamic_lds<dq2_kernel<D, NW, LOCAL>>(smem);
+  hipError_t e = ensure_dynamic_lds<dq2_kernel<D, NW, LOCAL>>(std::max(kDq2Smem<D, NW>, alone));
   if (e != hipSuccess) return e;
   return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, NW * 64, [&](const AttnParams& q, unsigned n) {
     hipLaunchKernelGGL(kern, dim3(n), dim3(NW * 64), smem, st, q);
@@ -25,8 +26,9 @@ static hipError_t launch_dq2_t(AttnParams p, hipStream_t st) {
 template <int D>
 static hipError_t launch_dq2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
-  if (choose_waves(p, D, true) == 8) return local ? launch_dq2_t<D, 8, true>(p, st) : launch_dq2_t<D, 8, false>(p, st);
-  return local ? launch_dq2_t<D, 4, true>(p, st) : launch_dq2_t<D, 4, false>(p, st);
+  const rules::Waves w = choose_waves(p, D, true);
+  if (w.n == 8) return local ? launch_dq2_t<D, 8, true>(p, w.pair, st) : launch_dq2_t<D, 8, false>(p, w.pair, st);
+  return local ? launch_dq2_t<D, 4, true>(p, w.pair, st) : launch_dq2_t<D, 4, false>(p, w.pair, st);
 }
 
 hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st) {

@@ -4,8 +4,8 @@
 // are shared by all packed heads) and walks the two KV regions in logical order, prompt tiles then own-response tiles.
 // The scores are computed transposed, S^T = K Q^T, so that a lane owns one query row and exp(S^T) is already laid out
 // as the B operand of O^T += V^T P^T:
-//   * 4 waves at head dim 64 (two workgroups fit a CU), else 8, two per SIMD, or 4 by the rule of row_block_waves (rules.h);
-//     each owns 32 query rows, two halves of 16: Q fragments (B operands) and the O^T accumulator stay in registers;
+//   * 4 waves, two workgroups a CU (three at head dim 64), or 8, two per SIMD, by the rule of row_block_waves (rules.h); each owns
+//     32 query rows, two halves of 16: Q fragments (B operands) and the O^T accumulator stay in registers;
 //   * the 16x16x32 MFMA, each K or V operand read from LDS feeding the two halves.  These kernels run into the card's power
 //     limit, not into its matrix rate: with all inputs zero the 32x32x16 form of this kernel took 16.0 ms for 16 x U(1024, 2048)
 //     behind 32768, 32 / 4 heads, d = 128, and 20.5 with normal ones.  On normal values a bare loop of 16x16x32 MFMAs reaches
@@ -14,9 +14,13 @@
 //   * K and V tiles (64 keys) are staged row-major, un-padded, XOR-swizzled by row (tiles.h) so that both the 16-byte K
 //     operand reads and the transposing V reads are bank-conflict free; V^T operands come from ds_read_b64_tr_b16
 //     (LDS transpose read), so nothing is transposed on the way into LDS;
-//   * the tiles travel global -> LDS directly (global_load_lds) into two rings of four slots, K three tiles ahead (requested
-//     by the first half of the waves) and V two (the second half): no staging registers, no LDS stores, one barrier per tile;
-//     the loop is unrolled over the slots, so that every operand address is a register plus an immediate;
+//   * the tiles travel global -> LDS directly (global_load_lds) into two rings, K requested by the first half of the waves and V by
+//     the second: no staging registers, no LDS stores, one barrier per tile; the loop is unrolled over the slots, so that every
+//     operand address is a register plus an immediate.  Eight waves have four slots each, K three tiles ahead and V two.  Four have three
+//     for K, two tiles ahead, and two for V, one ahead, at d = 128 exactly half of a CU's LDS: there the second half of V tile i-1
+//     is still read beside the first half of tile i, so that halves of tiles are requested, V from the middle of one tile to
+//     the middle of the next.  With the start and end of one workgroup beside the tiles of the other and half the rows in the last
+//     round: 32 x U(17, 256) behind 517, 32 / 8 heads 97 -> 73 us, 4 x U(789, 1163) behind 5059 403 -> 331 (eight waves -> four, d = 128);
 //   * each wave runs a software pipeline over 32-key half tiles: while the VALU does the softmax of half g, the matrix pipe
 //     computes the scores of half g+1 and the P V product of half g-1.  Two waves per SIMD do not hide a wave's own MFMA ->
 //     softmax -> MFMA dependency chain on this chip (their phases drift together at every barrier); interleaving
@@ -34,20 +38,22 @@
 
 namespace dkv {
 
-template <int D, int NWAVES>
+template <int D, int NWAVES, bool PAIR>
 struct F2Cfg {
   static constexpr int NW = NWAVES, NT = NW * 64, BN = 64;
   static constexpr int KS = D / 32, DB = D / 16;   // k-steps of a score, 16-wide head-dim blocks
   static constexpr int RB = 2 * D;                 // row bytes
   static constexpr int CPR = D / 8;                // 16-byte chunks per row
   static constexpr int TILE_BYTES = BN * RB;
+  static constexpr bool HALVES = PAIR;             // halves of tiles are requested
+  static constexpr int NK = HALVES ? 3 : 4, NV = HALVES ? 2 : 4;
 };
 
-template <int D, int NW, bool LOCAL>
-__global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
-  using C = F2Cfg<D, NW>;
+template <int D, int NW, bool PAIR, bool LOCAL>
+__global__ __launch_bounds__(NW * 64, PAIR && D == 64 ? 3 : 2) void fwd2_kernel(const AttnParams p) {
+  using C = F2Cfg<D, NW, PAIR>;
   constexpr int BN = C::BN;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring [4 tiles] | V ring [4 tiles]
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // K ring | V ring
   QBlock b;
   if (!decode_qblock<BN>(p, b, blockIdx.x, gridDim.x)) return;
   make_uniform(b);
@@ -61,8 +67,8 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   const int row0 = b.blk_row0 + (wave % p.RSH) * 32;
   const bool wave_valid = row0 < R;
 
-  constexpr int NSTAGE = 4;                           // ring slots per tensor: K ring, then V ring
-  constexpr int V_RING = NSTAGE * C::TILE_BYTES;
+  constexpr int NK = C::NK, NV = C::NV;               // ring slots: K ring, then V ring
+  constexpr int V_RING = NK * C::TILE_BYTES;
 
   bf16x8 qf[2][C::KS];   // rows row0 + i16 and row0 + 16 + i16
   {
@@ -75,9 +81,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   }
   // (the first tiles are requested under the loads of Q, which leave first: behind 16 to 32 KB of tiles they are late)
   __builtin_amdgcn_sched_barrier(0);
-  TileLoader<D, NW> loader(p, b, wave, lane, smem, V_RING);
+  TileLoader<D, NW, C::HALVES ? 32 : 64> loader(p, b, wave, lane, smem, V_RING);
   loader.request(0);
-  loader.request(1);
+  if (!C::HALVES || !loader.v) loader.request(1);
+  if (C::HALVES && !loader.v) {   // two whole K tiles, half a V tile
+    loader.request(2);
+    loader.request(3);
+  }
   // consumed (and therefore waited for) here: no compiler-placed vector-memory wait inside the main loop
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -284,13 +294,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     pcur[1] = __builtin_bit_cast(bf16x8, w1);
   };
 
-  // ---- prologue: K0 V0 K1 V1 landed and published, scores of the first half, K2 requested.  The first step multiplies
-  // P = 0 with the second half of V slot 3: whatever is there has to be finite.
+  // ---- prologue: K0 V0 K1 V1 (four waves: the first half of V0) landed and published, scores of the first half, K2 requested.  The
+  // first step multiplies P = 0 with the second half of the last V slot: whatever is there has to be finite.
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = 0; i < 32 * C::CPR; i += C::NT)
     if (32 * C::CPR % C::NT == 0 || i + tid < 32 * C::CPR)
-      *reinterpret_cast<u32x4*>(smem + V_RING + 3 * C::TILE_BYTES + 32 * C::RB + (i + tid) * 16) = zero4;
+      *reinterpret_cast<u32x4*>(smem + V_RING + (NV - 1) * C::TILE_BYTES + 32 * C::RB + (i + tid) * 16) = zero4;
   wait_vm<0>();
   __syncthreads();
 
@@ -312,20 +322,28 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   for (int h = 0; h < 2; ++h) m_ref[h] = fmaxf(m_ref[h], row_max(sA, h) * c);
   bf16x8 pre[LEAD];   // operands of the first four slots of step (tile 0, half 0): K half 1 of tile 0
 #pragma unroll
-  for (int i = 0; i < LEAD; ++i) pre[i] = operand(HT, 3 * T + HT, i);
-  if (!loader.v) loader.request(2);
+  for (int i = 0; i < LEAD; ++i) pre[i] = operand(HT, (NV - 1) * T + HT, i);
+  if (!C::HALVES && !loader.v) loader.request(2);
 
   int it = 0;
   // tile `it` in slot U; false: it was the last one
   auto tile = [&](auto Uc) __attribute__((always_inline)) -> bool {
-    constexpr int U = decltype(Uc)::value, UN = (U + 1) % NSTAGE, UP = (U + NSTAGE - 1) % NSTAGE;
-    // K tile it+3 replaces K tile it-1, V tile it+2 replaces V tile it-2: both were last read before the barrier that ended
-    // tile it-1
-    const bool issued = loader.request(loader.v ? (U + 2) % NSTAGE : UP);
+    constexpr int N = decltype(Uc)::value, U = N % NK, UN = (N + 1) % NK, V = N % NV, VP = (N + NV - 1) % NV;
+    // K tile it+3 replaces K tile it-1, V tile it+2 replaces V tile it-2 (four waves: K tile it+2 replaces K tile it-1, the second half of
+    // V tile it that of V tile it-2 and the first half of V tile it+1 that of V tile it-1): all were last read before the barrier that
+    // ended tile it-1
+    bool issued = false;
+    if constexpr (C::HALVES) {
+      loader.request(loader.v ? 2 * V + 1 : 2 * ((N + 2) % NK));
+      loader.request(loader.v ? 2 * VP : 2 * ((N + 2) % NK) + 1);
+    } else {
+      issued = loader.request(loader.v ? (N + 2) % NV : (N + NK - 1) % NK);
+    }
     const bool masked = always_masked || it == ctx_masked || it >= dec_masked;
-    step(masked && it > 0, sA, sB, pB, pA, pre, U * T + HT, UP * T + HT, UN * T, U * T, it, 0);
-    step(masked, sB, sA, pA, pB, pre, UN * T, U * T, UN * T + HT, U * T + HT, it, 1);
-    // tiles it+2 (K) and it+1 (V) must have landed; the loads requested at the top of this tile may stay in flight
+    step(masked && it > 0, sA, sB, pB, pA, pre, U * T + HT, VP * T + HT, UN * T, V * T, it, 0);
+    step(masked, sB, sA, pA, pB, pre, UN * T, V * T, UN * T + HT, V * T + HT, it, 1);
+    // tiles it+2 (K) and it+1 (V; four waves: its first half) must have landed; the loads that eight waves requested at the top of this
+    // tile may stay in flight
     if (__builtin_expect(issued, 1)) wait_vm<decltype(loader)::IPT>();
     else wait_vm<0>();
     __syncthreads();
@@ -336,9 +354,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
     if (!tile(std::integral_constant<int, 1>{})) break;
     if (!tile(std::integral_constant<int, 2>{})) break;
     if (!tile(std::integral_constant<int, 3>{})) break;
+    if constexpr (C::HALVES) {
+      if (!tile(std::integral_constant<int, 4>{})) break;
+      if (!tile(std::integral_constant<int, 5>{})) break;
+    }
   }
   // the product of the last half tile
-  pv_half(((b.n_tiles - 1) & (NSTAGE - 1)) * T + HT, pB);
+  pv_half(((b.n_tiles - 1) & (NV - 1)) * T + HT, pB);
 
   // ---- epilogue: lane owns a query row of each half, register r the head-dim column 4 lg + r of a 16-column block.  Stored from
   // here a row would leave in 8-byte pieces, 16 rows per instruction.  The wave's normalised 32 x D tile goes through
@@ -373,13 +395,13 @@ __global__ __launch_bounds__(NW * 64, 2) void fwd2_kernel(const AttnParams p) {
   }
 }
 
-template <int D, int NW, bool LOCAL>
+template <int D, int NW, bool PAIR, bool LOCAL>
 static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
-  using C = F2Cfg<D, NW>;
+  using C = F2Cfg<D, NW, PAIR>;
   fill_packing(p, NW);
-  const size_t smem = 4 * 2 * C::TILE_BYTES;
-  auto kern = fwd2_kernel<D, NW, LOCAL>;
-  hipError_t e = ensure_dynamic_lds<fwd2_kernel<D, NW, LOCAL>>(smem);
+  const size_t smem = (C::NK + C::NV) * C::TILE_BYTES;
+  auto kern = fwd2_kernel<D, NW, PAIR, LOCAL>;
+  hipError_t e = ensure_dynamic_lds<fwd2_kernel<D, NW, PAIR, LOCAL>>(smem);
   if (e != hipSuccess) return e;
   return launch_sequences(p, (int64_t)p.MB * p.HC * p.Hk, C::NT, [&](const AttnParams& q, unsigned n) {
     hipLaunchKernelGGL(kern, dim3(n), dim3(C::NT), smem, st, q);
@@ -390,9 +412,11 @@ static hipError_t launch_fwd2_t(AttnParams p, hipStream_t st) {
 template <int D>
 static hipError_t launch_fwd2_d(const AttnParams& p, hipStream_t st) {
   const bool local = p.window > 0;
+  const rules::Waves w = choose_waves(p, D, false);
   if constexpr (D != 64)   // (which takes four always)
-    if (choose_waves(p, D, false) == 8) return local ? launch_fwd2_t<D, 8, true>(p, st) : launch_fwd2_t<D, 8, false>(p, st);
-  return local ? launch_fwd2_t<D, 4, true>(p, st) : launch_fwd2_t<D, 4, false>(p, st);
+    if (w.n == 8) return local ? launch_fwd2_t<D, 8, false, true>(p, st) : launch_fwd2_t<D, 8, false, false>(p, st);
+  if (!w.pair) return local ? launch_fwd2_t<D, 4, false, true>(p, st) : launch_fwd2_t<D, 4, false, false>(p, st);
+  return local ? launch_fwd2_t<D, 4, true, true>(p, st) : launch_fwd2_t<D, 4, true, false>(p, st);
 }
 
 hipError_t launch_fwd2(const AttnParams& p, int head_dim, hipStream_t st) {

@@ -112,14 +112,14 @@ __device__ __forceinline__ void make_uniform(QBlock& b) {
   b.n_tiles = __builtin_amdgcn_readfirstlane(b.n_tiles);
 }
 
-// Global -> LDS loads of the 64-key tiles of a row block's schedule, in order (head dims 64, 96, 128).  Half of the workgroup's waves
-// request the K tiles, half the V tiles; a wave keeps the address of its next tile, the keys of the region from there on and the
+// Global -> LDS loads of the 64-key tiles of a row block's schedule, in order (head dims 64, 96, 128), or of their halves (BN = 32).
+// Half of the workgroup's waves request the K tiles, half the V tiles; a wave keeps the address of its next tile, the keys of the region from there on and the
 // lane offsets of a full tile, so that a request is a handful of scalar instructions.  Instruction t of a wave covers 1 KB of its
 // rows; lane l lands at LDS chunk position l % CPR of its row and fetches the chunk that the swizzle stores there.  Keys past the
 // end of a region re-read the last key: their scores are masked like any invisible key.
-template <int D, int NW>
+template <int D, int NW, int BN = 64>
 struct TileLoader {
-  static constexpr int BN = 64, CPR = D / 8, TILE_BYTES = BN * 2 * D;
+  static constexpr int CPR = D / 8, TILE_BYTES = BN * 2 * D, PER_TILE = 64 / BN;
   static constexpr int LW = NW / 2;                            // waves per tensor
   static constexpr int IPT = TILE_BYTES / 1024 / LW;           // load instructions per wave and tile
   static constexpr int RPI = 1024 / (2 * D);                   // whole rows per instruction (not at head dim 96)
@@ -135,21 +135,22 @@ struct TileLoader {
   uint64_t ptr, own_ptr;       // next tile; first one of the response
   int keys, tsb, left;         // keys of the region from the next tile on, bytes per token, tiles to request
   int own_keys, own_tsb;
+  int ctx_left;                // (BN = 32) requests left in the prompt
   uint32_t voff[NV];
 
   // the V ring lies v_ring bytes behind the K ring at `smem`
   __device__ __forceinline__ TileLoader(const AttnParams& p, const QBlock& b, int wave, int lane_, const unsigned char* smem, int v_ring)
       : lane(lane_), lwave(wave % LW), v(wave >= LW),
-        left(b.n_tiles) {
+        left(b.n_tiles * PER_TILE), ctx_left((b.n_ctx - b.c0) * PER_TILE) {
     lds = __builtin_amdgcn_readfirstlane((uint32_t)reinterpret_cast<uintptr_t>(smem) + (v ? v_ring : 0) +
                                          lwave * (kSplitRow<D> ? IPT * 1024 : 1024));
     const TView own = v ? p.vd : p.kd, ctx = v ? p.vc : p.kc;
-    own_ptr = first_tile(own, (int64_t)b.row_begin + b.d0 * BN, b.hk);
+    own_ptr = first_tile(own, (int64_t)b.row_begin + b.d0 * 64, b.hk);
     own_tsb = (int)own.ts * 2;
-    own_keys = b.R - b.d0 * BN;
-    ptr = first_tile(ctx, (int64_t)b.ctx_off + b.c0 * BN, b.hk);
+    own_keys = b.R - b.d0 * 64;
+    ptr = first_tile(ctx, (int64_t)b.ctx_off + b.c0 * 64, b.hk);
     tsb = (int)ctx.ts * 2;
-    keys = b.c0 < b.n_ctx ? b.P - b.c0 * BN : 0;
+    keys = b.c0 < b.n_ctx ? b.P - b.c0 * 64 : 0;
     lane_offsets();
   }
   __device__ __forceinline__ static uint64_t first_tile(const TView& x, int64_t row, int hk) {
@@ -171,7 +172,7 @@ struct TileLoader {
   __device__ __forceinline__ bool request(uint32_t slot) {
     if (left == 0) return false;
     --left;
-    if (__builtin_expect(keys <= 0, 0)) {
+    if (__builtin_expect(BN == 64 ? keys <= 0 : ctx_left-- == 0, 0)) {
       ptr = own_ptr;
       tsb = own_tsb;
       keys = own_keys;
@@ -188,9 +189,12 @@ struct TileLoader {
       });
     } else {
       const int l = opaque(lane);   // (rows and columns formed here: no registers in between)
+      // (the second half of a tile whose first half holds the region's last key: that key is behind `base`)
+      const int last = __builtin_amdgcn_readfirstlane(keys - 1), back = BN == 64 ? 0 : min(last, 0);
+      const uint64_t at = base + (uint64_t)((int64_t)back * __builtin_amdgcn_readfirstlane(tsb));
       static_for<IPT>([&](auto Tc) __attribute__((always_inline)) {
         constexpr int t = decltype(Tc)::value;
-        dma16_at<t * STEP>(reinterpret_cast<const void*>(base), (uint32_t)(__umul24((unsigned)min(row(t, l), keys - 1), (unsigned)tsb) + col(t, l)), dst);
+        dma16_at<t * STEP>(reinterpret_cast<const void*>(at), (uint32_t)(__umul24((unsigned)min(row(t, l), last - back), (unsigned)tsb) + col(t, l)), dst);
       });
     }
     ptr += (uint64_t)(uint32_t)tsb * BN;
@@ -209,9 +213,9 @@ static inline void fill_packing(AttnParams& p, int nst) {
   p.MB = (p.max_rows + p.BMR - 1) / p.BMR;
 }
 
-static inline int choose_waves(const AttnParams& p, int head_dim, bool dq, bool shared = false) {
-  const rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk};
-  return rules::row_block_waves(c, head_dim == 64 || (head_dim == 96 && dq), dq, shared);
+static inline rules::Waves choose_waves(const AttnParams& p, int head_dim, bool dq, bool shared = false) {
+  const rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk, p.total};
+  return rules::choose_waves(c, head_dim, dq, shared);
 }
 
 }  // namespace dkv

@@ -133,12 +133,11 @@ struct RowBlocks {
   int ctx_len;             // prompt keys in front of them
   bool window;
   int G, kv_heads;
+  int total = 0;           // rows of all sequences
 };
 
-// Four waves or eight?  A wave that has its SIMD to itself takes 0.7 of the time per tile, and half the rows make twice as many
-// workgroups; but where only one workgroup fits a CU, four waves get less done on it than two per SIMD.  So four
-//   * where the LDS has room for two workgroups of four (`pair`: head dim 64, and dQ of head dim 96): 0.71 to 0.89 of the time of
-//     eight over 1160 calls, at most 1.09;
+// Four waves or eight where one workgroup has a CU to itself?  A wave that has its SIMD to itself takes 0.7 of the time per tile, and half
+// the rows make twice as many workgroups; but four waves get less done on a CU than two per SIMD.  So four
 //   * where every workgroup has a CU to itself, counted with the longest sequence: row blocks that other sequences do not have are
 //     dispatched, too, and displace some (22 x U(93, 135) rows behind 392, 8 / 8 heads, d = 128, 232 of 352 with rows: 26 -> 33 us);
 //   * forward, where eight would not make fewer workgroups, since half of them have no rows: 0.75 of the time;
@@ -147,8 +146,8 @@ struct RowBlocks {
 //     are alike (1 x 1229 rows, window 918, 32 / 4 heads, 312 workgroups: 39 -> 50 us); with more sequences the long walks of the
 //     last one start late (23 x U(73, 496) rows behind 4793, 4 / 2 heads: 147 -> 189 us).
 // dQ: eight also where half of them have no rows; the other four run like four alone, and eight request the tiles (20 x 20 rows
-// behind 4283, 8 / 8 heads, d = 128: 99 us with four, 94 with eight).  But a launch that dK/dV shares takes four (`shared`).
-// Over 3400 forward and dQ calls of 19 us and more the choice takes 0.83 of the time of eight and 1.01 of that of the better one.
+// behind 4283, 8 / 8 heads, d = 128: 97 us with four, 94 with eight).  But a launch that dK/dV shares takes four (`shared`).
+// `pair`: two workgroups of four share a CU, which beats eight (choose_waves).
 inline int64_t row_block_count(const RowBlocks& c, int waves) {
   const Packing k = pack_heads(c.G, waves);
   const int64_t rows = 32 * k.subtiles;
@@ -164,9 +163,49 @@ inline int row_block_waves(const RowBlocks& c, bool pair, bool dq, bool shared) 
   return c.n_seqs <= 2 && !c.window && 4 * (int64_t)c.ctx_len <= c.longest && n <= 600 ? 4 : 8;
 }
 
-// K and V tiles that a dQ workgroup of four waves has room for, head dims 64 / 96 / 128.  Three at d = 64, so that three workgroups fit the LDS
+// One causal sequence in two rounds of eight waves, a CU each: the longest walks pair up with the shortest.  Rows, heads, d: forward and
+// dQ with eight -> pairs of four in us; 3900, 32 / 8, 128: 114 -> 125, 163 -> 169; 16000, 8 / 2, 128: 441 -> 477, 624 -> 654; 7400, 16 / 4, 96:
+// 166 -> 179, 218 -> 237.  The other side: 13000, 8 / 8, 128 (408 workgroups of eight) 371 -> 322, 470 -> 437; 4600, 32 / 8, 128 (576) 171 -> 162,
+// 242 -> 219.
+inline bool two_rounds_of_eight(const RowBlocks& c) {
+  const int64_t n = row_block_count(c, 8);
+  return c.n_seqs == 1 && !c.window && 4 * (int64_t)c.ctx_len <= c.longest && n > 416 && n <= 2 * kCus;
+}
+// Forward over long walks in a dozen rounds and more: the card's power bounds it, pairs of four waves request every tile for half the rows,
+// and the last round is short beside the others.  Sustained, eight -> pairs: 16 x U(1024, 2048) behind 32768, 32 / 4 heads, d = 128
+// 18.6 -> 19.1 ms, d = 96 15.4 -> 15.9.  The other side: 16 x U(512, 1024) behind 32768, 32 / 8 heads, d = 128 (six rounds of eight) 6.46 -> 5.92 ms.
+inline bool many_long_walks(const RowBlocks& c) {
+  const Packing k = pack_heads(c.G, 8);
+  const int64_t per_block = (int64_t)(c.G / k.heads) * c.kv_heads;
+  return !c.window && c.ctx_len + (int64_t)c.longest / 2 >= 8192 && (c.total / (32 * k.subtiles) + c.n_seqs / 2) * per_block >= 12 * kCus;
+}
+
+// Eight waves, or four in workgroups that share a CU (`pair`: two of them, three at head dim 64) or have one each?  With two, one starts
+// and ends beside the other's tiles, and the last round of a launch is half as long: over 45 drawn calls of 2 to 3000 GFLOP at d = 128 and
+// 96 each (forward and dQ of both calls) pairs take 0.80 to 0.83 of the time of eight (0.55 to 1.04), over 11 long ones 0.94 (dQ of 16 x 1024
+// behind 8192, 32 / 8 heads, d = 128 2.85 -> 2.67 ms, forward 1.94 and 1.94).  A CU each where all of them have one, or where the longest walks
+// of one or two causal sequences start first (1 x 3000, 16 / 4 heads, d = 128, 376 workgroups: forward 60 us in pairs, 58 without, dQ 80 and 77).
+struct Waves {
+  int n;
+  bool pair;
+};
+inline Waves choose_waves(const RowBlocks& c, int head_dim, bool dq, bool shared) {
+  if (dq && head_dim < 128) {   // (whose rings leave room for two or three workgroups in any case)
+    const bool eight = head_dim == 96 && two_rounds_of_eight(c);
+    return {row_block_waves(c, !eight, dq, shared), true};
+  }
+  const int64_t n = row_block_count(c, 4);
+  const int alone = row_block_waves(c, false, dq, shared);
+  if (alone == 4 && (n <= kCus || n != row_block_count(c, 8))) return {4, false};
+  if (head_dim != 64 && (n <= kCus || two_rounds_of_eight(c) || (!dq && many_long_walks(c)))) return {8, false};
+  return {4, true};
+}
+
+// K and V tiles that a dQ workgroup has room for, head dims 64 / 96 / 128.  Three at d = 64, so that three workgroups fit the LDS
 // of a CU (their registers do, too): with four and two workgroups dQ of 8 x U(131, 2048) behind 4096, 32 / 8 heads takes 730 us instead of 686.
-constexpr int dq_ring_slots(int head_dim) { return head_dim == 128 ? 4 : 3; }
+// At d = 128 four waves have three slots for K, two tiles ahead, and two for V, one ahead: exactly half of a CU's LDS.
+constexpr int dq_ring_slots(int head_dim, int waves = 8) { return head_dim == 128 && waves == 8 ? 4 : 3; }
+constexpr int dq_v_slots(int head_dim, int waves) { return head_dim == 128 && waves == 4 ? 2 : dq_ring_slots(head_dim, waves); }
 
 // Copies of a prompt row that one workgroup of the replicating copy writes.  More of them read the row less often; but one
 // workgroup then writes for longer than its share of the whole copy takes, and the few that there are keep the others waiting.
