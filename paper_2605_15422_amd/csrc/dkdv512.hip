@@ -23,6 +23,7 @@
 #include "common.h"
 #include "dma.h"
 #include "kvsched.h"
+#include "kvstore.h"
 #include "launch.h"
 #include "tiles.h"
 
@@ -512,34 +513,18 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
       }
     }
 
-    // ---- epilogue: C layout -> lane owns head-dim column, register r owns key crow(r); the dK
-    // accumulator holds -dK / scale
-    const bool to_acc = is_ctx ? (p.dkc_acc != nullptr) : (p.dkd_acc != nullptr);
-    float* acc_k = is_ctx ? p.dkc_acc : p.dkd_acc;
-    float* acc_v = is_ctx ? p.dvc_acc : p.dvd_acc;
+    // ---- epilogue: C layout -> lane owns head-dim column, register r owns key crow(r)
+    const GradStore out(args_again(), is_ctx, (int64_t)key_row_begin + key0, min(region_len - key0, BN), hk, D);
+    auto store = [&](auto sums) __attribute__((always_inline)) {
+      constexpr bool S = decltype(sums)::value;
+      uint32_t at_k = 4 * hi * out.row_k + (jb * 32 + l32) * (S ? 4 : 2), at_v = 4 * hi * out.row_v + (jb * 32 + l32) * 2;
+      out.tile32<S>(at_k, at_v, [&](int r, uint32_t ak, uint32_t av) __attribute__((always_inline)) {
 #pragma unroll
-    for (int db = 0; db < NDB; ++db) {
-      const int dcol = (jb + 4 * db) * 32 + l32;
-      const f32x16 gks = dk[db], gvs = dv[db];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = key0 + crow(r, hi);
-        if (key >= region_len) continue;
-        const float gk = -gks[r] * p.scale, gv = gvs[r];
-        if (to_acc) {
-          const int64_t off = ((int64_t)(key_row_begin + key) * p.Hk + hk) * D + dcol;
-          unsafeAtomicAdd(acc_k + off, gk);
-          unsafeAtomicAdd(acc_v + off, gv);
-        } else if (is_ctx) {
-          p.dkc.ptr[(int64_t)(key_row_begin + key) * p.dkc.ts + (int64_t)hk * p.dkc.hs + dcol] = (u16)(pack2_bf16(gk, 0.f) & 0xffffu);
-          p.dvc.ptr[(int64_t)(key_row_begin + key) * p.dvc.ts + (int64_t)hk * p.dvc.hs + dcol] = (u16)(pack2_bf16(gv, 0.f) & 0xffffu);
-        } else {
-          const int64_t grow = key_row_begin + key;
-          p.dkd.ptr[grow * p.dkd.ts + (int64_t)hk * p.dkd.hs + dcol] = (u16)(pack2_bf16(gk, 0.f) & 0xffffu);
-          p.dvd.ptr[grow * p.dvd.ts + (int64_t)hk * p.dvd.hs + dcol] = (u16)(pack2_bf16(gv, 0.f) & 0xffffu);
-        }
-      }
-    }
+        for (int db = 0; db < NDB; ++db) out.put<S>(ak, av, db * 128, dk[db][r], dv[db][r]);
+      });
+    };
+    if (out.sums) store(std::true_type{});
+    else store(std::false_type{});
   }
 }
 

@@ -27,6 +27,7 @@
 #include "common.h"
 #include "dma.h"
 #include "kvsched.h"
+#include "kvstore.h"
 #include "launch.h"
 #include "tiles.h"
 
@@ -374,33 +375,30 @@ __global__ __launch_bounds__(256, 2) void dkdvw_kernel(const AttnParams p, int n
   }
   wait_vm<0>();   // no load may land in LDS that belongs to another workgroup by then
 
-  // ---- epilogue: lane owns a head-dim column, register r key 4 lg + r of a tile; the dK accumulator holds -dK / scale
-  const bool to_acc = is_ctx ? (p.dkc_acc != nullptr) : (p.dkd_acc != nullptr);
-  float* acc_k = is_ctx ? p.dkc_acc : p.dkd_acc;
-  float* acc_v = is_ctx ? p.dvc_acc : p.dvd_acc;
-  const TViewOut ok = is_ctx ? p.dkc : p.dkd, ov = is_ctx ? p.dvc : p.dvd;
+  // ---- epilogue: lane owns a head-dim column, register r key 4 lg + r of a tile
+  // (head dim 128, whose vector registers are full: with the arguments read again the allocator spills four of them inside the loop,
+  // with those already read none; 16 x 1024 behind 8192, 32 / 8 heads 3.7 ms, with spills 5.2)
+  const auto args = [&]() __attribute__((always_inline)) {
+    if constexpr (D == 128) return &p;
+    else return args_again();
+  };
+  const GradStore out(args(), is_ctx, (int64_t)key_row_begin + key0, min(region_len - key0, BN), hk, D);
+  auto store = [&](auto sums) __attribute__((always_inline)) {
+    constexpr bool S = decltype(sums)::value;
+    const int l = opaque(lane), first = wave * KEYS + 4 * (l >> 4), col = l & 15;   // (formed here: no registers across the loop)
+    uint32_t at_k = first * out.row_k + col * (S ? 4 : 2), at_v = first * out.row_v + col * 2;
 #pragma unroll
-  for (int kt = 0; kt < NKT; ++kt)
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      f32x4 gks = dk[kt][db], gvs = dv[kt][db];
-      const int dcol = 16 * db + i16;
+    for (int kt = 0; kt < NKT; ++kt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int key = wkey0 + 16 * kt + 4 * lg + r;
-        if (key >= region_len) continue;
-        const float gk = -gks[r] * p.scale, gv = gvs[r];
-        const int64_t row = key_row_begin + key;
-        if (to_acc) {
-          const int64_t off = (row * p.Hk + hk) * D + dcol;
-          unsafeAtomicAdd(acc_k + off, gk);
-          unsafeAtomicAdd(acc_v + off, gv);
-        } else {
-          ok.ptr[row * ok.ts + (int64_t)hk * ok.hs + dcol] = (u16)(pack2_bf16(gk, 0.f) & 0xffffu);
-          ov.ptr[row * ov.ts + (int64_t)hk * ov.hs + dcol] = (u16)(pack2_bf16(gv, 0.f) & 0xffffu);
-        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) out.put<S>(at_k, at_v, 16 * db, dk[kt][db][r], dv[kt][db][r]);
+        at_k += r == 3 ? 13 * out.row_k : out.row_k;
+        if (!S) at_v += r == 3 ? 13 * out.row_v : out.row_v;
       }
-    }
+  };
+  if (out.sums) store(std::true_type{});
+  else store(std::false_type{});
 }
 
 template <int D>
