@@ -68,7 +68,7 @@ struct Cfg {
   static constexpr int EBLK = D / 64;            // a consumer wave owns head-dim blocks jb and jb + EBLK
 };
 
-template <int D, bool LOCAL>
+template <int D, bool LOCAL, int DIR>
 __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
   using C = Cfg<D>;
   constexpr bool LOADER = C::LOADER;
@@ -363,15 +363,16 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     const float* stat_lane = hi ? p.dvec : p.lse2;   // (the loader uses 64-bit lane addresses)
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
-    // blocks of 32 that see at least one key of the tile, from the last one down (RowWalk in kvsched.h), query heads of the
-    // group innermost.  All state is wave-uniform and advanced incrementally.
-    // With a window the order is sequences, heads, row blocks upwards: neighbouring key tiles then read a given (head, row
+    // blocks of 32 that see at least one key of the tile (upwards or downwards, kvsched.h), query heads of the group innermost.
+    // All state is wave-uniform and advanced incrementally.
+    // With a window the order is sequences, heads, row blocks: neighbouring key tiles then read a given (head, row
     // block) two intervals apart instead of 2 G, close enough for the second one to find it in the L2 (a tile reads
     // only the W + BN rows behind its keys, and without that reuse every tile fetches them from memory again).
     int seq = seq_lo, rb = 0, rb_lo = 0, rb_end = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
     const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
     int64_t st_row = 0, st_cur = 0;
     bool more = false;
+    WalkDir<DIR, D> dir;
     uint32_t gflags[NKS] = {};   // header wave: flags of the key subtiles for the current row group
     // Row blocks [plain_lo, plain_hi) (first rows) of a windowed run see every key of the tile, none masked: in the response
     // region those whose first row is at or past the tile's last key and whose last row is still inside the window of its
@@ -426,21 +427,22 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       if (LOCAL ? is_ctx : !decltype(first)::value || is_ctx) {
         const int key_hi = min(P, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W - P);
-        rb_lo = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
+        rb = !LOCAL && decltype(first)::value ? kb.rb_lo : 0;
         rb_end = rows > 0 ? (rows + HB - 1) / HB : 0;
         if (!LOCAL && seq == seq_hi - 1) rb_end = min(rb_end, kb.rb_hi);
       } else {
         const int key_hi = min(R, key0 + BN) - 1;
         if (LOCAL) rows = min(R, key_hi + W);
-        rb_lo = key0 / HB;
+        rb = key0 / HB;
         rb_end = (rows + HB - 1) / HB;
       }
-      rb = LOCAL ? rb_lo : rb_end - 1;
+      if constexpr (DIR != WALK_UP) dir.enter(rb, rb_end, is_ctx, P, R, G);
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(q_ptr + grow * q_ts + (int64_t)hk * G * q_hs);
       do_row = uniform_ptr(do_ptr + grow * do_ts + (int64_t)hk * G * do_hs);
       st_row = (int64_t)hk * G * total + grow;
       if (LOCAL) {
+        rb_lo = rb;
         g = 0;
         q_cur = q_row;
         do_cur = do_row;
@@ -448,17 +450,17 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
       }
     };
     auto next_group = [&]() __attribute__((always_inline)) {
-      if (!LOCAL && --rb >= rb_lo) {
-        q_row -= (int64_t)HB * q_ts;
-        do_row -= (int64_t)HB * do_ts;
-        st_row -= HB;
+      if (dir.next(rb, rb_end)) {
+        q_row += dir.step() * HB * q_ts;
+        do_row += dir.step() * HB * do_ts;
+        st_row += dir.step() * HB;
         enter_group();
         return;
       }
       more = false;
       while (++seq < seq_hi) {
         init_seq(std::false_type{});
-        if (rb_lo < rb_end) {
+        if (dir.any(rb, rb_end)) {
           more = true;
           enter_group();
           return;
@@ -548,6 +550,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
             st_cur = st_row;
             enter_group();
           } else {
+            rb = rb_end - 1;   // (next_group steps past the last row block: on to the next sequence)
             next_group();
           }
         } else {
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
     if (!LOADER || wave == LOAD_WAVE) {
       for (; seq < seq_hi; ++seq) {
         init_seq(std::true_type{});
-        if (rb_lo < rb_end) {
+        if (dir.any(rb, rb_end)) {
           more = true;
           enter_group();
           break;
@@ -780,13 +783,15 @@ hipError_t launch_t(AttnParams p, hipStream_t st) {
   if (!Cfg<D>::LOADER && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  hipError_t e = ensure_dynamic_lds<dkdv256_kernel<D, LOCAL>>(Cfg<D>::SMEM_BYTES);
-  if (e != hipSuccess) return e;
-  const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
-  auto kern = dkdv256_kernel<D, LOCAL>;
-  return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
-    hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q);
-    return hipGetLastError();
+  return launch_direction(p, D, [&](auto dir) {
+    constexpr auto kern = dkdv256_kernel<D, LOCAL, LOCAL ? WALK_UP : decltype(dir)::value>;
+    const hipError_t e = ensure_dynamic_lds<kern>(Cfg<D>::SMEM_BYTES);
+    if (e != hipSuccess) return e;
+    const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
+    return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
+      hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q);
+      return hipGetLastError();
+    });
   });
 }
 

@@ -54,6 +54,7 @@ constexpr int IPB = HB / 4;                      // 1 KB load instructions (one 
 constexpr int HALF = (NBUF / 2) * STAGE_BYTES;   // second base register of every LDS operand (16-bit offset field)
 static_assert(STAGE_BYTES + HT_BYTES + 1024 < 65536, "immediate offsets");
 
+template <int DIR>
 __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -332,13 +333,14 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
     const float* stat_ptr = p.dvec;
 
     // ---- row-block schedule (Alg. 1, "Q-row blocks in causal support of K_n"): sequences of the tile, row
-    // blocks of 16 that see at least one key of the tile, from the last one down (RowWalk in kvsched.h), query heads of the
-    // group innermost.  All state is wave-uniform and advanced incrementally.
-    int seq = seq_lo, rb = 0, rb_first = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
+    // blocks of 16 that see at least one key of the tile (upwards or downwards, kvsched.h), query heads of the group innermost.
+    // All state is wave-uniform and advanced incrementally.
+    int seq = seq_lo, rb = 0, rb_end = 0, g = 0, R = 0, row_begin = 0, row0 = 0, nvalid = 0;
     const u16 *q_row = nullptr, *do_row = nullptr, *q_cur = nullptr, *do_cur = nullptr;
     int64_t st_row = 0, st_cur = 0;
     bool more = false;
     uint32_t gflags = 0;
+    WalkDir<DIR, D> dir;
     auto enter_group = [&]() __attribute__((always_inline)) {
       row0 = rb * HB;
       nvalid = min(HB, R - row0);
@@ -360,28 +362,30 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
       row_begin = p.cu ? __builtin_amdgcn_readfirstlane(p.cu[seq]) : 0;
       R = p.cu ? (__builtin_amdgcn_readfirstlane(p.cu[seq + 1]) - row_begin) : p.total;
       if (is_ctx) {
-        rb_first = 0;
+        rb = 0;
+        rb_end = R > 0 ? (R + HB - 1) / HB : 0;
       } else {
-        rb_first = key0 / HB;
+        rb = key0 / HB;
+        rb_end = (R + HB - 1) / HB;
       }
-      rb = (R + HB - 1) / HB - 1;   // (below rb_first: none)
+      if constexpr (DIR != WALK_UP) dir.enter(rb, rb_end, is_ctx, P, R, G);
       const int64_t grow = (int64_t)row_begin + rb * HB;
       q_row = uniform_ptr(p.q.ptr + grow * q_ts + (int64_t)hk * G * q_hs);
       do_row = uniform_ptr(p.dout.ptr + grow * do_ts + (int64_t)hk * G * do_hs);
       st_row = (int64_t)hk * G * total + grow;
     };
     auto next_group = [&]() __attribute__((always_inline)) {
-      if (--rb >= rb_first) {
-        q_row -= (int64_t)HB * q_ts;
-        do_row -= (int64_t)HB * do_ts;
-        st_row -= HB;
+      if (dir.next(rb, rb_end)) {
+        q_row += dir.step() * HB * q_ts;
+        do_row += dir.step() * HB * do_ts;
+        st_row += dir.step() * HB;
         enter_group();
         return;
       }
       more = false;
       while (++seq < seq_hi) {
         init_seq();
-        if (rb >= rb_first) {
+        if (dir.any(rb, rb_end)) {
           more = true;
           enter_group();
           return;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
 
     for (; seq < seq_hi; ++seq) {
       init_seq();
-      if (rb >= rb_first) {
+      if (dir.any(rb, rb_end)) {
         more = true;
         enter_group();
         break;
@@ -539,12 +543,15 @@ hipError_t launch_dkdv512(const AttnParams& p0, hipStream_t st) {
   if (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32))
     return hipErrorInvalidValue;
-  hipError_t e = ensure_dynamic_lds<dkdv512_kernel>(SMEM_BYTES);
-  if (e != hipSuccess) return e;
-  const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
-  return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
-    hipLaunchKernelGGL(dkdv512_kernel, dim3(n), dim3(512), SMEM_BYTES, st, q);
-    return hipGetLastError();
+  return launch_direction(p, D, [&](auto dir) {
+    constexpr auto kern = dkdv512_kernel<decltype(dir)::value>;
+    const hipError_t e = ensure_dynamic_lds<kern>(SMEM_BYTES);
+    if (e != hipSuccess) return e;
+    const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
+    return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
+      hipLaunchKernelGGL(kern, dim3(n), dim3(512), SMEM_BYTES, st, q);
+      return hipGetLastError();
+    });
   });
 }
 

@@ -139,17 +139,47 @@ struct SubtileVis {
   }
 };
 
+// The key tiles of a causal sequence begin at different rows but all end at the last one: walked downwards, tiles that run side by side
+// read the same rows of Q and dO at the same time, once from memory for all of an XCD.  For short sequences the caches do the same, and the
+// masked diagonal blocks are better beside the start of a walk than at its end; rows behind a prompt share their time with prompt tiles, which
+// read the same rows anyway.  Measured, upwards -> downwards: d = 512, 8 / 2 heads, 14336 causal rows (117 MB of Q and dO for a KV head) 5.68 ->
+// 4.33 ms; d = 256, 4 / 2 heads, 4 x U(93, 270) behind 17497 (36 MB) the layer 4.02 -> 3.79 ms, 16 / 4 heads, 5383 causal rows (22 MB) 1892 -> 1816
+// us; d = 512, 4 / 2 heads, 2 x U(500, 1000) behind 3000 (12 MB) 955 -> 940 us; d = 192, 12 / 4 heads, 8 x U(131, 2048) behind 4096 (9 MB) the same;
+// d = 256, 4 / 2 heads, 2 x U(500, 1000) behind 3000 (6 MB) 616 -> 625.  The line lies at 16 MB.  A sequence's direction depends on its own
+// length alone, so that calls for one and for several groups give the same bits.
+__host__ __device__ inline bool walk_down(int rows, int G, int D) { return (int64_t)rows * G * D >= 4 << 20; }
+
+// Direction of the walks of a kernel: up, down (one sequence whose length the host knows), or each sequence's own.  The last
+// takes scalar registers that the main loops are short of (head dim 512: 5 % slower than either), so that it serves only calls
+// of several sequences some of which may walk down.
+enum : int { WALK_UP = 0, WALK_DOWN = 1, WALK_OWN = 2 };
+template <int DIR, int D>
+struct WalkDir {
+  int s = DIR == WALK_DOWN ? -1 : 1;
+  // row blocks [rb, end) of a sequence; downwards: from the last one, and `end` is the one before the first
+  __device__ __forceinline__ void enter(int& rb, int& end, bool is_ctx, int P, int R, int G) {
+    if (DIR == WALK_OWN) s = !is_ctx && P == 0 && walk_down(R, G, D) ? -1 : 1;
+    if (step() < 0) {
+      const int first = rb;
+      rb = end - 1;
+      end = first - 1;
+    }
+  }
+  __device__ __forceinline__ int step() const { return DIR == WALK_OWN ? s : DIR == WALK_DOWN ? -1 : 1; }
+  __device__ __forceinline__ bool any(int rb, int end) const { return step() < 0 ? rb > end : rb < end; }
+  __device__ __forceinline__ bool next(int& rb, int end) const {
+    rb += step();
+    return any(rb, end);
+  }
+};
+
 // Row-block schedule of a key tile (Alg. 1, "Q-row blocks in causal support of K_n"): the sequences of the tile, row blocks
 // of HB rows that see at least one of its keys, query heads of the KV group innermost.  It runs beside the MFMAs in the
 // waves that make the requests, so a step is straight-line scalar code: byte addresses advance by one of two precomputed
 // strides, and only another row block and the end of a sequence branch.  The empty asm statements keep the state in scalar
 // registers: left alone, the compiler moves row counts to vector registers, which the twelve-wave kernel does not have.
-// DOWN: from a sequence's last row block to its first.  The key tiles of a causal sequence begin at different rows but all end
-// at the last one: walked downwards, tiles that run side by side read the same rows of Q and dO at the same time, once from memory
-// for all of an XCD.  Measured, upwards -> downwards: head dim 512, causal rows alone (14336, 8 / 2 heads) 5.68 -> 4.33 ms; the layers
-// of 8 x U(1025, 2048) behind 14336, 8 / 2 heads, d = 512 26.6 -> 24.5 ms and of 8 x U(131, 2048) behind 4111, 16 / 4 heads, d = 96
-// (dkdvw) 1760 -> 1743 us; head dim 192 the same.  dkdv4 is not bound by these reads and keeps the order in which a short walk's masked
-// diagonal blocks lie beside its start (8 x U(65, 256) behind 1021, 32 / 8 heads, d = 128: downwards the layer takes 1.5 % longer).
+// DOWN (dkdvw): from a sequence's last row block to its first, see walk_down; the layer of 8 x U(131, 2048) behind 4111, 16 / 4 heads,
+// d = 96 1760 -> 1743 us.  dkdv4 is not bound by these reads and walks up.
 template <int HB, bool DOWN>
 struct RowWalk {
   uint64_t q, dout, st;      // byte addresses of the block's first row of Q, dO and D (of its head)

@@ -2,7 +2,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 #include "common.h"
+#include "kvsched.h"
 
 namespace dkv {
 
@@ -85,6 +87,14 @@ inline hipError_t launch_key_tiles(const AttnParams& p, int64_t prompt, int64_t 
   q = p;
   q.n_ctx_tiles = 0;
   return launch_sequences(q, per_seq, threads, launch);
+}
+
+// dK/dV kernels that know both directions of a walk (kvsched.h)
+template <typename F>
+inline hipError_t launch_direction(const AttnParams& p, int head_dim, F launch) {
+  if (p.window > 0 || (p.ctx_len > 0 && !p.grp) || !walk_down(p.max_rows, p.G, head_dim)) return launch(std::integral_constant<int, WALK_UP>{});
+  if (p.cu) return launch(std::integral_constant<int, WALK_OWN>{});
+  return launch(std::integral_constant<int, WALK_DOWN>{});
 }
 
 }  // namespace dkv
