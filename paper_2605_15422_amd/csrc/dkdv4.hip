@@ -69,13 +69,33 @@ constexpr int kDqWaves = 4;   // of the dQ workgroups in a launch of both
 //   1 x 1500 rows, 8 / 8 heads, d = 128 (96 + 96)                                    90.0 -> 53.0 us; d = 96 75.9 -> 51.5
 //   1 x 512 rows, 32 / 8 heads, d = 128 (32 + 128)                                   84.3 -> 69.3 us
 //   2 x <= 64 rows behind a prompt of 64, 8 / 2 heads, d = 128 (6 + 8)               31.8 -> 25.1 us; d = 64 24.5 -> 24.0
+// The dQ workgroups come behind those of dK/dV, or before them where their walks are the long ones (first_kv: their number).
+template <int D, bool LOCAL>
+__device__ __forceinline__ void dkdv4_workgroup(const AttnParams& p, int bid, int n_kv);
+
 template <int D, bool LOCAL, bool WITH_DQ>
-__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p, int n_kv) {
-  if (WITH_DQ && (int)blockIdx.x >= n_kv) {
+__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams p, int n_kv, int first_kv) {
+  const int bid = (int)blockIdx.x - first_kv;
+  if (WITH_DQ && (unsigned)bid >= (unsigned)n_kv) {
     if (threadIdx.x >= kDqWaves * 64) return;   // (waves that have ended do not take part in barriers)
-    dq2_workgroup<D, kDqWaves, LOCAL, false>(p, blockIdx.x - n_kv, gridDim.x - n_kv);
+    dq2_workgroup<D, kDqWaves, LOCAL, false>(p, bid < 0 ? blockIdx.x : blockIdx.x - n_kv, gridDim.x - n_kv);
     return;
   }
+  dkdv4_workgroup<D, LOCAL>(p, bid, n_kv);
+}
+// The same with dQ workgroups of eight waves, for causal sequences whose dQ is more than the CUs beside long walks of dK/dV can take.
+template <int D>
+__global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_dq8_kernel(const AttnParams p, int n_kv) {
+  if ((int)blockIdx.x >= n_kv) {
+    if (threadIdx.x >= 512) return;
+    dq2_workgroup<D, 8, false, false>(p, blockIdx.x - n_kv, gridDim.x - n_kv);
+    return;
+  }
+  dkdv4_workgroup<D, false>(p, blockIdx.x, n_kv);
+}
+
+template <int D, bool LOCAL>
+__device__ __forceinline__ void dkdv4_workgroup(const AttnParams& p, int bid, int n_kv) {
   constexpr int BN = 128, HB = 32;                 // keys per workgroup, query rows per block
   constexpr int KS = D / 16, DSUB = D / 32, RB = 2 * D, CPR = D / 8;
   constexpr int HT_BYTES = HB * RB;                // one Q or dO row block
@@ -103,7 +123,7 @@ __global__ __launch_bounds__(kWaves<D> * 64) void dkdv4_kernel(const AttnParams 
   const int W = p.window;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, n_kv)) return;
+  if (!decode_kvblock(p, BN, HB, kb, bid, n_kv)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;
@@ -538,13 +558,14 @@ static int64_t prompt_workgroups(const AttnParams& p) {
 static int64_t response_workgroups(const AttnParams& p) {
   return (int64_t)p.n_seqs * ((p.max_rows + kKeyTile - 1) / kKeyTile) * p.Hk;
 }
-static int64_t dq_workgroups(AttnParams& p) {
-  fill_packing(p, kDqWaves);
+static int64_t dq_workgroups(AttnParams& p, int waves) {
+  fill_packing(p, waves);
   return (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
 }
 
-template <int D, bool LOCAL, bool WITH_DQ>
-static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
+// DQ_WAVES: of the dQ workgroups in the launch (0: none); dq_first: they come before those of dK/dV
+template <int D, bool LOCAL, int DQ_WAVES>
+static hipError_t launch_dkdv4_t(AttnParams p, bool dq_first, hipStream_t st) {
   p.n_ctx_tiles = (p.ctx_len + kKeyTile - 1) / kKeyTile;
   p.n_dec_tiles = (p.max_rows + kKeyTile - 1) / kKeyTile;
   if (p.n_split < 1) p.n_split = 1;
@@ -552,51 +573,53 @@ static hipError_t launch_dkdv4_t(AttnParams p, hipStream_t st) {
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
        reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
     return hipErrorInvalidValue;
-  constexpr size_t smem = WITH_DQ && kDq2Smem<D, kDqWaves> > kDkdv4Smem<D> ? kDq2Smem<D, kDqWaves> : kDkdv4Smem<D>;
-  auto kern = dkdv4_kernel<D, LOCAL, WITH_DQ>;
-  const hipError_t e = ensure_dynamic_lds<dkdv4_kernel<D, LOCAL, WITH_DQ>>(smem);
+  constexpr size_t dq_smem = DQ_WAVES == 0 ? 0 : kDq2Smem<D, DQ_WAVES == 8 ? 8 : kDqWaves>, smem = std::max(dq_smem, kDkdv4Smem<D>);
+  constexpr auto kern = [] {
+    if constexpr (DQ_WAVES == 8) return dkdv4_dq8_kernel<D>;
+    else return dkdv4_kernel<D, LOCAL, DQ_WAVES != 0>;
+  }();
+  const hipError_t e = ensure_dynamic_lds<kern>(smem);
   if (e != hipSuccess) return e;
   constexpr int threads = kWaves<D> * 64;
-  if constexpr (WITH_DQ) {   // (few workgroups: dkdv4_dq_fits)
-    const unsigned n_kv = (unsigned)(prompt_workgroups(p) + response_workgroups(p)), n = n_kv + (unsigned)dq_workgroups(p);
+  if constexpr (DQ_WAVES != 0) {   // (few workgroups: dkdv4_dq_fits)
+    const unsigned n_kv = (unsigned)(prompt_workgroups(p) + response_workgroups(p)), n = n_kv + (unsigned)dq_workgroups(p, DQ_WAVES);
     if (n == 0) return hipSuccess;
-    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv);
+    if constexpr (DQ_WAVES == 8) hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv);
+    else hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv, dq_first ? (int)(n - n_kv) : 0);
     return hipGetLastError();
   }
   return launch_key_tiles(p, prompt_workgroups(p), (int64_t)p.n_dec_tiles * p.Hk, threads, [&](const AttnParams& q, unsigned n) {
-    hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, q, (int)n);
+    if constexpr (DQ_WAVES != 8) hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, q, (int)n, 0);
     return hipGetLastError();
   });
 }
 
-template <bool WITH_DQ>
-static hipError_t launch_dkdv4_d(const AttnParams& p, int head_dim, hipStream_t st) {
-  const bool local = p.window > 0;
+template <int DQ_WAVES>
+static hipError_t launch_dkdv4_d(const AttnParams& p, int head_dim, bool dq_first, hipStream_t st) {
+  constexpr bool L = DQ_WAVES != 8;   // (which knows no window)
+  const bool local = L && p.window > 0;
   switch (head_dim) {
-    case 64:  return local ? launch_dkdv4_t<64, true, WITH_DQ>(p, st) : launch_dkdv4_t<64, false, WITH_DQ>(p, st);
-    case 96:  return local ? launch_dkdv4_t<96, true, WITH_DQ>(p, st) : launch_dkdv4_t<96, false, WITH_DQ>(p, st);
-    case 128: return local ? launch_dkdv4_t<128, true, WITH_DQ>(p, st) : launch_dkdv4_t<128, false, WITH_DQ>(p, st);
+    case 64:  return local ? launch_dkdv4_t<64, L, DQ_WAVES>(p, dq_first, st) : launch_dkdv4_t<64, false, DQ_WAVES>(p, dq_first, st);
+    case 96:  return local ? launch_dkdv4_t<96, L, DQ_WAVES>(p, dq_first, st) : launch_dkdv4_t<96, false, DQ_WAVES>(p, dq_first, st);
+    case 128: return local ? launch_dkdv4_t<128, L, DQ_WAVES>(p, dq_first, st) : launch_dkdv4_t<128, false, DQ_WAVES>(p, dq_first, st);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<false>(p, head_dim, st); }
-hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<true>(p, head_dim, st); }
-
-// One launch where every workgroup of both kernels has one of the 256 CUs to itself: all calls measured there gained (1.02 to
-// 1.7 times, head dims 64, 96 and 128).  With more workgroups what can be won are the tails, against the preprocess.  Up to 2.5 workgroups a CU there is
-// such a tail where the responses are long for their prompt, since a response's tiles carry work that falls from the first to the
-// last; a long prompt's tiles are cut into full rounds of even parts.  Measured over 110 drawn calls with such responses: those
-// whose launches changed became 1.02 to 1.56 times faster, none slower: 2 x U(206, 654) behind 807, 12 / 4 heads, d = 128, 103 ->
-// 69 us; 5 x U(369, 431) behind 1158, 8 / 2 heads, d = 128, 112 -> 84.  The other side: 776 + 704 workgroups (8 x U(500, 1500) behind 300,
-// 8 / 8 heads), d = 96, 149 -> 167 us; nothing to be won: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128 113.5 -> 114.0, 2 x U(74, 105) behind
-// 3540, 32 / 8 heads 161 -> 161, window 512, 1 x 3000, 8 / 8 heads 68.0 -> 66.7.  Causal rows alone stay at one a CU, where one launch for
-// 256 + 256 workgroups would be the better one, too (1 x 2048, 16 / 16 heads, d = 128 117 -> 82 us, d = 64 76 -> 54).
-int64_t dkdv4_dq_room(AttnParams p, int head_dim) {
-  if (head_dim > 128 || choose_waves(p, head_dim, true, true).n != kDqWaves) return -1;
-  const bool tails = p.ctx_len > 0 && !p.grp && p.window == 0 && p.total >= 0.3 * p.ctx_len * p.n_seqs;
-  return (tails ? 640 : 256) - response_workgroups(p) - dq_workgroups(p);
+// The dQ workgroups beside those of dK/dV (rules.h)
+static rules::Beside dq_beside(AttnParams p, int head_dim) {
+  if (head_dim > 128) return {};
+  p.n_split = 1;
+  const rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk, p.total};
+  return rules::dq_beside(c, p.grp && p.n_groups > 1, prompt_workgroups(p), response_workgroups(p));
 }
+
+hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<0>(p, head_dim, false, st); }
+hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) {
+  const rules::Beside b = dq_beside(p, head_dim);
+  return b.waves == 8 ? launch_dkdv4_d<8>(p, head_dim, false, st) : launch_dkdv4_d<kDqWaves>(p, head_dim, b.first, st);
+}
+int64_t dkdv4_dq_room(const AttnParams& p, int head_dim) { return dq_beside(p, head_dim).room; }
 bool dkdv4_dq_fits(const AttnParams& p, int head_dim) { return prompt_workgroups(p) <= dkdv4_dq_room(p, head_dim); }
 
 }  // namespace dkv

@@ -16,7 +16,7 @@ hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
 // dK/dV of Call 2 at head dims 96 and 128 without a window, two workgroups a CU
 hipError_t launch_dkdvw(const AttnParams& p, int head_dim, hipStream_t st);
 // both in one launch (row statistics given), for calls with few workgroups: up to dkdv4_dq_room prompt workgroups
-int64_t dkdv4_dq_room(AttnParams p, int head_dim);
+int64_t dkdv4_dq_room(const AttnParams& p, int head_dim);
 bool dkdv4_dq_fits(const AttnParams& p, int head_dim);
 hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st);
 // kernels for head dims 192 / 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)

@@ -201,6 +201,45 @@ inline Waves choose_waves(const RowBlocks& c, int head_dim, bool dq, bool shared
   return {4, true};
 }
 
+// ---- Backward of head dims 64 / 96 / 128: dK/dV and dQ in one launch ----
+// Behind a preprocess that forms the row statistics the two are independent, a workgroup of either has its CU to itself, and the tails
+// of both are filled.
+struct Beside {
+  int waves = 0;          // of the dQ workgroups
+  bool first = false;     // they come before those of dK/dV
+  int64_t room = -1;      // up to so many prompt workgroups share the launch
+};
+// One launch
+//   * where every workgroup of both kernels has one of the 256 CUs to itself: all calls measured there gained (1.02 to 1.7 times);
+//   * up to 960 workgroups where the responses are long for their prompt: a response's tiles carry work that falls from the first to the
+//     last.  2 x U(206, 654) behind 807, 12 / 4 heads, d = 128, 103 -> 69 us; 2 x U(1601, 1891) behind 567 (500 workgroups) 209 -> 155;
+//     2 x U(791, 2882) behind 185 (744) 265 -> 204; 8 x U(681, 2345) behind 733, 4 / 2 heads, d = 96 (908) 201 -> 181.  The other side: 14 x
+//     U(1283, 2013) behind 2863, 4 / 2 heads, d = 96 (1390) 554 -> 576 us; short responses: 12 x U(67, 112) behind 1602, 16 / 4 heads, d = 128
+//     113.5 -> 114.0, 19 x U(128, 266) behind 1291, 12 / 4 heads, d = 64 118 -> 124;
+//   * few rows behind a long prompt, up to 320 dQ workgroups, whose walks are at least a third of those of the prompt tiles: dQ first, the
+//     prompt tiles on the other CUs.  110 calls take 0.62 to 1.04 of their time, 0.85 together: 4 x U(50, 138) behind 12628, 32 / 4 heads, d = 96 393
+//     -> 287 us, 1 x 298 behind 4336, 32 / 8 heads, d = 64 133 -> 82.  The other side: 17 x U(119, 150) behind 31574, 32 / 8 heads, d = 64
+//     (680 dQ workgroups) 2459 -> 2729 us; walks of a sixth: 8 x U(91, 152) behind 1631, 32 / 4 heads, d = 96 134 -> 146;
+//   * one causal sequence up to 416 key tiles: its first tile's walk is twice the mean.  With eight waves a dQ workgroup from 240 tiles on (dQ
+//     is too much work for the CUs that dK/dV leaves idle), if eight make enough workgroups.  1 x 5000, 32 / 8 heads, d = 128 (320 tiles) 778 ->
+//     664 us (four waves 716), 1 x 4111, 16 / 4, d = 96 (132) 434 -> 352 (359 with eight), 1 x 3000, 8 / 8, d = 128 (192) 149 -> 89.  The other
+//     side: 7200, 32 / 8, d = 64 (456) 769 -> 784.
+inline Beside dq_beside(const RowBlocks& c, bool several_groups, int64_t prompt_tiles, int64_t resp_tiles) {
+  const int64_t n4 = row_block_count(c, 4);
+  if (c.n_seqs == 1 && c.ctx_len == 0 && !several_groups && !c.window) {
+    if (resp_tiles + n4 <= kCus) return {4, false, 0};
+    if (resp_tiles > 416) return {};
+    return {resp_tiles >= 240 && row_block_count(c, 8) >= 240 ? 8 : 4, false, 0};
+  }
+  const bool one_prompt = c.ctx_len > 0 && !several_groups && !c.window;
+  const bool tails = one_prompt && c.total >= 0.3 * c.ctx_len * c.n_seqs;
+  const int64_t room = (tails ? 960 : kCus) - resp_tiles - n4;
+  // walks in intervals of dK/dV (64 keys of dQ: 1.2)
+  const double dq_walk = 10 + ((double)c.ctx_len + c.longest) / 53, part = c.total / 32.0 * c.G + c.n_seqs * (c.G / 2.0);
+  if (one_prompt && room < prompt_tiles && n4 <= 320 && 3 * dq_walk >= part) return {4, true, 1 << 20};
+  return {4, false, room};
+}
+
 // K and V tiles that a dQ workgroup has room for, head dims 64 / 96 / 128.  Three at d = 64, so that three workgroups fit the LDS
 // of a CU (their registers do, too): with four and two workgroups dQ of 8 x U(131, 2048) behind 4096, 32 / 8 heads takes 730 us instead of 686.
 // At d = 128 four waves have three slots for K, two tiles ahead, and two for V, one ahead: exactly half of a CU's LDS.

@@ -1,0 +1,65 @@
+"""dQ beside dK/dV in one launch past one workgroup a CU: one causal sequence with dQ workgroups of four and of eight waves, and few rows
+behind a long prompt with dQ first.  Bit for bit what the two kernels give in launches of their own (prompt gradients: sums of
+parts, to rounding)."""
+import numpy as np
+import pytest
+
+from paper_2605_15422_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _apart(s, run):
+    from paper_2605_15422_amd import binding as B
+    out = []
+    for flags in ((0,), (B.FLAG_SKIP_DKDV, B.FLAG_SKIP_PRE | B.FLAG_SKIP_DQ)):
+        out.append(run([type(s).from_buffer_copy(bytes(s)) for _ in flags], flags))
+    return out
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("H,Hk,P", [(16, 4, 2081), (8, 8, 2500), (32, 8, 3873), (8, 2, 16350), (32, 8, 6657)])
+def test_one_causal_sequence(d, H, Hk, P):
+    import torch
+    from paper_2605_15422_amd import binding as B, runner
+    print("case causal beside", d, H, Hk, P, flush=True)
+    dg = B.upload(W.make_workload(W.Shape("beside", 1, P, 0, 0, H, Hk, d, 0, seed=400 + d), resp_lens=np.asarray([0])))
+    b = runner.alloc(dg)
+    runner.forward(dg, b, call2=False)
+
+    def run(shapes, flags):
+        o = [torch.full_like(x, float("nan")) for x in (dg.q_c, dg.k_c, dg.v_c)]
+        b.ws_ctx_bwd.fill_(0xFF)
+        for s, f in zip(shapes, flags):
+            s.flags = f
+            B.dualkv_ctx_bwd(s, dg.do_c, b.o_c, b.lse_c, dg.q_c, dg.k_c, dg.v_c, *o, None, None, b.ws_ctx_bwd)
+        torch.cuda.synchronize()
+        return o
+    for x, y in zip(*_apart(dg.shape_c, run)):
+        assert not torch.isnan(x).any() and torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("H,Hk,P,lens", [(32, 8, 4300, [20, 33]), (12, 4, 9000, [0, 1, 130]), (8, 8, 4097, [64] * 7), (32, 4, 8321, [97])])
+def test_few_rows_behind_a_long_prompt(d, H, Hk, P, lens):
+    import torch
+    from paper_2605_15422_amd import binding as B, runner
+    print("case dQ first", d, H, Hk, P, lens, flush=True)
+    dg = B.upload(W.make_workload(W.Shape("first", len(lens), P, 0, 0, H, Hk, d, 0, seed=500 + d), resp_lens=np.asarray(lens)))
+    b = runner.alloc(dg)
+    runner.forward(dg, b, call1=False)
+
+    def run(shapes, flags):
+        o = [torch.full_like(x, float("nan")) for x in (dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d)]
+        b.ws_bwd.fill_(0xFF)
+        for s, f in zip(shapes, flags):
+            s.flags = f
+            B.dualkv_bwd(s, dg.do_d, b.o_d, b.lse_d, dg.q_d, dg.k_c, dg.v_c, dg.k_d, dg.v_d, dg.cu_dev, dg.cu_host, *o, None, None, b.ws_bwd)
+        torch.cuda.synchronize()
+        return o
+    one, two = _apart(dg.shape_c, run)
+    for k, (x, y) in enumerate(zip(one, two)):
+        assert not torch.isnan(x).any()
+        # (fp32 sums in another order, one rounding to bf16)
+        if k in (1, 2): assert (x.double() - y.double()).norm() <= 2.0**-9 * y.double().norm()
+        else: assert torch.equal(x.view(torch.int16), y.view(torch.int16))
