@@ -118,6 +118,16 @@ dkv::rules::PromptTiles prompt_tiles(const dualkv_shape* s, const Groups& g) {
   return c;
 }
 
+// dQ in the launch of dK/dV?
+dkv::rules::Beside dq_beside(AttnParams p, int d) {
+  p.n_split = 1;
+  const dkv::KeyTiles t = dkv::key_tiles(p, dkv::dkdv_key_tile(d));
+  const dkv::rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk, p.total};
+  const bool groups = p.grp && p.n_groups > 1;
+  const int64_t resp = p.n_seqs * t.per_seq;
+  return d <= 128 ? dkv::rules::dq_beside(c, groups, t.prompt, resp) : dkv::rules::dq_beside_wide(c, groups, d == 512, resp);
+}
+
 // parts of a prompt tile to launch (with a window a tile sees few rows of each sequence: whole sequences, as many as fill the chip)
 // and whether the kernel of which two workgroups share a CU takes the call's dK/dV
 struct CtxParts {
@@ -127,7 +137,7 @@ struct CtxParts {
 CtxParts ctx_parts(const AttnParams& p, const dualkv_shape* s, const Groups& g) {
   dkv::rules::PromptTiles c = prompt_tiles(s, g);
   if (s->window > 0) return {dkv::rules::most_parts(c), false};
-  c.shared = dkv::dkdv4_dq_room(p, s->head_dim);
+  c.shared = dq_beside(p, s->head_dim).room;
   const int n = dkv::rules::prompt_parts(c);
   // (two terms: a call for several groups and one for each of them give the same bits)
   if ((s->head_dim == 96 || s->head_dim == 128) && (s->flags & DUALKV_FLAG_ACCUM_CTX_F32)) {
@@ -209,9 +219,11 @@ hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, bool pair
   hipError_t e = hipSuccess;
   if (do_pre && do_dq && !overlap(p.dq, p.q, rows, p.H, d) && !overlap(p.dq, p.dout, rows, p.H, d) &&
       !overlap(p.dq, p.o, rows, p.H, d)) {
-    if (do_dkdv && !pair && dkv::dkdv4_dq_fits(p, d)) {
+    const dkv::rules::Beside b = dq_beside(p, d);
+    if (do_dkdv && !pair && dkv::key_tiles(p, dkv::dkdv_key_tile(d)).prompt <= b.room) {
       if ((e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
-      return dkv::launch_dkdv4_dq(p, d, st);
+      if (d <= 128) return dkv::launch_dkdv4_dq(p, d, b.waves, b.first, st);
+      return d <= 256 ? dkv::launch_dkdv256_dq(p, d, b.first, st) : dkv::launch_dkdv512_dq(p, b.first, st);
     }
     if ((e = run_dq(p, d, st)) != hipSuccess) return e;
     return do_dkdv ? run_dkdv(p, d, pair, st) : hipSuccess;

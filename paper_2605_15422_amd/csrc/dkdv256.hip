@@ -28,6 +28,7 @@
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
+#include "dq256.h"
 #include "kvsched.h"
 #include "kvstore.h"
 #include "launch.h"
@@ -68,8 +69,9 @@ struct Cfg {
   static constexpr int EBLK = D / 64;            // a consumer wave owns head-dim blocks jb and jb + EBLK
 };
 
+// workgroup `bid` of `nblk`
 template <int D, bool LOCAL, int DIR>
-__global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
+__device__ __forceinline__ void workgroup(const AttnParams& p, int bid, int nblk) {
   using C = Cfg<D>;
   constexpr bool LOADER = C::LOADER;
   constexpr int KS = C::KS, RB = C::RB, CPR = C::CPR, HT_BYTES = C::HT_BYTES, STAT_OFF = C::STAT_OFF, HDR_OFF = C::HDR_OFF;
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
   const int W = p.window;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, gridDim.x)) return;
+  if (!decode_kvblock(p, BN, HB, kb, bid, nblk)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;
@@ -774,24 +776,55 @@ __global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p) {
   }
 }
 
+template <int D, bool LOCAL, int DIR>
+__global__ __launch_bounds__(512) void dkdv256_kernel(const AttnParams p, int n_kv) {
+  workgroup<D, LOCAL, DIR>(p, blockIdx.x, n_kv);
+}
+// with dQ in the same launch (dkdv4.hip): n_kv workgroups of dK/dV from first_kv on
+template <int D, int DIR>
+__global__ __launch_bounds__(512) void dkdv256_dq_kernel(const AttnParams p, int n_kv, int first_kv) {
+  const int bid = (int)blockIdx.x - first_kv;
+  if ((unsigned)bid >= (unsigned)n_kv) dq256::workgroup<D, false>(p, bid < 0 ? blockIdx.x : blockIdx.x - n_kv, gridDim.x - n_kv);
+  else workgroup<D, false, DIR>(p, bid, n_kv);
+}
+
+template <int D>
+bool stats_in_reach(const AttnParams& p) {
+  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 192 does not)
+  return Cfg<D>::LOADER || (reinterpret_cast<uintptr_t>(p.lse2) >= reinterpret_cast<uintptr_t>(p.dvec) &&
+                            reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) < (1ull << 32));
+}
+
 template <int D, bool LOCAL>
 hipError_t launch_t(AttnParams p, hipStream_t st) {
-  p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
-  p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
-  if (p.n_split < 1) p.n_split = 1;
-  // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 192 does not)
-  if (!Cfg<D>::LOADER && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
-      reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
-    return hipErrorInvalidValue;
+  const KeyTiles t = key_tiles(p, BN);
+  if (!stats_in_reach<D>(p)) return hipErrorInvalidValue;
   return launch_direction(p, D, [&](auto dir) {
     constexpr auto kern = dkdv256_kernel<D, LOCAL, LOCAL ? WALK_UP : decltype(dir)::value>;
     const hipError_t e = ensure_dynamic_lds<kern>(Cfg<D>::SMEM_BYTES);
     if (e != hipSuccess) return e;
-    const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
-    return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
-      hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q);
+    return launch_key_tiles(p, t.prompt, t.per_seq, 512, [&](const AttnParams& q, unsigned n) {
+      hipLaunchKernelGGL(kern, dim3(n), dim3(512), Cfg<D>::SMEM_BYTES, st, q, (int)n);
       return hipGetLastError();
     });
+  });
+}
+
+template <int D>
+hipError_t launch_dq_t(AttnParams p, bool dq_first, hipStream_t st) {
+  const KeyTiles t = key_tiles(p, BN);
+  if (!stats_in_reach<D>(p)) return hipErrorInvalidValue;
+  fill_packing(p, dq256::NSUB);
+  // (no more workgroups than rules::dq_beside_wide lets share a launch)
+  const unsigned n_kv = (unsigned)(t.prompt + p.n_seqs * t.per_seq), n_dq = (unsigned)((int64_t)p.n_seqs * p.MB * p.HC * p.Hk);
+  if (n_kv + n_dq == 0) return hipSuccess;
+  return launch_direction(p, D, [&](auto dir) {
+    constexpr auto kern = dkdv256_dq_kernel<D, decltype(dir)::value>;
+    constexpr size_t smem = std::max(Cfg<D>::SMEM_BYTES, dq256::Cfg<D>::SMEM_BYTES);
+    const hipError_t e = ensure_dynamic_lds<kern>(smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(n_kv + n_dq), dim3(512), smem, st, p, (int)n_kv, dq_first ? (int)n_dq : 0);
+    return hipGetLastError();
   });
 }
 
@@ -802,6 +835,13 @@ hipError_t launch_dkdv256(const AttnParams& p, int head_dim, hipStream_t st) {
   switch (head_dim) {
     case 192: return local ? launch_t<192, true>(p, st) : launch_t<192, false>(p, st);
     case 256: return local ? launch_t<256, true>(p, st) : launch_t<256, false>(p, st);
+  }
+  return hipErrorInvalidValue;
+}
+hipError_t launch_dkdv256_dq(const AttnParams& p, int head_dim, bool dq_first, hipStream_t st) {
+  switch (head_dim) {
+    case 192: return launch_dq_t<192>(p, dq_first, st);
+    case 256: return launch_dq_t<256>(p, dq_first, st);
   }
   return hipErrorInvalidValue;
 }

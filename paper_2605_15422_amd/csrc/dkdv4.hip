@@ -552,12 +552,6 @@ template <int D>
 constexpr size_t kDkdv4Smem = kStages<D> * (2 * 32 * 2 * D + 256 + 64) + 2 * kGroups<D> * 16384;
 
 constexpr int kKeyTile = 128;
-static int64_t prompt_workgroups(const AttnParams& p) {
-  return (int64_t)(p.grp ? p.n_groups : 1) * ((p.ctx_len + kKeyTile - 1) / kKeyTile) * p.Hk * (p.n_split < 1 ? 1 : p.n_split);
-}
-static int64_t response_workgroups(const AttnParams& p) {
-  return (int64_t)p.n_seqs * ((p.max_rows + kKeyTile - 1) / kKeyTile) * p.Hk;
-}
 static int64_t dq_workgroups(AttnParams& p, int waves) {
   fill_packing(p, waves);
   return (int64_t)p.n_seqs * p.MB * p.HC * p.Hk;
@@ -566,9 +560,7 @@ static int64_t dq_workgroups(AttnParams& p, int waves) {
 // DQ_WAVES: of the dQ workgroups in the launch (0: none); dq_first: they come before those of dK/dV
 template <int D, bool LOCAL, int DQ_WAVES>
 static hipError_t launch_dkdv4_t(AttnParams p, bool dq_first, hipStream_t st) {
-  p.n_ctx_tiles = (p.ctx_len + kKeyTile - 1) / kKeyTile;
-  p.n_dec_tiles = (p.max_rows + kKeyTile - 1) / kKeyTile;
-  if (p.n_split < 1) p.n_split = 1;
+  const KeyTiles t = key_tiles(p, kKeyTile);
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset (the loader wave of head dim 96 does not)
   if (!kSplitRow<D> && (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
        reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32)))
@@ -581,14 +573,14 @@ static hipError_t launch_dkdv4_t(AttnParams p, bool dq_first, hipStream_t st) {
   const hipError_t e = ensure_dynamic_lds<kern>(smem);
   if (e != hipSuccess) return e;
   constexpr int threads = kWaves<D> * 64;
-  if constexpr (DQ_WAVES != 0) {   // (few workgroups: dkdv4_dq_fits)
-    const unsigned n_kv = (unsigned)(prompt_workgroups(p) + response_workgroups(p)), n = n_kv + (unsigned)dq_workgroups(p, DQ_WAVES);
+  if constexpr (DQ_WAVES != 0) {   // (no more workgroups than rules::dq_beside lets share a launch)
+    const unsigned n_kv = (unsigned)(t.prompt + p.n_seqs * t.per_seq), n = n_kv + (unsigned)dq_workgroups(p, DQ_WAVES);
     if (n == 0) return hipSuccess;
     if constexpr (DQ_WAVES == 8) hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv);
     else hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, p, (int)n_kv, dq_first ? (int)(n - n_kv) : 0);
     return hipGetLastError();
   }
-  return launch_key_tiles(p, prompt_workgroups(p), (int64_t)p.n_dec_tiles * p.Hk, threads, [&](const AttnParams& q, unsigned n) {
+  return launch_key_tiles(p, t.prompt, t.per_seq, threads, [&](const AttnParams& q, unsigned n) {
     if constexpr (DQ_WAVES != 8) hipLaunchKernelGGL(kern, dim3(n), dim3(threads), smem, st, q, (int)n, 0);
     return hipGetLastError();
   });
@@ -606,20 +598,9 @@ static hipError_t launch_dkdv4_d(const AttnParams& p, int head_dim, bool dq_firs
   return hipErrorInvalidValue;
 }
 
-// The dQ workgroups beside those of dK/dV (rules.h)
-static rules::Beside dq_beside(AttnParams p, int head_dim) {
-  if (head_dim > 128) return {};
-  p.n_split = 1;
-  const rules::RowBlocks c = {p.n_seqs, p.max_rows, p.ctx_len, p.window > 0, p.G, p.Hk, p.total};
-  return rules::dq_beside(c, p.grp && p.n_groups > 1, prompt_workgroups(p), response_workgroups(p));
-}
-
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st) { return launch_dkdv4_d<0>(p, head_dim, false, st); }
-hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st) {
-  const rules::Beside b = dq_beside(p, head_dim);
-  return b.waves == 8 ? launch_dkdv4_d<8>(p, head_dim, false, st) : launch_dkdv4_d<kDqWaves>(p, head_dim, b.first, st);
+hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, int dq_waves, bool dq_first, hipStream_t st) {
+  return dq_waves == 8 ? launch_dkdv4_d<8>(p, head_dim, false, st) : launch_dkdv4_d<kDqWaves>(p, head_dim, dq_first, st);
 }
-int64_t dkdv4_dq_room(const AttnParams& p, int head_dim) { return dq_beside(p, head_dim).room; }
-bool dkdv4_dq_fits(const AttnParams& p, int head_dim) { return prompt_workgroups(p) <= dkdv4_dq_room(p, head_dim); }
 
 }  // namespace dkv

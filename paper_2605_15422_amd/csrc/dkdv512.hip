@@ -22,6 +22,7 @@
 #include <type_traits>
 #include "common.h"
 #include "dma.h"
+#include "dq512.h"
 #include "kvsched.h"
 #include "kvstore.h"
 #include "launch.h"
@@ -54,8 +55,19 @@ constexpr int IPB = HB / 4;                      // 1 KB load instructions (one 
 constexpr int HALF = (NBUF / 2) * STAGE_BYTES;   // second base register of every LDS operand (16-bit offset field)
 static_assert(STAGE_BYTES + HT_BYTES + 1024 < 65536, "immediate offsets");
 
-template <int DIR>
-__global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
+// WITH_DQ: n_kv workgroups of dK/dV from first_kv on, the others dQ (dkdv4.hip).  (One body in the kernel itself: as a function that two kernels
+// call, the plain one took 5 % longer.)
+template <int DIR, bool WITH_DQ>
+__global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p, int n_kv, int first_kv) {
+  int bid = blockIdx.x, nblk = gridDim.x;
+  if constexpr (WITH_DQ) {
+    bid -= first_kv;
+    if ((unsigned)bid >= (unsigned)n_kv) {
+      dq512::workgroup<false>(p, bid < 0 ? blockIdx.x : blockIdx.x - n_kv, gridDim.x - n_kv);
+      return;
+    }
+    nblk = n_kv;
+  }
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -63,7 +75,7 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
   const int l32 = lane & 31, hi = lane >> 5;
 
   KVBlock kb;
-  if (!decode_kvblock(p, BN, HB, kb, blockIdx.x, gridDim.x)) return;
+  if (!decode_kvblock(p, BN, HB, kb, bid, nblk)) return;
   const bool is_ctx = kb.is_ctx;
   const int hk = kb.hk, key0 = kb.key0, seq_lo = kb.seq_lo, seq_hi = kb.seq_hi, P = kb.P;
   int region_len, key_row_begin;
@@ -534,25 +546,33 @@ __global__ __launch_bounds__(512) void dkdv512_kernel(const AttnParams p) {
 
 }  // namespace
 
-hipError_t launch_dkdv512(const AttnParams& p0, hipStream_t st) {
-  AttnParams p = p0;
-  p.n_ctx_tiles = (p.ctx_len + BN - 1) / BN;
-  p.n_dec_tiles = (p.max_rows + BN - 1) / BN;
-  if (p.n_split < 1) p.n_split = 1;
+template <bool WITH_DQ>
+static hipError_t launch(AttnParams p, bool dq_first, hipStream_t st) {
+  const KeyTiles t = key_tiles(p, BN);
   // the kernel addresses LSE*log2e as D + 32-bit unsigned byte offset
   if (reinterpret_cast<uintptr_t>(p.lse2) < reinterpret_cast<uintptr_t>(p.dvec) ||
       reinterpret_cast<uintptr_t>(p.lse2) - reinterpret_cast<uintptr_t>(p.dvec) >= (1ull << 32))
     return hipErrorInvalidValue;
+  unsigned n_dq = 0;
+  if (WITH_DQ) {   // (no more workgroups than rules::dq_beside_wide lets share a launch)
+    fill_packing(p, dq512::NSUB);
+    n_dq = (unsigned)((int64_t)p.n_seqs * p.MB * p.HC * p.Hk);
+  }
   return launch_direction(p, D, [&](auto dir) {
-    constexpr auto kern = dkdv512_kernel<decltype(dir)::value>;
-    const hipError_t e = ensure_dynamic_lds<kern>(SMEM_BYTES);
+    constexpr auto kern = dkdv512_kernel<decltype(dir)::value, WITH_DQ>;
+    constexpr size_t smem = WITH_DQ && dq512::SMEM_BYTES > SMEM_BYTES ? dq512::SMEM_BYTES : SMEM_BYTES;
+    const hipError_t e = ensure_dynamic_lds<kern>(smem);
     if (e != hipSuccess) return e;
-    const int64_t prompt = (int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split;
-    return launch_key_tiles(p, prompt, (int64_t)p.n_dec_tiles * p.Hk, 512, [&](const AttnParams& q, unsigned n) {
-      hipLaunchKernelGGL(kern, dim3(n), dim3(512), SMEM_BYTES, st, q);
+    const auto go = [&](const AttnParams& q, unsigned n_kv) {
+      hipLaunchKernelGGL(kern, dim3(n_kv + n_dq), dim3(512), smem, st, q, (int)n_kv, dq_first ? (int)n_dq : 0);
       return hipGetLastError();
-    });
+    };
+    if (!WITH_DQ) return launch_key_tiles(p, t.prompt, t.per_seq, 512, go);
+    const unsigned n_kv = (unsigned)(t.prompt + p.n_seqs * t.per_seq);
+    return n_kv + n_dq ? go(p, n_kv) : hipSuccess;
   });
 }
+hipError_t launch_dkdv512(const AttnParams& p, hipStream_t st) { return launch<false>(p, false, st); }
+hipError_t launch_dkdv512_dq(const AttnParams& p, bool dq_first, hipStream_t st) { return launch<true>(p, dq_first, st); }
 
 }  // namespace dkv

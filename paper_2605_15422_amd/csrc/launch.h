@@ -15,10 +15,10 @@ hipError_t launch_dq2(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dkdv4(const AttnParams& p, int head_dim, hipStream_t st);
 // dK/dV of Call 2 at head dims 96 and 128 without a window, two workgroups a CU
 hipError_t launch_dkdvw(const AttnParams& p, int head_dim, hipStream_t st);
-// both in one launch (row statistics given), for calls with few workgroups: up to dkdv4_dq_room prompt workgroups
-int64_t dkdv4_dq_room(const AttnParams& p, int head_dim);
-bool dkdv4_dq_fits(const AttnParams& p, int head_dim);
-hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, hipStream_t st);
+// dK/dV and dQ in one launch (row statistics given), by the rules of dq_beside (rules.h)
+hipError_t launch_dkdv4_dq(const AttnParams& p, int head_dim, int dq_waves, bool dq_first, hipStream_t st);
+hipError_t launch_dkdv256_dq(const AttnParams& p, int head_dim, bool dq_first, hipStream_t st);
+hipError_t launch_dkdv512_dq(const AttnParams& p, bool dq_first, hipStream_t st);
 // kernels for head dims 192 / 256 (forward, dQ: 128 rows per workgroup; dK/dV: 64-key tile)
 hipError_t launch_fwd256(const AttnParams& p, int head_dim, hipStream_t st);
 hipError_t launch_dq256(const AttnParams& p, int head_dim, hipStream_t st);
@@ -89,6 +89,16 @@ inline hipError_t launch_key_tiles(const AttnParams& p, int64_t prompt, int64_t 
   return launch_sequences(q, per_seq, threads, launch);
 }
 
+// dK/dV workgroups: of the prompt tiles (with their parts), and per sequence; fills the kernel's fields
+struct KeyTiles {
+  int64_t prompt, per_seq;
+};
+inline KeyTiles key_tiles(AttnParams& p, int key_tile) {
+  p.n_ctx_tiles = (p.ctx_len + key_tile - 1) / key_tile;
+  p.n_dec_tiles = (p.max_rows + key_tile - 1) / key_tile;
+  if (p.n_split < 1) p.n_split = 1;
+  return {(int64_t)(p.grp ? p.n_groups : 1) * p.n_ctx_tiles * p.Hk * p.n_split, (int64_t)p.n_dec_tiles * p.Hk};
+}
 // dK/dV kernels that know both directions of a walk (kvsched.h)
 template <typename F>
 inline hipError_t launch_direction(const AttnParams& p, int head_dim, F launch) {

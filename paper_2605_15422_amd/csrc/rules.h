@@ -240,6 +240,26 @@ inline Beside dq_beside(const RowBlocks& c, bool several_groups, int64_t prompt_
   return {4, false, room};
 }
 
+// Head dims 192 to 512, whose dQ workgroups have a CU to themselves in any case: a shared launch loses nothing but the
+// pass of the preprocess.
+//   * One causal sequence up to 600 key tiles: 0.56 to 0.98 of the time.  1 x 4236 rows, 8 / 2 heads, d = 192 464 -> 371 us; 1 x 1562, 8 / 8, d =
+//     256 108 -> 63; 1 x 9219, 8 / 2, d = 512 (578 tiles) 3303 -> 3138; past that the tails are short: 1 x 5980, 32 / 8, d = 192 (752) 1429 -> 1372,
+//     1 x 7082, 12 / 4, d = 512 (888) 2583 -> 2557.
+//   * Responses up to 700 dQ workgroups, those first where their walks are at least half of those of the prompt tiles: 44 calls take 0.58
+//     to 1.01 of their time, 0.81 together (one 1.03: 7 x U(96, 546) behind 1472, 16 / 4, d = 256 273 -> 281); 3 x U(48, 88) behind 7082, 12 / 4, d = 512
+//     504 -> 328 us, 2 x U(902, 1069) behind 73, 16 / 4, d = 256 153 -> 119.  The other side: 12 x U(443, 946) behind 295, 32 / 8, d = 256 (2880)
+//     791 -> 799.
+inline Beside dq_beside_wide(const RowBlocks& c, bool several_groups, bool d512, int64_t resp_tiles) {
+  if (c.window || several_groups) return {};
+  if (c.ctx_len == 0) return c.n_seqs == 1 && resp_tiles <= 600 ? Beside{8, false, 0} : Beside{};
+  const Packing k = pack_heads(c.G, d512 ? 2 : 4);
+  const int64_t rows = 32 * k.subtiles, n = c.n_seqs * ((c.longest + rows - 1) / rows) * (c.G / k.heads) * c.kv_heads;
+  if (n > 700) return {};
+  // walks in intervals of dK/dV: its row block, and 32 keys of dQ (head dim 512: half of either) take 1.5
+  const double dq_walk = ((double)c.ctx_len + c.longest) / (d512 ? 10.7 : 21.3), part = (double)c.total * c.G / (d512 ? 16 : 32);
+  return {8, 2 * dq_walk >= part, 1 << 20};
+}
+
 // K and V tiles that a dQ workgroup has room for, head dims 64 / 96 / 128.  Three at d = 64, so that three workgroups fit the LDS
 // of a CU (their registers do, too): with four and two workgroups dQ of 8 x U(131, 2048) behind 4096, 32 / 8 heads takes 730 us instead of 686.
 // At d = 128 four waves have three slots for K, two tiles ahead, and two for V, one ahead: exactly half of a CU's LDS.

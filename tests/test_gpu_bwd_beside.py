@@ -1,5 +1,5 @@
-"""dQ beside dK/dV in one launch past one workgroup a CU: one causal sequence with dQ workgroups of four and of eight waves, and few rows
-behind a long prompt with dQ first.  Bit for bit what the two kernels give in launches of their own (prompt gradients: sums of
+"""dQ beside dK/dV in one launch past one workgroup a CU: one causal sequence (head dims 64 to 128 with dQ workgroups of four and of eight
+waves), rows behind a prompt with dQ first and last.  Bit for bit what the two kernels give in launches of their own (prompt gradients: sums of
 parts, to rounding)."""
 import numpy as np
 import pytest
@@ -17,8 +17,12 @@ def _apart(s, run):
     return out
 
 
-@pytest.mark.parametrize("d", [64, 96, 128])
-@pytest.mark.parametrize("H,Hk,P", [(16, 4, 2081), (8, 8, 2500), (32, 8, 3873), (8, 2, 16350), (32, 8, 6657)])
+CAUSAL = [(d, *x) for d in (64, 96, 128) for x in ((16, 4, 2081), (8, 8, 2500), (32, 8, 3873), (8, 2, 16350), (32, 8, 6657))] + [
+    (192, 2, 1, 65), (192, 8, 2, 3001), (192, 4, 4, 9600), (192, 16, 2, 2735), (256, 6, 2, 1023), (256, 8, 2, 4097), (256, 4, 4, 9700),
+    (512, 2, 2, 31), (512, 8, 2, 2049), (512, 6, 2, 1500), (512, 4, 2, 9700)]
+
+
+@pytest.mark.parametrize("d,H,Hk,P", CAUSAL)
 def test_one_causal_sequence(d, H, Hk, P):
     import torch
     from paper_2605_15422_amd import binding as B, runner
@@ -39,9 +43,12 @@ def test_one_causal_sequence(d, H, Hk, P):
         assert not torch.isnan(x).any() and torch.equal(x.view(torch.int16), y.view(torch.int16))
 
 
-@pytest.mark.parametrize("d", [64, 96, 128])
-@pytest.mark.parametrize("H,Hk,P,lens", [(32, 8, 4300, [20, 33]), (12, 4, 9000, [0, 1, 130]), (8, 8, 4097, [64] * 7), (32, 4, 8321, [97])])
-def test_few_rows_behind_a_long_prompt(d, H, Hk, P, lens):
+ROWS = [(d, *x) for d in (64, 96, 128) for x in ((32, 8, 4300, [20, 33]), (12, 4, 9000, [0, 1, 130]), (8, 8, 4097, [64] * 7), (32, 4, 8321, [97]))] + [
+    (d, *x) for d in (192, 256, 512) for x in ((8, 2, 3001, [20, 0, 33]), (12, 4, 70, [700, 31]), (4, 4, 500, [129] * 9), (8, 1, 1, [1, 64]))]
+
+
+@pytest.mark.parametrize("d,H,Hk,P,lens", ROWS)
+def test_rows_behind_a_prompt(d, H, Hk, P, lens):
     import torch
     from paper_2605_15422_amd import binding as B, runner
     print("case dQ first", d, H, Hk, P, lens, flush=True)
