@@ -223,13 +223,16 @@ struct Beside {
 //   * one causal sequence up to 416 key tiles: its first tile's walk is twice the mean.  With eight waves a dQ workgroup from 240 tiles on (dQ
 //     is too much work for the CUs that dK/dV leaves idle), if eight make enough workgroups.  1 x 5000, 32 / 8 heads, d = 128 (320 tiles) 778 ->
 //     664 us (four waves 716), 1 x 4111, 16 / 4, d = 96 (132) 434 -> 352 (359 with eight), 1 x 3000, 8 / 8, d = 128 (192) 149 -> 89.  The other
-//     side: 7200, 32 / 8, d = 64 (456) 769 -> 784.
+//     side: 7200, 32 / 8, d = 64 (456) 769 -> 784;
+//   * several causal sequences up to as many tiles (Call 1 of several groups; counted with the longest).  The layers of eight
+//     groups behind prompts of up to 517, 32 / 8 heads, d = 128 473 -> 457 us, three behind 1500, 12 / 4, 313 -> 274, eight behind 100, 32 / 8,
+//     d = 64 329 -> 328.  Call 2 of several groups gains nothing (0.98 to 1.09).
 inline Beside dq_beside(const RowBlocks& c, bool several_groups, int64_t prompt_tiles, int64_t resp_tiles) {
   const int64_t n4 = row_block_count(c, 4);
-  if (c.n_seqs == 1 && c.ctx_len == 0 && !several_groups && !c.window) {
+  if (c.ctx_len == 0 && !several_groups && !c.window) {
     if (resp_tiles + n4 <= kCus) return {4, false, 0};
     if (resp_tiles > 416) return {};
-    return {resp_tiles >= 240 && row_block_count(c, 8) >= 240 ? 8 : 4, false, 0};
+    return {row_block_count(c, 8) >= 240 && (c.n_seqs > 1 || resp_tiles >= 240) ? 8 : 4, false, 0};
   }
   const bool one_prompt = c.ctx_len > 0 && !several_groups && !c.window;
   const bool tails = one_prompt && c.total >= 0.3 * c.ctx_len * c.n_seqs;
@@ -242,7 +245,7 @@ inline Beside dq_beside(const RowBlocks& c, bool several_groups, int64_t prompt_
 
 // Head dims 192 to 512, whose dQ workgroups have a CU to themselves in any case: a shared launch loses nothing but the
 // pass of the preprocess.
-//   * One causal sequence up to 600 key tiles: 0.56 to 0.98 of the time.  1 x 4236 rows, 8 / 2 heads, d = 192 464 -> 371 us; 1 x 1562, 8 / 8, d =
+//   * Causal sequences up to 600 key tiles: 0.56 to 0.98 of the time.  1 x 4236 rows, 8 / 2 heads, d = 192 464 -> 371 us; 1 x 1562, 8 / 8, d =
 //     256 108 -> 63; 1 x 9219, 8 / 2, d = 512 (578 tiles) 3303 -> 3138; past that the tails are short: 1 x 5980, 32 / 8, d = 192 (752) 1429 -> 1372,
 //     1 x 7082, 12 / 4, d = 512 (888) 2583 -> 2557.
 //   * Responses up to 700 dQ workgroups, those first where their walks are at least half of those of the prompt tiles: 44 calls take 0.58
@@ -251,7 +254,7 @@ inline Beside dq_beside(const RowBlocks& c, bool several_groups, int64_t prompt_
 //     791 -> 799.
 inline Beside dq_beside_wide(const RowBlocks& c, bool several_groups, bool d512, int64_t resp_tiles) {
   if (c.window || several_groups) return {};
-  if (c.ctx_len == 0) return c.n_seqs == 1 && resp_tiles <= 600 ? Beside{8, false, 0} : Beside{};
+  if (c.ctx_len == 0) return resp_tiles <= 600 ? Beside{8, false, 0} : Beside{};
   const Packing k = pack_heads(c.G, d512 ? 2 : 4);
   const int64_t rows = 32 * k.subtiles, n = c.n_seqs * ((c.longest + rows - 1) / rows) * (c.G / k.heads) * c.kv_heads;
   if (n > 700) return {};
