@@ -177,15 +177,33 @@ int bind_groups(AttnParams& p, const Groups& g, int n_seqs, void* seqctx, hipStr
                                                                                                          : DUALKV_E_HIP;
 }
 
-// May an output view and an input view of `rows` rows of H heads share elements?  Views that interleave in one buffer (the
-// same token stride, different columns) do not.
-bool overlap(const TViewOut& a, const TView& b, int64_t rows, int H, int d) {
+// May an output view of `rows` rows and an input view of `rows_b` rows (as many), both of H heads, share elements?  Views that interleave
+// in one buffer (the same token stride, different columns) do not.
+bool overlap(const TViewOut& a, const TView& b, int64_t rows, int H, int d, int64_t rows_b = -1) {
+  if (rows_b < 0) rows_b = rows;
   const int64_t wa = (H - 1) * a.hs + d, wb = (H - 1) * b.hs + d;   // elements from a row's first to its last
   const int64_t off = (int64_t)((intptr_t)b.ptr - (intptr_t)a.ptr) / 2;   // (both 16-byte aligned)
-  if (off >= (rows - 1) * a.ts + wa || -off >= (rows - 1) * b.ts + wb) return false;
+  if (off >= (rows - 1) * a.ts + wa || -off >= (rows_b - 1) * b.ts + wb) return false;
   if (a.ts != b.ts) return true;
   const int64_t col = ((off % a.ts) + a.ts) % a.ts;                 // first column of b inside a's rows
   return col < wa || col + wb > a.ts;
+}
+
+// Do the gradients of the keys and values lie over the keys and values?  (A workgroup of dK/dV has read its tile by the time it writes, but
+// dQ, which reads all of them, must be done then.)
+bool gradients_over_keys(const AttnParams& p, int64_t rows, int64_t ctx_rows, int d) {
+  const struct {
+    const TViewOut& out;
+    int64_t rows;
+  } outs[] = {{p.dkd, rows}, {p.dvd, rows}, {p.dkc, ctx_rows}, {p.dvc, ctx_rows}};
+  const struct {
+    const TView& in;
+    int64_t rows;
+  } ins[] = {{p.kd, rows}, {p.vd, rows}, {p.kc, ctx_rows}, {p.vc, ctx_rows}};
+  for (const auto& o : outs)
+    for (const auto& i : ins)
+      if (o.out.ptr && i.in.ptr && o.rows > 0 && i.rows > 0 && overlap(o.out, i.in, o.rows, p.Hk, d, i.rows)) return true;
+  return false;
 }
 
 int hip_rc(hipError_t e) { return e == hipSuccess ? DUALKV_OK : DUALKV_E_HIP; }
@@ -213,14 +231,14 @@ hipError_t run_dkdv(const AttnParams& p, int d, bool pair, hipStream_t st) {
 // at d = 256, window 1024, N = 8, P = 57344, R = 8192, 8 / 2 heads: 2 to 3 %).  Calls that leave CUs idle run both kernels side by side
 // behind the preprocess (dkdv4.hip).  The preprocess also serves calls without dQ, and calls whose dQ overwrites what the
 // dK/dV kernel has to read (dQ is written last then).
-hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int d, bool pair, hipStream_t st) {
+hipError_t run_bwd(AttnParams& p, uint32_t flags, int64_t rows, int64_t ctx_rows, int d, bool pair, hipStream_t st) {
   const bool do_dq = rows > 0 && !(flags & DUALKV_FLAG_SKIP_DQ), do_dkdv = !(flags & DUALKV_FLAG_SKIP_DKDV);
   const bool do_pre = rows > 0 && !(flags & DUALKV_FLAG_SKIP_PRE);
   hipError_t e = hipSuccess;
   if (do_pre && do_dq && !overlap(p.dq, p.q, rows, p.H, d) && !overlap(p.dq, p.dout, rows, p.H, d) &&
       !overlap(p.dq, p.o, rows, p.H, d)) {
     const dkv::rules::Beside b = dq_beside(p, d);
-    if (do_dkdv && !pair && dkv::key_tiles(p, dkv::dkdv_key_tile(d)).prompt <= b.room) {
+    if (do_dkdv && !pair && dkv::key_tiles(p, dkv::dkdv_key_tile(d)).prompt <= b.room && !gradients_over_keys(p, rows, ctx_rows, d)) {
       if ((e = dkv::launch_dot_do_o(p.dout, p.o, p.lse, p.dvec, p.lse2, (int)rows, p.H, d, st)) != hipSuccess) return e;
       if (d <= 128) return dkv::launch_dkdv4_dq(p, d, b.waves, b.first, st);
       return d <= 256 ? dkv::launch_dkdv256_dq(p, d, b.first, st) : dkv::launch_dkdv512_dq(p, b.first, st);
@@ -387,7 +405,7 @@ int ctx_bwd_impl(const dualkv_shape* shape, dualkv_tin do_c, dualkv_tin o_c, con
   p.dvec = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.dvec_off);
   p.lse2 = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.lse2_off);
   if ((rc = bind_ctx_groups(p, shape, groups, static_cast<char*>(workspace) + w.total, st))) return rc;
-  return hip_rc(run_bwd(p, shape->flags, P, d, false, st));
+  return hip_rc(run_bwd(p, shape->flags, P, 0, d, false, st));
 }
 
 
@@ -464,7 +482,7 @@ int bwd_impl(const dualkv_shape* shape, dualkv_tin do_d, dualkv_tin o_d, const f
     p.dkc = view(dk_c);
     p.dvc = view(dv_c);
   }
-  if ((rc = hip_rc(run_bwd(p, shape->flags, T, d, parts.pair, st)))) return rc;
+  if ((rc = hip_rc(run_bwd(p, shape->flags, T, P, d, parts.pair, st)))) return rc;
   if (scratch && !(shape->flags & DUALKV_FLAG_SKIP_DKDV)) {
     // Stage 2 (Alg. 2): cast the accumulated prompt gradients once
     if ((rc = hip_rc(dkv::launch_convert2_ctx(p.dkc_acc, view(dk_c), p.dvc_acc, view(dv_c), P, p.Hk, d, st)))) return rc;

@@ -70,3 +70,29 @@ def test_rows_behind_a_prompt(d, H, Hk, P, lens):
         # (fp32 sums in another order, one rounding to bf16)
         if k in (1, 2): assert (x.double() - y.double()).norm() <= 2.0**-9 * y.double().norm()
         else: assert torch.equal(x.view(torch.int16), y.view(torch.int16))
+
+
+@pytest.mark.parametrize("d,H,Hk,P,lens", [(128, 16, 4, 1000, []), (64, 8, 2, 300, [500, 31, 200]), (96, 32, 8, 4300, [20, 33]), (256, 8, 2, 900, []),
+                                           (512, 8, 2, 600, [64, 33])])
+def test_gradients_over_the_keys(d, H, Hk, P, lens):
+    """dK and dV written over K and V: dQ is done by then."""
+    import torch
+    from paper_2605_15422_amd import binding as B, runner
+    print("case in place", d, H, Hk, P, lens, flush=True)
+    dg = B.upload(W.make_workload(W.Shape("inplace", max(len(lens), 1), P, 0, 0, H, Hk, d, 0, seed=600 + d), resp_lens=np.asarray(lens or [0])))
+    b = runner.alloc(dg)
+    runner.layer_step(dg, b)
+    s = dg.shape_c
+    if lens:
+        k, v = dg.k_d.clone(), dg.v_d.clone()
+        dq = torch.full_like(dg.q_d, float("nan"))
+        B.dualkv_bwd(s, dg.do_d, b.o_d, b.lse_d, dg.q_d, dg.k_c, dg.v_c, k, v, dg.cu_dev, dg.cu_host, dq, b.dk_c2, b.dv_c2, k, v, None, None, b.ws_bwd)
+        want = (b.dq_d, b.dk_d, b.dv_d)
+    else:
+        k, v = dg.k_c.clone(), dg.v_c.clone()
+        dq = torch.full_like(dg.q_c, float("nan"))
+        B.dualkv_ctx_bwd(s, dg.do_c, b.o_c, b.lse_c, dg.q_c, k, v, dq, k, v, None, None, b.ws_ctx_bwd)
+        want = (b.dq_c, b.dk_c1, b.dv_c1)
+    torch.cuda.synchronize()
+    for x, y in zip((dq, k, v), want):
+        assert torch.equal(x.view(torch.int16), y.view(torch.int16))
