@@ -197,7 +197,11 @@ inline Waves choose_waves(const RowBlocks& c, int head_dim, bool dq, bool shared
   const int64_t n = row_block_count(c, 4);
   const int alone = row_block_waves(c, false, dq, shared);
   if (alone == 4 && (n <= kCus || n != row_block_count(c, 8))) return {4, false};
-  if (head_dim != 64 && (n <= kCus || two_rounds_of_eight(c) || (!dq && many_long_walks(c)))) return {8, false};
+  if (head_dim == 64) {   // (three to a CU leave others idle where two to a CU are one round: 56 row blocks of 8 heads 1304 -> 1336 us the layer)
+    const Packing k = pack_heads(c.G, 4);
+    return {4, (c.total / (32 * k.subtiles) + c.n_seqs / 2) * (int64_t)(c.G / k.heads) * c.kv_heads > 2 * kCus};
+  }
+  if ((n <= kCus || two_rounds_of_eight(c) || (!dq && many_long_walks(c)))) return {8, false};
   return {4, true};
 }
 

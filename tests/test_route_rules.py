@@ -55,7 +55,9 @@ WAVES = [
     ((128, 1, 16, 1992, 32768, 0, 32, 4, 25926), (4, True)),
     ((128, 0, 4, 100, 300, 0, 8, 2, 300), (4, False)),          # a CU each
     ((128, 0, 1, 3000, 0, 0, 16, 4, 3000), (4, False)),         # pairs 58 -> 60 us
-    # test_gpu_half_tiles.py: eight waves for one sequence, pairs for two
+    *(((d, 0, 70, 130, P, 0, 16, 4, 3570), (4, True)) for d in (64, 96, 128) for P in (1, 161)),   # test_gpu_half_tiles.py, edges
+    ((128, 1, 70, 130, 161, 0, 16, 4, 3570), (4, True)),
+    # the same: eight waves for one sequence, pairs for two
     *(((d, q, 1, P, 0, 0, H, Hk, P), (8, False) if d == 128 or not q else (8, True)) for d, H, Hk, P in
       ((96, 32, 8, 3393), (96, 8, 8, 13569), (128, 32, 8, 3393), (128, 8, 2, 16384)) for q in (0, 1)),
     *(((d, q, 2, P, 0, 0, H, Hk, 2 * P), (4, True)) for d, H, Hk, P in ((96, 32, 8, 3393), (128, 32, 8, 3393), (128, 8, 2, 16384)) for q in (0, 1)),
